@@ -77,6 +77,8 @@ constexpr int64_t kMaxXmin = (int64_t)1 << 40;
 constexpr int64_t kFitBlockMin = 2048;
 // Host datasets up to this many bytes go through pinned staging.
 constexpr size_t kPinStageMax = (size_t)64 << 20;
+// Escalation slots for replicates the batched heavy form cannot finish.
+constexpr int64_t kBatchEsc = 4096;
 
 // P(X > h) under exponent a: the pure law (K = 0) or the truncated law on
 // 1..K (finite sums).
@@ -307,7 +309,11 @@ double tuned_cost(const Tuning& t, int f, double alpha, int64_t n) {
 struct Plan {
   std::vector<DevCell> cells;
   std::vector<Unit> units;    // lane and wave units (LPT order)
-  std::vector<Unit> hunits;   // heavy units
+  // heavy-form units: [batched pure law | batched cutoff law | the rest]
+  std::vector<Unit> hunits;
+  int n_bpure = 0, n_bcut = 0;  // lengths of the first two parts
+  int64_t batch_R = 0, batch_max_n = 0;  // replicates and largest n of the batched parts
+  int64_t heavy8 = 0;  // heavy cells' replicates in groups of 8 (sizes the heavy scratch)
   std::vector<int> cell_unit_begin, cell_unit_end;  // per cell range in `units`
   int64_t total_R = 0;
   int64_t max_n = 0;
@@ -338,12 +344,12 @@ double trunc_cost(int64_t n, uint32_t K) { return 2.2e-3 * ((double)n + 8.6 * (d
 
 // Time for one cell alone under form f (tuned cost v ns per replicate with
 // the device busy): its work units (kBlock replicates per workgroup for the
-// lane and wave forms, 8 for the heavy form, which fits two workgroups per
+// lane and wave forms, kBatchWaves for the heavy form; one workgroup per
 // compute unit) run in rounds of as many units as the device holds at once,
 // and a unit takes v x (replicates the device holds at once).
 double cell_makespan(int f, double v, int64_t R, int n_cu) {
-  const double per = f == (int)kModeHeavy ? 8.0 : (double)kBlock;
-  const double conc = f == (int)kModeHeavy ? 2.0 * n_cu : (double)n_cu;
+  const double per = f == (int)kModeHeavy ? (double)kBatchWaves : (double)kBlock;
+  const double conc = (double)n_cu;
   return std::ceil(std::ceil((double)R / per) / conc) * v * conc * per;
 }
 
@@ -388,6 +394,66 @@ uint32_t choose_form(double alpha, int64_t n, const Tuning* t, uint32_t K = 0, i
   if (n <= 65535 && (double)n * tail_prob(alpha, kHLB, K) <= 2.0) return kModeLane;
   if (form_eligible(kModeWave, alpha, n, K)) return kModeWave;
   return kModeHeavy;
+}
+
+// Whether a heavy-form cell runs in the batched kernel: the pure law or the
+// law with a cutoff, and the most populated bucket of the larger draws (16
+// per octave of the table index, the first one) expected to hold at most half
+// of what the kernel gathers in one go.  Others (and replicates that exceed
+// the room after all) run in the sorting kernel.
+bool batch_eligible(const DevCell& d) {
+  if (d.K != 0u || d.n > ((int64_t)1 << 20)) return false;
+  const double b = d.alpha - 1.0;
+  double t;
+  if (d.xmin > 1)  // P(X >= xmin + kHW), the continuous law's: an estimate is enough
+    t = std::pow((double)d.xmin / ((double)d.xmin + (double)kHW), b);
+  else
+    t = tail_prob(d.alpha, kHW);
+  return (double)d.n * t * (1.0 - std::pow(17.0 / 16.0, -b)) <= 128.0;
+}
+
+// Units of the heavy-form cells, longest replicates first.  A batched unit
+// holds the same number of replicates (up to 64) for each of the kernel's
+// waves, as many as leaves about eight units for each compute unit; a unit of
+// the sorting kernel holds 8 replicates (2 per wave).
+void plan_heavy(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) {
+  std::stable_sort(cells.begin(), cells.end(),
+                   [&](int a, int b) { return P.cells[a].n > P.cells[b].n; });
+  double work = 0.0;
+  // a replicate costs about its draws plus 2,000 draws' time for fit and KS
+  auto cost = [](const DevCell& d) { return (double)d.n + 2000.0; };
+  std::vector<char> batch(P.cells.size(), 0);
+  for (int i : cells) {
+    const DevCell& d = P.cells[i];
+    P.heavy8 += (d.R + 7) / 8;
+    if (!batch_eligible(d)) continue;
+    batch[i] = 1;
+    P.batch_R += d.R;
+    P.batch_max_n = std::max(P.batch_max_n, d.n);
+    work += cost(d) * (double)d.R;
+  }
+  const double unit_work = work / (8.0 * n_cu);
+  for (int part = 0; part < 3; ++part) {
+    const size_t begin = P.hunits.size();
+    for (int i : cells) {
+      const DevCell& d = P.cells[i];
+      if (part != (batch[i] ? (d.xmin > 1 ? 1 : 0) : 2)) continue;
+      const int waves = part == 1 ? kBatchWavesCut : kBatchWaves;
+      const int64_t per_wave =
+          std::min<int64_t>(64, std::max<int64_t>(1, (int64_t)(unit_work / cost(d) / waves)));
+      const int64_t step = part == 2 ? 8 : per_wave * waves;
+      for (int64_t r = 0; r < d.R; r += step) {
+        Unit u;
+        u.cell = i;
+        u.r0 = (rlo ? rlo[i] : 0) + r;
+        u.count = (int32_t)std::min<int64_t>(step, d.R - r);
+        P.hunits.push_back(u);
+      }
+    }
+    const int count = (int)(P.hunits.size() - begin);
+    if (part == 0) P.n_bpure = count;
+    if (part == 1) P.n_bcut = count;
+  }
 }
 
 // rlo (optional): cell i covers replicates rlo[i] .. rlo[i] + replicates - 1
@@ -476,7 +542,7 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
     if (m != kModeHeavy) P.lw_R += z.replicates;
   }
   // units: kBlock replicates (one per lane, or 64 per wave) for lane/wave
-  // cells, 8 replicates (2 per wave) for heavy cells.  The longest-first
+  // cells (heavy cells: plan_heavy).  The longest-first
   // order weighs a unit by how long it occupies its workgroup: per-replicate
   // cost (from the tuning table when there is one; the truncated law: draws
   // plus its K-term sums, see trunc_cost) times the replicates its busiest
@@ -494,18 +560,13 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
     int64_t r_begin, r_end;  // units start at r_begin, r_begin + kBlock, ... < r_end
   };
   std::vector<Run> runs;
+  std::vector<int> heavy_cells;
   size_t n_units = 0;
   for (int i = 0; i < n_cells; ++i) {
     const DevCell& d = P.cells[i];
     const int64_t r0 = rlo ? rlo[i] : 0;
     if (d.mode == kModeHeavy) {
-      for (int64_t r = 0; r < d.R; r += 8) {
-        Unit u;
-        u.cell = i;
-        u.r0 = r0 + r;
-        u.count = (int32_t)std::min<int64_t>(8, d.R - r);
-        P.hunits.push_back(u);
-      }
+      heavy_cells.push_back(i);
       continue;
     }
     if (d.R <= 0) continue;
@@ -544,6 +605,7 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
       P.units.push_back(u);
     }
   }
+  if (!heavy_cells.empty()) plan_heavy(P, heavy_cells, rlo, n_cu);
   return ZPL_OK;
 }
 
@@ -599,6 +661,8 @@ struct Launch {
   int sim_grid = 0;
   int heavy_grid = 0;
   int64_t hstride = 0;
+  int batch_grid = 0;      // workgroups of the batched heavy kernels
+  int64_t bstride = 0;     // int64 of scratch per wave of them
   int64_t gcap = 0;
   int64_t maxR = 1;
   PlanLayout lay;
@@ -614,9 +678,12 @@ zpl_status prepare(zpl_ctx* c, const Plan& P, int n_q, bool need_dbuf, Launch& L
   ZPL_TRY(ensure(c, c->tables, sizeof(double) * (size_t)kH * nc));
   ZPL_TRY(ensure(c, c->guides, sizeof(uint16_t) * (size_t)(kGuide + 1) * nc));
   // escalation list: a slot for every lane/wave replicate (each escalates at
-  // most once), so it cannot overflow below 2^31 such replicates
+  // most once), so these cannot overflow it below 2^31 such replicates, and
+  // kBatchEsc for the batched heavy form's (batch_eligible keeps them rare)
   const uint32_t esc_cap =
-      (uint32_t)std::min<int64_t>(std::max<int64_t>(P.lw_R, 64), (int64_t)1 << 31);
+      (uint32_t)std::min<int64_t>(std::max<int64_t>(P.lw_R, 64) +
+                                      std::min<int64_t>(P.batch_R, kBatchEsc),
+                                  (int64_t)1 << 31);
   ZPL_TRY(ensure(c, c->esc, sizeof(uint64_t) * esc_cap));
   c->esc_cap = esc_cap;
   const int sim_grid =
@@ -627,11 +694,23 @@ zpl_status prepare(zpl_ctx* c, const Plan& P, int n_q, bool need_dbuf, Launch& L
   ZPL_TRY(ensure(c, c->list_c, sizeof(uint32_t) * nwaves * kListCap));
   ZPL_TRY(ensure(c, c->wslots, (size_t)kWaveSlotBytes * 64 * nwaves));
   L.hstride = heavy_stride(P.max_n);
-  int hg = (int)std::min<int64_t>((int64_t)P.hunits.size() + 64, (int64_t)c->n_cu * 2);
+  int hg = (int)std::min<int64_t>(P.heavy8 + 64, (int64_t)c->n_cu * 2);
   // keep the heavy scratch (one area per wave) within a quarter of the budget
   while (hg > 1 && (uint64_t)hg * kHeavyWaves * L.hstride * 8 > c->budget / 4) hg /= 2;
-  L.heavy_grid = hg;
-  ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)hg * kHeavyWaves * L.hstride));
+  const int64_t area = (int64_t)hg * kHeavyWaves * L.hstride;
+  L.heavy_grid = (int)std::min<int64_t>(hg, (int64_t)P.hunits.size() - P.n_bpure - P.n_bcut + 64);
+  ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)area));
+  // the batched kernels run before the sorting one and share its scratch: as
+  // many workgroups as there are compute units or units, fewer while a wave's
+  // share does not hold one replicate (records, counts, draws)
+  if (P.n_bpure + P.n_bcut > 0) {
+    const int64_t least = 64 * (kWaveSlotBytes / 8) + kHW / 2 + P.batch_max_n;
+    int bg = std::min(std::max(P.n_bpure, P.n_bcut), c->n_cu);
+    while (bg > 1 && area / ((int64_t)bg * kBatchWaves) < least) bg = (bg + 1) / 2;
+    L.batch_grid = bg;
+    L.bstride = area / ((int64_t)bg * kBatchWaves) & ~(int64_t)31;
+    if (L.bstride < least) return fail(ZPL_ENOMEM, "heavy scratch too small for a batch");
+  }
   if (need_dbuf) ZPL_TRY(ensure(c, c->dbuf, sizeof(double) * (size_t)P.total_R));
   // bracket gather: at most ~12% of a cell's replicates fall in a bracket
   int64_t maxR = 1;
@@ -686,10 +765,17 @@ zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, O
                             err, s));
   }
   HIP_TRY(mark(2));
+  const Unit* hunits = (const Unit*)(plan + L.lay.hunits);
+  for (int cut = 0; cut < 2; ++cut)
+    HIP_TRY(launch_batch(std::min(L.batch_grid, cut ? P.n_bcut : P.n_bpure), cut != 0, dcells,
+                         (const double*)c->tables.p, (const uint16_t*)c->guides.p, c->ln,
+                         hunits + (cut ? P.n_bpure : 0), cut ? P.n_bcut : P.n_bpure,
+                         queues + 4 + cut, out, (uint64_t*)c->esc.p, escc, c->esc_cap,
+                         (int64_t*)c->heavy.p, L.bstride, err, s));
   HIP_TRY(launch_heavy(L.heavy_grid, dcells, (const double*)c->tables.p,
-                       (const uint16_t*)c->guides.p, c->ln, (const Unit*)(plan + L.lay.hunits),
-                       (int)P.hunits.size(), (const uint64_t*)c->esc.p, escc, c->esc_cap,
-                       queues + 2, out, (int64_t*)c->heavy.p, L.hstride, s));
+                       (const uint16_t*)c->guides.p, c->ln, hunits + P.n_bpure + P.n_bcut,
+                       (int)P.hunits.size() - P.n_bpure - P.n_bcut, (const uint64_t*)c->esc.p,
+                       escc, c->esc_cap, queues + 2, out, (int64_t*)c->heavy.p, L.hstride, s));
   HIP_TRY(mark(3));
   if (n_q > 0 && Dsel)
     HIP_TRY(launch_select(Dsel, dcells, nc, n_q, (const uint32_t*)(plan + L.lay.qnum),
@@ -832,8 +918,8 @@ zpl_status run_cells(zpl_ctx* c, const zpl_cell* cells, int n_cells, const uint3
 
 // Measures the cost of each eligible form at every grid point: a probe cell
 // with enough replicates to give every compute unit one unit of work (lane
-// and wave forms: kBlock replicates per workgroup; heavy form: 8 per
-// workgroup of its grid), timed with events around the simulation and heavy
+// and wave forms: kBlock replicates per workgroup; heavy form: 4 per
+// wavefront), timed with events around the simulation and heavy
 // launches (table build excluded), best of two runs.
 zpl_status autotune_grid(zpl_ctx* c, const double* alphas, int na, const int64_t* ns, int nn,
                          std::vector<zpl_tune_entry>& out, hipStream_t s) {
@@ -851,7 +937,7 @@ zpl_status autotune_grid(zpl_ctx* c, const double* alphas, int na, const int64_t
       for (int f = 0; f < 3 && st == ZPL_OK; ++f) {
         e.ns_per_replicate[f] = -1.0;
         if (!form_eligible((uint32_t)f, alphas[ia], ns[in])) continue;
-        const int64_t R = f == kModeHeavy ? (int64_t)c->n_cu * 2 * 8 : (int64_t)c->n_cu * kBlock;
+        const int64_t R = f == kModeHeavy ? (int64_t)c->n_cu * kBatchWaves * 4 : (int64_t)c->n_cu * kBlock;
         st = ensure(c, c->dbuf, sizeof(double) * (size_t)R);
         if (st != ZPL_OK) break;
         const zpl_cell z = {alphas[ia], ns[in], R, 0x7475656eull, (uint32_t)(ia * nn + in), 0};
@@ -1425,7 +1511,7 @@ zpl_status zpl_create(zpl_ctx** out, int32_t device, uint64_t mem_budget_bytes) 
   c->device = device;
   c->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
   c->budget = mem_budget_bytes ? mem_budget_bytes : (64ull << 30);
-  hipError_t e = hipMalloc(&c->ln, sizeof(double) * (kH + 2));
+  hipError_t e = hipMalloc(&c->ln, (sizeof(double) + sizeof(uint64_t)) * (kH + 2));
   if (e != hipSuccess) {
     delete c;
     return fail(ZPL_ENOMEM, "hipMalloc(ln): %s", hipGetErrorString(e));

@@ -1731,6 +1731,12 @@ __global__ __launch_bounds__(64 * kHeavyWaves, 2) void k_heavy(
   }
 }
 
+}  // namespace zpl
+
+#include "zpl_batch.hpp"
+
+namespace zpl {
+
 // ---------------------------------------------------------------------------
 // Dataset fit: S, alpha_hat and D of caller data x[0..n) (one wave per
 // dataset).  Same histogram/list/finish arithmetic as the simulated
@@ -2042,11 +2048,13 @@ __global__ __launch_bounds__(256) void k_guide(DevCell* __restrict__ cells,
   }
 }
 
-// ln k for k = 0..kH+1 (ln 0 unused, set to 0).
+// ln k for k = 0..kH+1 (ln 0 unused, set to 0), then ln k 2^53 as integers.
 __global__ void k_ln_table(double* ln) {
   const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (k > kH + 1) return;
-  ln[k] = k == 0 ? 0.0 : log((double)k);
+  const double l = k == 0 ? 0.0 : log((double)k);
+  ln[k] = l;
+  reinterpret_cast<uint64_t*>(ln + kH + 2)[k] = (uint64_t)(l * 0x1p53);
 }
 
 __global__ void k_fill_u32(uint32_t* p, int n, uint32_t v) {
@@ -2715,6 +2723,23 @@ hipError_t launch_heavy(int grid, const DevCell* cells, const double* tables,
   if (grid <= 0) return hipSuccess;
   k_heavy<<<grid, 64 * kHeavyWaves, 0, s>>>(cells, tables, guides, ln, units, n_units, esc_list, esc_count,
                               esc_cap, queues, out, scratch, stride);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch(int grid, bool cut, const DevCell* cells, const double* tables,
+                        const uint16_t* guides, const double* ln, const Unit* units, int n_units,
+                        uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
+                        uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
+                        hipStream_t s) {
+  if (n_units <= 0 || grid <= 0) return hipSuccess;
+  if (cut)
+    k_batch<true, kBatchWavesCut><<<grid, 64 * kBatchWavesCut, 0, s>>>(
+        cells, tables, guides, ln, units, n_units, queue, out, esc_list, esc_count, esc_cap,
+        scratch, stride, err);
+  else
+    k_batch<false, kBatchWaves><<<grid, 64 * kBatchWaves, 0, s>>>(
+        cells, tables, guides, ln, units, n_units, queue, out, esc_list, esc_count, esc_cap,
+        scratch, stride, err);
   return hipGetLastError();
 }
 

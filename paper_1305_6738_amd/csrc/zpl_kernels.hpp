@@ -46,6 +46,13 @@ constexpr int kListCap = 16 * (kHW + kCW);
 // global scratch (sorted there).
 constexpr int kHeavyWaves = 4;
 constexpr int kHeavyHist = 1024;
+// Batched heavy form: wave64 per workgroup (one workgroup per compute unit),
+// for cells without and with a lower cutoff.  Three waves per SIMD are better
+// for the former (heavy tails of 10,000 draws: 5.81 against 6.16 ms at two),
+// two for the latter, whose survival values take more registers (1,000 draws:
+// 7.18 against 7.90 ms at three).
+constexpr int kBatchWaves = 12;
+constexpr int kBatchWavesCut = 8;
 // Allocation-free fit: the overflow values and the compact list of one
 // dataset of up to kNoAllocMaxN values live in a fixed device array of
 // kNoAllocStride int64 (the heavy layout's stride for that n:

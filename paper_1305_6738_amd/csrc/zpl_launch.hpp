@@ -7,6 +7,7 @@
 
 namespace zpl {
 
+// ln k for k = 0..kH+1 (doubles), then ln k 2^53 as integers (uint64).
 hipError_t launch_ln_table(double* ln, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t s);
 // CDF tables (the truncated law's only when any_trunc: a cell with K > 0)
@@ -24,6 +25,14 @@ hipError_t launch_heavy(int grid, const DevCell* cells, const double* tables,
                         int n_units, const uint64_t* esc_list, const uint32_t* esc_count,
                         uint32_t esc_cap, uint32_t* queues, Outputs out, int64_t* scratch,
                         int64_t stride, hipStream_t s);
+// Batched heavy-form units of pure-law cells (cut = false) or of cells with a
+// lower cutoff (cut = true); scratch: an area of `stride` int64 for each wave
+// of the grid (kBatchWaves or kBatchWavesCut per workgroup).
+hipError_t launch_batch(int grid, bool cut, const DevCell* cells, const double* tables,
+                        const uint16_t* guides, const double* ln, const Unit* units, int n_units,
+                        uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
+                        uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
+                        hipStream_t s);
 hipError_t launch_fit(int grid, const int64_t* const* xs, const int64_t* ns, int n_sets,
                       const double* ln, int64_t* scratch, int64_t stride, double* ahat,
                       double* D, uint32_t* flags, uint32_t* status, uint32_t K, hipStream_t s);
