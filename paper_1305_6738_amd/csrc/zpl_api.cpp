@@ -441,7 +441,11 @@ void plan_heavy(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) 
       const int waves = part == 1 ? kBatchWavesCut : kBatchWaves;
       const int64_t per_wave =
           std::min<int64_t>(64, std::max<int64_t>(1, (int64_t)(unit_work / cost(d) / waves)));
-      const int64_t step = part == 2 ? 8 : per_wave * waves;
+      int64_t step = part == 2 ? 8 : per_wave * waves;
+      // too few replicates for every wave of the device: spread over the
+      // compute units, so that the waves of a SIMD do not share its issue slots
+      if (part != 2 && per_wave == 1)
+        step = std::min<int64_t>(waves, std::max<int64_t>(1, (P.batch_R + n_cu - 1) / n_cu));
       for (int64_t r = 0; r < d.R; r += step) {
         Unit u;
         u.cell = i;

@@ -15,16 +15,109 @@
 
 namespace zpl {
 
+// Sums, maxima and scans over the wave by DPP lane moves, which stay in the
+// vector ALU: a step takes its few issue cycles, where a shuffle through the
+// LDS crossbar takes over a hundred (a wave's six-step sum measured about
+// 0.35 us so, and a replicate's fit takes about ten of them).  Steps 1..8
+// shift within rows of 16 lanes, the two broadcasts carry a row's last lane to
+// the next row and the lower half's to the upper: an inclusive scan, lane 63
+// holding the total.  Lanes without a source take 0, so 0 must be the
+// operation's identity.  Every lane of the wave must be active.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp0_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRows, 0xf, false);
+}
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp0_u64(uint64_t v) {
+  return ((uint64_t)dpp0_u32<kCtrl, kRows>((uint32_t)(v >> 32)) << 32) |
+         dpp0_u32<kCtrl, kRows>((uint32_t)v);
+}
+template <class T, class Op>
+__device__ __forceinline__ T dpp_scan(T v, Op op) {
+  if constexpr (sizeof(T) == 4) {
+    v = op(v, dpp0_u32<0x111, 0xf>(v));
+    v = op(v, dpp0_u32<0x112, 0xf>(v));
+    v = op(v, dpp0_u32<0x114, 0xf>(v));
+    v = op(v, dpp0_u32<0x118, 0xf>(v));
+    v = op(v, dpp0_u32<0x142, 0xa>(v));
+    v = op(v, dpp0_u32<0x143, 0xc>(v));
+  } else {
+    v = op(v, dpp0_u64<0x111, 0xf>(v));
+    v = op(v, dpp0_u64<0x112, 0xf>(v));
+    v = op(v, dpp0_u64<0x114, 0xf>(v));
+    v = op(v, dpp0_u64<0x118, 0xf>(v));
+    v = op(v, dpp0_u64<0x142, 0xa>(v));
+    v = op(v, dpp0_u64<0x143, 0xc>(v));
+  }
+  return v;
+}
+__device__ __forceinline__ uint32_t lane63_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint64_t lane63_u64(uint64_t v) {
+  return ((uint64_t)lane63_u32((uint32_t)(v >> 32)) << 32) | lane63_u32((uint32_t)v);
+}
+__device__ __forceinline__ uint32_t dpp_sum_u32(uint32_t v) {
+  return lane63_u32(dpp_scan(v, [](uint32_t a, uint32_t b) { return a + b; }));
+}
+__device__ __forceinline__ uint32_t dpp_or_u32(uint32_t v) {
+  return lane63_u32(dpp_scan(v, [](uint32_t a, uint32_t b) { return a | b; }));
+}
+__device__ __forceinline__ uint32_t dpp_max_u32(uint32_t v) {
+  return lane63_u32(dpp_scan(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }));
+}
+__device__ __forceinline__ uint64_t dpp_sum_u64(uint64_t v) {
+  return lane63_u64(dpp_scan(v, [](uint64_t a, uint64_t b) { return a + b; }));
+}
+// Largest of the wave's values, none of them negative.
+__device__ __forceinline__ double dpp_max_f64(double v) {
+  const uint64_t b = dpp_scan((uint64_t)__double_as_longlong(v), [](uint64_t x, uint64_t y) {
+    return (uint64_t)__double_as_longlong(
+        fmax(__longlong_as_double((long long)x), __longlong_as_double((long long)y)));
+  });
+  return __longlong_as_double((long long)lane63_u64(b));
+}
+__device__ __forceinline__ uint32_t dpp_incl_scan_u32(uint32_t v) {
+  return dpp_scan(v, [](uint32_t a, uint32_t b) { return a + b; });
+}
+
 // Support values are handled as the table index j = v - (xmin - 1) (v itself
 // for the pure law): 1..kHW in the LDS histogram, larger ones in the wave's
 // global scratch.
+//
+// Deferred draws wait in two rings and are resolved 64 at a time.  A tail draw
+// makes one proposal per pass; a rejected one goes back into the ring with its
+// next attempt, one that needs a double-double floor into the second ring, so
+// that a wave runs that long path with all its lanes (at alpha = 1.2 one
+// proposal in 80 needs it, which was half of all passes).  The first ring
+// holds fewer than 64 entries before an iteration's at most 256, and a pass
+// of either ring puts back at most what it takes out, but for at most 64 that
+// come from the second: 384.
+constexpr int kBatchRing = 384;
+constexpr int kHardRing = 128;
 struct alignas(16) BatchLds {
   // bins j = 1..kHW, a pad slot per lane, three rows of per-lane counts of
   // j = 1..3 (the wave form's layout); the bucket table of the larger draws
   // during the KS
   uint32_t hist[kHW + 64 + 3 * 64];
-  uint64_t ring[kRing];  // deferred draws; the gathered draws during the KS
+  uint64_t ring[kBatchRing];  // deferred draws; the gathered draws during the KS
+  uint64_t hard[kHardRing];   // tail proposals whose floor FP64 does not decide
 };
+
+// LDS words as such (address space 3): the functions below are called, not
+// inlined, so that their registers and constants do not crowd the draw loops
+// around the calls, and through a generic pointer their LDS accesses would be
+// flat ones, which are not ordered with the callers' LDS instructions.
+typedef __attribute__((address_space(3))) uint32_t LdsU32;
+typedef __attribute__((address_space(3))) uint64_t LdsU64;
+__device__ __forceinline__ void lds_inc(LdsU32* p) {
+  __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
 
 // The larger draws' buckets: 16 per octave of j, j >= kHW.
 constexpr int kBucketBits = 4;
@@ -85,22 +178,17 @@ __device__ __forceinline__ double readlane_f64(double v, int src) {
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
-__device__ __forceinline__ uint32_t wave_incl_scan32(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t o = (uint32_t)__shfl_up((int)v, d, 64);
-    if (lane >= d) v += o;
-  }
-  return v;
-}
 // Inclusive sum within each group of 16 lanes.
-__device__ __forceinline__ uint32_t row_incl_scan32(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 16; d <<= 1) {
-    const uint32_t o = (uint32_t)__shfl_up((int)v, d, 16);
-    if ((lane & 15) >= d) v += o;
-  }
-  return v;
+__device__ __forceinline__ uint32_t row_incl_scan_u32(uint32_t v) {
+  v += dpp0_u32<0x111, 0xf>(v);
+  v += dpp0_u32<0x112, 0xf>(v);
+  v += dpp0_u32<0x114, 0xf>(v);
+  return v + dpp0_u32<0x118, 0xf>(v);
+}
+// The previous lane's value (0 in lane 0).
+__device__ __forceinline__ uint32_t prev_lane_u32(uint32_t v) { return dpp0_u32<0x138, 0xf>(v); }
+__device__ __forceinline__ double prev_lane_f64(double v) {
+  return __longlong_as_double((long long)dpp0_u64<0x138, 0xf>((uint64_t)__double_as_longlong(v)));
 }
 
 // The stored counts of one replicate: 16-bit for n < 65536, else 32-bit.
@@ -142,16 +230,31 @@ struct CountView {
 constexpr double kPruneMargin = 1e-12;
 
 // D of one replicate by a whole wave, given D0, the largest term over the
-// first jh values (those up to 16, taken from the head sums), and z16 =
-// zeta(a, 17).  cv: the counts of j = 1..hi (hi a multiple of 256, zero
+// values up to 16 (the first jh, taken from the head sums), and z16 =
+// zeta(a, 17).  counts: those of j = 1..hi (hi a multiple of 256, zero
 // above); ov[-1 - p], p < oc: the draws above kHW.  Negative when a bucket in
 // reach of the maximum holds more than kGather draws (the caller redoes the
 // replicate another way).
 template <bool kCut>
-__device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView& cv, int hi,
-                                          const int64_t* __restrict__ ov, uint32_t oc, int64_t n,
-                                          double D0, double z16, int jh, BatchLds* L,
-                                          const double* __restrict__ ln, int lane) {
+static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_,
+                                              const uint32_t* counts, bool wide_, int hi_,
+                                              const int64_t* ov_, uint32_t oc_, int64_t n_,
+                                              double D0, double z16, LdsU32* tab, LdsU64* list,
+                                              const double* ln_) {
+  // every argument is the wave's
+  const int lane = lane_id();
+  const int64_t n = uniform64(n_);
+  const int hi = __builtin_amdgcn_readfirstlane(hi_);
+  const uint32_t oc = (uint32_t)__builtin_amdgcn_readfirstlane((int)oc_);
+  const int64_t* __restrict__ ov = reinterpret_cast<const int64_t*>(uniform64((int64_t)ov_));
+  const double* __restrict__ ln = reinterpret_cast<const double*>(uniform64((int64_t)ln_));
+  const CountView cv{reinterpret_cast<const uint32_t*>(uniform64((int64_t)counts)),
+                     __builtin_amdgcn_readfirstlane((int)wide_) != 0};
+  KsLaw<kCut> w;
+  w.E = em_coef(a);
+  w.iz = iz;
+  w.xmin = kCut ? uniform64(xmin_) : 1;
+  const int jh = w.xmin < 17 ? 17 - (int)w.xmin : 0;
   const double idn = 1.0 / (double)n;
   const int64_t off = kCut ? w.xmin - 1 : 0;
   const uint32_t nu = (uint32_t)n;
@@ -160,12 +263,12 @@ __device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView&
   // 1. the histogram in 64 chunks of 16 values, one per lane
   uint32_t last = 0, sum = 0;
   if (16 * lane < hi) sum = cv.sum16(lane, last);
-  const uint32_t Cr = wave_incl_scan32(sum, lane), Cl = Cr - sum;
+  const uint32_t Cr = dpp_incl_scan_u32(sum), Cl = Cr - sum;
   const double zr = w.survival(off + 16 * (lane + 1), ln);  // right edge of the chunk
   {
     const double z = zr * w.iz, s = (double)(nu - Cr) * idn;
-    const double Dlow = fmax(D, wave_max_f64(fabs(z - s)));
-    double zl = shfl_f64(z, lane > 0 ? lane - 1 : 0), sl = (double)(nu - Cl) * idn;
+    const double Dlow = fmax(D, dpp_max_f64(fabs(z - s)));
+    double zl = prev_lane_f64(z), sl = (double)(nu - Cl) * idn;
     if (lane == 0) {
       zl = 1.0;
       sl = 1.0;
@@ -185,11 +288,11 @@ __device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView&
       const int pc = p < 0 ? 0 : p;
       const int b = 16 * pc + (lane & 15);
       const uint32_t cnt = p < 0 ? 0u : cv.at(b);
-      const uint32_t Ca = (uint32_t)__shfl((int)Cl, pc, 64) + row_incl_scan32(cnt, lane);
+      const uint32_t Ca = (uint32_t)__shfl((int)Cl, pc, 64) + row_incl_scan_u32(cnt);
       const int64_t v = off + b + 1;
       const double zv = w.survival(v, ln);
-      double zp = shfl_f64(zv, lane > 0 ? lane - 1 : 0);
-      uint32_t cp = (uint32_t)__shfl_up((int)cnt, 1, 64);
+      double zp = prev_lane_f64(zv);
+      uint32_t cp = prev_lane_u32(cnt);
       const double zq = shfl_f64(zr, pc > 0 ? pc - 1 : 0);
       const uint32_t cq = (uint32_t)__shfl((int)last, pc > 0 ? pc - 1 : 0, 64);
       if ((lane & 15) == 0) {
@@ -207,7 +310,7 @@ __device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView&
         D = fmax(D, fmax(t1, t2));
       }
     }
-    D = wave_max_f64(D);
+    D = dpp_max_f64(D);
   }
   if (oc == 0u) return D;
   // 2. the larger draws: none can matter when their whole mass is below D
@@ -215,12 +318,11 @@ __device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView&
   if (fmax(zE * w.iz, (double)oc * idn) <= D - kPruneMargin) return D;
   const bool has_top = __builtin_amdgcn_readlane((int)last, 63) != 0;  // j = kHW was drawn
   const uint32_t nbody = nu - oc;
-  uint32_t* tab = L->hist;
   wave_sync();
   for (int k = lane; k < kHW; k += 64) tab[k] = 0u;
   wave_sync();
   for (uint32_t p = (uint32_t)lane; p < oc; p += 64u)
-    atomicAdd(&tab[bucket_of((uint64_t)ov[-1 - (int64_t)p])], 1u);
+    lds_inc(&tab[bucket_of((uint64_t)ov[-1 - (int64_t)p])]);
   wave_sync();
   // an octave per lane, then the buckets of the octaves in reach, four
   // octaves per round; a bucket in reach keeps an entry, the others zero
@@ -229,27 +331,22 @@ __device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView&
     const bool oct = lane < (kBuckets >> kBucketBits);
     uint32_t cs = 0;
     if (oct) {
-      const uint4* q = reinterpret_cast<const uint4*>(tab + 16 * lane);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint4 t = q[k];
-        cs += t.x + t.y + t.z + t.w;
-      }
+      for (int k = 0; k < 16; ++k) cs += tab[16 * lane + k];
     }
-    const uint32_t cr = wave_incl_scan32(cs, lane), cl = cr - cs;
+    const uint32_t cr = dpp_incl_scan_u32(cs), cl = cr - cs;
     const int64_t tr = (int64_t)min((uint64_t)off + bucket_end(16 * (oct ? lane : 52) + 15),
                                     (uint64_t)INT64_MAX);
     const double zo = w.survival(tr, ln) * w.iz;
     const double s = (double)(oc - cr) * idn;
-    double Dlow = fmax(D, wave_max_f64(fabs(zo - s)));
-    double zl = shfl_f64(zo, lane > 0 ? lane - 1 : 0);
+    double Dlow = fmax(D, dpp_max_f64(fabs(zo - s)));
+    double zl = prev_lane_f64(zo);
     if (lane == 0) zl = zE * w.iz;
     const bool need = cs != 0u && fmax(zl - s, (double)(oc - cl) * idn - zo) > Dlow - kPruneMargin;
     uint64_t mask = __ballot(need);
     if (oct && cs != 0u && !need) {
-      uint4* q = reinterpret_cast<uint4*>(tab + 16 * lane);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) q[k] = uint4{0u, 0u, 0u, 0u};
+      for (int k = 0; k < 16; ++k) tab[16 * lane + k] = 0u;
     }
     while (mask != 0ull) {
       int p = -1;
@@ -262,33 +359,32 @@ __device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView&
       const int pc = p < 0 ? 0 : p;
       const int b = 16 * pc + (lane & 15);
       const uint32_t cnt = p < 0 ? 0u : tab[b];
-      const uint32_t ca = (uint32_t)__shfl((int)cl, pc, 64) + row_incl_scan32(cnt, lane);
+      const uint32_t ca = (uint32_t)__shfl((int)cl, pc, 64) + row_incl_scan_u32(cnt);
       const int64_t t = (int64_t)min((uint64_t)off + bucket_end(b), (uint64_t)INT64_MAX);
       const double z = w.survival(t, ln) * w.iz;
       const double sb = (double)(oc - ca) * idn;
-      double zp = shfl_f64(z, lane > 0 ? lane - 1 : 0);
+      double zp = prev_lane_f64(z);
       const double zq = shfl_f64(zl, pc);
       if ((lane & 15) == 0) zp = zq;
-      Dlow = fmax(Dlow, wave_max_f64(p < 0 ? 0.0 : fabs(z - sb)));
+      Dlow = fmax(Dlow, dpp_max_f64(p < 0 ? 0.0 : fabs(z - sb)));
       const bool in = cnt != 0u &&
                       fmax(zp - sb, (double)(oc - (ca - cnt)) * idn - z) > Dlow - kPruneMargin;
       if (p >= 0) tab[b] = in ? bucket_entry(cnt, ca - cnt) : 0u;
       total += in ? cnt : 0u;
     }
-    total = wave_sum_u32(total);
+    total = dpp_sum_u32(total);
   }
   wave_sync();
   // 3. the draws of the buckets in reach, gathered into LDS: in one pass when
   // they fit, else a window of buckets at a time.  A draw equal to the value
   // just below a gathered bucket is gathered as well (it decides a term).
-  uint64_t* list = L->ring;
   int wlo = 0;
   while (total != 0u && wlo < kBuckets) {
     int whi = kBuckets;
     if (total > (uint32_t)kGather) {
       const uint32_t e = wlo + lane < kBuckets ? tab[wlo + lane] : 0u;
       const uint32_t c = (e >> 31) ? ((e >> 22) & 511u) : 0u;
-      const uint32_t cum = wave_incl_scan32(c, lane);
+      const uint32_t cum = dpp_incl_scan_u32(c);
       const uint64_t fit = __ballot(cum <= (uint32_t)kGather);
       const int take = fit == ~0ull ? 64 : __ffsll((long long)~fit) - 1;
       if (take == 0) return -1.0;  // one bucket above the room
@@ -312,11 +408,11 @@ __device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView&
       const uint64_t mt = __ballot(take);
       if (mt != 0ull) {
         const uint32_t pos = m + (uint32_t)__popcll(mt & below);
-        if (take && pos < (uint32_t)kRing) list[pos] = j;
+        if (take && pos < (uint32_t)kBatchRing) list[pos] = j;
         m += (uint32_t)__popcll(mt);
       }
     }
-    if (m > (uint32_t)kRing) return -1.0;
+    if (m > (uint32_t)kBatchRing) return -1.0;
     wave_sync();
     for (uint32_t i0 = 0; i0 < m; i0 += 64u) {
       const uint32_t i = i0 + (uint32_t)lane;
@@ -345,7 +441,7 @@ __device__ __forceinline__ double ks_rest(const KsLaw<kCut>& w, const CountView&
     wave_sync();
     wlo = whi;
   }
-  return wave_max_f64(D);
+  return dpp_max_f64(D);
 }
 
 // ln x 2^53 as an integer, from the context's table behind the logarithms.
@@ -354,6 +450,45 @@ __device__ __forceinline__ const uint64_t* ln_fixed_table(const double* ln) {
 }
 __device__ __forceinline__ uint64_t ln_fixed_at(int64_t v, const double* __restrict__ ln) {
   return v <= (int64_t)(kH + 1) ? ln_fixed_table(ln)[v] : (uint64_t)(log((double)v) * 0x1p53);
+}
+
+// One proposal of the tail sampler (tail_draw_from): taken (X), rejected,
+// rejected above 2^63, or undecided in FP64 (tail_hard repeats it with the
+// floor in double-double).  The last attempt that an entry can hold is taken
+// as the sampler's last resort is (never reached: it would follow 2^21
+// rejections).
+constexpr uint32_t kTailAttempts = (1u << 21) - 1u;
+constexpr uint32_t kTailTaken = 0, kTailRejected = 1, kTailCapped = 2, kTailHard = 3;
+struct TailTry {
+  int64_t X;
+  uint32_t code;
+};
+static __device__ __noinline__ TailTry tail_try(double m0, double beta, double gm, uint32_t k0,
+                                                uint32_t k1, uint32_t i, uint32_t rep,
+                                                uint32_t stream, uint32_t attempt) {
+  const Words4 w = philox4x32_10(i, rep, stream, kTailDomain | attempt, k0, k1);
+  if (attempt == kTailAttempts) return TailTry{(int64_t)m0, kTailTaken};
+  const double V = u53(w.w0, w.w1);
+  const double W = u53(w.w2, w.w3);
+  const double z = -log(V) / beta;
+  const double y = m0 * exp(z);
+  if (y >= 0x1p63 * (1.0 + 0x1p-40)) return TailTry{0, kTailCapped};
+  const double fy = floor(y);
+  const double tol = y * 0x1p-44;
+  if (!(y < 0x1p52 && (y - fy) > tol && (fy + 1.0 - y) > tol)) return TailTry{0, kTailHard};
+  const double wg = W * gm;
+  const bool take = wg * beta <= 1.0 - 0x1p-39 || wg <= tail_g(beta, fy);
+  return TailTry{(int64_t)fy, take ? kTailTaken : kTailRejected};
+}
+static __device__ __noinline__ TailTry tail_hard(double m0, double beta, double gm, uint32_t k0,
+                                                 uint32_t k1, uint32_t i, uint32_t rep,
+                                                 uint32_t stream, uint32_t attempt) {
+  const Words4 w = philox4x32_10(i, rep, stream, kTailDomain | attempt, k0, k1);
+  int64_t X;
+  if (!tail_floor_dd(u53(w.w0, w.w1), beta, m0, &X)) return TailTry{0, kTailCapped};
+  const double wg = u53(w.w2, w.w3) * gm;
+  const bool take = wg * beta <= 1.0 - 0x1p-39 || wg <= tail_g(beta, (double)X);
+  return TailTry{X, take ? kTailTaken : kTailRejected};
 }
 
 // The draws of replicate rep by one wave (the wave form's pipelined loop):
@@ -389,23 +524,56 @@ __device__ __forceinline__ void draw_batch_replicate(const DevCell& c, uint32_t 
       ovn += (uint32_t)__popcll(mb);
     }
   };
-  auto drain = [&](int m) {
+  uint32_t hh = 0, hn = 0;  // the second ring, wave-uniform
+  auto wrap = [](uint32_t p, int size) { return p >= (uint32_t)size ? p - (uint32_t)size : p; };
+  const double m0 = kCut ? (double)(c.xmin + kH) : kTailM;
+  // resolves m entries (one per lane) of the ring, or of the second one
+  auto drain = [&](uint32_t m, bool second) {
     wave_sync();
     int64_t j = 0;
-    if (lane < m) {
-      uint32_t p = qh + (uint32_t)lane;
-      if (p >= (uint32_t)kRing) p -= (uint32_t)kRing;
-      const uint64_t e = L->ring[p];
+    uint32_t code = kTailTaken;
+    uint64_t e = 0;
+    if ((uint32_t)lane < m) {
+      e = second ? L->hard[wrap(hh + (uint32_t)lane, kHardRing)]
+                 : L->ring[wrap(qh + (uint32_t)lane, kBatchRing)];
       if (e >> 63) {
-        const double m0 = kCut ? (double)(c.xmin + kH) : kTailM;
-        j = tail_draw_from(m0, c.beta, c.gm, c.k0, c.k1, (uint32_t)e, rep, c.stream, &fl);
-        if constexpr (kCut) j -= c.xmin - 1;
+        const TailTry t =
+            second ? tail_hard(m0, c.beta, c.gm, c.k0, c.k1, (uint32_t)e, rep, c.stream,
+                               (uint32_t)(e >> 32) & kTailAttempts)
+                   : tail_try(m0, c.beta, c.gm, c.k0, c.k1, (uint32_t)e, rep, c.stream,
+                              (uint32_t)(e >> 32) & kTailAttempts);
+        code = t.code;
+        j = kCut ? t.X - (c.xmin - 1) : t.X;
+        if (code == kTailCapped) fl |= kFlagTailCapped;
       } else {
         j = (int64_t)slow_search(e & ((1ull << 53) - 1), T, guide, sh);
       }
-      if (j <= kHW) atomicAdd(&L->hist[j - 1], 1u);
     }
-    xm = max(xm, j <= kHW ? (int)j : 0);
+    if (second) {
+      hh = wrap(hh + m, kHardRing);
+      hn -= m;
+    } else {
+      qh = wrap(qh + m, kBatchRing);
+      qn -= m;
+    }
+    const uint64_t mr = __ballot(code == kTailRejected || code == kTailCapped);
+    if (mr != 0ull) {
+      if ((mr >> lane) & 1ull)
+        L->ring[wrap(wrap(qh + qn, kBatchRing) + (uint32_t)__popcll(mr & below), kBatchRing)] =
+            e + (1ull << 32);
+      qn += (uint32_t)__popcll(mr);
+    }
+    const uint64_t mh = __ballot(code == kTailHard);
+    if (mh != 0ull) {
+      if (code == kTailHard)
+        L->hard[wrap(wrap(hh + hn, kHardRing) + (uint32_t)__popcll(mh & below), kHardRing)] = e;
+      hn += (uint32_t)__popcll(mh);
+    }
+    if (code != kTailTaken) j = 0;
+    if (j >= 1 && j <= kHW) {
+      atomicAdd(&L->hist[j - 1], 1u);
+      xm = max(xm, (int)j);
+    }
     put_big(j);
   };
   auto gen = [&](uint32_t j0, uint64_t (&Uo)[2 * kWaveBlocks]) {
@@ -462,33 +630,104 @@ __device__ __forceinline__ void draw_batch_replicate(const DevCell& c, uint32_t 
 #pragma unroll
       for (int d = 0; d < 2 * kWaveBlocks; ++d) put_big((int64_t)x[d]);
     }
-    ring_append(L->ring, qh, qn, def, [&](int d) {
+    ring_append<2 * kWaveBlocks, kBatchRing>(L->ring, qh, qn, def, [&](int d) {
       return defer_entry(U[d], timax,
                          2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1),
                          0);
     }, lane);
-    while (qn >= 64u) {
-      drain(64);
-      qh = qh + 64u >= (uint32_t)kRing ? qh + 64u - (uint32_t)kRing : qh + 64u;
-      qn -= 64u;
+    while (qn >= 64u || hn >= 64u) {
+      const bool second = hn >= 64u;
+      drain(64u, second);
     }
 #pragma unroll
     for (int d = 0; d < 2 * kWaveBlocks; ++d) U[d] = Un[d];
   }
-  if (qn > 0u) drain((int)qn);
-  fl = wave_or_u32(fl);
-  hi = ((int)min(wave_max_i64((int64_t)xm), (int64_t)kHW) + 255) & ~255;
+  while (qn > 0u || hn > 0u) {
+    const bool second = hn >= 64u || qn == 0u;
+    drain(min(second ? hn : qn, 64u), second);
+  }
+  fl = dpp_or_u32(fl);
+  hi = ((int)min(dpp_max_u32((uint32_t)xm), (uint32_t)kHW) + 255) & ~255;
   hi = hi < 256 ? 256 : hi;
   wave_sync();
-  const uint32_t c1 = wave_sum_u32(L->hist[kWaveOwn + lane]);
-  const uint32_t c2 = wave_sum_u32(L->hist[kWaveOwn + 64 + lane]);
-  const uint32_t c3 = wave_sum_u32(L->hist[kWaveOwn + 128 + lane]);
+  const uint32_t c1 = dpp_sum_u32(L->hist[kWaveOwn + lane]);
+  const uint32_t c2 = dpp_sum_u32(L->hist[kWaveOwn + 64 + lane]);
+  const uint32_t c3 = dpp_sum_u32(L->hist[kWaveOwn + 128 + lane]);
   if (lane == 0) {
     L->hist[0] += c1;  // drains count 1..3 into the bins themselves
     L->hist[1] += c2;
     L->hist[2] += c3;
   }
   wave_sync();
+}
+
+// MLE and the values up to 16 of the KS, one replicate per lane: alpha_hat,
+// 1 / normaliser, zeta(a, 17) and the largest term over those values.
+struct HeadOut {
+  double a, iz, z16, D;
+  uint32_t flags;
+};
+template <bool kCut>
+static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin,
+                                                 const uint32_t* counts, bool wide,
+                                                 uint32_t flags, const double* __restrict__ ln) {
+  HeadOut o;
+  o.flags = flags;
+  const CountView cv{counts, wide};
+  double suf[17];
+  if constexpr (kCut) {
+    U128 Sx = {0, 0};
+    u128_add_mul(Sx, (uint64_t)n, ln_fixed(xmin, ln));
+    if (S.lo == Sx.lo && S.hi == Sx.hi) {  // every value at the cutoff: one counts as xmin + 1
+      S = U128{0, 0};
+      u128_add_mul(S, (uint64_t)(n - 1), ln_fixed(xmin, ln));
+      u128_add(S, ln_fixed(xmin + 1, ln), 0);
+      o.flags |= kFlagAllOnes;
+    }
+    o.a = mle_alpha_hz(u128_to_S(S) / (double)n, xmin, ln, &o.flags);
+    const EmCoef E = em_coef(o.a);
+    survival_head_cut(E, ln, suf);
+    double zx = 0.0;
+#pragma unroll
+    for (int t = 1; t <= 16; ++t)
+      if (xmin - 1 == t) zx = suf[t];
+    if (xmin > 17) zx = survival_rel(E, xmin - 1, xmin);
+    o.iz = 1.0 / zx;
+  } else {
+    double Sd;
+    if (S.lo == 0 && S.hi == 0) {  // every draw was 1: S := ln 2
+      Sd = ln[2];
+      o.flags |= kFlagAllOnes;
+    } else {
+      Sd = u128_to_S(S);
+    }
+    o.a = mle_alpha(Sd / (double)n, ln, &o.flags);
+    survival_head(em_coef(o.a), ln, suf);
+    o.iz = 1.0 / suf[0];
+  }
+  o.z16 = suf[16];
+  const double idn = 1.0 / (double)n;
+  const int off = kCut ? (int)(xmin < 17 ? xmin - 1 : 16) : 0;
+  uint32_t c16[16];  // read ahead of the terms' branches
+#pragma unroll
+  for (int v = 1; v <= 16; ++v) {
+    const uint32_t t = cv.at(v > off ? v - 1 - off : 0);
+    c16[v - 1] = v > off ? t : 0u;
+  }
+  int64_t C = 0;
+  double D = 0.0;
+#pragma unroll
+  for (int v = 1; v <= 16; ++v) {
+    const uint32_t cn = c16[v - 1];
+    if (cn) {
+      const double t2 = fabs(fma(suf[v - 1], o.iz, -(double)(n - C) * idn));
+      C += cn;
+      const double t1 = fabs(fma(suf[v], o.iz, -(double)(n - C) * idn));
+      D = fmax(D, fmax(t1, t2));
+    }
+  }
+  o.D = D;
+  return o;
 }
 
 // Replicates r0 .. r0 + nrep - 1 of a cell by one wave, in batches that fill
@@ -555,9 +794,9 @@ __device__ __forceinline__ void replicate_batch(const DevCell& c, int32_t cell_i
         shi += lf >> 32;
         if (want_fp) fp += mix64((uint64_t)v);
       }
-      slo = wave_sum_u64(slo);
-      shi = wave_sum_u64(shi);
-      if (want_fp) fp = wave_sum_u64(fp);
+      slo = dpp_sum_u64(slo);
+      shi = dpp_sum_u64(shi);
+      if (want_fp) fp = dpp_sum_u64(fp);
       if (lane == 0) {
         WaveSlot sl;
         sl.S = U128{slo + (shi << 32), (shi >> 32) + (slo + (shi << 32) < slo ? 1u : 0u)};
@@ -574,94 +813,45 @@ __device__ __forceinline__ void replicate_batch(const DevCell& c, int32_t cell_i
     }
     wave_sync_global();  // the batch's records, counts and draws, before they are read back
     // MLE and the head of the KS, one replicate per lane
-    double a = 2.0, D = 0.0, iz = 1.0, z16 = 0.0;
-    uint32_t flags = 0, esc = 0, oc = 0, hib = 256;
+    HeadOut h = {2.0, 1.0, 0.0, 0.0, 0u};
+    uint32_t esc = 0, oc = 0, hib = 256;
     uint64_t fp = 0;
     int64_t ovtop = 0;
-    const int jh = off < 16 ? 16 - (int)off : 0;
     if (lane < q) {
       const WaveSlot sl = slots[lane];
-      flags = sl.flags;
       esc = sl.esc;
       oc = sl.len;
       hib = sl.off;
       fp = sl.fp;
       ovtop = sl.xmax;
-      const CountView cv{reinterpret_cast<const uint32_t*>(counts + lane * cw), wide};
-      double suf[17];
-      if constexpr (kCut) {
-        U128 S = sl.S, Sx = {0, 0};
-        u128_add_mul(Sx, (uint64_t)n, ln_fixed(c.xmin, ln));
-        if (S.lo == Sx.lo && S.hi == Sx.hi) {  // every value at the cutoff: one counts as xmin + 1
-          S = U128{0, 0};
-          u128_add_mul(S, (uint64_t)(n - 1), ln_fixed(c.xmin, ln));
-          u128_add(S, ln_fixed(c.xmin + 1, ln), 0);
-          flags |= kFlagAllOnes;
-        }
-        a = mle_alpha_hz(u128_to_S(S) / (double)n, c.xmin, ln, &flags);
-        const EmCoef E = em_coef(a);
-        survival_head_cut(E, ln, suf);
-        double zx = 0.0;
-#pragma unroll
-        for (int t = 1; t <= 16; ++t)
-          if (c.xmin - 1 == t) zx = suf[t];
-        if (c.xmin > 17) zx = survival_rel(E, c.xmin - 1, c.xmin);
-        iz = 1.0 / zx;
-      } else {
-        double Sd;
-        if (sl.S.lo == 0 && sl.S.hi == 0) {  // every draw was 1: S := ln 2
-          Sd = ln[2];
-          flags |= kFlagAllOnes;
-        } else {
-          Sd = u128_to_S(sl.S);
-        }
-        a = mle_alpha(Sd / (double)n, ln, &flags);
-        survival_head(em_coef(a), ln, suf);
-        iz = 1.0 / suf[0];
-      }
-      z16 = suf[16];
-      const double idn = 1.0 / (double)n;
-      int64_t C = 0;
-#pragma unroll
-      for (int v = 1; v <= 16; ++v) {
-        const int b = v - 1 - (int)(kCut ? (off < 16 ? off : 16) : 0);
-        const uint32_t cn = b >= 0 && b < jh ? cv.at(b < 0 ? 0 : b) : 0u;
-        if (cn) {
-          const double t2 = fabs(fma(suf[v - 1], iz, -(double)(n - C) * idn));
-          C += cn;
-          const double t1 = fabs(fma(suf[v], iz, -(double)(n - C) * idn));
-          D = fmax(D, fmax(t1, t2));
-        }
-      }
+      h = head_lane<kCut>(sl.S, n, c.xmin, reinterpret_cast<const uint32_t*>(counts + lane * cw),
+                          wide, sl.flags, ln);
     }
     // the rest of the KS, one replicate per wave
     for (int i = 0; i < q; ++i) {
       if (__builtin_amdgcn_readlane((int)esc, i) != 0) continue;
-      KsLaw<kCut> w;
-      w.E = em_coef(readlane_f64(a, i));
-      w.iz = readlane_f64(iz, i);
-      w.xmin = kCut ? c.xmin : 1;
-      const CountView cv{reinterpret_cast<const uint32_t*>(counts + i * cw), wide};
       const int64_t tp =
           ((int64_t)__builtin_amdgcn_readlane((int)(ovtop >> 32), i) << 32) |
           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ovtop, i);
       const double Di = ks_rest<kCut>(
-          w, cv, __builtin_amdgcn_readlane((int)hib, i), scratch + tp,
-          (uint32_t)__builtin_amdgcn_readlane((int)oc, i), n, readlane_f64(D, i),
-          readlane_f64(z16, i), jh, L, ln, lane);
-      if (lane == i) D = Di;
+          readlane_f64(h.a, i), readlane_f64(h.iz, i), c.xmin,
+          reinterpret_cast<const uint32_t*>(counts + i * cw), wide,
+          __builtin_amdgcn_readlane((int)hib, i), scratch + tp,
+          (uint32_t)__builtin_amdgcn_readlane((int)oc, i), n, readlane_f64(h.D, i),
+          readlane_f64(h.z16, i), (LdsU32*)L->hist, (LdsU64*)L->ring, ln);
+      if (lane == i) h.D = Di;
     }
     hi = kHW;  // the bucket tables went through the histogram
     if (lane < q) {
       const int64_t rep = r0 + done + lane;
-      if (esc != 0u || D < 0.0) {
+      if (esc != 0u || h.D < 0.0) {
         const uint32_t slot = atomicAdd(esc_count, 1u);
         if (slot < esc_cap)
           esc_list[slot] = ((uint64_t)(uint32_t)cell_id << 32) | (uint32_t)rep;
         else
           atomicOr(err, kErrEscOverflow);
       } else {
-        write_outputs(out, c.out_off + rep, D, a, flags, fp, 0);
+        write_outputs(out, c.out_off + rep, h.D, h.a, h.flags, fp, 0);
       }
     }
     wave_sync_global();  // the next batch overwrites the records

@@ -875,7 +875,7 @@ constexpr int kRing = 320;
 // Appends the draws d with def[d] set (at most 4 per lane) to the ring at
 // head qh holding qn entries; qn is wave-uniform.  Positions come from a
 // wave prefix sum of the per-lane counts (three ballots of its bits).
-template <int ND, class Entry>
+template <int ND, int kSize = kRing, class Entry>
 __device__ __forceinline__ void ring_append(uint64_t* ring, uint32_t qh, uint32_t& qn,
                                             const bool (&def)[ND], Entry entry, int lane) {
   static_assert(ND <= 4, "per-lane count must fit in 3 bits");
@@ -890,7 +890,7 @@ __device__ __forceinline__ void ring_append(uint64_t* ring, uint32_t qh, uint32_
 #pragma unroll
   for (int d = 0; d < ND; ++d) {
     if (def[d]) {
-      ring[pos >= (uint32_t)kRing ? pos - (uint32_t)kRing : pos] = entry(d);
+      ring[pos >= (uint32_t)kSize ? pos - (uint32_t)kSize : pos] = entry(d);
       ++pos;
     }
   }
