@@ -77,8 +77,11 @@ constexpr int64_t kMaxXmin = (int64_t)1 << 40;
 constexpr int64_t kFitBlockMin = 2048;
 // Host datasets up to this many bytes go through pinned staging.
 constexpr size_t kPinStageMax = (size_t)64 << 20;
-// Escalation slots for replicates the batched heavy form cannot finish.
-constexpr int64_t kBatchEsc = 4096;
+// int64 of scratch that each wavefront's worth of a lane- or wave-form unit
+// brings in (its lane-form slots are taken from it).
+constexpr int64_t kFormScratch = 30912;
+// Escalation slots for heavy-form replicates.
+constexpr int64_t kHeavyEsc = 4096;
 
 // P(X > h) under exponent a: the pure law (K = 0) or the truncated law on
 // 1..K (finite sums).
@@ -126,7 +129,7 @@ struct zpl_ctx {
   // work queues, escalation count and error word, cleared by the table
   // kernel, then the quantile results, so that error word and quantiles come
   // back with one copy (layout: PlanLayout)
-  DevBuf plan, ctr, tables, guides, esc, list_v, list_c, wslots, heavy, dbuf, gather, fit_x,
+  DevBuf plan, ctr, tables, guides, esc, slots, heavy, dbuf, gather, fit_x,
       fit_ptrs, fit_ns, fit_out, fit_st, count, boot_d, scan;
   // pinned host staging
   void* pin = nullptr;
@@ -308,21 +311,29 @@ double tuned_cost(const Tuning& t, int f, double alpha, int64_t n) {
 // ---------------------------------------------------------------------------
 struct Plan {
   std::vector<DevCell> cells;
-  std::vector<Unit> units;    // lane and wave units (LPT order)
-  // heavy-form units: [batched pure law | batched cutoff law | the rest]
+  std::vector<Unit> units;    // lane units (longest first)
+  // wave- and heavy-form units: [no cutoff | lower cutoff]
   std::vector<Unit> hunits;
-  int n_bpure = 0, n_bcut = 0;  // lengths of the first two parts
-  int64_t batch_R = 0, batch_max_n = 0;  // replicates and largest n of the batched parts
-  int64_t heavy8 = 0;  // heavy cells' replicates in groups of 8 (sizes the heavy scratch)
+  int n_bpure = 0, n_bcut = 0;  // lengths of the two parts
+  int64_t batch_R = 0;          // their replicates
+  int64_t max_room = 0;         // largest DevCell::room among their cells
+  bool bounded = false;         // some cell's room is less than its n
+  // what the form of each cell alone sizes the scratch by: units of kBlock
+  // lane- and wave-form replicates, and of 8 heavy-form ones
+  int64_t sim_units = 0, heavy8 = 0;
+  int lane_block = kBlock;  // replicates of a lane-form unit
   std::vector<int> cell_unit_begin, cell_unit_end;  // per cell range in `units`
   int64_t total_R = 0;
   int64_t max_n = 0;
   int64_t lw_R = 0;  // replicates in lane and wave cells
+  int64_t wave_R = 0;  // those in wave cells
 };
 
 // Forms a tuned planner may pick: the lane form only where a replicate rarely
-// overflows its per-lane list, the wave form only where the LDS overflow
-// area almost surely holds a replicate's large values.
+// overflows its per-lane list; the wave form up to kWaveTail values above the
+// histogram (wave and heavy cells run in the same kernel and differ in the
+// scratch they bring in).
+constexpr int kWaveTail = 248;
 bool form_eligible(uint32_t m, double alpha, int64_t n, uint32_t K = 0) {
   if (m == kModeLane) {  // values above the column: kLaneCap slots in scratch
     if (n > 65535) return false;
@@ -331,7 +342,7 @@ bool form_eligible(uint32_t m, double alpha, int64_t n, uint32_t K = 0) {
   }
   if (m == kModeWave) {
     const double mu = (double)n * tail_prob(alpha, kHW, K);
-    return mu + 8.0 * std::sqrt(mu) + 8.0 <= (double)kCW;
+    return mu + 8.0 * std::sqrt(mu) + 8.0 <= (double)kWaveTail;
   }
   return true;
 }
@@ -344,12 +355,13 @@ double trunc_cost(int64_t n, uint32_t K) { return 2.2e-3 * ((double)n + 8.6 * (d
 
 // Time for one cell alone under form f (tuned cost v ns per replicate with
 // the device busy): its work units (kBlock replicates per workgroup for the
-// lane and wave forms, kBatchWaves for the heavy form; one workgroup per
-// compute unit) run in rounds of as many units as the device holds at once,
-// and a unit takes v x (replicates the device holds at once).
+// lane and wave forms; the heavy form's replicates spread over the device, in
+// effect 8 for each of two workgroups per compute unit) run in rounds of as
+// many units as the device holds at once, and a unit takes v x (replicates the
+// device holds at once).
 double cell_makespan(int f, double v, int64_t R, int n_cu) {
-  const double per = f == (int)kModeHeavy ? (double)kBatchWaves : (double)kBlock;
-  const double conc = (double)n_cu;
+  const double per = f == (int)kModeHeavy ? 8.0 : (double)kBlock;
+  const double conc = f == (int)kModeHeavy ? 2.0 * n_cu : (double)n_cu;
   return std::ceil(std::ceil((double)R / per) / conc) * v * conc * per;
 }
 
@@ -396,55 +408,51 @@ uint32_t choose_form(double alpha, int64_t n, const Tuning* t, uint32_t K = 0, i
   return kModeHeavy;
 }
 
-// Whether a heavy-form cell runs in the batched kernel: the pure law or the
-// law with a cutoff, and the most populated bucket of the larger draws (16
-// per octave of the table index, the first one) expected to hold at most half
-// of what the kernel gathers in one go.  Others (and replicates that exceed
-// the room after all) run in the sorting kernel.
-bool batch_eligible(const DevCell& d) {
-  if (d.K != 0u || d.n > ((int64_t)1 << 20)) return false;
-  const double b = d.alpha - 1.0;
-  double t;
-  if (d.xmin > 1)  // P(X >= xmin + kHW), the continuous law's: an estimate is enough
-    t = std::pow((double)d.xmin / ((double)d.xmin + (double)kHW), b);
+// Scratch kept free for a wave- or heavy-form replicate's values above the
+// histogram before it is begun: the mean count plus twelve standard
+// deviations, or n where that is no less (and for the law with a cutoff, whose
+// tail is estimated by the continuous one).
+int64_t batch_room(const DevCell& d) {
+  double p;
+  if (d.xmin > 1)
+    p = std::pow((double)d.xmin / ((double)d.xmin + (double)kHW), d.alpha - 1.0) * 1.25;
   else
-    t = tail_prob(d.alpha, kHW);
-  return (double)d.n * t * (1.0 - std::pow(17.0 / 16.0, -b)) <= 128.0;
+    p = tail_prob(d.alpha, kHW, d.K);
+  const double mu = (double)d.n * std::min(p, 1.0);
+  return std::min<int64_t>(d.n, (int64_t)(mu + 12.0 * std::sqrt(mu)) + 64);
 }
 
-// Units of the heavy-form cells, longest replicates first.  A batched unit
+// Units of the wave- and heavy-form cells, longest replicates first.  A unit
 // holds the same number of replicates (up to 64) for each of the kernel's
-// waves, as many as leaves about eight units for each compute unit; a unit of
-// the sorting kernel holds 8 replicates (2 per wave).
-void plan_heavy(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) {
+// waves, as many as leaves about eight units for each compute unit.
+void plan_batch(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) {
+  // a replicate costs about its draws plus 2,000 draws' time for fit and KS
+  auto cost = [](const DevCell& d) { return (double)d.n + 2000.0; };
   std::stable_sort(cells.begin(), cells.end(),
                    [&](int a, int b) { return P.cells[a].n > P.cells[b].n; });
   double work = 0.0;
-  // a replicate costs about its draws plus 2,000 draws' time for fit and KS
-  auto cost = [](const DevCell& d) { return (double)d.n + 2000.0; };
-  std::vector<char> batch(P.cells.size(), 0);
   for (int i : cells) {
-    const DevCell& d = P.cells[i];
-    P.heavy8 += (d.R + 7) / 8;
-    if (!batch_eligible(d)) continue;
-    batch[i] = 1;
+    DevCell& d = P.cells[i];
+    if (d.mode == kModeHeavy) P.heavy8 += (d.R + 7) / 8;
+    const int64_t room = batch_room(d);
+    d.room = (uint32_t)room;
+    P.max_room = std::max(P.max_room, room);
+    P.bounded = P.bounded || room < d.n;
     P.batch_R += d.R;
-    P.batch_max_n = std::max(P.batch_max_n, d.n);
     work += cost(d) * (double)d.R;
   }
   const double unit_work = work / (8.0 * n_cu);
-  for (int part = 0; part < 3; ++part) {
-    const size_t begin = P.hunits.size();
+  for (int cut = 0; cut < 2; ++cut) {
+    const int waves = cut ? kBatchWavesCut : kBatchWaves;
     for (int i : cells) {
       const DevCell& d = P.cells[i];
-      if (part != (batch[i] ? (d.xmin > 1 ? 1 : 0) : 2)) continue;
-      const int waves = part == 1 ? kBatchWavesCut : kBatchWaves;
+      if ((d.xmin > 1) != (cut != 0)) continue;
       const int64_t per_wave =
           std::min<int64_t>(64, std::max<int64_t>(1, (int64_t)(unit_work / cost(d) / waves)));
-      int64_t step = part == 2 ? 8 : per_wave * waves;
+      int64_t step = per_wave * waves;
       // too few replicates for every wave of the device: spread over the
       // compute units, so that the waves of a SIMD do not share its issue slots
-      if (part != 2 && per_wave == 1)
+      if (per_wave == 1)
         step = std::min<int64_t>(waves, std::max<int64_t>(1, (P.batch_R + n_cu - 1) / n_cu));
       for (int64_t r = 0; r < d.R; r += step) {
         Unit u;
@@ -454,9 +462,7 @@ void plan_heavy(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) 
         P.hunits.push_back(u);
       }
     }
-    const int count = (int)(P.hunits.size() - begin);
-    if (part == 0) P.n_bpure = count;
-    if (part == 1) P.n_bcut = count;
+    (cut ? P.n_bcut : P.n_bpure) = (int)P.hunits.size() - (cut ? P.n_bpure : 0);
   }
 }
 
@@ -544,33 +550,29 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
     P.total_R += z.replicates;
     P.max_n = std::max(P.max_n, z.n);
     if (m != kModeHeavy) P.lw_R += z.replicates;
+    if (m == kModeWave) P.wave_R += z.replicates;
   }
-  // units: kBlock replicates (one per lane, or 64 per wave) for lane/wave
-  // cells (heavy cells: plan_heavy).  The longest-first
-  // order weighs a unit by how long it occupies its workgroup: per-replicate
-  // cost (from the tuning table when there is one; the truncated law: draws
-  // plus its K-term sums, see trunc_cost) times the replicates its busiest
-  // wave runs one after another -- min(count, 64) in the wave form, one per
-  // lane (64 in these units) in the lane form.  Weighing by count instead
-  // sent each wave-form cell's last, partial unit to the end of the queue,
-  // where it ran as long as a full one on an otherwise idle device.
-  // Every unit of a cell but the last holds kBlock replicates, so a cell's
-  // units take at most two weights: the order is built from at most two runs
-  // of units per cell (sorted by weight, then cell; a run keeps ascending
-  // replicates), not by sorting the units themselves.
+  // Lane-form units: up to kBlock replicates, one per lane (wave- and heavy-form
+  // cells: plan_batch).  The longest-first order weighs a unit by its
+  // per-replicate cost (from the tuning table when there is one; the truncated
+  // law: draws plus its K-term sums, see trunc_cost): a unit's waves take that
+  // long however many of its lanes hold a replicate.  Sorted by cell, not by
+  // unit: a cell's units follow one another with ascending replicates.
   struct Run {
     double w;
     int cell;
-    int64_t r_begin, r_end;  // units start at r_begin, r_begin + kBlock, ... < r_end
+    int64_t r_begin, r_end;  // its replicates
   };
   std::vector<Run> runs;
-  std::vector<int> heavy_cells;
+  std::vector<int> batch_cells;
   size_t n_units = 0;
+  int64_t lane_R = 0;
+  double lane_work = 0.0, batch_work = 0.0;
   for (int i = 0; i < n_cells; ++i) {
     const DevCell& d = P.cells[i];
-    const int64_t r0 = rlo ? rlo[i] : 0;
-    if (d.mode == kModeHeavy) {
-      heavy_cells.push_back(i);
+    if (d.mode != kModeHeavy) P.sim_units += (d.R + kBlock - 1) / kBlock;
+    if (d.mode != kModeLane) {
+      batch_cells.push_back(i);
       continue;
     }
     if (d.R <= 0) continue;
@@ -579,19 +581,24 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
       const double v = d.K ? trunc_cost(d.n, d.K) : tuned_cost(*tune, (int)d.mode, d.alpha, d.n);
       if (v > 0.0) w = v;
     }
-    auto weight = [&](int64_t count) {
-      return w * (d.mode == kModeLane ? 64.0 : (double)std::min<int64_t>(count, 64));
-    };
-    const int64_t r_last = (d.R - 1) / kBlock * kBlock;
-    const double w_last = weight(d.R - r_last);
-    if (r_last > 0 && weight(kBlock) != w_last) {
-      runs.push_back({weight(kBlock), i, 0, r_last});
-      runs.push_back({w_last, i, r_last, d.R});
-    } else {
-      runs.push_back({w_last, i, 0, d.R});
-    }
-    n_units += (size_t)((d.R + kBlock - 1) / kBlock);
+    runs.push_back({w, i, 0, d.R});
+    lane_R += d.R;
+    lane_work += (double)d.R * ((double)d.n + 200.0);
   }
+  for (int i : batch_cells)
+    batch_work += (double)P.cells[i].R * ((double)P.cells[i].n + 2000.0);
+  // A lane-form unit is kBlock replicates when there are enough to give the
+  // compute units that the lane form's share of the work comes to one each;
+  // else fewer, down to one wave's (of the sizes that divide kBlock), so that
+  // they all have one: 10,000 replicates of 100 draws alone measured 96 us in
+  // 14 workgroups and 42 us in 157.
+  const double cus = std::max(1.0, n_cu * lane_work / std::max(lane_work + batch_work, 1.0));
+  for (int b : {64, 128, 192, 256, 384, kBlock}) {
+    P.lane_block = b;
+    if ((double)lane_R <= cus * b) break;
+  }
+  for (const Run& g : runs)
+    n_units += (size_t)((g.r_end + P.lane_block - 1) / P.lane_block);
   // longest units first; ties by cell so a workgroup tends to keep its table
   std::sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) {
     if (a.w != b.w) return a.w > b.w;
@@ -601,15 +608,15 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
   for (const Run& g : runs) {
     const DevCell& d = P.cells[g.cell];
     const int64_t r0 = rlo ? rlo[g.cell] : 0;
-    for (int64_t r = g.r_begin; r < g.r_end; r += kBlock) {
+    for (int64_t r = g.r_begin; r < g.r_end; r += P.lane_block) {
       Unit u;
       u.cell = g.cell;
       u.r0 = r0 + r;
-      u.count = (int32_t)std::min<int64_t>(kBlock, d.R - r);
+      u.count = (int32_t)std::min<int64_t>(P.lane_block, d.R - r);
       P.units.push_back(u);
     }
   }
-  if (!heavy_cells.empty()) plan_heavy(P, heavy_cells, rlo, n_cu);
+  if (!batch_cells.empty()) plan_batch(P, batch_cells, rlo, n_cu);
   return ZPL_OK;
 }
 
@@ -662,11 +669,9 @@ PlanLayout plan_layout(const Plan& P, int n_q) {
 }
 
 struct Launch {
-  int sim_grid = 0;
-  int heavy_grid = 0;
-  int64_t hstride = 0;
-  int batch_grid = 0;      // workgroups of the batched heavy kernels
-  int64_t bstride = 0;     // int64 of scratch per wave of them
+  SimGrid sim = {0, 0, 0, 0, 0};
+  int cut_grid = 0, esc_grid = 0;      // workgroups of the cutoff and escalation kernels
+  int64_t cstride = 0, estride = 0;    // int64 of scratch per wave of each
   int64_t gcap = 0;
   int64_t maxR = 1;
   PlanLayout lay;
@@ -681,40 +686,45 @@ zpl_status prepare(zpl_ctx* c, const Plan& P, int n_q, bool need_dbuf, Launch& L
   c->err_off = L.lay.err;
   ZPL_TRY(ensure(c, c->tables, sizeof(double) * (size_t)kH * nc));
   ZPL_TRY(ensure(c, c->guides, sizeof(uint16_t) * (size_t)(kGuide + 1) * nc));
-  // escalation list: a slot for every lane/wave replicate (each escalates at
-  // most once), so these cannot overflow it below 2^31 such replicates, and
-  // kBatchEsc for the batched heavy form's (batch_eligible keeps them rare)
-  const uint32_t esc_cap =
-      (uint32_t)std::min<int64_t>(std::max<int64_t>(P.lw_R, 64) +
-                                      std::min<int64_t>(P.batch_R, kBatchEsc),
-                                  (int64_t)1 << 31);
+  // escalation list: a slot for every replicate that may need one (each
+  // escalates at most once), so it cannot overflow below 2^31 of them
+  // (heavy-form replicates escalate only beyond twelve standard deviations)
+  const int64_t esc_R =
+      P.lw_R + (P.bounded ? std::min<int64_t>(P.batch_R - P.wave_R, kHeavyEsc) : 0);
+  const uint32_t esc_cap = (uint32_t)std::min<int64_t>(std::max<int64_t>(esc_R, 64), (int64_t)1 << 31);
   ZPL_TRY(ensure(c, c->esc, sizeof(uint64_t) * esc_cap));
   c->esc_cap = esc_cap;
-  const int sim_grid =
-      (int)std::min<int64_t>((int64_t)P.units.size(), (int64_t)c->n_cu);
-  L.sim_grid = sim_grid;
-  const size_t nwaves = (size_t)std::max(sim_grid, 1) * kWaves;
-  ZPL_TRY(ensure(c, c->list_v, sizeof(int64_t) * nwaves * kListCap));
-  ZPL_TRY(ensure(c, c->list_c, sizeof(uint32_t) * nwaves * kListCap));
-  ZPL_TRY(ensure(c, c->wslots, (size_t)kWaveSlotBytes * 64 * nwaves));
-  L.hstride = heavy_stride(P.max_n);
-  int hg = (int)std::min<int64_t>(P.heavy8 + 64, (int64_t)c->n_cu * 2);
-  // keep the heavy scratch (one area per wave) within a quarter of the budget
-  while (hg > 1 && (uint64_t)hg * kHeavyWaves * L.hstride * 8 > c->budget / 4) hg /= 2;
-  const int64_t area = (int64_t)hg * kHeavyWaves * L.hstride;
-  L.heavy_grid = (int)std::min<int64_t>(hg, (int64_t)P.hunits.size() - P.n_bpure - P.n_bcut + 64);
+  L.sim.lane_wgs = (int)std::min<int64_t>((int64_t)P.units.size(), (int64_t)c->n_cu);
+  L.sim.lane_waves = P.lane_block / 64;
+  const int64_t slots = (int64_t)L.sim.lane_wgs * L.sim.lane_waves * kLaneScratch;
+  ZPL_TRY(ensure(c, c->slots, sizeof(int64_t) * (size_t)slots));
+  // Scratch of the wave and heavy forms.  The least a wave of a batch kernel
+  // works with is one replicate (records, counts, its room), an escalated one
+  // needs all of its draws; the more there is, the more replicates a wave
+  // finishes together.  Its size follows the forms: 2.9 MiB for each workgroup
+  // of kBlock lane- and wave-form replicates less the lane form's slots, and
+  // four areas of a sorted replicate's size (heavy_stride) for each 8
+  // heavy-form ones, up to two per compute unit and a quarter of the budget.
+  const int64_t hstride = heavy_stride(P.max_n);
+  int64_t hg = std::min<int64_t>(P.heavy8 + 64, (int64_t)c->n_cu * 2);
+  while (hg > 1 && (uint64_t)hg * 4 * hstride * 8 > c->budget / 4) hg /= 2;
+  const int64_t sim_wgs = std::max<int64_t>(1, std::min<int64_t>(P.sim_units, c->n_cu));
+  const int64_t area = hg * 4 * hstride + sim_wgs * kWaves * kFormScratch -
+                       slots - (esc_R - P.lw_R);
   ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)area));
-  // the batched kernels run before the sorting one and share its scratch: as
-  // many workgroups as there are compute units or units, fewer while a wave's
-  // share does not hold one replicate (records, counts, draws)
-  if (P.n_bpure + P.n_bcut > 0) {
-    const int64_t least = 64 * (kWaveSlotBytes / 8) + kHW / 2 + P.batch_max_n;
-    int bg = std::min(std::max(P.n_bpure, P.n_bcut), c->n_cu);
-    while (bg > 1 && area / ((int64_t)bg * kBatchWaves) < least) bg = (bg + 1) / 2;
-    L.batch_grid = bg;
-    L.bstride = area / ((int64_t)bg * kBatchWaves) & ~(int64_t)31;
-    if (L.bstride < least) return fail(ZPL_ENOMEM, "heavy scratch too small for a batch");
-  }
+  const int64_t fixed = 64 * (kWaveSlotBytes / 8) + kHW / 2;
+  auto share = [&](int units, int waves, int64_t room, int& grid, int64_t& stride) {
+    int64_t g = std::min<int64_t>(units, c->n_cu);
+    while (g > 1 && area / (g * waves) < fixed + room) g = (g + 1) / 2;
+    grid = (int)g;
+    stride = g > 0 ? area / (g * waves) & ~(int64_t)31 : 0;
+  };
+  share(P.n_bpure, kBatchWaves, P.max_room, L.sim.batch_wgs, L.sim.stride);
+  L.sim.grid = std::min(L.sim.lane_wgs + L.sim.batch_wgs, c->n_cu);
+  share(P.n_bcut, kBatchWavesCut, P.max_room, L.cut_grid, L.cstride);
+  L.esc_grid = 0;
+  if (!P.units.empty() || P.bounded)
+    share(64, kEscWaves, P.max_n, L.esc_grid, L.estride);
   if (need_dbuf) ZPL_TRY(ensure(c, c->dbuf, sizeof(double) * (size_t)P.total_R));
   // bracket gather: at most ~12% of a cell's replicates fall in a bracket
   int64_t maxR = 1;
@@ -750,36 +760,36 @@ zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, O
                         any_trunc, queues, L.lay.ctr_words));
   HIP_TRY(mark(1));
   const Unit* units = (const Unit*)(plan + L.lay.units);
-  if (launch == ZPL_LAUNCH_PLAIN) {
+  const Unit* hunits = (const Unit*)(plan + L.lay.hunits);
+  auto simulate = [&](const SimGrid& g, const Unit* u, int nu, uint32_t* queue, int nb) {
+    return launch_simulate(g, dcells, (const double*)c->tables.p, (const uint16_t*)c->guides.p,
+                           c->ln, u, nu, hunits, nb, queue, queues + 2, out,
+                           (uint64_t*)c->esc.p, escc, c->esc_cap, (int64_t*)c->slots.p,
+                           (int64_t*)c->heavy.p, err, s);
+  };
+  if (launch == ZPL_LAUNCH_PLAIN) {  // the lane-form cells one by one, then the others
     for (int i = 0; i < nc; ++i) {
       const int b = P.cell_unit_begin[i], e = P.cell_unit_end[i];
       if (e <= b) continue;
-      const int grid = std::min(e - b, c->n_cu);
-      HIP_TRY(launch_simulate(grid, dcells, (const double*)c->tables.p,
-                              (const uint16_t*)c->guides.p, c->ln, units + b, e - b,
-                              queues + 8 + i, out, (uint64_t*)c->esc.p, escc, c->esc_cap,
-                              (int64_t*)c->list_v.p, (uint32_t*)c->list_c.p, c->wslots.p,
-                              err, s));
+      const int grid = std::min(e - b, L.sim.lane_wgs);
+      HIP_TRY(simulate(SimGrid{grid, grid, L.sim.lane_waves, 0, 0}, units + b, e - b,
+                       queues + 8 + i, 0));
     }
+    if (P.n_bpure > 0)
+      HIP_TRY(simulate(SimGrid{L.sim.batch_wgs, 0, 0, L.sim.batch_wgs, L.sim.stride}, units, 0,
+                       queues, P.n_bpure));
   } else {
-    HIP_TRY(launch_simulate(L.sim_grid, dcells, (const double*)c->tables.p,
-                            (const uint16_t*)c->guides.p, c->ln, units, (int)P.units.size(),
-                            queues + 0, out, (uint64_t*)c->esc.p, escc, c->esc_cap,
-                            (int64_t*)c->list_v.p, (uint32_t*)c->list_c.p, c->wslots.p,
-                            err, s));
+    HIP_TRY(simulate(L.sim, units, (int)P.units.size(), queues, P.n_bpure));
   }
   HIP_TRY(mark(2));
-  const Unit* hunits = (const Unit*)(plan + L.lay.hunits);
-  for (int cut = 0; cut < 2; ++cut)
-    HIP_TRY(launch_batch(std::min(L.batch_grid, cut ? P.n_bcut : P.n_bpure), cut != 0, dcells,
-                         (const double*)c->tables.p, (const uint16_t*)c->guides.p, c->ln,
-                         hunits + (cut ? P.n_bpure : 0), cut ? P.n_bcut : P.n_bpure,
-                         queues + 4 + cut, out, (uint64_t*)c->esc.p, escc, c->esc_cap,
-                         (int64_t*)c->heavy.p, L.bstride, err, s));
-  HIP_TRY(launch_heavy(L.heavy_grid, dcells, (const double*)c->tables.p,
-                       (const uint16_t*)c->guides.p, c->ln, hunits + P.n_bpure + P.n_bcut,
-                       (int)P.hunits.size() - P.n_bpure - P.n_bcut, (const uint64_t*)c->esc.p,
-                       escc, c->esc_cap, queues + 2, out, (int64_t*)c->heavy.p, L.hstride, s));
+  HIP_TRY(launch_cutoff(L.cut_grid, dcells, (const double*)c->tables.p,
+                        (const uint16_t*)c->guides.p, c->ln, hunits + P.n_bpure, P.n_bcut,
+                        queues + 3, out, (uint64_t*)c->esc.p, escc, c->esc_cap,
+                        (int64_t*)c->heavy.p, L.cstride, err, s));
+  HIP_TRY(launch_escalated(L.esc_grid, dcells, (const double*)c->tables.p,
+                           (const uint16_t*)c->guides.p, c->ln, queues + 4, out,
+                           (uint64_t*)c->esc.p, escc, c->esc_cap, (int64_t*)c->heavy.p, L.estride,
+                           err, s));
   HIP_TRY(mark(3));
   if (n_q > 0 && Dsel)
     HIP_TRY(launch_select(Dsel, dcells, nc, n_q, (const uint32_t*)(plan + L.lay.qnum),
@@ -946,7 +956,7 @@ zpl_status autotune_grid(zpl_ctx* c, const double* alphas, int na, const int64_t
         if (st != ZPL_OK) break;
         const zpl_cell z = {alphas[ia], ns[in], R, 0x7475656eull, (uint32_t)(ia * nn + in), 0};
         const zpl_sim_opts o = {ZPL_LAUNCH_BATCHED, f + 1, 0, 0};
-        Outputs po{(double*)c->dbuf.p, nullptr, nullptr, nullptr, nullptr};
+        Outputs po{(double*)c->dbuf.p, nullptr, nullptr, nullptr};
         double best = -1.0;
         for (int rep = 0; rep < 2 && st == ZPL_OK; ++rep) {
           st = run_cells(c, &z, 1, nullptr, nullptr, 0, nullptr, po, &o, s);
@@ -1335,7 +1345,7 @@ zpl_status Server::run_slice(std::vector<Req*>& finished) {
     total += win[i];
   }
   ZPL_TRY(ensure(c, c->boot_d, sizeof(double) * (size_t)total));
-  Outputs out{(double*)c->boot_d.p, nullptr, nullptr, nullptr, nullptr};
+  Outputs out{(double*)c->boot_d.p, nullptr, nullptr, nullptr};
   ZPL_TRY(run_cells(c, cells.data(), na, nullptr, nullptr, 0, nullptr, out, nullptr, s,
                     rlo.data()));
   // counts of D_b >= D_obs per window: cells {out_off = window start, R = window}
@@ -1515,7 +1525,8 @@ zpl_status zpl_create(zpl_ctx** out, int32_t device, uint64_t mem_budget_bytes) 
   c->device = device;
   c->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
   c->budget = mem_budget_bytes ? mem_budget_bytes : (64ull << 30);
-  hipError_t e = hipMalloc(&c->ln, (sizeof(double) + sizeof(uint64_t)) * (kH + 2));
+  hipError_t e = hipMalloc(&c->ln, (sizeof(double) + sizeof(uint64_t)) * (kH + 2) +
+                                         sizeof(double) * 2 * kGuessN);
   if (e != hipSuccess) {
     delete c;
     return fail(ZPL_ENOMEM, "hipMalloc(ln): %s", hipGetErrorString(e));
@@ -1546,7 +1557,7 @@ void zpl_destroy(zpl_ctx* c) {
   (void)hipDeviceSynchronize();
   if (c->graph_valid) (void)hipGraphExecDestroy(c->graph_exec);
   DevBuf* bufs[] = {&c->plan,   &c->ctr,      &c->tables, &c->guides, &c->esc,
-                    &c->list_v, &c->list_c,   &c->wslots, &c->heavy,  &c->gather,
+                    &c->slots, &c->heavy,  &c->gather,
                     &c->dbuf,   &c->fit_x,    &c->fit_ptrs, &c->fit_ns, &c->fit_out,
                     &c->fit_st, &c->count,    &c->boot_d, &c->scan};
   for (DevBuf* b : bufs)
@@ -1569,7 +1580,7 @@ zpl_status zpl_simulate_cells(zpl_ctx* c, const zpl_cell* cells, int32_t n_cells
   if (!c) return fail(ZPL_EINVAL, "ctx is NULL");
   if (n_cells < 1 || !cells) return fail(ZPL_EINVAL, "need at least one cell");
   HIP_TRY(hipSetDevice(c->device));
-  Outputs out{d_out, alpha_hat_out, flags_out, fingerprint_out, nullptr};
+  Outputs out{d_out, alpha_hat_out, flags_out, fingerprint_out};
   return run_cells(c, cells, n_cells, q_num, q_den, quantiles ? n_q : 0, quantiles, out, opts,
                    (hipStream_t)stream);
 }
@@ -1614,7 +1625,7 @@ zpl_status zpl_critical_table(zpl_ctx* c, const double* gammas, int32_t n_gamma,
   std::vector<double> q((size_t)n_runs * n_q);
   for (int64_t r0 = 0; r0 < n_runs; r0 += cap) {
     const int nr = (int)std::min<int64_t>(cap, n_runs - r0);
-    Outputs out{nullptr, nullptr, nullptr, nullptr, nullptr};
+    Outputs out{nullptr, nullptr, nullptr, nullptr};
     ZPL_TRY(run_cells(c, runs.data() + r0, nr, q_num, q_den, n_q, q.data() + r0 * n_q, out,
                       nullptr, s));
   }
@@ -1836,7 +1847,7 @@ zpl_status zpl_bootstrap_pvalue(zpl_ctx* c, const int64_t* x, int64_t n, int32_t
   zpl_cell cell = {*alpha_hat, n, B, seed, stream_id, 0};
   ZPL_TRY(ensure(c, c->boot_d, sizeof(double) * (size_t)B + 64));
   ZPL_TRY(ensure(c, c->count, sizeof(unsigned long long) + sizeof(double)));
-  Outputs out{(double*)c->boot_d.p, nullptr, nullptr, nullptr, nullptr};
+  Outputs out{(double*)c->boot_d.p, nullptr, nullptr, nullptr};
   ZPL_TRY(run_cells(c, &cell, 1, nullptr, nullptr, 0, nullptr, out, nullptr, s));
   // D_obs to the device, count D_b >= D_obs
   ZPL_TRY(ensure_pinned(c, 64));

@@ -82,7 +82,7 @@ __device__ __forceinline__ uint32_t dpp_incl_scan_u32(uint32_t v) {
 }
 
 // Support values are handled as the table index j = v - (xmin - 1) (v itself
-// for the pure law): 1..kHW in the LDS histogram, larger ones in the wave's
+// without a cutoff): 1..kHW in the LDS histogram, larger ones in the wave's
 // global scratch.
 //
 // Deferred draws wait in two rings and are resolved 64 at a time.  A tail draw
@@ -95,72 +95,80 @@ __device__ __forceinline__ uint32_t dpp_incl_scan_u32(uint32_t v) {
 // come from the second: 384.
 constexpr int kBatchRing = 384;
 constexpr int kHardRing = 128;
+// Histogram layout: bins of j = 1..kHW, one pad slot per lane (the draw loop's
+// no-op counts, never read), then three rows of per-lane counts of j = 1, 2 and
+// 3 (most draws: a lane counting into its own slot never conflicts with
+// another lane).
+constexpr int kWavePad = kHW;
+constexpr int kWaveOwn = kHW + 64;
+// Draw blocks per lane per iteration of the draw loop.
+constexpr int kWaveBlocks = 2;
+static_assert(kWaveBlocks == 2, "the draw loop keeps four table reads in flight");
 struct alignas(16) BatchLds {
-  // bins j = 1..kHW, a pad slot per lane, three rows of per-lane counts of
-  // j = 1..3 (the wave form's layout); the bucket table of the larger draws
-  // during the KS
+  // during the KS the bin table of the larger draws
   uint32_t hist[kHW + 64 + 3 * 64];
   uint64_t ring[kBatchRing];  // deferred draws; the gathered draws during the KS
   uint64_t hard[kHardRing];   // tail proposals whose floor FP64 does not decide
 };
 
-// LDS words as such (address space 3): the functions below are called, not
-// inlined, so that their registers and constants do not crowd the draw loops
-// around the calls, and through a generic pointer their LDS accesses would be
-// flat ones, which are not ordered with the callers' LDS instructions.
-typedef __attribute__((address_space(3))) uint32_t LdsU32;
-typedef __attribute__((address_space(3))) uint64_t LdsU64;
-__device__ __forceinline__ void lds_inc(LdsU32* p) {
-  __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ int64_t uniform64(int64_t v) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// The larger draws' buckets: 16 per octave of j, j >= kHW.
+// The larger draws are counted in tables of kHW bins: first 16 per octave of
+// j (j >= kHW), then, for a bin in reach of the maximum that holds too many
+// draws to gather, a power-of-two range of j in equal bins of 2^sh values.
 constexpr int kBucketBits = 4;
 constexpr int kBuckets = (63 - 10) << kBucketBits;  // octaves 10..62
-static_assert(kHW == 1024 && kBuckets <= kHW, "the bucket table takes the histogram's place");
-// Gathered draws per pass (the ring's room, less ghosts) and the largest count
-// of one bucket; a replicate with a larger bucket in reach of the maximum goes
-// to the heavy kernel.
-constexpr int kGather = 256;
+static_assert(kHW == 1024 && kBuckets <= kHW, "the bin table takes the histogram's place");
+// Draws gathered per pass (the ring's room, less the draws just below a bin),
+// and the count from which a bin is split instead.
+constexpr uint32_t kGather = 256;
+constexpr uint32_t kManyDraws = 255;
+// A bin in reach keeps the number of larger draws below it (n <= 2^31), with
+// the mark for a draw just below its first value.
+constexpr uint32_t kNoBin = 0xffffffffu;
+constexpr uint32_t kBelowDrawn = 0x80000000u;
 
-__device__ __forceinline__ int bucket_of(uint64_t j) {
-  const int e = 63 - __clzll((long long)j);
-  return ((e - 10) << kBucketBits) + (int)((j >> (e - kBucketBits)) & ((1u << kBucketBits) - 1u));
-}
-// Largest j of bucket b (up to 2^63 - 1).
-__device__ __forceinline__ uint64_t bucket_end(int b) {
-  const int e = 10 + (b >> kBucketBits);
-  const uint64_t m = (uint64_t)(b & ((1 << kBucketBits) - 1)) + (1u << kBucketBits) + 1u;
-  return (m << (e - kBucketBits)) - 1u;
-}
+struct Bins {
+  uint64_t lo;  // first j
+  int sh;       // negative: 16 per octave from kHW on
+  __device__ __forceinline__ int of(uint64_t j) const {
+    if (sh >= 0) return (int)((j - lo) >> sh);
+    const int e = 63 - __clzll((long long)j);
+    return ((e - 10) << kBucketBits) + (int)((j >> (e - kBucketBits)) & ((1u << kBucketBits) - 1u));
+  }
+  __device__ __forceinline__ uint64_t start(int b) const {
+    if (sh >= 0) return lo + ((uint64_t)b << sh);
+    const int e = 10 + (b >> kBucketBits);
+    return ((uint64_t)(b & ((1 << kBucketBits) - 1)) + (1u << kBucketBits)) << (e - kBucketBits);
+  }
+  __device__ __forceinline__ int width_bits(int b) const {
+    return sh >= 0 ? sh : 10 + (b >> kBucketBits) - kBucketBits;
+  }
+  __device__ __forceinline__ uint64_t end(int b) const {  // last j of bin b
+    return start(b) + ((uint64_t)1 << width_bits(b)) - 1u;
+  }
+};
 
-// A flagged bucket's entry: bit 31, its count (9 bits, saturated), and the
-// larger draws below it (22 bits).
-constexpr int64_t kBatchMaxN = (int64_t)1 << 20;
-__device__ __forceinline__ uint32_t bucket_entry(uint32_t count, uint32_t below) {
-  return 0x80000000u | ((count > 511u ? 511u : count) << 22) | below;
-}
+// The laws: the functions below are instantiated for each, so that one does
+// not take the registers of another's sums.
+enum Law { kPure = 0, kCutoff = 1, kTrunc = 2 };
 
 // The law at alpha_hat as the KS needs it.
-template <bool kCut>
+template <int kLaw>
 struct KsLaw {
   EmCoef E;
   double iz;     // 1 / normaliser
-  int64_t xmin;  // kCut: the cutoff
+  int64_t xmin;  // the cutoff (1 without)
+  TruncEnd te;   // the truncated law's (trunc_em)
   // sum of k^-a over k > t (t >= 16), relative to xmin^-a for cutoffs above 17
   __device__ __forceinline__ double survival(int64_t t, const double* __restrict__ ln) const {
-    if constexpr (kCut)
+    if constexpr (kLaw == kCutoff)
       return xmin > 17 ? survival_rel(E, t, xmin) : survival_next_cut(E, t, ln);
+    else if constexpr (kLaw == kTrunc)
+      return trunc_tail(E, te, t, ln[t < (int64_t)kH ? t + 1 : 0]);
     else
       return survival_next(E, t, ln);
   }
   __device__ __forceinline__ double point(int64_t v, const double* __restrict__ ln) const {
-    if constexpr (kCut)
+    if constexpr (kLaw == kCutoff)
       if (xmin > 17) return pow_rel(E.s, v, xmin);
     return pow_neg(E.s, ln_value(v, ln));
   }
@@ -225,41 +233,55 @@ struct CountView {
   }
 };
 
-// Distances closer than this to the largest one found are always evaluated:
-// far above the rounding of a bound (a few 2^-53), far below any distance.
-constexpr double kPruneMargin = 1e-12;
-
 // D of one replicate by a whole wave, given D0, the largest term over the
-// values up to 16 (the first jh, taken from the head sums), and z16 =
-// zeta(a, 17).  counts: those of j = 1..hi (hi a multiple of 256, zero
-// above); ov[-1 - p], p < oc: the draws above kHW.  Negative when a bucket in
-// reach of the maximum holds more than kGather draws (the caller redoes the
-// replicate another way).
-template <bool kCut>
-static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_,
+// values up to 16 (taken from the head sums), and z16 = zeta(a, 17).  counts:
+// those of j = 1..hi (hi a multiple of 256, zero above); ov[-1 - p], p < oc:
+// the draws above kHW, in any order.  tab, list, level: the wave's LDS
+// (kHW + 256 words, kBatchRing and kHardRing entries).
+template <int kLaw>
+static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_, uint32_t K_,
                                               const uint32_t* counts, bool wide_, int hi_,
                                               const int64_t* ov_, uint32_t oc_, int64_t n_,
                                               double D0, double z16, LdsU32* tab, LdsU64* list,
-                                              const double* ln_) {
+                                              LdsU64* level, const double* ln_) {
   // every argument is the wave's
   const int lane = lane_id();
-  const int64_t n = uniform64(n_);
+  const uint32_t nu = (uint32_t)uniform64(n_);
+  const double idn = 1.0 / (double)n_;
   const int hi = __builtin_amdgcn_readfirstlane(hi_);
   const uint32_t oc = (uint32_t)__builtin_amdgcn_readfirstlane((int)oc_);
   const int64_t* __restrict__ ov = reinterpret_cast<const int64_t*>(uniform64((int64_t)ov_));
   const double* __restrict__ ln = reinterpret_cast<const double*>(uniform64((int64_t)ln_));
   const CountView cv{reinterpret_cast<const uint32_t*>(uniform64((int64_t)counts)),
                      __builtin_amdgcn_readfirstlane((int)wide_) != 0};
-  KsLaw<kCut> w;
+  KsLaw<kLaw> w;
   w.E = em_coef(a);
   w.iz = iz;
-  w.xmin = kCut ? uniform64(xmin_) : 1;
-  const int jh = w.xmin < 17 ? 17 - (int)w.xmin : 0;
-  const double idn = 1.0 / (double)n;
-  const int64_t off = kCut ? w.xmin - 1 : 0;
-  const uint32_t nu = (uint32_t)n;
+  w.xmin = kLaw == kCutoff ? uniform64(xmin_) : 1;
+  if constexpr (kLaw == kTrunc)
+    w.te = trunc_end(w.E, (uint32_t)__builtin_amdgcn_readfirstlane((int)K_), ln);
+  const int64_t off = w.xmin - 1;
+  const int jh = off < 16 ? 16 - (int)off : 0;  // values up to 16
   const uint64_t below = lanes_below(lane);
-  double D = D0;
+  double D = D0;  // the lane's largest term
+  // the two terms of a sample value v: zv and zv1 the survival sums past v and
+  // past v - 1, Cb draws below v, c equal to it
+  auto terms = [&](double zv, double zv1, uint32_t Cb, uint32_t c) {
+    const double t2 = fabs(fma(zv1, w.iz, -(double)(nu - Cb) * idn));
+    const double t1 = fabs(fma(zv, w.iz, -(double)(nu - Cb - c) * idn));
+    D = fmax(D, fmax(t1, t2));
+  };
+  // the next four set bits of mask, one for each 16 lanes (-1: none)
+  auto next4 = [&](uint64_t& mask) {
+    int p = -1;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int q = mask != 0ull ? __ffsll((long long)mask) - 1 : -1;
+      mask &= mask - 1ull;
+      if ((lane >> 4) == g) p = q;
+    }
+    return p;
+  };
   // 1. the histogram in 64 chunks of 16 values, one per lane
   uint32_t last = 0, sum = 0;
   if (16 * lane < hi) sum = cv.sum16(lane, last);
@@ -278,13 +300,7 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
     uint64_t mask = __ballot(need);
     // four chunks per round, one value per lane
     while (mask != 0ull) {
-      int p = -1;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int q = mask != 0ull ? __ffsll((long long)mask) - 1 : -1;
-        mask &= mask - 1ull;
-        if ((lane >> 4) == g) p = q;
-      }
+      const int p = next4(mask);
       const int pc = p < 0 ? 0 : p;
       const int b = 16 * pc + (lane & 15);
       const uint32_t cnt = p < 0 ? 0u : cv.at(b);
@@ -303,154 +319,208 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
         zp = z16;
         cp = 1u;
       }
-      if (cnt != 0u && b >= jh) {
-        const double zv1 = cp != 0u ? zp : zv + w.point(v, ln);
-        const double t2 = fabs(fma(zv1, w.iz, -(double)(nu - (Ca - cnt)) * idn));
-        const double t1 = fabs(fma(zv, w.iz, -(double)(nu - Ca) * idn));
-        D = fmax(D, fmax(t1, t2));
-      }
+      if (cnt != 0u && b >= jh) terms(zv, cp != 0u ? zp : zv + w.point(v, ln), Ca - cnt, cnt);
     }
     D = dpp_max_f64(D);
   }
-  if (oc == 0u) return D;
   // 2. the larger draws: none can matter when their whole mass is below D
   const double zE = readlane_f64(zr, 63);
-  if (fmax(zE * w.iz, (double)oc * idn) <= D - kPruneMargin) return D;
+  if (oc == 0u || fmax(zE * w.iz, (double)oc * idn) <= D - kPruneMargin) return D;
   const bool has_top = __builtin_amdgcn_readlane((int)last, 63) != 0;  // j = kHW was drawn
   const uint32_t nbody = nu - oc;
-  wave_sync();
-  for (int k = lane; k < kHW; k += 64) tab[k] = 0u;
-  wave_sync();
-  for (uint32_t p = (uint32_t)lane; p < oc; p += 64u)
-    lds_inc(&tab[bucket_of((uint64_t)ov[-1 - (int64_t)p])]);
-  wave_sync();
-  // an octave per lane, then the buckets of the octaves in reach, four
-  // octaves per round; a bucket in reach keeps an entry, the others zero
-  uint32_t total = 0;
-  {
-    const bool oct = lane < (kBuckets >> kBucketBits);
-    uint32_t cs = 0;
-    if (oct) {
-#pragma unroll
-      for (int k = 0; k < 16; ++k) cs += tab[16 * lane + k];
-    }
-    const uint32_t cr = dpp_incl_scan_u32(cs), cl = cr - cs;
-    const int64_t tr = (int64_t)min((uint64_t)off + bucket_end(16 * (oct ? lane : 52) + 15),
-                                    (uint64_t)INT64_MAX);
-    const double zo = w.survival(tr, ln) * w.iz;
-    const double s = (double)(oc - cr) * idn;
-    double Dlow = fmax(D, dpp_max_f64(fabs(zo - s)));
-    double zl = prev_lane_f64(zo);
-    if (lane == 0) zl = zE * w.iz;
-    const bool need = cs != 0u && fmax(zl - s, (double)(oc - cl) * idn - zo) > Dlow - kPruneMargin;
-    uint64_t mask = __ballot(need);
-    if (oct && cs != 0u && !need) {
-#pragma unroll
-      for (int k = 0; k < 16; ++k) tab[16 * lane + k] = 0u;
-    }
-    while (mask != 0ull) {
-      int p = -1;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int q = mask != 0ull ? __ffsll((long long)mask) - 1 : -1;
-        mask &= mask - 1ull;
-        if ((lane >> 4) == g) p = q;
+  LdsU8* many = (LdsU8*)(tab + kHW);  // counts of the bins in reach, up to kManyDraws
+  int depth = 0, next = 0;
+  Bins B{(uint64_t)kHW, -1};
+  while (depth >= 0) {
+    // the table of the range; draws below it; whether the value just below it
+    // was drawn
+    wave_sync();
+    for (int k = lane; k < kHW; k += 64) tab[k] = 0u;
+    wave_sync();
+    const uint64_t bhi = B.sh >= 0 ? B.end(kHW - 1) : ~0ull;
+    uint32_t lower = 0, edge = 0;
+    for (uint32_t p = (uint32_t)lane; p < oc; p += 64u) {
+      const uint64_t j = (uint64_t)ov[-1 - (int64_t)p];
+      if (j >= B.lo && j <= bhi)
+        lds_inc(&tab[B.of(j)]);
+      else if (j < B.lo) {
+        ++lower;
+        edge |= j + 1u == B.lo ? 1u : 0u;
       }
+    }
+    wave_sync();
+    if (B.sh >= 0) {
+      lower = dpp_sum_u32(lower);
+      edge = dpp_or_u32(edge);
+    }
+    // 16 bins per lane, then those of the lanes in reach, four lanes' bins per
+    // round: a single value is evaluated, a wider bin kept when in reach
+    uint32_t cs = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) cs += tab[16 * lane + k];
+    const uint32_t cr = lower + dpp_incl_scan_u32(cs), cl = cr - cs;
+    const bool real = B.sh >= 0 || lane < (kBuckets >> kBucketBits);
+    auto right = [&](int b) {
+      return (int64_t)min((uint64_t)off + B.end(b), (uint64_t)INT64_MAX);
+    };
+    const double zo = w.survival(right(real ? 16 * lane + 15 : 15), ln);
+    const double zlo = B.sh >= 0 && B.lo > (uint64_t)kHW
+                           ? w.survival(off + (int64_t)B.lo - 1, ln)
+                           : zE;
+    double Dlow = fmax(D, dpp_max_f64(real ? fabs(zo * w.iz - (double)(oc - cr) * idn) : 0.0));
+    double zl = prev_lane_f64(zo);
+    if (lane == 0) zl = zlo;
+    const bool need = cs != 0u && fmax(zl * w.iz - (double)(oc - cr) * idn,
+                                       (double)(oc - cl) * idn - zo * w.iz) > Dlow - kPruneMargin;
+    if (!need && B.sh != 0) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) tab[16 * lane + k] = kNoBin;
+    }
+    uint64_t mask = __ballot(need);
+    uint32_t small = 0, large = 0;
+    while (mask != 0ull) {
+      const int p = next4(mask);
       const int pc = p < 0 ? 0 : p;
       const int b = 16 * pc + (lane & 15);
       const uint32_t cnt = p < 0 ? 0u : tab[b];
       const uint32_t ca = (uint32_t)__shfl((int)cl, pc, 64) + row_incl_scan_u32(cnt);
-      const int64_t t = (int64_t)min((uint64_t)off + bucket_end(b), (uint64_t)INT64_MAX);
-      const double z = w.survival(t, ln) * w.iz;
-      const double sb = (double)(oc - ca) * idn;
-      double zp = prev_lane_f64(z);
+      const int64_t t = right(b);
+      const double zv = w.survival(t, ln);
+      double zp = prev_lane_f64(zv);
       const double zq = shfl_f64(zl, pc);
       if ((lane & 15) == 0) zp = zq;
-      Dlow = fmax(Dlow, dpp_max_f64(p < 0 ? 0.0 : fabs(z - sb)));
-      const bool in = cnt != 0u &&
-                      fmax(zp - sb, (double)(oc - (ca - cnt)) * idn - z) > Dlow - kPruneMargin;
-      if (p >= 0) tab[b] = in ? bucket_entry(cnt, ca - cnt) : 0u;
-      total += in ? cnt : 0u;
-    }
-    total = dpp_sum_u32(total);
-  }
-  wave_sync();
-  // 3. the draws of the buckets in reach, gathered into LDS: in one pass when
-  // they fit, else a window of buckets at a time.  A draw equal to the value
-  // just below a gathered bucket is gathered as well (it decides a term).
-  int wlo = 0;
-  while (total != 0u && wlo < kBuckets) {
-    int whi = kBuckets;
-    if (total > (uint32_t)kGather) {
-      const uint32_t e = wlo + lane < kBuckets ? tab[wlo + lane] : 0u;
-      const uint32_t c = (e >> 31) ? ((e >> 22) & 511u) : 0u;
-      const uint32_t cum = dpp_incl_scan_u32(c);
-      const uint64_t fit = __ballot(cum <= (uint32_t)kGather);
-      const int take = fit == ~0ull ? 64 : __ffsll((long long)~fit) - 1;
-      if (take == 0) return -1.0;  // one bucket above the room
-      whi = wlo + take;
-      if (__ballot(c != 0u && lane < take) == 0ull) {
-        wlo = whi;
-        continue;
+      if (B.sh == 0) {
+        const bool pres = B.lo + (uint64_t)b == (uint64_t)kHW + 1u
+                              ? has_top
+                              : (b > 0 ? tab[b - 1] != 0u : edge != 0u);
+        if (cnt != 0u) terms(zv, pres ? zp : zv + w.point(t, ln), nbody + ca - cnt, cnt);
+      } else {
+        const double sb = (double)(oc - ca) * idn;
+        Dlow = fmax(Dlow, dpp_max_f64(p < 0 ? 0.0 : fabs(zv * w.iz - sb)));
+        const bool in = cnt != 0u && fmax(zp * w.iz - sb, (double)(oc - (ca - cnt)) * idn -
+                                                              zv * w.iz) > Dlow - kPruneMargin;
+        if (p >= 0) {
+          tab[b] = in ? ca - cnt : kNoBin;
+          many[b] = (uint8_t)(cnt < kManyDraws ? cnt : kManyDraws);
+        }
+        small += in && cnt < kManyDraws ? cnt : 0u;
+        large |= in && cnt >= kManyDraws ? 1u : 0u;
       }
     }
-    uint32_t m = 0;  // wave-uniform
-    for (uint32_t p0 = 0; p0 < oc; p0 += 64u) {
-      const uint32_t p = p0 + (uint32_t)lane;
-      bool take = false;
-      uint64_t j = 0;
-      if (p < oc) {
-        j = (uint64_t)ov[-1 - (int64_t)p];
-        const int b = bucket_of(j), b1 = bucket_of(j + 1u);
-        take = (b >= wlo && b < whi && (tab[b] >> 31) != 0u) ||
-               (b1 != b && b1 >= wlo && b1 < whi && (tab[b1] >> 31) != 0u);
-      }
-      const uint64_t mt = __ballot(take);
-      if (mt != 0ull) {
-        const uint32_t pos = m + (uint32_t)__popcll(mt & below);
-        if (take && pos < (uint32_t)kBatchRing) list[pos] = j;
-        m += (uint32_t)__popcll(mt);
-      }
-    }
-    if (m > (uint32_t)kBatchRing) return -1.0;
-    wave_sync();
-    for (uint32_t i0 = 0; i0 < m; i0 += 64u) {
-      const uint32_t i = i0 + (uint32_t)lane;
-      const bool valid = i < m;
-      const uint64_t j = valid ? list[i] : (uint64_t)kHW + 1u;
-      const int b = bucket_of(j);
-      const uint32_t e = tab[b];
-      const uint64_t jlo = b > 0 ? bucket_end(b - 1) + 1u : (uint64_t)kHW;
-      uint32_t lt = 0, eq = 0, pres = j == (uint64_t)kHW + 1u && has_top ? 1u : 0u;
-      for (uint32_t k = 0; k < m; ++k) {
-        const uint64_t x = list[k];
-        lt += (x >= jlo && x < j) ? 1u : 0u;
-        eq += x == j ? 1u : 0u;
-        pres |= x + 1u == j ? 1u : 0u;
-      }
-      if (valid && b >= wlo && b < whi && (e >> 31) != 0u) {
-        const uint32_t Cb = nbody + (e & 0x3fffffu) + lt;
-        const int64_t v = off + (int64_t)j;
-        const double zv = w.survival(v, ln);
-        const double zv1 = pres ? w.survival(v - 1, ln) : zv + w.point(v, ln);
-        const double t2 = fabs(fma(zv1, w.iz, -(double)(nu - Cb) * idn));
-        const double t1 = fabs(fma(zv, w.iz, -(double)(nu - Cb - eq) * idn));
-        D = fmax(D, fmax(t1, t2));
-      }
+    if (B.sh != 0) {
+      small = next == 0 ? dpp_sum_u32(small) : 0u;
+      large = dpp_or_u32(large);
     }
     wave_sync();
-    wlo = whi;
+    // 3. the draws of the smaller bins in reach, gathered into LDS: in one pass
+    // when they fit, else a window of bins at a time.  A draw equal to the
+    // value just below a bin marks the bin's entry (it decides a term).
+    int wlo = 0;
+    while (small != 0u && wlo < kHW) {
+      int whi = kHW;
+      if (small > kGather) {
+        const int b = wlo + lane;
+        uint32_t c = 0;
+        if (b < kHW && tab[b] != kNoBin) c = many[b];
+        c = c < kManyDraws ? c : 0u;
+        const uint64_t fit = __ballot(dpp_incl_scan_u32(c) <= kGather);
+        const int take = fit == ~0ull ? 64 : __ffsll((long long)~fit) - 1;  // at least one
+        whi = wlo + take < kHW ? wlo + take : kHW;
+        if (__ballot(c != 0u && lane < take) == 0ull) {
+          wlo = whi;
+          continue;
+        }
+      }
+      auto wanted = [&](uint64_t j) {
+        if (j < B.lo || j > bhi) return false;
+        const int b = B.of(j);
+        return b >= wlo && b < whi && tab[b] != kNoBin && many[b] < kManyDraws;
+      };
+      uint32_t m = 0;  // wave-uniform
+      for (uint32_t p0 = 0; p0 < oc; p0 += 64u) {
+        const uint32_t p = p0 + (uint32_t)lane;
+        bool take = false;
+        uint64_t j = 0;
+        if (p < oc) {
+          j = (uint64_t)ov[-1 - (int64_t)p];
+          take = wanted(j);
+          if (wanted(j + 1u) && (j < B.lo || B.of(j) != B.of(j + 1u)))
+            lds_or(&tab[B.of(j + 1u)], kBelowDrawn);
+        }
+        const uint64_t mt = __ballot(take);
+        if (mt != 0ull) {
+          const uint32_t pos = m + (uint32_t)__popcll(mt & below);
+          if (take) list[pos] = j;  // at most kGather of them
+          m += (uint32_t)__popcll(mt);
+        }
+      }
+      wave_sync();
+      for (uint32_t i0 = 0; i0 < m; i0 += 64u) {
+        const uint32_t i = i0 + (uint32_t)lane;
+        const uint64_t j = i < m ? list[i] : 0ull;
+        const bool valid = i < m;
+        const uint32_t entry = valid ? tab[B.of(j)] : 0u;
+        const uint64_t jlo = valid ? B.start(B.of(j)) : 0ull;
+        uint32_t lt = 0, eq = 0;
+        uint32_t pres = j == (uint64_t)kHW + 1u ? (has_top ? 1u : 0u)
+                                                 : (j == jlo ? entry >> 31 : 0u);
+        for (uint32_t k = 0; k < m; ++k) {
+          const uint64_t x = list[k];
+          lt += (x >= jlo && x < j) ? 1u : 0u;
+          eq += x == j ? 1u : 0u;
+          pres |= x + 1u == j ? 1u : 0u;
+        }
+        if (valid) {
+          const int64_t v = off + (int64_t)j;
+          const double zv = w.survival(v, ln);
+          const double zv1 = pres ? w.survival(v - 1, ln) : zv + w.point(v, ln);
+          terms(zv, zv1, nbody + (entry & ~kBelowDrawn) + lt, eq);
+        }
+      }
+      wave_sync();
+      wlo = whi;
+    }
+    D = dpp_max_f64(D);
+    // 4. the bins with many draws, one after another, as ranges of their own
+    int child = -1;
+    if (large != 0u) {
+      for (int b0 = next & ~63; b0 < kHW && child < 0; b0 += 64) {
+        const int b = b0 + lane;
+        const uint64_t hit =
+            __ballot(b >= next && tab[b] != kNoBin && many[b] == (uint8_t)kManyDraws);
+        if (hit != 0ull) child = b0 + __ffsll((long long)hit) - 1;
+      }
+    }
+    if (child >= 0) {
+      if (lane == 0) {
+        level[3 * depth] = B.lo;
+        level[3 * depth + 1] = (uint64_t)(int64_t)B.sh;
+        level[3 * depth + 2] = (uint64_t)(child + 1);
+      }
+      const int bits = B.width_bits(child);
+      B = Bins{B.start(child), bits > 10 ? bits - 10 : 0};
+      next = 0;
+      ++depth;
+    } else {
+      --depth;
+      if (depth >= 0) {
+        wave_sync();
+        B.lo = (uint64_t)uniform64((int64_t)level[3 * depth]);
+        B.sh = (int)uniform64((int64_t)level[3 * depth + 1]);
+        next = (int)uniform64((int64_t)level[3 * depth + 2]);
+      }
+    }
   }
-  return dpp_max_f64(D);
+  return D;
 }
 
-// ln x 2^53 as an integer, from the context's table behind the logarithms.
-__device__ __forceinline__ const uint64_t* ln_fixed_table(const double* ln) {
-  return reinterpret_cast<const uint64_t*>(ln + kH + 2);
-}
-__device__ __forceinline__ uint64_t ln_fixed_at(int64_t v, const double* __restrict__ ln) {
-  return v <= (int64_t)(kH + 1) ? ln_fixed_table(ln)[v] : (uint64_t)(log((double)v) * 0x1p53);
-}
+// Record of one replicate of a batch.
+struct WaveSlot {
+  U128 S;
+  uint64_t fp;
+  int64_t top;  // its larger draws lie below this offset of the scratch
+  uint32_t hi, len, flags, esc;
+};
 
 // One proposal of the tail sampler (tail_draw_from): taken (X), rejected,
 // rejected above 2^63, or undecided in FP64 (tail_hard repeats it with the
@@ -491,31 +561,50 @@ static __device__ __noinline__ TailTry tail_hard(double m0, double beta, double 
   return TailTry{X, take ? kTailTaken : kTailRejected};
 }
 
-// The draws of replicate rep by one wave (the wave form's pipelined loop):
-// counts of j <= kHW into L->hist (the rows of 1..3 added in at the end),
-// larger ones to top[-1 - p], p < ovn, as far as `room` reaches (ovn counts
-// them all).  On entry bins [0, hi) may be nonzero and are cleared; on return
-// hi covers the bins that may be nonzero.
+// The draws of replicate rep of a cell by one wave (a loop pipelined as the
+// lane form's): counts of j <= kHW into the histogram (the rows of 1..3 added
+// in at the end), larger ones to top[-1 - p], p < ovn, as far as `room` reaches
+// (ovn counts them all).  On entry bins [0, hi) may be nonzero and are cleared;
+// on return hi covers the bins that may be nonzero.  Called, like the stages
+// after it: in one body the persistent kernel keeps all their constants in
+// registers and the draw loop spills.
+struct DrawOut {
+  uint32_t fl, ovn;
+  int hi;
+};
 template <bool kCut>
-__device__ __forceinline__ void draw_batch_replicate(const DevCell& c, uint32_t rep, BatchLds* L,
-                                                     int64_t* __restrict__ top, uint32_t room,
-                                                     int lane, const uint64_t* __restrict__ T,
-                                                     const uint32_t* __restrict__ guide,
-                                                     uint32_t& fl, uint32_t& ovn, int& hi) {
+static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint32_t rep_,
+                                                      LdsU32* hist, LdsU64* ring, LdsU64* hard,
+                                                      int64_t* top_, uint32_t room_,
+                                                      const LdsU64* T, const LdsU32* guide,
+                                                      int hi_) {
+  const int lane = lane_id();
   const uint64_t below = lanes_below(lane);
-  for (int k = lane; k < hi; k += 64) L->hist[k] = 0u;
+  const DevCell& c = *reinterpret_cast<const DevCell*>(uniform64((int64_t)cell));
+  const uint32_t rep = (uint32_t)__builtin_amdgcn_readfirstlane((int)rep_);
+  const uint32_t room = (uint32_t)__builtin_amdgcn_readfirstlane((int)room_);
+  int64_t* __restrict__ top = reinterpret_cast<int64_t*>(uniform64((int64_t)top_));
+  const int hi0 = __builtin_amdgcn_readfirstlane(hi_);
+  for (int k = lane; k < hi0; k += 64) hist[k] = 0u;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) L->hist[kWaveOwn + k * 64 + lane] = 0u;
+  for (int k = 0; k < 3; ++k) hist[kWaveOwn + k * 64 + lane] = 0u;
   wave_sync();
-  const uint32_t nblk = (uint32_t)((c.n + 1) >> 1);
-  const uint32_t n32 = (uint32_t)c.n;
-  const uint64_t timax = table_int(c.tmax);
-  const int sh = (int)c.gsh;
+  const uint32_t n32 = (uint32_t)uniform64(c.n);
+  const uint32_t nblk = (n32 >> 1) + (n32 & 1u);
+  const uint64_t timax = (uint64_t)uniform64((int64_t)table_int(c.tmax));
+  const int sh = __builtin_amdgcn_readfirstlane((int)c.gsh);
+  const uint32_t ck0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.k0);
+  const uint32_t ck1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.k1);
+  const uint32_t cs = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.stream);
+  const double m0 = kCut ? (double)(c.xmin + kH) : kTailM;
+  const double beta = c.beta, gm = c.gm;
+  const int64_t off = kCut ? uniform64(c.xmin) - 1 : 0;
   int xm = 0;
-  fl = 0;
-  ovn = 0;
-  uint32_t qh = 0, qn = 0;  // deferred draws, wave-uniform
-  // the value of one lane (j, or 0 for none) counted in converged code
+  uint32_t fl = 0, ovn = 0;
+  uint32_t qh = 0, qn = 0;  // the first ring, wave-uniform
+  uint32_t hh = 0, hn = 0;  // the second
+  auto wrap = [](uint32_t p, int size) { return p >= (uint32_t)size ? p - (uint32_t)size : p; };
+  // larger draws (j > kHW) of the lanes that have one, in converged code
   auto put_big = [&](int64_t j) {
     const uint64_t mb = __ballot(j > kHW);
     if (mb != 0ull) {
@@ -524,65 +613,13 @@ __device__ __forceinline__ void draw_batch_replicate(const DevCell& c, uint32_t 
       ovn += (uint32_t)__popcll(mb);
     }
   };
-  uint32_t hh = 0, hn = 0;  // the second ring, wave-uniform
-  auto wrap = [](uint32_t p, int size) { return p >= (uint32_t)size ? p - (uint32_t)size : p; };
-  const double m0 = kCut ? (double)(c.xmin + kH) : kTailM;
-  // resolves m entries (one per lane) of the ring, or of the second one
-  auto drain = [&](uint32_t m, bool second) {
-    wave_sync();
-    int64_t j = 0;
-    uint32_t code = kTailTaken;
-    uint64_t e = 0;
-    if ((uint32_t)lane < m) {
-      e = second ? L->hard[wrap(hh + (uint32_t)lane, kHardRing)]
-                 : L->ring[wrap(qh + (uint32_t)lane, kBatchRing)];
-      if (e >> 63) {
-        const TailTry t =
-            second ? tail_hard(m0, c.beta, c.gm, c.k0, c.k1, (uint32_t)e, rep, c.stream,
-                               (uint32_t)(e >> 32) & kTailAttempts)
-                   : tail_try(m0, c.beta, c.gm, c.k0, c.k1, (uint32_t)e, rep, c.stream,
-                              (uint32_t)(e >> 32) & kTailAttempts);
-        code = t.code;
-        j = kCut ? t.X - (c.xmin - 1) : t.X;
-        if (code == kTailCapped) fl |= kFlagTailCapped;
-      } else {
-        j = (int64_t)slow_search(e & ((1ull << 53) - 1), T, guide, sh);
-      }
-    }
-    if (second) {
-      hh = wrap(hh + m, kHardRing);
-      hn -= m;
-    } else {
-      qh = wrap(qh + m, kBatchRing);
-      qn -= m;
-    }
-    const uint64_t mr = __ballot(code == kTailRejected || code == kTailCapped);
-    if (mr != 0ull) {
-      if ((mr >> lane) & 1ull)
-        L->ring[wrap(wrap(qh + qn, kBatchRing) + (uint32_t)__popcll(mr & below), kBatchRing)] =
-            e + (1ull << 32);
-      qn += (uint32_t)__popcll(mr);
-    }
-    const uint64_t mh = __ballot(code == kTailHard);
-    if (mh != 0ull) {
-      if (code == kTailHard)
-        L->hard[wrap(wrap(hh + hn, kHardRing) + (uint32_t)__popcll(mh & below), kHardRing)] = e;
-      hn += (uint32_t)__popcll(mh);
-    }
-    if (code != kTailTaken) j = 0;
-    if (j >= 1 && j <= kHW) {
-      atomicAdd(&L->hist[j - 1], 1u);
-      xm = max(xm, (int)j);
-    }
-    put_big(j);
-  };
   auto gen = [&](uint32_t j0, uint64_t (&Uo)[2 * kWaveBlocks]) {
-    uint32_t k0 = c.k0, k1 = c.k1;  // round keys per block (see lane_wave)
+    uint32_t k0 = ck0, k1 = ck1;  // round keys per block (see lane_wave)
     asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
     for (int b = 0; b < kWaveBlocks; ++b) {
-      const Words4 w = philox4x32_10(j0 + 64u * (uint32_t)b + (uint32_t)lane, rep, c.stream, 0u,
-                                     k0, k1);
+      const Words4 w =
+          philox4x32_10(j0 + 64u * (uint32_t)b + (uint32_t)lane, rep, cs, 0u, k0, k1);
       Uo[2 * b] = m53(w.w0, w.w1);
       Uo[2 * b + 1] = m53(w.w2, w.w3);
     }
@@ -592,12 +629,13 @@ __device__ __forceinline__ void draw_batch_replicate(const DevCell& c, uint32_t 
   gen(0u, U);
 #pragma unroll
   for (int d = 0; d < 2 * kWaveBlocks; ++d) gi[d] = guide_index(U[d], sh);
-  for (uint32_t j0 = 0; j0 < nblk; j0 += 64u * kWaveBlocks) {
+  for (uint32_t j0 = 0;;) {
     uint32_t gg[2 * kWaveBlocks];
 #pragma unroll
     for (int d = 0; d < 2 * kWaveBlocks; ++d) gg[d] = guide[gi[d]];
     uint64_t Un[2 * kWaveBlocks] = {1ull, 1ull, 1ull, 1ull};
-    if (j0 + 64u * kWaveBlocks < nblk) gen(j0 + 64u * kWaveBlocks, Un);  // none past the end
+    const bool more = j0 + 64u * kWaveBlocks < nblk;
+    if (more) gen(j0 + 64u * kWaveBlocks, Un);  // none past the end
     asm volatile("" : "+v"(Un[0]), "+v"(Un[1]), "+v"(Un[2]), "+v"(Un[3]));  // made here
     uint64_t t[2 * kWaveBlocks];
 #pragma unroll
@@ -623,59 +661,199 @@ __device__ __forceinline__ void draw_batch_replicate(const DevCell& c, uint32_t 
       const uint32_t xm1 = (uint32_t)(x[d] - 1);
       const int slot = xm1 < 3u ? kWaveOwn + (int)xm1 * 64 + lane
                                 : (xm1 < (uint32_t)kHW ? (int)xm1 : kWavePad + lane);
-      atomicAdd(&L->hist[slot], 1u);
+      lds_inc(&hist[slot]);
       xm = max(xm, x[d]);  // values above kHW are clamped once, below
     }
     if (__ballot(big) != 0ull) {
 #pragma unroll
       for (int d = 0; d < 2 * kWaveBlocks; ++d) put_big((int64_t)x[d]);
     }
-    ring_append<2 * kWaveBlocks, kBatchRing>(L->ring, qh, qn, def, [&](int d) {
-      return defer_entry(U[d], timax,
-                         2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1),
-                         0);
-    }, lane);
-    while (qn >= 64u || hn >= 64u) {
-      const bool second = hn >= 64u;
-      drain(64u, second);
+    // deferred draws into the first ring: positions from a prefix sum of the
+    // lanes' counts (three ballots of its bits)
+    {
+      uint32_t nd = 0;
+#pragma unroll
+      for (int d = 0; d < 2 * kWaveBlocks; ++d) nd += def[d] ? 1u : 0u;
+      if (__ballot(nd != 0u) != 0ull) {
+        const uint64_t b0 = __ballot(nd & 1u), b1 = __ballot(nd & 2u), b2 = __ballot(nd & 4u);
+        uint32_t pos = qh + qn + (uint32_t)(__popcll(b0 & below) + 2 * __popcll(b1 & below) +
+                                            4 * __popcll(b2 & below));
+#pragma unroll
+        for (int d = 0; d < 2 * kWaveBlocks; ++d) {
+          if (def[d]) {
+            const uint32_t i =
+                2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1);
+            ring[wrap(pos, kBatchRing)] = defer_entry(U[d], timax, i, 0);
+            ++pos;
+          }
+        }
+        qn += (uint32_t)(__popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2));
+      }
     }
+    // resolve 64 entries (one per lane) at a time, at the end the rest
+    while (qn >= 64u || hn >= 64u || (!more && (qn | hn) != 0u)) {
+      const bool second = hn >= 64u || qn == 0u;
+      const uint32_t m = min(second ? hn : qn, 64u);
+      wave_sync();
+      int64_t j = 0;
+      uint32_t code = kTailTaken;
+      uint64_t e = 0;
+      if ((uint32_t)lane < m) {
+        e = second ? hard[wrap(hh + (uint32_t)lane, kHardRing)]
+                   : ring[wrap(qh + (uint32_t)lane, kBatchRing)];
+        if (e >> 63) {
+          const uint32_t attempt = (uint32_t)(e >> 32) & kTailAttempts;
+          const TailTry t = second ? tail_hard(m0, beta, gm, ck0, ck1, (uint32_t)e, rep, cs, attempt)
+                                   : tail_try(m0, beta, gm, ck0, ck1, (uint32_t)e, rep, cs, attempt);
+          code = t.code;
+          j = t.X - off;
+          if (code == kTailCapped) fl |= kFlagTailCapped;
+        } else {
+          j = (int64_t)lds_search(e & ((1ull << 53) - 1), T, guide, sh);
+        }
+      }
+      if (second) {
+        hh = wrap(hh + m, kHardRing);
+        hn -= m;
+      } else {
+        qh = wrap(qh + m, kBatchRing);
+        qn -= m;
+      }
+      const uint64_t mr = __ballot(code == kTailRejected || code == kTailCapped);
+      if (mr != 0ull) {
+        if ((mr >> lane) & 1ull)
+          ring[wrap(wrap(qh + qn, kBatchRing) + (uint32_t)__popcll(mr & below), kBatchRing)] =
+              e + (1ull << 32);
+        qn += (uint32_t)__popcll(mr);
+      }
+      const uint64_t mh = __ballot(code == kTailHard);
+      if (mh != 0ull) {
+        if (code == kTailHard)
+          hard[wrap(wrap(hh + hn, kHardRing) + (uint32_t)__popcll(mh & below), kHardRing)] = e;
+        hn += (uint32_t)__popcll(mh);
+      }
+      if (code != kTailTaken) j = 0;
+      if (j >= 1 && j <= kHW) {
+        lds_inc(&hist[j - 1]);
+        xm = max(xm, (int)j);
+      }
+      put_big(j);
+    }
+    if (!more) break;
+    j0 += 64u * kWaveBlocks;
 #pragma unroll
     for (int d = 0; d < 2 * kWaveBlocks; ++d) U[d] = Un[d];
   }
-  while (qn > 0u || hn > 0u) {
-    const bool second = hn >= 64u || qn == 0u;
-    drain(min(second ? hn : qn, 64u), second);
-  }
-  fl = dpp_or_u32(fl);
-  hi = ((int)min(dpp_max_u32((uint32_t)xm), (uint32_t)kHW) + 255) & ~255;
-  hi = hi < 256 ? 256 : hi;
+  DrawOut o;
+  o.fl = dpp_or_u32(fl);
+  o.ovn = ovn;
+  const int hi = ((int)min(dpp_max_u32((uint32_t)xm), (uint32_t)kHW) + 255) & ~255;
+  o.hi = hi < 256 ? 256 : hi;
   wave_sync();
-  const uint32_t c1 = dpp_sum_u32(L->hist[kWaveOwn + lane]);
-  const uint32_t c2 = dpp_sum_u32(L->hist[kWaveOwn + 64 + lane]);
-  const uint32_t c3 = dpp_sum_u32(L->hist[kWaveOwn + 128 + lane]);
+  const uint32_t c1 = dpp_sum_u32(hist[kWaveOwn + lane]);
+  const uint32_t c2 = dpp_sum_u32(hist[kWaveOwn + 64 + lane]);
+  const uint32_t c3 = dpp_sum_u32(hist[kWaveOwn + 128 + lane]);
   if (lane == 0) {
-    L->hist[0] += c1;  // drains count 1..3 into the bins themselves
-    L->hist[1] += c2;
-    L->hist[2] += c3;
+    hist[0] += c1;  // the rings' draws count 1..3 into the bins themselves
+    hist[1] += c2;
+    hist[2] += c3;
   }
   wave_sync();
+  return o;
+}
+
+// Counts of one replicate to scratch, and the exact sum of ln v 2^53 over its
+// draws (as sums of the low and the high words) with, when want_fp, the
+// multiset fingerprint.
+struct SumOut {
+  uint64_t lo, hi, fp;
+};
+static __device__ __noinline__ SumOut sum_replicate(const LdsU32* hist, int hi_, uint32_t* cp_,
+                                                    bool wide_, const int64_t* ov_, uint32_t oc_,
+                                                    int64_t off_, bool want_fp_,
+                                                    const double* ln_) {
+  const int lane = lane_id();
+  const int hi = __builtin_amdgcn_readfirstlane(hi_);
+  const uint32_t oc = (uint32_t)__builtin_amdgcn_readfirstlane((int)oc_);
+  const int64_t off = uniform64(off_);
+  const bool wide = __builtin_amdgcn_readfirstlane((int)wide_) != 0;
+  const bool want_fp = __builtin_amdgcn_readfirstlane((int)want_fp_) != 0;
+  uint32_t* __restrict__ cp = reinterpret_cast<uint32_t*>(uniform64((int64_t)cp_));
+  const int64_t* __restrict__ ov = reinterpret_cast<const int64_t*>(uniform64((int64_t)ov_));
+  const double* __restrict__ ln = reinterpret_cast<const double*>(uniform64((int64_t)ln_));
+  uint64_t slo = 0, shi = 0, fp = 0;
+  for (int b0 = 0; b0 < hi; b0 += 256) {
+    uint32_t cs[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cs[k] = hist[b0 + 4 * lane + k];
+    if (wide)
+      *reinterpret_cast<uint4*>(cp + b0 + 4 * lane) = uint4{cs[0], cs[1], cs[2], cs[3]};
+    else
+      *reinterpret_cast<uint2*>(cp + (b0 >> 1) + 2 * lane) =
+          uint2{cs[0] | (cs[1] << 16), cs[2] | (cs[3] << 16)};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t v = off + b0 + 4 * lane + k + 1;
+      if (__ballot(cs[k] != 0u) != 0ull) {
+        const uint64_t lf = ln_fixed_at(v, ln);
+        slo += (uint64_t)cs[k] * (uint32_t)lf;
+        shi += (uint64_t)cs[k] * (uint32_t)(lf >> 32);
+        if (want_fp) fp += (uint64_t)cs[k] * mix64((uint64_t)v);
+      }
+    }
+  }
+  if (oc != 0u) wave_sync_global();  // read back by other lanes than the writers
+  for (uint32_t p = (uint32_t)lane; p < oc; p += 64u) {
+    const int64_t v = off + ov[-1 - (int64_t)p];
+    const uint64_t lf = ln_fixed_at(v, ln);
+    slo += (uint32_t)lf;
+    shi += lf >> 32;
+    if (want_fp) fp += mix64((uint64_t)v);
+  }
+  SumOut o;
+  o.lo = dpp_sum_u64(slo);
+  o.hi = dpp_sum_u64(shi);
+  o.fp = want_fp ? dpp_sum_u64(fp) : 0ull;
+  return o;
 }
 
 // MLE and the values up to 16 of the KS, one replicate per lane: alpha_hat,
-// 1 / normaliser, zeta(a, 17) and the largest term over those values.
+// 1 / normaliser, zeta(a, 17) and the largest term over those values.  D is
+// final (done) where no larger value can reach it, and under the truncated law
+// below trunc_em's range (K < 161), whose whole KS runs here.
 struct HeadOut {
   double a, iz, z16, D;
-  uint32_t flags;
+  uint32_t flags, done;
 };
-template <bool kCut>
-static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin,
+// The distinct values of stored counts 1..K, K <= kHW (see ListSrc).
+struct CountSrc {
+  CountView cv;
+  uint32_t K;
+  uint32_t v;  // next value above 16
+  __device__ __forceinline__ uint32_t small(int x) const {
+    return (uint32_t)x <= K ? cv.at(x - 1) : 0u;
+  }
+  __device__ __forceinline__ bool next_large(int64_t& x, uint32_t& c) {
+    for (; v <= K; ++v) {
+      c = cv.at((int)v - 1);
+      if (c) {
+        x = (int64_t)v++;
+        return true;
+      }
+    }
+    return false;
+  }
+};
+template <int kLaw>
+static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin, uint32_t K,
                                                  const uint32_t* counts, bool wide,
                                                  uint32_t flags, const double* __restrict__ ln) {
   HeadOut o;
   o.flags = flags;
+  o.done = 0u;
   const CountView cv{counts, wide};
   double suf[17];
-  if constexpr (kCut) {
+  if constexpr (kLaw == kCutoff) {
     U128 Sx = {0, 0};
     u128_add_mul(Sx, (uint64_t)n, ln_fixed(xmin, ln));
     if (S.lo == Sx.lo && S.hi == Sx.hi) {  // every value at the cutoff: one counts as xmin + 1
@@ -701,13 +879,27 @@ static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin
     } else {
       Sd = u128_to_S(S);
     }
-    o.a = mle_alpha(Sd / (double)n, ln, &o.flags);
-    survival_head(em_coef(o.a), ln, suf);
+    if constexpr (kLaw == kTrunc) {
+      o.a = mle_alpha_trunc(Sd / (double)n, K, ln, &o.flags);
+      if (!trunc_em(o.a, K)) {
+        CountSrc src{cv, K, 17};
+        o.D = ks_distance_trunc(src, o.a, K, n, ln);
+        o.iz = 1.0;
+        o.z16 = 0.0;
+        o.done = 1u;
+        return o;
+      }
+      const EmCoef E = em_coef(o.a);
+      survival_head_trunc(E, trunc_end(E, K, ln), ln, suf);
+    } else {
+      o.a = mle_alpha_start(Sd / (double)n, ln, mle_guess_table(ln), &o.flags);
+      survival_head(em_coef(o.a), ln, suf);
+    }
     o.iz = 1.0 / suf[0];
   }
   o.z16 = suf[16];
   const double idn = 1.0 / (double)n;
-  const int off = kCut ? (int)(xmin < 17 ? xmin - 1 : 16) : 0;
+  const int off = kLaw == kCutoff ? (int)(xmin < 17 ? xmin - 1 : 16) : 0;
   uint32_t c16[16];  // read ahead of the terms' branches
 #pragma unroll
   for (int v = 1; v <= 16; ++v) {
@@ -727,24 +919,27 @@ static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin
     }
   }
   o.D = D;
+  // past 16 both distributions lie between their values there and 1
+  if (fmax(o.z16 * o.iz, (double)(n - C) * idn) <= D - kPruneMargin) o.done = 1u;
   return o;
 }
 
 // Replicates r0 .. r0 + nrep - 1 of a cell by one wave, in batches that fill
 // its scratch (`stride` int64): 64 records, then the counts of each replicate
-// from below and the draws above kHW from the end.  The heavy layout's stride
-// holds at least one replicate's n draws and counts; more replicates join
-// while n draws still fit.  A replicate that the KS cannot finish within LDS
-// goes to the escalation list.
+// from below and the draws above kHW from the end.  A replicate is begun while
+// c.room of those still fit (all n of them, or what the cell's replicates
+// hardly ever exceed); one that exceeds the rest after all is drawn again as
+// the first of the next batch, or goes to the escalation list if it was.
 template <bool kCut>
-__device__ __forceinline__ void replicate_batch(const DevCell& c, int32_t cell_id, int64_t r0,
-                                                int nrep, BatchLds* L, int64_t* scratch,
+__device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t cell_id,
+                                                int64_t r0, int nrep, BatchLds* L, int64_t* scratch,
                                                 int64_t stride, int lane,
                                                 const uint64_t* __restrict__ T,
                                                 const uint32_t* __restrict__ guide,
                                                 const double* __restrict__ ln, const Outputs& out,
                                                 uint64_t* esc_list, uint32_t* esc_count,
                                                 uint32_t esc_cap, uint32_t* err) {
+  const DevCell& c = cells[cell_id];
   const int64_t n = c.n;
   const bool wide = n >= 65536;
   const int64_t cw = wide ? kHW / 2 : kHW / 4;  // int64 per replicate's counts
@@ -757,63 +952,39 @@ __device__ __forceinline__ void replicate_batch(const DevCell& c, int32_t cell_i
   int done = 0;
   while (done < nrep) {
     int q = 0;
+    bool full = false;
     int64_t top = stride;  // the larger draws of the next replicate lie below it
-    while (done + q < nrep && q < 64 && (q == 0 || top - (kRecords + (q + 1) * cw) >= n)) {
+    while (done + q < nrep && q < 64 && !full &&
+           (q == 0 || top - (kRecords + (q + 1) * cw) >= (int64_t)c.room)) {
       const uint32_t rep = (uint32_t)(r0 + done + q);
-      uint32_t fl, ovn;
       const uint32_t room = (uint32_t)min(top - (kRecords + (q + 1) * cw), n);
-      draw_batch_replicate<kCut>(c, rep, L, scratch + top, room, lane, T, guide, fl, ovn, hi);
-      // counts to scratch; exact sums of the low and high words of ln x 2^53
-      uint32_t* cp = reinterpret_cast<uint32_t*>(counts + q * cw);
-      uint64_t slo = 0, shi = 0, fp = 0;
-      for (int b0 = 0; b0 < hi; b0 += 256) {
-        const uint4 h = *reinterpret_cast<const uint4*>(L->hist + b0 + 4 * lane);
-        if (wide)
-          *reinterpret_cast<uint4*>(cp + b0 + 4 * lane) = h;
-        else
-          *reinterpret_cast<uint2*>(cp + (b0 >> 1) + 2 * lane) =
-              uint2{h.x | (h.y << 16), h.z | (h.w << 16)};
-        const uint32_t cs[4] = {h.x, h.y, h.z, h.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int64_t v = off + b0 + 4 * lane + k + 1;
-          if (__ballot(cs[k] != 0u) != 0ull) {
-            const uint64_t lf = ln_fixed_at(v, ln);
-            slo += (uint64_t)cs[k] * (uint32_t)lf;
-            shi += (uint64_t)cs[k] * (uint32_t)(lf >> 32);
-            if (want_fp) fp += (uint64_t)cs[k] * mix64((uint64_t)v);
-          }
-        }
-      }
-      const uint32_t no = ovn < room ? ovn : room;
-      if (no != 0u) wave_sync_global();  // read back by other lanes than the writers
-      for (uint32_t p = (uint32_t)lane; p < no; p += 64u) {
-        const int64_t v = off + scratch[top - 1 - (int64_t)p];
-        const uint64_t lf = ln_fixed_at(v, ln);
-        slo += (uint32_t)lf;
-        shi += lf >> 32;
-        if (want_fp) fp += mix64((uint64_t)v);
-      }
-      slo = dpp_sum_u64(slo);
-      shi = dpp_sum_u64(shi);
-      if (want_fp) fp = dpp_sum_u64(fp);
+      const DrawOut dr = draw_replicate<kCut>(&c, rep, (LdsU32*)L->hist, (LdsU64*)L->ring,
+                                              (LdsU64*)L->hard, scratch + top, room,
+                                              (const LdsU64*)T, (const LdsU32*)guide, hi);
+      hi = dr.hi;
+      full = dr.ovn > room;
+      if (full && q > 0) break;
+      const uint32_t no = full ? 0u : dr.ovn;
+      const SumOut su = sum_replicate((const LdsU32*)L->hist, hi,
+                                      reinterpret_cast<uint32_t*>(counts + q * cw), wide,
+                                      scratch + top, no, off, want_fp, ln);
       if (lane == 0) {
         WaveSlot sl;
-        sl.S = U128{slo + (shi << 32), (shi >> 32) + (slo + (shi << 32) < slo ? 1u : 0u)};
-        sl.fp = fp;
-        sl.xmax = top;
-        sl.off = (uint32_t)hi;
+        sl.S = U128{su.lo + (su.hi << 32),
+                    (su.hi >> 32) + (su.lo + (su.hi << 32) < su.lo ? 1u : 0u)};
+        sl.fp = su.fp;
+        sl.top = top;
+        sl.hi = (uint32_t)hi;
         sl.len = no;
-        sl.flags = fl;
-        sl.esc = ovn > room ? 1u : 0u;
+        sl.flags = dr.fl;
+        sl.esc = full ? 1u : 0u;
         slots[q] = sl;
       }
       top -= no;
       ++q;
     }
     wave_sync_global();  // the batch's records, counts and draws, before they are read back
-    // MLE and the head of the KS, one replicate per lane
-    HeadOut h = {2.0, 1.0, 0.0, 0.0, 0u};
+    HeadOut h = {2.0, 1.0, 0.0, 0.0, 0u, 1u};
     uint32_t esc = 0, oc = 0, hib = 256;
     uint64_t fp = 0;
     int64_t ovtop = 0;
@@ -821,37 +992,56 @@ __device__ __forceinline__ void replicate_batch(const DevCell& c, int32_t cell_i
       const WaveSlot sl = slots[lane];
       esc = sl.esc;
       oc = sl.len;
-      hib = sl.off;
+      hib = sl.hi;
       fp = sl.fp;
-      ovtop = sl.xmax;
-      h = head_lane<kCut>(sl.S, n, c.xmin, reinterpret_cast<const uint32_t*>(counts + lane * cw),
-                          wide, sl.flags, ln);
+      ovtop = sl.top;
+      const uint32_t* cnt = reinterpret_cast<const uint32_t*>(counts + lane * cw);
+      if (esc == 0u) {
+        if constexpr (kCut)
+          h = head_lane<kCutoff>(sl.S, n, c.xmin, 0u, cnt, wide, sl.flags, ln);
+        else if (c.K)
+          h = head_lane<kTrunc>(sl.S, n, 1, c.K, cnt, wide, sl.flags, ln);
+        else
+          h = head_lane<kPure>(sl.S, n, 1, 0u, cnt, wide, sl.flags, ln);
+      }
     }
     // the rest of the KS, one replicate per wave
-    for (int i = 0; i < q; ++i) {
-      if (__builtin_amdgcn_readlane((int)esc, i) != 0) continue;
+    uint64_t left = __ballot(h.done == 0u);
+    while (left != 0ull) {
+      const int i = __ffsll((long long)left) - 1;
+      left &= left - 1ull;
       const int64_t tp =
           ((int64_t)__builtin_amdgcn_readlane((int)(ovtop >> 32), i) << 32) |
           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ovtop, i);
-      const double Di = ks_rest<kCut>(
-          readlane_f64(h.a, i), readlane_f64(h.iz, i), c.xmin,
-          reinterpret_cast<const uint32_t*>(counts + i * cw), wide,
-          __builtin_amdgcn_readlane((int)hib, i), scratch + tp,
-          (uint32_t)__builtin_amdgcn_readlane((int)oc, i), n, readlane_f64(h.D, i),
-          readlane_f64(h.z16, i), (LdsU32*)L->hist, (LdsU64*)L->ring, ln);
+      auto rest = [&](auto fn) {
+        return fn(readlane_f64(h.a, i), readlane_f64(h.iz, i), c.xmin, c.K,
+                  reinterpret_cast<const uint32_t*>(counts + i * cw), wide,
+                  __builtin_amdgcn_readlane((int)hib, i), scratch + tp,
+                  (uint32_t)__builtin_amdgcn_readlane((int)oc, i), n, readlane_f64(h.D, i),
+                  readlane_f64(h.z16, i), (LdsU32*)L->hist, (LdsU64*)L->ring, (LdsU64*)L->hard,
+                  ln);
+      };
+      double Di;
+      if constexpr (kCut)
+        Di = rest([](auto... x) { return ks_rest<kCutoff>(x...); });
+      else if (c.K)
+        Di = rest([](auto... x) { return ks_rest<kTrunc>(x...); });
+      else
+        Di = rest([](auto... x) { return ks_rest<kPure>(x...); });
       if (lane == i) h.D = Di;
     }
-    hi = kHW;  // the bucket tables went through the histogram
+    // the bin tables of larger draws went through the histogram
+    if (__ballot(h.done == 0u && oc != 0u) != 0ull) hi = kHW;
     if (lane < q) {
       const int64_t rep = r0 + done + lane;
-      if (esc != 0u || h.D < 0.0) {
+      if (esc != 0u) {
         const uint32_t slot = atomicAdd(esc_count, 1u);
         if (slot < esc_cap)
           esc_list[slot] = ((uint64_t)(uint32_t)cell_id << 32) | (uint32_t)rep;
         else
           atomicOr(err, kErrEscOverflow);
       } else {
-        write_outputs(out, c.out_off + rep, h.D, h.a, h.flags, fp, 0);
+        write_outputs(out, c.out_off + rep, h.D, h.a, h.flags, fp);
       }
     }
     wave_sync_global();  // the next batch overwrites the records
@@ -859,50 +1049,153 @@ __device__ __forceinline__ void replicate_batch(const DevCell& c, int32_t cell_i
   }
 }
 
-// Persistent kernel of the batched replicates: a workgroup takes a unit (up
-// to 64 replicates of one cell for each of its waves) from the queue and gives each
-// wave a contiguous share.
-template <int kWavesPer>
-struct BatchKernelLds {
+// The cell's table and guide, and a region per wave.
+template <class Region, int kWavesPer>
+struct KernelLds {
   alignas(16) uint64_t T[kH];  // floor(F(k) 2^53)
   uint32_t guide[kGuide];
-  BatchLds w[kWavesPer];
+  Region w[kWavesPer];
   int unit;
 };
-static_assert(sizeof(BatchKernelLds<kBatchWaves>) <= 160 * 1024, "one workgroup per compute unit");
+union SimRegion {
+  LaneRegion lane;
+  BatchLds batch;
+};
+static_assert(sizeof(KernelLds<SimRegion, kWaves>) <= 160 * 1024, "one workgroup per compute unit");
 
-template <bool kCut, int kWavesPer>
-__global__ __launch_bounds__(64 * kWavesPer, kWavesPer / 4) void k_batch(
+// Takes the next unit of a queue for the whole workgroup and stages its cell's
+// table when that changes; false when the queue is empty.
+template <class Lds>
+__device__ __forceinline__ bool next_unit(Lds& L, uint32_t* queue, const Unit* __restrict__ units,
+                                          int n_units, const DevCell* __restrict__ cells,
+                                          const double* __restrict__ tables,
+                                          const uint16_t* __restrict__ guides, int& loaded,
+                                          Unit& un, int nthreads) {
+  const int tid = (int)threadIdx.x;
+  __syncthreads();  // the previous unit's table is no longer read
+  if (tid == 0) L.unit = (int)atomicAdd(queue, 1u);
+  __syncthreads();
+  const int u = L.unit;
+  if (u >= n_units) return false;
+  un = units[u];
+  if (un.cell != loaded) {
+    load_cell_tables(L.T, L.guide, tables + (size_t)un.cell * kH,
+                     guides + (size_t)un.cell * (kGuide + 1), cells[un.cell], tid, nthreads);
+    loaded = un.cell;
+    __syncthreads();
+  }
+  return true;
+}
+
+// Persistent simulation kernel: workgroups pull units from two queues, first
+// those of the lane form (up to kBlock replicates of a cell, one per lane;
+// workgroups 0 .. lane_wgs - 1), then those of the wave and heavy forms (each
+// wave a contiguous share; the last batch_wgs workgroups).  Both kinds in one
+// launch: one after the other each would end on a device that runs dry.
+// Three waves per SIMD: the twelve waves' LDS regions and the shared table
+// fit one workgroup per compute unit, and the register budget is 168 per lane.
+static_assert(kBlock == 64 * kWaves && kWaves == kBatchWaves, "twelve waves per workgroup");
+__global__ __launch_bounds__(kBlock, 3) void k_simulate(
+    SimGrid g, const DevCell* __restrict__ cells, const double* __restrict__ tables,
+    const uint16_t* __restrict__ guides, const double* __restrict__ ln,
+    const Unit* __restrict__ lane_units, int n_lane, const Unit* __restrict__ batch_units,
+    int n_batch, uint32_t* lane_queue, uint32_t* batch_queue, Outputs out, uint64_t* esc_list,
+    uint32_t* esc_count, uint32_t esc_cap, int64_t* slots, int64_t* scratch, uint32_t* err) {
+  __shared__ KernelLds<SimRegion, kWaves> L;
+  const int wave = (int)threadIdx.x >> 6;
+  const int lane = lane_id();
+  int loaded = -1;
+  Unit un;
+  if ((int)blockIdx.x < g.lane_wgs) {
+    int64_t* mine = slots + ((int64_t)blockIdx.x * g.lane_waves + wave) * kLaneScratch;
+    while (next_unit(L, lane_queue, lane_units, n_lane, cells, tables, guides, loaded, un,
+                     kBlock)) {
+      const int first = wave * 64;
+      if (first < un.count)
+        lane_wave(cells, un.cell, un.r0 + first, un.count - first < 64 ? un.count - first : 64,
+                  &L.w[wave].lane, lane, L.T, L.guide, ln, out, esc_list, esc_count, esc_cap, err,
+                  mine);
+    }
+  }
+  const int b = (int)blockIdx.x - (g.grid - g.batch_wgs);
+  if (b >= 0) {
+    int64_t* mine = scratch + ((int64_t)b * kBatchWaves + wave) * g.stride;
+    while (next_unit(L, batch_queue, batch_units, n_batch, cells, tables, guides, loaded, un,
+                     kBlock)) {
+      const int share = (un.count + kBatchWaves - 1) / kBatchWaves;
+      const int first = wave * share;
+      if (first < un.count)
+        replicate_batch<false>(cells, un.cell, un.r0 + first,
+                               un.count - first < share ? un.count - first : share,
+                               &L.w[wave].batch, mine, g.stride, lane, L.T, L.guide, ln, out,
+                               esc_list, esc_count, esc_cap, err);
+    }
+  }
+}
+
+// The cells with a lower cutoff (heavy form).
+__global__ __launch_bounds__(64 * kBatchWavesCut, kBatchWavesCut / 4) void k_cutoff(
     const DevCell* __restrict__ cells, const double* __restrict__ tables,
     const uint16_t* __restrict__ guides, const double* __restrict__ ln,
     const Unit* __restrict__ units, int n_units, uint32_t* queue, Outputs out,
     uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* scratch, int64_t stride,
     uint32_t* err) {
-  __shared__ BatchKernelLds<kWavesPer> L;
+  __shared__ KernelLds<BatchLds, kBatchWavesCut> L;
+  const int wave = (int)threadIdx.x >> 6;
+  const int lane = lane_id();
+  int64_t* mine = scratch + ((int64_t)blockIdx.x * kBatchWavesCut + wave) * stride;
+  int loaded = -1;
+  Unit un;
+  while (next_unit(L, queue, units, n_units, cells, tables, guides, loaded, un,
+                   64 * kBatchWavesCut)) {
+    const int share = (un.count + kBatchWavesCut - 1) / kBatchWavesCut;
+    const int first = wave * share;
+    if (first < un.count)
+      replicate_batch<true>(cells, un.cell, un.r0 + first,
+                            un.count - first < share ? un.count - first : share, &L.w[wave], mine,
+                            stride, lane, L.T, L.guide, ln, out, esc_list, esc_count, esc_cap, err);
+  }
+}
+
+// The replicates on the escalation list, with scratch for a replicate's every
+// draw: a workgroup takes up to kEscWaves of them, those of the same cell side
+// by side.
+__global__ __launch_bounds__(64 * kEscWaves, kEscWaves / 4) void k_escalated(
+    const DevCell* __restrict__ cells, const double* __restrict__ tables,
+    const uint16_t* __restrict__ guides, const double* __restrict__ ln, uint32_t* queue,
+    Outputs out, uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* scratch,
+    int64_t stride, uint32_t* err) {
+  __shared__ KernelLds<BatchLds, kEscWaves> L;
   const int tid = (int)threadIdx.x;
   const int wave = tid >> 6;
   const int lane = tid & 63;
-  int64_t* mine = scratch + ((int64_t)blockIdx.x * kWavesPer + wave) * stride;
+  int64_t* mine = scratch + ((int64_t)blockIdx.x * kEscWaves + wave) * stride;
+  const uint32_t ne = *esc_count < esc_cap ? *esc_count : esc_cap;
   int loaded = -1;
   for (;;) {
-    if (tid == 0) L.unit = (int)atomicAdd(queue, 1u);
+    if (tid == 0) L.unit = (int)atomicAdd(queue, (uint32_t)kEscWaves);
     __syncthreads();
-    const int u = L.unit;
-    if (u >= n_units) break;
-    const Unit un = units[u];
-    const DevCell c = cells[un.cell];
-    if (un.cell != loaded) {
-      load_cell_tables(L.T, L.guide, tables + (size_t)un.cell * kH,
-                       guides + (size_t)un.cell * (kGuide + 1), c, tid, 64 * kWavesPer);
-      loaded = un.cell;
-      __syncthreads();
+    const uint32_t e0 = (uint32_t)L.unit;
+    if (e0 >= ne) break;
+    const uint32_t e1 = e0 + kEscWaves < ne ? e0 + kEscWaves : ne;
+    for (uint32_t e = e0; e < e1;) {
+      const int cell = (int)(esc_list[e] >> 32);
+      uint32_t same = 1;
+      while (e + same < e1 && (int)(esc_list[e + same] >> 32) == cell) ++same;
+      const DevCell c = cells[cell];
+      if (cell != loaded) {
+        __syncthreads();
+        load_cell_tables(L.T, L.guide, tables + (size_t)cell * kH,
+                         guides + (size_t)cell * (kGuide + 1), c, tid, 64 * kEscWaves);
+        loaded = cell;
+        __syncthreads();
+      }
+      if ((uint32_t)wave < same)
+        replicate_batch<false>(cells, cell, (int64_t)(uint32_t)esc_list[e + (uint32_t)wave], 1,
+                               &L.w[wave], mine, stride, lane, L.T, L.guide, ln, out, esc_list,
+                               esc_count, 0u, err);
+      e += same;
     }
-    const int share = (un.count + kWavesPer - 1) / kWavesPer;
-    const int first = wave * share;
-    if (first < un.count)
-      replicate_batch<kCut>(c, un.cell, un.r0 + first,
-                            un.count - first < share ? un.count - first : share, &L.w[wave], mine,
-                            stride, lane, L.T, L.guide, ln, out, esc_list, esc_count, esc_cap, err);
     __syncthreads();
   }
 }

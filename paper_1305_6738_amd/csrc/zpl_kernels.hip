@@ -101,23 +101,6 @@ __device__ __forceinline__ int fast_draw(uint64_t m, const uint64_t* __restrict_
   return fast_select(gg, ti, m);
 }
 
-// fast_draw for four draws at once, in phases (all guide reads, then all
-// table reads, then the selections) so that the reads of each phase are in
-// flight together: two LDS round trips per four draws instead of eight.
-__device__ __forceinline__ void fast_draw4(const uint64_t (&m)[4], const uint64_t* __restrict__ T,
-                                           const uint32_t* __restrict__ guide, int sh,
-                                           int (&x)[4]) {
-  uint32_t gg[4];
-#pragma unroll
-  for (int d = 0; d < 4; ++d) gg[d] = guide[guide_index(m[d], sh)];
-  uint64_t t[4];
-#pragma unroll
-  for (int d = 0; d < 4; ++d) t[d] = T[(int)(gg[d] & 0xffffu) - 1];
-  asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));  // reads stay unconditional
-#pragma unroll
-  for (int d = 0; d < 4; ++d) x[d] = fast_select(gg[d], t[d], m[d]);
-}
-
 // Full search of a deferred body draw.
 __device__ __forceinline__ int slow_search(uint64_t m, const uint64_t* __restrict__ T,
                                            const uint32_t* __restrict__ guide, int sh) {
@@ -209,41 +192,98 @@ __device__ __forceinline__ double ks_distance(Src& src, const EmCoef& E,
   return D;
 }
 
-// KS distance (eq. 3) under the truncated law on 1..K: F(t) = P(t)/Z with
-// P(t) = sum_{k<=t} k^-a accumulated in ascending k as the distinct values
-// are visited, and Z = Z_K(a) (zeta3_trunc_fast: Euler-Maclaurin for large
-// K, else the K terms from K down).  Same terms as
-// ks_distance: |F(v) - C(v)/n| and |F(v-1) - C(v-1)/n| per distinct v.
+// KS distance (eq. 3) under the truncated law on 1..K.  Where its sums go by
+// Euler-Maclaurin (trunc_em), as ks_distance with the survival sums of
+// trunc_tail.  Else (K < 161) F(t) = P(t)/Z with P(t) = sum_{k<=t} k^-a
+// accumulated in ascending k as the distinct values are visited, and Z the K
+// terms from K down.  The terms are |F(v) - C(v)/n| and |F(v-1) - C(v-1)/n|
+// per distinct v either way.
 template <class Src>
 __device__ __forceinline__ double ks_distance_trunc(Src& src, double a, uint32_t K, int64_t n,
                                                     const double* __restrict__ ln) {
-  const double Z = zeta3_trunc_fast(a, K, ln).z0;  // the normaliser Z_K(a)
-  const double iz = 1.0 / Z, idn = 1.0 / (double)n;
+  const double idn = 1.0 / (double)n;
   int64_t C = 0;
-  double D = 0.0, P = 0.0;
-  int64_t k = 0;  // P = P(k)
-  auto term = [&](int64_t v, uint32_t c) {
-    while (k < v - 1) {
-      ++k;
-      P += k == 1 ? 1.0 : pow_neg(a, ln[k]);
+  double D = 0.0;
+  if (trunc_em(a, K)) {
+    const EmCoef E = em_coef(a);
+    const TruncEnd te = trunc_end(E, K, ln);
+    double suf[17];
+    survival_head_trunc(E, te, ln, suf);
+    const double iz = 1.0 / suf[0];
+    auto term = [&](double zv, double zv1, uint32_t c) {
+      const double t2 = fabs(fma(zv1, iz, -(double)(n - C) * idn));
+      C += c;
+      const double t1 = fabs(fma(zv, iz, -(double)(n - C) * idn));
+      D = fmax(D, fmax(t1, t2));
+    };
+#pragma unroll
+    for (int v = 1; v <= 16; ++v) {
+      const uint32_t c = src.small(v);
+      if (c) term(suf[v], suf[v - 1], c);
     }
-    const double t2 = fabs(fma(P, iz, -(double)C * idn));
-    ++k;
-    P += k == 1 ? 1.0 : pow_neg(a, ln[k]);
+    double zprev = suf[16];
+    int64_t vprev = 16, v;
+    uint32_t c;
+    while (src.next_large(v, c)) {
+      const double zv = trunc_tail(E, te, v, ln[v + 1]);  // v <= K <= kH
+      term(zv, v - 1 == vprev ? zprev : zv + pow_neg(a, ln[v]), c);
+      zprev = zv;
+      vprev = v;
+    }
+    return D;
+  }
+  const double iz = 1.0 / zeta3_trunc(a, K, ln).z0;  // the normaliser Z_K(a)
+  double pw[kDirect + 1];
+  direct_powers(a, K, ln, pw);
+  double P = 0.0;  // P(k - 1), then P(k)
+  auto term = [&](double Pl, double Pv, uint32_t c) {
+    const double t2 = fabs(fma(Pl, iz, -(double)C * idn));
     C += c;
-    const double t1 = fabs(fma(P, iz, -(double)C * idn));
+    const double t1 = fabs(fma(Pv, iz, -(double)C * idn));
     D = fmax(D, fmax(t1, t2));
   };
 #pragma unroll
-  for (int v = 1; v <= 16; ++v) {
-    const uint32_t c = src.small(v);
-    if (c) term(v, c);
+  for (int k = 1; k <= kDirect; ++k) {
+    const double Pk = P + pw[k];
+    const uint32_t ck = src.small(k);
+    if (ck) term(P, Pk, ck);
+    P = Pk;
   }
   int64_t v;
   uint32_t c;
-  while (src.next_large(v, c)) term(v, c);
+  bool have = src.next_large(v, c);
+  int64_t k = kDirect;  // P = P(k)
+  while (have) {
+    while (k < v - 1) {
+      ++k;
+      P += pow_neg(a, ln[k]);
+    }
+    ++k;
+    const double Pk = P + pow_neg(a, ln[k]);
+    term(P, Pk, c);
+    P = Pk;
+    have = src.next_large(v, c);
+  }
   return D;
 }
+
+// The MLE's start table, behind the logarithms and their fixed-point form in
+// the context's constants (k_ln_table, k_mle_guess).
+__device__ __forceinline__ const double* mle_guess_table(const double* ln) {
+  return ln + 2 * (kH + 2);
+}
+
+// ln x 2^53 as an integer, from the context's table behind the logarithms.
+__device__ __forceinline__ const uint64_t* ln_fixed_table(const double* ln) {
+  return reinterpret_cast<const uint64_t*>(ln + kH + 2);
+}
+__device__ __forceinline__ uint64_t ln_fixed_at(int64_t v, const double* __restrict__ ln) {
+  return v <= (int64_t)(kH + 1) ? ln_fixed_table(ln)[v] : (uint64_t)(log((double)v) * 0x1p53);
+}
+
+// Distances closer than this to the largest one found are always evaluated:
+// far above the rounding of a bound (a few 2^-53), far below any distance.
+constexpr double kPruneMargin = 1e-12;
 
 // S (with the paper's all-ones rule), alpha_hat (eq. 2) and D (eq. 3), for
 // the pure law (K = 0) or the truncated law on 1..K.
@@ -264,7 +304,7 @@ __device__ __forceinline__ void finish_replicate(Src& src, const U128& S, int64_
     D = ks_distance_trunc(src, a, K, n, ln);
     ahat = a;
   } else {
-    const double a = mle_alpha(Sd / (double)n, ln, &fl);
+    const double a = mle_alpha_start(Sd / (double)n, ln, mle_guess_table(ln), &fl);
     const EmCoef E = em_coef(a);
     double suf[17];
     survival_head(E, ln, suf);
@@ -275,22 +315,24 @@ __device__ __forceinline__ void finish_replicate(Src& src, const U128& S, int64_
 }
 
 __device__ __forceinline__ void write_outputs(const Outputs& o, int64_t idx, double D,
-                                              double a, uint32_t fl, uint64_t fp,
-                                              int64_t xmax) {
+                                              double a, uint32_t fl, uint64_t fp) {
   if (o.D) o.D[idx] = D;
   if (o.ahat) o.ahat[idx] = a;
   if (o.flags) o.flags[idx] = fl;
   if (o.fp) o.fp[idx] = fp;
-  if (o.xmax) o.xmax[idx] = xmax;
 }
 
 // ---------------------------------------------------------------------------
 // Distinct-value sources.
 // ---------------------------------------------------------------------------
+// LDS words as such (address space 3) for functions that are called, not
+// inlined: through a generic pointer their LDS accesses would be flat ones,
+// which are not ordered with the callers' LDS instructions.
+typedef __attribute__((address_space(3))) uint32_t LdsU32;
 // Lane mode: a per-lane column of packed 16-bit counters for values 1..kHLB
 // (dword b holds values 2b+1 and 2b+2) and a sorted per-lane overflow list.
 struct LaneSrc {
-  const uint32_t* hist;  // element (b, lane) at hist[b * 64]
+  const LdsU32* hist;    // element (b, lane) at hist[b * 64]
   const int64_t* ov;     // element (p, lane) at ov[p * 64]
   int oc;
   int bin;  // next value to inspect in 17..kHLB
@@ -508,7 +550,7 @@ __device__ __forceinline__ void finish_replicate_wave(const int64_t* lv, const u
   } else {
     Sd = u128_to_S(S);
   }
-  const double a = mle_alpha(Sd / (double)n, ln, &fl);
+  const double a = mle_alpha_start(Sd / (double)n, ln, mle_guess_table(ln), &fl);
   const EmCoef E = em_coef(a);
   double suf[17];
   survival_head(E, ln, suf);
@@ -530,26 +572,20 @@ __device__ __forceinline__ void wave_sync_global() {
 // Builds the compact (value, count) list of one replicate from a histogram
 // of values 1..nbins (hist[v-1]) and a sorted overflow array ov[0..oc),
 // appending at lv/lc (length returned).  Also returns, identical on every
-// lane, the exact 128-bit sum of ln x and, when want_fp, the multiset
-// fingerprint and the largest value.  The histogram is consumed: when every
+// lane, the exact 128-bit sum of ln x.  The histogram is consumed: when every
 // count fits in 21 bits (n < 2^21) its nonzero bins are also packed as
 // (v << 21 | count) into hist[0..) in list order, so the sums read them from
 // LDS instead of reading the global list back.
 struct Summary {
   U128 S;
-  uint64_t fp;
-  int64_t xmax;
   int len;
 };
 
 __device__ Summary build_list(uint32_t* hist, int nbins, const int64_t* ov, int oc, int64_t* lv,
-                              uint32_t* lc, int lane, const double* __restrict__ ln, int64_t n,
-                              bool want_fp) {
+                              uint32_t* lc, int lane, const double* __restrict__ ln, int64_t n) {
   const uint64_t below = lanes_below(lane);
   const bool packed = n < ((int64_t)1 << 21);
   U128 S = {0, 0};
-  uint64_t fp = 0;
-  int64_t xmax = 0;
   int len = 0;
   // 1. non-zero histogram bins, four per lane per step (16-byte LDS reads;
   //    nbins is a multiple of 256), compacted in ascending order.  A bin's
@@ -598,15 +634,11 @@ __device__ Summary build_list(uint32_t* hist, int nbins, const int64_t* ov, int 
       lv[pos] = v;
       lc[pos] = cnt;
       u128_add_mul(S, cnt, ln_fixed(v, ln));
-      if (want_fp) {
-        fp += (uint64_t)cnt * mix64((uint64_t)v);
-        xmax = v > xmax ? v : xmax;
-      }
     }
     len += __popcll(m);
     if (sm) run0 = p0 + 63 - __clzll((long long)sm);
   }
-  // 3. exact S (and fingerprint, max) over the histogram part of the list
+  // 3. exact S over the histogram part of the list
   if (packed) {
     wave_sync();
     for (int q = lane; q < hlen; q += 64) {
@@ -614,10 +646,6 @@ __device__ Summary build_list(uint32_t* hist, int nbins, const int64_t* ov, int 
       const int64_t v = (int64_t)(e >> 21);
       const uint32_t c = e & ((1u << 21) - 1u);
       u128_add_mul(S, c, ln_fixed(v, ln));
-      if (want_fp) {
-        fp += (uint64_t)c * mix64((uint64_t)v);
-        xmax = v > xmax ? v : xmax;
-      }
     }
   } else {
     wave_sync_global();  // the list is in global memory
@@ -625,16 +653,10 @@ __device__ Summary build_list(uint32_t* hist, int nbins, const int64_t* ov, int 
       const int64_t v = lv[q];
       const uint32_t c = lc[q];
       u128_add_mul(S, c, ln_fixed(v, ln));
-      if (want_fp) {
-        fp += (uint64_t)c * mix64((uint64_t)v);
-        xmax = v > xmax ? v : xmax;
-      }
     }
   }
   Summary s;
   s.S = wave_sum_u128(S);
-  s.fp = want_fp ? wave_sum_u64(fp) : 0ull;
-  s.xmax = want_fp ? wave_max_i64(xmax) : 0;
   s.len = len;
   return s;
 }
@@ -858,52 +880,15 @@ __device__ void wave_sort_global(int64_t* g, int P, int lane) {
   }
 }
 
-__device__ __forceinline__ int64_t resolve_entry(uint64_t e, uint32_t rep, const DevCell& c,
-                                                 const uint64_t* __restrict__ T,
-                                                 const uint32_t* __restrict__ guide,
-                                                 uint32_t& fl) {
-  if (e >> 63)
-    return tail_draw(c.beta, c.gm, c.k0, c.k1, (uint32_t)e, rep, c.stream, &fl);  // inline: no call in the draw loop
-  return (int64_t)slow_search(e & ((1ull << 53) - 1), T, guide, (int)c.gsh);
-}
-
-// Ring of deferred draws (lane and wave forms).  Before an iteration's
+// Ring of deferred draws (lane form).  Before an iteration's
 // appends (at most 64 lanes x 4 draws) it holds fewer than 64 entries, so
 // 320 entries never overflow.
 constexpr int kRing = 320;
 
-// Appends the draws d with def[d] set (at most 4 per lane) to the ring at
-// head qh holding qn entries; qn is wave-uniform.  Positions come from a
-// wave prefix sum of the per-lane counts (three ballots of its bits).
-template <int ND, int kSize = kRing, class Entry>
-__device__ __forceinline__ void ring_append(uint64_t* ring, uint32_t qh, uint32_t& qn,
-                                            const bool (&def)[ND], Entry entry, int lane) {
-  static_assert(ND <= 4, "per-lane count must fit in 3 bits");
-  uint32_t nd = 0;
-#pragma unroll
-  for (int d = 0; d < ND; ++d) nd += def[d] ? 1u : 0u;
-  if (__ballot(nd != 0u) == 0ull) return;
-  const uint64_t below = lanes_below(lane);
-  const uint64_t m0 = __ballot(nd & 1u), m1 = __ballot(nd & 2u), m2 = __ballot(nd & 4u);
-  uint32_t pos = qh + qn + (uint32_t)(__popcll(m0 & below) + 2 * __popcll(m1 & below) +
-                                      4 * __popcll(m2 & below));
-#pragma unroll
-  for (int d = 0; d < ND; ++d) {
-    if (def[d]) {
-      ring[pos >= (uint32_t)kSize ? pos - (uint32_t)kSize : pos] = entry(d);
-      ++pos;
-    }
-  }
-  qn += (uint32_t)(__popcll(m0) + 2 * __popcll(m1) + 4 * __popcll(m2));
-}
-
 // ---------------------------------------------------------------------------
-// LDS of the simulation kernel: the cell's CDF table and packed guide, and one
-// region per wave (lane form or wave form).
+// A wave's LDS in the lane form.
 // ---------------------------------------------------------------------------
 static_assert(kHLB % 2 == 0, "two 16-bit counters per dword; value kHLB + 1 maps to the pad row");
-static_assert(64 * 2 * kLaneCap <= kListCap,
-              "the lane form's value slots and sorted lists fit the wave's list scratch");
 struct alignas(16) LaneRegion {
   // dword b of lane l at hist[b * 64 + l]; row kHLB / 2 is a pad that takes
   // the draw loop's no-op counts (never read)
@@ -912,32 +897,6 @@ struct alignas(16) LaneRegion {
   uint32_t ovc[64];  // values the drains added to a lane's list (may exceed its room)
   uint32_t fl[64];   // flags per lane
 };
-
-// Wave-form histogram layout: bins of values 1..kHW, one pad slot per lane
-// (the draw loop's no-op counts, never read), then three rows of per-lane
-// counts of the values 1, 2 and 3 (most draws: a lane counting into its own
-// slot never conflicts with another lane).
-constexpr int kWavePad = kHW;
-constexpr int kWaveOwn = kHW + 64;
-struct alignas(16) WaveRegion {
-  uint32_t hist[kHW + 64 + 3 * 64];
-  int64_t ov[kCW];
-  uint64_t ring[kRing];     // deferred draws
-  uint32_t ovc;
-};
-
-union WaveLds {
-  LaneRegion lane;
-  WaveRegion wave;
-};
-
-struct SimLds {
-  alignas(16) uint64_t T[kH];  // floor(F(k) 2^53)
-  uint32_t guide[kGuide];
-  WaveLds w[kWaves];
-  int unit;
-};
-static_assert(sizeof(SimLds) <= 160 * 1024, "the simulation kernel's LDS fits one compute unit");
 
 // Out of line: inlined into the persistent kernels' cell switch it takes
 // registers from their hot loops.
@@ -959,74 +918,382 @@ __device__ __forceinline__ void load_cell_tables(uint64_t* T, uint32_t* guide,
 }
 
 // ---------------------------------------------------------------------------
-// Lane form: one replicate per lane.  Fast-path draws go straight into the
-// lane's histogram column; deferred draws from all lanes are resolved 64 at a
-// time by whichever lane picks them up, into the owner's column.
+// Lane form: one replicate per lane.
 // ---------------------------------------------------------------------------
-// The lane's larger values take kLaneCap slots of the wave's global scratch,
-// slot s of lane l at spill[s * 64 + l].  The lane's own draws fill slots
-// 0, 1, ... (a register count); the drains, which resolve any lane's draws,
-// fill slots kLaneCap - 1, kLaneCap - 2, ... (an LDS count per owner).
-__device__ __forceinline__ void lane_slot_store(LaneRegion* L, int64_t* spill, int owner, int s,
-                                                int64_t x) {
-  spill[s * 64 + owner] = x;
+// Buckets of a lane's values above the column, eight per octave: 48.., 52..,
+// 56.., 60.., 64.., 72.., ..., the last one (11264..) open.
+constexpr int kLaneBuckets = 64;
+__device__ __forceinline__ int lane_bucket(uint64_t v) {
+  const int e = 63 - __clzll((long long)v);
+  const int b = 8 * (e - 5) + (int)((v >> (e - 3)) & 7u) - 4;
+  return b < kLaneBuckets - 1 ? b : kLaneBuckets - 1;
 }
-__device__ __forceinline__ void lane_insert(LaneRegion* L, int64_t* spill, int owner, int64_t x) {
-  if (x <= kHLB) {
-    const int v = (int)x - 1;
-    atomicAdd(&L->hist[(v >> 1) * 64 + owner], 1u << ((v & 1) * 16));
-  } else {
-    const uint32_t p = atomicAdd(&L->ovc[owner], 1u);
-    if (p < (uint32_t)kLaneCap) lane_slot_store(L, spill, owner, kLaneCap - 1 - (int)p, x);
-  }
+__device__ __forceinline__ uint64_t lane_bucket_start(int b) {
+  return (uint64_t)(8 + ((b + 4) & 7)) << (2 + ((b + 4) >> 3));
 }
 
-// Resolves ring entries [qh, qh + m) (one per lane) into the owners'
-// columns.  The leading wave_sync makes entries written by other lanes
-// visible; every caller is in wave-uniform control flow.
-__device__ __forceinline__ void lane_drain(LaneRegion* L, int64_t* spill, int m, uint32_t qh,
-                                           int64_t rep0, const DevCell& c,
-                                           const uint64_t* __restrict__ T,
-                                           const uint32_t* __restrict__ guide, int lane) {
-  wave_sync();
-  if (lane < m) {
-    uint32_t p = qh + (uint32_t)lane;
-    if (p >= (uint32_t)kRing) p -= (uint32_t)kRing;
-    const uint64_t e = L->ring[p];
-    const int owner = (int)((e >> 53) & 63u);
-    uint32_t fl = 0;
-    const int64_t x = resolve_entry(e, (uint32_t)(rep0 + owner), c, T, guide, fl);
-    if (fl) atomicOr(&L->fl[owner], fl);
-    lane_insert(L, spill, owner, x);
+// The finish's use of the wave's LDS region once the columns are read.
+typedef __attribute__((address_space(3))) uint8_t LdsU8;
+typedef __attribute__((address_space(3))) uint64_t LdsU64;
+constexpr int kLanePairs =
+    ((int)sizeof(LaneRegion) - 64 * kLaneBuckets - 64 * 4 - 64 * 8) / 8;  // gathered values
+static_assert(kLanePairs >= kLaneCap, "one lane's values always fit");
+
+// S, MLE and KS distance of one replicate per lane (called, not inlined: the
+// draw loop keeps its registers); every lane of the wave takes part, ok marks
+// those with a replicate.  region: the wave's LDS, the lane's packed counts at
+// dword b * 64 + lane; slots: its values above them, unsorted (the first myc
+// slots and the last od of kLaneCap), with as many free ones behind.
+// The KS needs no sort: past 16, past kHLB and between the edges of each
+// bucket both distributions are bounded by their values at the edges, and only
+// a bucket whose bound reaches the largest distance found has its values
+// looked at.  Those of all lanes are gathered into LDS and evaluated 64 at a
+// time whichever lane they belong to (a few lanes have most of them), each
+// ranked among its own lane's.  A rank sort of every value above the column
+// instead took 2.0 of 5.1 ns per replicate at alpha = 1.75, n = 1,000.
+struct LaneOut {
+  double a, D;
+  uint64_t fp;
+  uint32_t flags;
+};
+static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slots, int myc, int od,
+                                                   bool ok, int64_t n, uint32_t fl, bool want_fp,
+                                                   const double* __restrict__ ln) {
+  LaneOut o;
+  o.fp = 0;
+  const int lane = lane_id();
+  const LdsU32* column = region + lane;
+  const int oc = myc + od;
+  int64_t* more = slots + 64 * kLaneCap;
+  auto ov = [&](int q) -> int64_t {
+    return slots[(q < myc ? q : kLaneCap - od + (q - myc)) * 64];
+  };
+  // exact sums of the low and high words of ln v 2^53
+  uint64_t slo = 0, shi = 0;
+#pragma unroll 4
+  for (int q = 0; q < oc; ++q) {
+    const int64_t v = ov(q);
+    const uint64_t lf = ln_fixed_at(v, ln);
+    slo += (uint32_t)lf;
+    shi += lf >> 32;
+    if (want_fp) o.fp += mix64((uint64_t)v);
   }
+  for (int b = 0; b < kHLB / 2; ++b) {
+    const uint32_t wv = column[b * 64];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const uint32_t k = half ? (wv >> 16) : (wv & 0xffffu);
+      const int64_t v = 2 * b + half + 1;
+      const uint64_t lf = ln_fixed_table(ln)[v];
+      slo += (uint64_t)k * (uint32_t)lf;
+      shi += (uint64_t)k * (uint32_t)(lf >> 32);
+      if (want_fp) o.fp += (uint64_t)k * mix64((uint64_t)v);
+    }
+  }
+  const uint64_t s1 = slo + (shi << 32);
+  const U128 S{s1, (shi >> 32) + (s1 < slo ? 1u : 0u)};
+  o.flags = fl;
+  double Sd;
+  if (S.lo == 0 && S.hi == 0) {  // every draw was 1: S := ln 2
+    Sd = ln[2];
+    o.flags |= kFlagAllOnes;
+  } else {
+    Sd = u128_to_S(S);
+  }
+  o.a = mle_alpha_start(Sd / (double)n, ln, mle_guess_table(ln), &o.flags);
+  const EmCoef E = em_coef(o.a);
+  const double idn = 1.0 / (double)n;
+  const uint32_t nu = (uint32_t)n;  // lane form: n <= 65535
+  double D = 0.0, iz, zprev;
+  uint32_t C = 0;
+  {
+    double suf[17];
+    survival_head(E, ln, suf);
+    iz = 1.0 / suf[0];
+#pragma unroll
+    for (int v = 1; v <= 16; ++v) {
+      const uint32_t wv = column[((v - 1) >> 1) * 64];
+      const uint32_t c = (v & 1) ? (wv & 0xffffu) : (wv >> 16);
+      if (c) {
+        const double t2 = fabs(fma(suf[v - 1], iz, -(double)(nu - C) * idn));
+        C += c;
+        const double t1 = fabs(fma(suf[v], iz, -(double)(nu - C) * idn));
+        D = fmax(D, fmax(t1, t2));
+      }
+    }
+    zprev = suf[16];
+  }
+  bool live = ok && fmax(zprev * iz, (double)(nu - C) * idn) > D - kPruneMargin;
+  bool prev = true;  // zprev is the survival sum past v - 1
+  if (live) {
+    for (int v = 17; v <= kHLB; ++v) {
+      const uint32_t wv = column[((v - 1) >> 1) * 64];
+      const uint32_t c = (v & 1) ? (wv & 0xffffu) : (wv >> 16);
+      if (c) {
+        const double zv = hurwitz_tail(E, (double)(v + 1), ln[v + 1]);
+        const double zv1 = prev ? zprev : zv + pow_neg(E.s, ln[v]);
+        const double t2 = fabs(fma(zv1, iz, -(double)(nu - C) * idn));
+        C += c;
+        const double t1 = fabs(fma(zv, iz, -(double)(nu - C) * idn));
+        D = fmax(D, fmax(t1, t2));
+        zprev = zv;
+      }
+      prev = c != 0u;
+    }
+    if (!prev) zprev = hurwitz_tail(E, (double)(kHLB + 1), ln[kHLB + 1]);
+    live = oc > 0 && fmax(zprev * iz, (double)oc * idn) > D - kPruneMargin;
+  }
+  if (__ballot(live) == 0ull) {
+    o.D = D;
+    return o;
+  }
+  // the lane's bucket counts, then in their place the counts below each bucket
+  wave_sync();  // every column has been read
+  LdsU8* cum = (LdsU8*)region;  // bucket b of lane l at cum[b * 64 + l]
+  LdsU32* ends = region + 16 * kLaneBuckets;       // 64 inclusive counts
+  LdsU64* dmax = (LdsU64*)(ends + 64);             // 64 distances
+  LdsU64* pairs = dmax + 64;                       // kLanePairs values
+#pragma unroll 4
+  for (int k = lane; k < 16 * kLaneBuckets; k += 64) region[k] = 0u;
+  wave_sync();
+  uint64_t um = 0ull;  // buckets in reach
+  if (live) {
+    for (int q = 0; q < oc; ++q) {
+      LdsU8* c = cum + 64 * lane_bucket((uint64_t)ov(q)) + lane;
+      *c = (uint8_t)(*c + 1u);
+    }
+    // each bucket's bound, kept in scratch, and the largest distance at an edge
+    uint32_t lower = 0;
+    double zl = zprev * iz, Dlow = D;
+    int nb = 0;
+    for (; nb < kLaneBuckets; ++nb) {
+      const uint32_t c = cum[64 * nb + lane];
+      cum[64 * nb + lane] = (uint8_t)lower;
+      const double sl = (double)((uint32_t)oc - lower) * idn;
+      lower += c;
+      const double sr = (double)((uint32_t)oc - lower) * idn;
+      const double zr = nb < kLaneBuckets - 1
+                            ? iz * survival_next(E, (int64_t)lane_bucket_start(nb + 1) - 1, ln)
+                            : 0.0;
+      more[64 * nb] = __double_as_longlong(c ? fmax(zl - sr, sl - zr) : 0.0);
+      Dlow = fmax(Dlow, fabs(zr - sr));
+      if (fmax(zr, sr) <= Dlow - kPruneMargin) {
+        ++nb;
+        break;
+      }
+      zl = zr;
+    }
+    for (int b = 0; b < nb; ++b)
+      if (__longlong_as_double(more[64 * b]) > Dlow - kPruneMargin) um |= 1ull << b;
+  }
+  uint64_t pm = 0ull;  // buckets whose first value's predecessor was drawn
+  uint32_t cnt = 0;
+  if (um != 0ull) {
+#pragma unroll 4
+    for (int q = 0; q < oc; ++q) {
+      const uint64_t v = (uint64_t)ov(q);
+      const int b = lane_bucket(v), b1 = lane_bucket(v + 1u);
+      cnt += (uint32_t)((um >> b) & 1ull);
+      if (b1 != b) pm |= 1ull << b1;
+    }
+  }
+  uint32_t incl = cnt;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)incl, d, 64);
+    if (lane >= d) incl += u;
+  }
+  ends[lane] = incl;
+  dmax[lane] = (uint64_t)__double_as_longlong(D);
+  const uint32_t total = (uint32_t)__shfl((int)incl, 63, 64);
+  const uint32_t info = (uint32_t)oc | (prev ? 0x10000u : 0u);
+  for (uint32_t done = 0; done < total;) {  // windows of whole lanes that fit
+    const bool mine = cnt != 0u && incl - cnt >= done && incl - done <= (uint32_t)kLanePairs;
+    uint32_t p = incl - cnt - done;
+    if (mine) {
+#pragma unroll 4
+      for (int q = 0; q < oc; ++q) {
+        const int64_t v = ov(q);
+        if ((um >> lane_bucket((uint64_t)v)) & 1ull) pairs[p++] = (uint64_t)v;
+      }
+    }
+    // the last lane of the window (lanes in order: the prefix counts ascend)
+    const uint64_t in = __ballot(mine);
+    const uint32_t next = (uint32_t)__shfl((int)incl, 63 - __clzll((long long)in), 64);
+    wave_sync();
+    for (uint32_t f0 = done; f0 < next; f0 += 64u) {
+      const uint32_t f = f0 + (uint32_t)lane;
+      const bool valid = f < next;
+      int owner = 0;  // the first lane whose inclusive count exceeds f
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1)
+        if (ends[owner + step - 1] <= f) owner += step;
+      owner = valid ? owner : 0;
+      const uint32_t e1 = ends[owner], e0 = owner > 0 ? ends[owner - 1] : 0u;
+      auto from = [&](uint64_t x) {
+        const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)x, owner, 64);
+        const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(x >> 32), owner, 64);
+        return ((uint64_t)hi << 32) | lo;
+      };
+      const double as = __longlong_as_double((long long)from((uint64_t)__double_as_longlong(o.a)));
+      const double izo = __longlong_as_double((long long)from((uint64_t)__double_as_longlong(iz)));
+      const uint64_t pmo = from(pm);
+      const uint32_t io = (uint32_t)__shfl((int)info, owner, 64);
+      if (valid) {
+        const int64_t v = (int64_t)pairs[f - done];
+        const int b = lane_bucket((uint64_t)v);
+        const int64_t start = (int64_t)lane_bucket_start(b);
+        uint32_t lt = 0, eq = 0;
+        bool pres = v == kHLB + 1 ? (io >> 16) != 0u : (v == start && ((pmo >> b) & 1ull) != 0ull);
+        for (uint32_t k = e0 - done; k < e1 - done; ++k) {
+          const int64_t x = (int64_t)pairs[k];
+          lt += x < v && x >= start ? 1u : 0u;
+          eq += x == v ? 1u : 0u;
+          pres = pres || (x == v - 1 && x >= start);
+        }
+        const uint32_t Cb = nu - (io & 0xffffu) + cum[64 * b + owner] + lt;
+        const EmCoef Eo = em_coef(as);
+        const double zv = survival_next(Eo, v, ln);
+        const double zv1 =
+            pres ? survival_next(Eo, v - 1, ln) : zv + pow_neg(as, ln_value(v, ln));
+        const double t2 = fabs(fma(zv1, izo, -(double)(nu - Cb) * idn));
+        const double t1 = fabs(fma(zv, izo, -(double)(nu - Cb - eq) * idn));
+        __hip_atomic_fetch_max(&dmax[owner], (uint64_t)__double_as_longlong(fmax(t1, t2)),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    wave_sync();
+    done = next;
+  }
+  o.D = __longlong_as_double((long long)dmax[lane]);
+  return o;
+}
+
+// The same under the truncated law, each lane by itself: its values above the
+// column (few: they are rare under the planner's rule) sorted by rank.
+static __device__ __noinline__ LaneOut lane_finish_trunc(const LdsU32* column, int64_t* slots,
+                                                         int myc, int od, int64_t n, uint32_t fl,
+                                                         uint32_t K, bool want_fp,
+                                                         const double* __restrict__ ln) {
+  LaneOut o;
+  o.fp = 0;
+  const int oc = myc + od;
+  int64_t* more = slots + 64 * kLaneCap;
+  auto ov = [&](int q) -> int64_t {
+    return slots[(q < myc ? q : kLaneCap - od + (q - myc)) * 64];
+  };
+  U128 S = {0, 0};
+  for (int i = 0; i < oc; ++i) {
+    const int64_t v = ov(i);
+    int rank = 0;  // values below it, plus equal ones stored before it
+    for (int j = 0; j < oc; ++j) {
+      const int64_t x = ov(j);
+      rank += x < v || (x == v && j < i) ? 1 : 0;
+    }
+    more[rank * 64] = v;
+    u128_add(S, ln_fixed(v, ln), 0);
+    if (want_fp) o.fp += mix64((uint64_t)v);
+  }
+  for (int b = 0; b < kHLB / 2; ++b) {
+    const uint32_t wv = column[b * 64];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const uint32_t k = half ? (wv >> 16) : (wv & 0xffffu);
+      const int64_t v = 2 * b + half + 1;
+      u128_add_mul(S, k, ln_fixed(v, ln));
+      if (want_fp) o.fp += (uint64_t)k * mix64((uint64_t)v);
+    }
+  }
+  LaneSrc src{column, more, oc, 17, 0};
+  finish_replicate(src, S, n, fl, ln, K, o.a, o.D, o.flags);
+  return o;
+}
+
+// The whole tail draw of a deferred entry (called: rare, and long).
+struct TailDraw {
+  int64_t X;
+  uint32_t fl;
+};
+static __device__ __noinline__ TailDraw tail_draw_call(double beta, double gm, uint32_t k0,
+                                                       uint32_t k1, uint32_t i, uint32_t rep,
+                                                       uint32_t stream) {
+  TailDraw t;
+  t.fl = 0;
+  t.X = tail_draw(beta, gm, k0, k1, i, rep, stream, &t.fl);
+  return t;
+}
+
+__device__ __forceinline__ void lds_inc(LdsU32* p) {
+  __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_add(LdsU32* p, uint32_t v) {
+  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_or(LdsU32* p, uint32_t v) {
+  __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ uint32_t uniform32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+// slow_search through LDS pointers.
+__device__ __forceinline__ int lds_search(uint64_t m, const LdsU64* T, const LdsU32* guide,
+                                          int sh) {
+  const uint32_t g = guide[guide_index(m, sh)];
+  int lo = (int)(g & 0xffffu), hi = (int)((g >> 16) & (kDeferred - 1));
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (T[mid - 1] >= m)
+      hi = mid;
+    else
+      lo = mid + 1;
+  }
+  return lo;
 }
 
 // Draw blocks per iteration of the lane form's loop (two draws each).
 constexpr int kLaneBlocks = 2;  // four draws per lane and iteration
 static_assert(kLaneBlocks == 2, "the draw loop keeps four table reads in flight");
 
-__device__ __forceinline__ void lane_wave(const DevCell& c, int32_t cell_id, int64_t rep0,
-                                          int count, LaneRegion* L, int lane,
-                                          const uint64_t* __restrict__ T,
-                                          const uint32_t* __restrict__ guide,
-                                          const double* __restrict__ ln, const Outputs& out,
-                                          uint64_t* esc_list, uint32_t* esc_count,
-                                          uint32_t esc_cap, uint32_t* err, int64_t* spill) {
-  const bool active = lane < count;
+// The draws of replicates rep0 + lane, lane < count (called, so that the loop's
+// registers are its own): fast-path draws go straight into the lane's column,
+// deferred draws of all lanes wait in a ring (head qh, qn entries) and are
+// resolved 64 at a time by whichever lane picks them up, into the owner's
+// column or slots.  Values above the column take kLaneCap slots of the wave's
+// scratch, slot s of lane l at spill[s * 64 + l]: the lane's own draws fill
+// slots 0, 1, ... (the count returned), the resolved ones slots kLaneCap - 1,
+// kLaneCap - 2, ... (counted in L.ovc; either may exceed the room).
+static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_, int count_,
+                                              LdsU32* region, int64_t* spill_, const LdsU64* T,
+                                              const LdsU32* guide) {
+  const int lane = lane_id();
+  const DevCell& c = *reinterpret_cast<const DevCell*>(uniform64((int64_t)cell));
+  const uint32_t rep0 = uniform32((uint32_t)rep0_);
+  const bool active = lane < count_;
+  int64_t* __restrict__ spill = reinterpret_cast<int64_t*>(uniform64((int64_t)spill_));
+  LdsU32* hist = region + lane;
+  LdsU64* ring = (LdsU64*)(region + offsetof(LaneRegion, ring) / 4);
+  LdsU32* ovc = region + offsetof(LaneRegion, ovc) / 4;
+  LdsU32* lfl = region + offsetof(LaneRegion, fl) / 4;
 #pragma unroll
-  for (int b = 0; b < kHLB / 2; ++b) L->hist[b * 64 + lane] = 0u;
-  L->ovc[lane] = 0u;
-  L->fl[lane] = 0u;
+  for (int b = 0; b < kHLB / 2; ++b) hist[b * 64] = 0u;
+  ovc[lane] = 0u;
+  lfl[lane] = 0u;
   wave_sync();
-  const int64_t n = c.n;
-  const uint32_t r = (uint32_t)(rep0 + lane);
-  const uint32_t nblk = (uint32_t)((n + 1) >> 1);
-  // Deferred draws wait in a ring (head qh, qn entries, both wave-uniform).
+  const uint32_t n32 = uniform32((uint32_t)c.n);  // lane form: n <= 65535
+  const uint32_t nblk = (n32 + 1) >> 1;
+  const uint32_t r = rep0 + (uint32_t)lane;
+  const uint64_t timax = (uint64_t)uniform64((int64_t)table_int(c.tmax));
+  const int sh = (int)uniform32(c.gsh);
+  const uint32_t ck0 = uniform32(c.k0), ck1 = uniform32(c.k1), cs = uniform32(c.stream);
+  const double beta = c.beta, gm = c.gm;
+  const uint64_t below = lanes_below(lane);
   uint32_t qh = 0, qn = 0;
   int myc = 0;  // the lane's own values above the column
-  const uint64_t timax = table_int(c.tmax);
-  const int sh = (int)c.gsh;
-  const uint32_t n32 = (uint32_t)n;  // draw indexes are 32-bit
   // The loop is software-pipelined: an iteration issues the guide reads of
   // its uniforms, generates the next iteration's uniforms while they are in
   // flight, issues the table reads, and computes the next guide indexes while
@@ -1034,11 +1301,11 @@ __device__ __forceinline__ void lane_wave(const DevCell& c, int32_t cell_id, int
   auto gen = [&](uint32_t j, uint64_t (&Uo)[2 * kLaneBlocks]) {
     // the round keys are recomputed per block with scalar adds rather than
     // kept live across the loop (where they would be spilled)
-    uint32_t k0 = c.k0, k1 = c.k1;
+    uint32_t k0 = ck0, k1 = ck1;
     asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
     for (int b = 0; b < kLaneBlocks; ++b) {
-      const Words4 w = philox4x32_10(j + (uint32_t)b, r, c.stream, 0u, k0, k1);
+      const Words4 w = philox4x32_10(j + (uint32_t)b, r, cs, 0u, k0, k1);
       Uo[2 * b] = m53(w.w0, w.w1);
       Uo[2 * b + 1] = m53(w.w2, w.w3);
     }
@@ -1048,7 +1315,7 @@ __device__ __forceinline__ void lane_wave(const DevCell& c, int32_t cell_id, int
   gen(0u, U);
 #pragma unroll
   for (int d = 0; d < 2 * kLaneBlocks; ++d) gi[d] = guide_index(U[d], sh);
-  for (uint32_t j = 0; j < nblk; j += kLaneBlocks) {
+  for (uint32_t j = 0;;) {
     uint32_t gg[2 * kLaneBlocks];
 #pragma unroll
     for (int d = 0; d < 2 * kLaneBlocks; ++d) gg[d] = guide[gi[d]];
@@ -1066,433 +1333,135 @@ __device__ __forceinline__ void lane_wave(const DevCell& c, int32_t cell_id, int
     int x[2 * kLaneBlocks];
     bool def[2 * kLaneBlocks];
     bool big = false;
-    int xf[2 * kLaneBlocks];
-#pragma unroll
-    for (int d = 0; d < 2 * kLaneBlocks; ++d) xf[d] = fast_select(gg[d], t[d], U[d]);
+    uint32_t nd = 0;
 #pragma unroll
     for (int d = 0; d < 2 * kLaneBlocks; ++d) {
       const bool valid = active && 2u * j + (uint32_t)d < n32;
-      const int xd = xf[d];
+      const int xd = fast_select(gg[d], t[d], U[d]);
       const bool drawn = xd < kDeferred;
       x[d] = valid && drawn ? xd : -1;
       def[d] = valid && !drawn;
+      nd += def[d] ? 1u : 0u;
       big = big || x[d] > kHLB;
       // own column, no branch: values outside 1..kHLB count into the pad row
       const uint32_t xm1 = (uint32_t)(x[d] - 1);
       const uint32_t v = xm1 < (uint32_t)kHLB ? xm1 : (uint32_t)kHLB;
-      atomicAdd(&L->hist[(v >> 1) * 64 + lane], 1u << ((v & 1u) * 16u));
+      lds_add(&hist[(v >> 1) * 64], 1u << ((v & 1u) * 16u));
     }
     if (__ballot(big) != 0ull) {  // values above the column, into the lane's own slots
 #pragma unroll
       for (int d = 0; d < 2 * kLaneBlocks; ++d) {
         if (x[d] > kHLB) {
-          if (myc < kLaneCap) lane_slot_store(L, spill, lane, myc, x[d]);
+          if (myc < kLaneCap) spill[myc * 64 + lane] = x[d];
           ++myc;
         }
       }
     }
-    ring_append(L->ring, qh, qn, def, [&](int d) {
-      return defer_entry(U[d], timax, 2u * j + (uint32_t)d, lane);
-    }, lane);
-    while (qn >= 64u) {
-      lane_drain(L, spill, 64, qh, rep0, c, T, guide, lane);
-      qh = qh + 64u >= (uint32_t)kRing ? qh + 64u - (uint32_t)kRing : qh + 64u;
-      qn -= 64u;
+    // deferred draws into the ring (positions from three ballots of the counts)
+    if (__ballot(nd != 0u) != 0ull) {
+      const uint64_t b0 = __ballot(nd & 1u), b1 = __ballot(nd & 2u), b2 = __ballot(nd & 4u);
+      uint32_t pos = qh + qn + (uint32_t)(__popcll(b0 & below) + 2 * __popcll(b1 & below) +
+                                          4 * __popcll(b2 & below));
+#pragma unroll
+      for (int d = 0; d < 2 * kLaneBlocks; ++d) {
+        if (def[d]) {
+          ring[pos >= (uint32_t)kRing ? pos - (uint32_t)kRing : pos] =
+              defer_entry(U[d], timax, 2u * j + (uint32_t)d, lane);
+          ++pos;
+        }
+      }
+      qn += (uint32_t)(__popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2));
     }
+    j += (uint32_t)kLaneBlocks;
+    const bool more = j < nblk;
+    while (qn >= 64u || (!more && qn != 0u)) {
+      const uint32_t m = min(qn, 64u);
+      wave_sync();
+      if ((uint32_t)lane < m) {
+        const uint32_t p = qh + (uint32_t)lane;
+        const uint64_t e = ring[p >= (uint32_t)kRing ? p - (uint32_t)kRing : p];
+        const uint32_t owner = (uint32_t)(e >> 53) & 63u;
+        int64_t v;
+        if (e >> 63) {
+          const TailDraw td = tail_draw_call(beta, gm, ck0, ck1, (uint32_t)e, rep0 + owner, cs);
+          v = td.X;
+          if (td.fl) lds_or(&lfl[owner], td.fl);
+        } else {
+          v = (int64_t)lds_search(e & ((1ull << 53) - 1), T, guide, sh);
+        }
+        if (v <= kHLB) {
+          const uint32_t b = (uint32_t)v - 1u;
+          lds_add(&region[(b >> 1) * 64 + owner], 1u << ((b & 1u) * 16u));
+        } else {
+          const uint32_t s = __hip_atomic_fetch_add(&ovc[owner], 1u, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (s < (uint32_t)kLaneCap)
+            spill[(kLaneCap - 1 - (int)s) * 64 + (int)owner] = v;
+        }
+      }
+      qh = qh + m >= (uint32_t)kRing ? qh + m - (uint32_t)kRing : qh + m;
+      qn -= m;
+    }
+    if (!more) break;
 #pragma unroll
     for (int d = 0; d < 2 * kLaneBlocks; ++d) U[d] = Un[d];
   }
-  if (qn > 0u) lane_drain(L, spill, (int)qn, qh, rep0, c, T, guide, lane);
-  wave_sync_global();  // other lanes' drains wrote to this lane's spill entries
-  if (!active) return;
-  const int od = (int)L->ovc[lane];
-  const int oc = myc + od;
+  wave_sync_global();  // other lanes wrote to this lane's slots
+  return myc;
+}
+
+__device__ __forceinline__ void lane_wave(const DevCell* cells, int32_t cell_id, int64_t rep0,
+                                          int count, LaneRegion* L, int lane, const uint64_t* T,
+                                          const uint32_t* guide, const double* __restrict__ ln,
+                                          const Outputs& out, uint64_t* esc_list,
+                                          uint32_t* esc_count, uint32_t esc_cap, uint32_t* err,
+                                          int64_t* spill) {
+  const DevCell& c = cells[cell_id];
+  LdsU32* region = (LdsU32*)L->hist;
+  int myc = lane_draws(&c, rep0, count, region, spill, (const LdsU64*)T, (const LdsU32*)guide);
+  int od = (int)L->ovc[lane];
   const uint32_t fl = L->fl[lane];
-  if (oc > kLaneCap) {
+  bool ok = lane < count;
+  if (ok && myc + od > kLaneCap) {
     const uint32_t slot = atomicAdd(esc_count, 1u);
     if (slot < esc_cap)
-      esc_list[slot] = ((uint64_t)(uint32_t)cell_id << 32) | r;
+      esc_list[slot] = ((uint64_t)(uint32_t)cell_id << 32) | (uint32_t)(rep0 + lane);
     else
       atomicOr(err, kErrEscOverflow);
-    return;
+    ok = false;
   }
-  uint32_t* h = L->hist + lane;
-  U128 S = {0, 0};
-  uint64_t fp = 0;
-  int64_t xmax = 0;
-  // The larger values sorted into the scratch after the spill area: each
-  // goes to its rank (values below it, plus equal ones stored before it; no
-  // data-dependent moves), eight values at a time against one pass over all
-  // of them (independent reads), and the order-free sums are taken on the way.
-  // Value q of the lane: its own slots 0..myc-1, then the drains' slots.
-  const int64_t* g = spill + lane;
-  int64_t* srt = spill + 64 * kLaneCap + lane;  // entry p at srt[p * 64]
-  auto ovv = [&](int q) -> int64_t {
-    return g[(q < myc ? q : kLaneCap - od + (q - myc)) * 64];
-  };
-  for (int i0 = 0; i0 < oc; i0 += 8) {
-    int64_t v[8];
-    int rank[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      v[t] = i0 + t < oc ? ovv(i0 + t) : INT64_MAX;
-      rank[t] = 0;
-    }
-#pragma unroll 4
-    for (int j = 0; j < oc; ++j) {
-      const int64_t w = ovv(j);
-#pragma unroll
-      for (int t = 0; t < 8; ++t) rank[t] += (w < v[t] || (w == v[t] && j < i0 + t)) ? 1 : 0;
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      if (i0 + t < oc) {
-        srt[rank[t] * 64] = v[t];
-        u128_add(S, ln_fixed(v[t], ln), 0);
-        fp += mix64((uint64_t)v[t]);
-        xmax = v[t] > xmax ? v[t] : xmax;
-      }
-    }
-  }
-  for (int b = 0; b < kHLB / 2; ++b) {
-    const uint32_t wv = h[b * 64];
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const uint32_t k = half ? (wv >> 16) : (wv & 0xffffu);
-      const int64_t v = 2 * b + half + 1;
-      if (k) {
-        u128_add_mul(S, k, ln_fixed(v, ln));
-        fp += (uint64_t)k * mix64((uint64_t)v);
-        xmax = v > xmax ? v : xmax;
-      }
-    }
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the sorted list is read back
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  LaneSrc src{h, srt, oc, 17, 0};
-  double a, D;
-  uint32_t flags;
-  finish_replicate(src, S, n, fl, ln, c.K, a, D, flags);
-  write_outputs(out, c.out_off + rep0 + lane, D, a, flags, fp, xmax);
-}
-
-// ---------------------------------------------------------------------------
-// Wave form: one wave draws one replicate at a time into an LDS histogram;
-// finishes are deferred and run one replicate per lane.
-// ---------------------------------------------------------------------------
-struct WaveSlot {
-  U128 S;
-  uint64_t fp;
-  int64_t xmax;
-  uint32_t off, len, flags, esc;
-};
-
-__device__ __forceinline__ void wave_insert(WaveRegion* L, int64_t x) {
-  if (x <= kHW) {
-    atomicAdd(&L->hist[x - 1], 1u);
+  if (!ok) myc = od = 0;
+  const bool want_fp = out.fp != nullptr;
+  LaneOut o;
+  if (c.K) {
+    if (ok)
+      o = lane_finish_trunc(region + lane, spill + lane, myc, od, c.n, fl, c.K, want_fp, ln);
   } else {
-    const uint32_t p = atomicAdd(&L->ovc, 1u);
-    if (p < (uint32_t)kCW) L->ov[p] = x;
+    o = lane_finish(region, spill + lane, myc, od, ok, c.n, fl, want_fp, ln);
   }
-}
-
-// Resolves ring entries [qh, qh + m) (one per lane) into the histogram (see
-// lane_drain).
-// xm: the lane's largest value counted in the histogram so far.
-__device__ __forceinline__ void wave_drain(WaveRegion* L, int m, uint32_t qh, uint32_t rep,
-                                           const DevCell& c, const uint64_t* __restrict__ T,
-                                           const uint32_t* __restrict__ guide, uint32_t& fl,
-                                           int& xm, int lane) {
-  wave_sync();
-  int64_t v = 0;
-  if (lane < m) {
-    uint32_t p = qh + (uint32_t)lane;
-    if (p >= (uint32_t)kRing) p -= (uint32_t)kRing;
-    v = resolve_entry(L->ring[p], rep, c, T, guide, fl);
-    wave_insert(L, v);
-  }
-  xm = max(xm, v <= kHW ? (int)v : 0);
-}
-
-// Draw blocks per lane per iteration of the wave form's loop.
-constexpr int kWaveBlocks = 2;
-static_assert(kWaveBlocks == 2, "the draw loop keeps four table reads in flight");
-
-__device__ __forceinline__ void wave_batch(const DevCell& c, int32_t cell_id, int64_t r0,
-                                           int nrep, WaveRegion* L, WaveSlot* slots,
-                                           int64_t* __restrict__ lv, uint32_t* __restrict__ lc,
-                                           int lane, const uint64_t* __restrict__ T,
-                                           const uint32_t* __restrict__ guide,
-                                           const double* __restrict__ ln, const Outputs& out,
-                                           uint64_t* esc_list, uint32_t* esc_count,
-                                           uint32_t esc_cap, uint32_t* err) {
-  const int64_t n = c.n;
-  const uint32_t nblk = (uint32_t)((n + 1) >> 1);
-  int done = 0;
-  // histogram bins [0, hi) may be nonzero: the whole histogram at first (the
-  // region's LDS held other data), afterwards the 256-bin blocks up to the
-  // previous replicate's largest histogram value (the list build packs its
-  // entries below that too)
-  int hi = kHW;
-  while (done < nrep) {
-    // fill a batch of replicates while the list area has room for a worst case
-    int q = 0;
-    uint32_t used = 0;
-    while (done + q < nrep && q < 64 && used + (uint32_t)(kHW + kCW) <= (uint32_t)kListCap) {
-      const uint32_t r = (uint32_t)(r0 + done + q);
-      for (int k = lane; k < hi; k += 64) L->hist[k] = 0u;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) L->hist[kWaveOwn + k * 64 + lane] = 0u;
-      if (lane == 0) L->ovc = 0u;
-      wave_sync();
-      int xm = 0;  // the lane's largest table value (clamped to kHW after the loop)
-      uint32_t fl = 0;
-      uint32_t qh = 0, qn = 0;  // deferred-draw ring, wave-uniform
-      const uint64_t timax = table_int(c.tmax);
-      const int sh = (int)c.gsh;
-      const uint32_t n32 = (uint32_t)n;  // n <= 2^31
-      // software-pipelined as the lane form's loop
-      auto gen = [&](uint32_t j0, uint64_t (&Uo)[2 * kWaveBlocks]) {
-        uint32_t k0 = c.k0, k1 = c.k1;  // round keys per block (see lane_wave)
-        asm volatile("" : "+s"(k0), "+s"(k1));
-#pragma unroll
-        for (int b = 0; b < kWaveBlocks; ++b) {
-          const Words4 w = philox4x32_10(j0 + 64u * (uint32_t)b + (uint32_t)lane, r, c.stream,
-                                         0u, k0, k1);
-          Uo[2 * b] = m53(w.w0, w.w1);
-          Uo[2 * b + 1] = m53(w.w2, w.w3);
-        }
-      };
-      uint64_t U[2 * kWaveBlocks];  // uniforms as 53-bit integers m
-      int gi[2 * kWaveBlocks];      // their guide bins
-      gen(0u, U);
-#pragma unroll
-      for (int d = 0; d < 2 * kWaveBlocks; ++d) gi[d] = guide_index(U[d], sh);
-      for (uint32_t j0 = 0; j0 < nblk; j0 += 64u * kWaveBlocks) {
-        uint32_t gg[2 * kWaveBlocks];
-#pragma unroll
-        for (int d = 0; d < 2 * kWaveBlocks; ++d) gg[d] = guide[gi[d]];
-        uint64_t Un[2 * kWaveBlocks] = {1ull, 1ull, 1ull, 1ull};
-        if (j0 + 64u * kWaveBlocks < nblk) gen(j0 + 64u * kWaveBlocks, Un);  // none past the end
-        asm volatile("" : "+v"(Un[0]), "+v"(Un[1]), "+v"(Un[2]), "+v"(Un[3]));  // made here
-        uint64_t t[2 * kWaveBlocks];
-#pragma unroll
-        for (int d = 0; d < 2 * kWaveBlocks; ++d) t[d] = T[(int)(gg[d] & 0xffffu) - 1];
-        __builtin_amdgcn_sched_barrier(0);  // the table reads issue before the index math
-#pragma unroll
-        for (int d = 0; d < 2 * kWaveBlocks; ++d) gi[d] = guide_index(Un[d], sh);
-        asm volatile("" : "+v"(gi[0]), "+v"(gi[1]), "+v"(gi[2]), "+v"(gi[3]));  // made here
-        asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));  // reads stay unconditional
-        int x[2 * kWaveBlocks];
-        bool def[2 * kWaveBlocks];
-        bool big = false;
-        int xf[2 * kWaveBlocks];
-#pragma unroll
-        for (int d = 0; d < 2 * kWaveBlocks; ++d) xf[d] = fast_select(gg[d], t[d], U[d]);
-#pragma unroll
-        for (int d = 0; d < 2 * kWaveBlocks; ++d) {
-          const uint32_t i = 2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1);
-          const bool valid = i < n32;
-          const int xd = xf[d];
-          const bool drawn = xd < kDeferred;
-          x[d] = valid && drawn ? xd : -1;
-          def[d] = valid && !drawn;
-          big = big || x[d] > kHW;
-          // 1..3 count into the lane's own row, 4..kHW into their bin, and
-          // every other lane adds 1 to its pad slot (no divergent branch)
-          const uint32_t xm1 = (uint32_t)(x[d] - 1);
-          const int slot = xm1 < 3u ? kWaveOwn + (int)xm1 * 64 + lane
-                                    : (xm1 < (uint32_t)kHW ? (int)xm1 : kWavePad + lane);
-          atomicAdd(&L->hist[slot], 1u);
-          xm = max(xm, x[d]);  // values above kHW are clamped once, below
-        }
-        if (__ballot(big) != 0ull) {  // values above the histogram
-#pragma unroll
-          for (int d = 0; d < 2 * kWaveBlocks; ++d)
-            if (x[d] > kHW) wave_insert(L, x[d]);
-        }
-        ring_append(L->ring, qh, qn, def, [&](int d) {
-          return defer_entry(U[d], timax,
-                             2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1),
-                             0);
-        }, lane);
-        while (qn >= 64u) {
-          wave_drain(L, 64, qh, r, c, T, guide, fl, xm, lane);
-          qh = qh + 64u >= (uint32_t)kRing ? qh + 64u - (uint32_t)kRing : qh + 64u;
-          qn -= 64u;
-        }
-#pragma unroll
-        for (int d = 0; d < 2 * kWaveBlocks; ++d) U[d] = Un[d];
-      }
-      if (qn > 0u) wave_drain(L, (int)qn, qh, r, c, T, guide, fl, xm, lane);
-      fl = wave_or_u32(fl);
-      // bins the list build reads: whole 256-bin blocks up to the largest
-      // histogram value (every lane's xm is defined: set in converged code)
-      hi = ((int)min(wave_max_i64((int64_t)xm), (int64_t)kHW) + 255) & ~255;
-      hi = hi < 256 ? 256 : hi;
-      wave_sync();
-      // the own rows' totals, read and summed in converged code
-      const uint32_t c1 = wave_sum_u32(L->hist[kWaveOwn + lane]);
-      const uint32_t c2 = wave_sum_u32(L->hist[kWaveOwn + 64 + lane]);
-      const uint32_t c3 = wave_sum_u32(L->hist[kWaveOwn + 128 + lane]);
-      if (lane == 0) {
-        L->hist[0] += c1;  // drains count 1..3 into the bins themselves
-        L->hist[1] += c2;
-        L->hist[2] += c3;
-      }
-      wave_sync();
-      const uint32_t oc = L->ovc;
-      if (oc > (uint32_t)kCW) {
-        if (lane == 0) {
-          const uint32_t slot = atomicAdd(esc_count, 1u);
-          if (slot < esc_cap)
-            esc_list[slot] = ((uint64_t)(uint32_t)cell_id << 32) | r;
-          else
-            atomicOr(err, kErrEscOverflow);
-          slots[q].esc = 1u;
-        }
-        wave_sync();
-        ++q;
-        continue;
-      }
-      if (oc > 1 && oc <= 64u) {
-        const int64_t v = wave_sort64(lane < (int)oc ? L->ov[lane] : INT64_MAX, lane);
-        if (lane < (int)oc) L->ov[lane] = v;
-        wave_sync();
-      } else if (oc > 64u) {
-        const int P = next_pow2((int)oc);
-        static_assert(kCW <= 256, "the wave form's overflow is sorted in registers");
-        wave_sort_small_n(L->ov, P, (int)oc, lane);  // one LDS read and one write per value
-        wave_sync();
-      }
-      Summary s;
-      [[clang::always_inline]] s = build_list(L->hist, hi, L->ov, (int)oc, lv + used, lc + used,
-                                              lane, ln, n, out.fp != nullptr || out.xmax != nullptr);
-      if (lane == 0) {
-        WaveSlot sl;
-        sl.S = s.S;
-        sl.fp = s.fp;
-        sl.xmax = s.xmax;
-        sl.off = used;
-        sl.len = (uint32_t)s.len;
-        sl.flags = fl;
-        sl.esc = 0u;
-        slots[q] = sl;
-      }
-      used += (uint32_t)s.len;
-      ++q;
-    }
-    // the batch's lists and slots (global stores by various lanes) become
-    // visible to every lane once, here, before the finishes read them; each
-    // replicate wrote disjoint positions, so no ordering is needed earlier
-    wave_sync_global();
-    // deferred finishes, one replicate per lane
-    if (lane < q) {
-      const WaveSlot sl = slots[lane];
-      if (!sl.esc) {
-        ListSrc src(lv + sl.off, lc + sl.off, (int)sl.len);
-        double a, D;
-        uint32_t flags;
-        finish_replicate(src, sl.S, n, sl.flags, ln, c.K, a, D, flags);
-        write_outputs(out, c.out_off + r0 + done + lane, D, a, flags, sl.fp, sl.xmax);
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    wave_sync();
-    done += q;
-  }
+  if (ok) write_outputs(out, c.out_off + rep0 + lane, o.D, o.a, o.flags, o.fp);
 }
 
 // ---------------------------------------------------------------------------
-// Persistent simulation kernel: workgroups pull units (a cell and up to 512
-// replicates) from a global queue; the cell's table and guide are staged in
-// LDS when the cell changes.  Lane-form units give one replicate to each
-// lane; wave-form units give 64 replicates to each wave.
-// ---------------------------------------------------------------------------
-// Three waves per SIMD: the twelve waves' LDS regions and the shared table
-// fit one workgroup per compute unit, and the register budget is 168 per lane.
-static_assert(kBlock == 768, "twelve waves per workgroup, one workgroup per compute unit");
-__global__ __launch_bounds__(kBlock, 3) void k_simulate(
-    const DevCell* __restrict__ cells, const double* __restrict__ tables,
-    const uint16_t* __restrict__ guides, const double* __restrict__ ln,
-    const Unit* __restrict__ units, int n_units, uint32_t* queue, Outputs out,
-    uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* list_v,
-    uint32_t* list_c, WaveSlot* wslots, uint32_t* err) {
-  __shared__ SimLds L;
-  const int tid = (int)threadIdx.x;
-  const int wave = tid >> 6;
-  const int lane = tid & 63;
-  const int64_t gwave = (int64_t)blockIdx.x * kWaves + wave;
-  int64_t* lv = list_v + gwave * kListCap;
-  uint32_t* lc = list_c + gwave * kListCap;
-  WaveSlot* slots = wslots + gwave * 64;
-  int loaded = -1;
-
-  for (;;) {
-    if (tid == 0) L.unit = (int)atomicAdd(queue, 1u);
-    __syncthreads();
-    const int u = L.unit;
-    if (u >= n_units) break;
-    const Unit un = units[u];
-    const DevCell c = cells[un.cell];
-    if (un.cell != loaded) {
-      load_cell_tables(L.T, L.guide, tables + (size_t)un.cell * kH,
-                       guides + (size_t)un.cell * (kGuide + 1), c, tid, kBlock);
-      loaded = un.cell;
-      __syncthreads();
-    }
-    const int first = wave * 64;
-    if (first < un.count) {
-      const int nrep = (un.count - first) < 64 ? (un.count - first) : 64;
-      if (c.mode == kModeLane)
-        lane_wave(c, un.cell, un.r0 + first, nrep, &L.w[wave].lane, lane, L.T, L.guide, ln, out,
-                  esc_list, esc_count, esc_cap, err, lv);
-      else
-        wave_batch(c, un.cell, un.r0 + first, nrep, &L.w[wave].wave, slots, lv, lc, lane, L.T,
-                   L.guide, ln, out, esc_list, esc_count, esc_cap, err);
-    }
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Heavy form: 4 waves per workgroup share the table and guide; each wave
-// draws one replicate at a time, keeps values above kHeavyHist in its global
-// scratch and sorts them there.  Runs the planned heavy units, then every
-// replicate that overflowed the lane or wave form.
+// One dataset by one wave (the fits): values above kHeavyHist in global scratch,
+// sorted there.
 // ---------------------------------------------------------------------------
 struct alignas(16) HeavyWave {
-  uint32_t hist[kHeavyHist + 64];  // values 1..kHeavyHist; then one no-op pad slot per lane
-  uint64_t ring[kRing];            // deferred draws (simulated replicates)
+  uint32_t hist[kHeavyHist];  // values 1..kHeavyHist
   uint32_t ones[64];  // per-lane count of values equal to 1 (the most frequent value)
   uint32_t ovc;
-};
-
-struct HeavyLds {
-  uint64_t T[kH];  // floor(F(k) 2^53)
-  uint32_t guide[kGuide];
-  HeavyWave w[kHeavyWaves];
-  int item;
-};
-static_assert(2 * sizeof(HeavyLds) <= 160 * 1024, "two heavy workgroups per compute unit");
-
-struct GlobalSync {
-  __device__ void operator()() const { wave_sync_global(); }
 };
 
 // Histogram/overflow fill, sort, compact list and finish of one replicate by
 // one wave.  fill(sink, flags) calls sink(x) for every value.
 // K = 0: the pure law; K > 0: the truncated law on 1..K (values above K are
-// invalid, like values below 1).  kInlineList: the list build is inlined (the
-// fit kernels; out of line, with the histogram reached through a flat
-// pointer, a fit has been seen to return a wrong estimate); else the
-// compiler decides (the heavy kernel keeps it out of line, which spares its
-// registers, and passes every test).
-template <bool kInlineList, class Fill>
+// invalid, like values below 1).  The list build is inlined (out of line, with
+// the histogram reached through a flat pointer, a fit has been seen to return
+// a wrong estimate).
+template <class Fill>
 __device__ void heavy_core(HeavyWave* W, int64_t n, Fill fill, int64_t* gov, int64_t* lv,
-                           uint32_t* lc, const double* __restrict__ ln, uint32_t K, bool want_fp,
-                           double& a, double& D, uint32_t& flags, uint64_t& fp, int64_t& xmax,
-                           bool& ok, int64_t xmin = 1) {
+                           uint32_t* lc, const double* __restrict__ ln, uint32_t K, double& a, double& D,
+                           uint32_t& flags, bool& ok, int64_t xmin = 1) {
   const int lane = lane_id();
   for (int k = lane; k < kHeavyHist; k += 64) W->hist[k] = 0u;
   W->ones[lane] = 0u;
@@ -1537,35 +1506,9 @@ __device__ void heavy_core(HeavyWave* W, int64_t n, Fill fill, int64_t* gov, int
     wave_sort_global(gov, P, lane);
   }
   Summary s;
-  if constexpr (kInlineList) {
-    [[clang::always_inline]] s = build_list(W->hist, kHeavyHist, gov, oc, lv, lc, lane, ln, n,
-                                            want_fp);
-  } else {
-    s = build_list(W->hist, kHeavyHist, gov, oc, lv, lc, lane, ln, n, want_fp);
-  }
+  [[clang::always_inline]] s = build_list(W->hist, kHeavyHist, gov, oc, lv, lc, lane, ln, n);
   wave_sync_global();
   finish_replicate_wave(lv, lc, s.len, s.S, n, fl, ln, lane, K, a, D, flags, xmin);
-  fp = s.fp;
-  xmax = s.xmax;
-}
-
-// Adds one value per lane (lanes with valid set) to a simulated heavy-form
-// replicate, in wave-uniform control flow: ones to the wave's scalar count
-// (ballot), 2..kHeavyHist to the LDS histogram (lanes with nothing to add put
-// a zero into their own pad slot), larger values to the global overflow array
-// at positions from a ballot prefix (no atomics on a shared counter).
-__device__ __forceinline__ void heavy_put(HeavyWave* W, int64_t* gov, int64_t v, bool valid,
-                                          uint32_t& ones, uint32_t& ovn, int lane,
-                                          uint64_t below) {
-  ones += (uint32_t)__popcll(__ballot(valid && v == 1));
-  const bool hb = valid && v >= 2 && v <= kHeavyHist;
-  atomicAdd(&W->hist[hb ? (int)v - 1 : kHeavyHist + lane], 1u);  // pads are never read
-  const bool big = valid && v > kHeavyHist;
-  const uint64_t mb = __ballot(big);
-  if (mb != 0ull) {
-    if (big) gov[ovn + (uint32_t)__popcll(mb & below)] = v;
-    ovn += (uint32_t)__popcll(mb);
-  }
 }
 
 // Resolves a deferred draw of a cell with a lower cutoff (xmin = 1 for the
@@ -1579,156 +1522,6 @@ __device__ __forceinline__ int64_t resolve_entry_cut(uint64_t e, uint32_t rep, c
     return tail_draw_from((double)(c.xmin + kH), c.beta, c.gm, c.k0, c.k1, (uint32_t)e, rep,
                           c.stream, &fl);
   return (c.xmin - 1) + (int64_t)slow_search(e & ((1ull << 53) - 1), T, guide, (int)c.gsh);
-}
-
-// Resolves ring entries [qh, qh + m) (one per lane) into the replicate.
-__device__ __forceinline__ void heavy_drain(HeavyWave* W, int64_t* gov, int m, uint32_t qh,
-                                            uint32_t rep, const DevCell& c,
-                                            const uint64_t* __restrict__ T,
-                                            const uint32_t* __restrict__ guide, uint32_t& fl,
-                                            uint32_t& ones, uint32_t& ovn, int lane,
-                                            uint64_t below) {
-  wave_sync();  // entries appended by other lanes
-  int64_t v = 0;
-  if (lane < m) {
-    uint32_t p = qh + (uint32_t)lane;
-    if (p >= (uint32_t)kRing) p -= (uint32_t)kRing;
-    v = resolve_entry_cut(W->ring[p], rep, c, T, guide, fl);
-  }
-  heavy_put(W, gov, v, lane < m, ones, ovn, lane, below);
-}
-
-// One simulated replicate by one wave: the wave form's draw loop (two Philox
-// blocks per lane per iteration, guide lookups in phases, deferred draws in a
-// ring resolved 64 at a time) with the values above the LDS histogram in the
-// wave's global overflow array; then heavy_core's sort, list and finish.
-__device__ void heavy_replicate(HeavyWave* W, const uint64_t* __restrict__ T,
-                                const uint32_t* __restrict__ guide, const DevCell& c,
-                                uint32_t rep, int64_t* gov, int64_t* lv, uint32_t* lc,
-                                const double* __restrict__ ln, const Outputs& out) {
-  const int lane = lane_id();
-  const int64_t n = c.n;
-  const uint32_t nblk = (uint32_t)((n + 1) >> 1);
-  const uint64_t timax = table_int(c.tmax);
-  const int64_t off = c.xmin - 1;  // table index j is the value off + j
-  auto fill = [&](auto, uint32_t& fl) {
-    const uint64_t below = lanes_below(lane);
-    uint32_t ones = 0, ovn = 0;  // wave-uniform
-    uint32_t qh = 0, qn = 0;     // deferred-draw ring, wave-uniform
-    for (uint32_t j0 = 0; j0 < nblk; j0 += 64u * kWaveBlocks) {
-      // round keys per block (see lane_wave); the cell is the wave's, so its
-      // key is uniform: read from the first lane into scalar registers
-      uint32_t k0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.k0);
-      uint32_t k1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.k1);
-      asm volatile("" : "+s"(k0), "+s"(k1));
-      uint64_t U[2 * kWaveBlocks];
-#pragma unroll
-      for (int b = 0; b < kWaveBlocks; ++b) {
-        const Words4 w = philox4x32_10(j0 + 64u * (uint32_t)b + (uint32_t)lane, rep, c.stream,
-                                       0u, k0, k1);
-        U[2 * b] = m53(w.w0, w.w1);
-        U[2 * b + 1] = m53(w.w2, w.w3);
-      }
-      int xf[2 * kWaveBlocks];
-      fast_draw4(U, T, guide, (int)c.gsh, xf);
-      bool def[2 * kWaveBlocks];
-#pragma unroll
-      for (int d = 0; d < 2 * kWaveBlocks; ++d) {
-        const uint32_t i =
-            2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1);
-        const bool valid = (int64_t)i < n;
-        const bool drawn = xf[d] < kDeferred;
-        def[d] = valid && !drawn;
-        heavy_put(W, gov, off + (int64_t)xf[d], valid && drawn, ones, ovn, lane, below);
-      }
-      ring_append(W->ring, qh, qn, def, [&](int d) {
-        return defer_entry(U[d], timax,
-                           2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1),
-                           0);
-      }, lane);
-      while (qn >= 64u) {
-        heavy_drain(W, gov, 64, qh, rep, c, T, guide, fl, ones, ovn, lane, below);
-        qh = qh + 64u >= (uint32_t)kRing ? qh + 64u - (uint32_t)kRing : qh + 64u;
-        qn -= 64u;
-      }
-    }
-    if (qn > 0u) heavy_drain(W, gov, (int)qn, qh, rep, c, T, guide, fl, ones, ovn, lane, below);
-    if (lane == 0) {
-      W->ones[0] = ones;
-      W->ovc = ovn;
-    }
-  };
-  double a = 0.0, D = 0.0;
-  uint32_t flags = 0;
-  uint64_t fp;
-  int64_t xmax;
-  bool ok;
-  heavy_core<false>(W, n, fill, gov, lv, lc, ln, c.K, out.fp != nullptr || out.xmax != nullptr, a, D,
-             flags, fp, xmax, ok, c.xmin);
-  if (lane == 0) write_outputs(out, c.out_off + rep, D, a, flags, fp, xmax);
-  wave_sync_global();
-}
-
-// Two waves per SIMD (two workgroups per compute unit, which the LDS allows):
-// the register budget is then 256 per lane, against about 310 the compiler
-// takes when unbounded (one wave per SIMD); the few values it spills cost far
-// less than the halved latency hiding (the heavy form runs 1.6x faster).
-__global__ __launch_bounds__(64 * kHeavyWaves, 2) void k_heavy(
-    const DevCell* __restrict__ cells, const double* __restrict__ tables,
-    const uint16_t* __restrict__ guides, const double* __restrict__ ln,
-    const Unit* __restrict__ units, int n_units, const uint64_t* __restrict__ esc_list,
-    const uint32_t* __restrict__ esc_count, uint32_t esc_cap, uint32_t* queues,
-    Outputs out, int64_t* scratch, int64_t scratch_stride) {
-  __shared__ HeavyLds L;
-  const int tid = (int)threadIdx.x;
-  const int wave = tid >> 6;
-  const int64_t gw = (int64_t)blockIdx.x * kHeavyWaves + wave;
-  int64_t* gov = scratch + gw * scratch_stride;
-  // list area after the overflow area: values then counts
-  const int64_t half = scratch_stride / 2;
-  int64_t* lv = gov + half;
-  uint32_t* lc = reinterpret_cast<uint32_t*>(lv + half / 2);
-  int loaded = -1;
-  // planned heavy units: each wave takes every 4th replicate of the unit
-  for (;;) {
-    if (tid == 0) L.item = (int)atomicAdd(&queues[0], 1u);
-    __syncthreads();
-    const int u = L.item;
-    __syncthreads();
-    if (u >= n_units) break;
-    const Unit un = units[u];
-    const DevCell c = cells[un.cell];
-    if (un.cell != loaded) {
-      load_cell_tables(L.T, L.guide, tables + (size_t)un.cell * kH,
-                       guides + (size_t)un.cell * (kGuide + 1), c, tid, 64 * kHeavyWaves);
-      loaded = un.cell;
-      __syncthreads();
-    }
-    for (int k = wave; k < un.count; k += kHeavyWaves)
-      heavy_replicate(&L.w[wave], L.T, L.guide, c, (uint32_t)(un.r0 + k), gov, lv, lc, ln, out);
-    __syncthreads();
-  }
-  // replicates that overflowed the lane or wave form (wave 0 of each group)
-  const uint32_t ne = *esc_count < esc_cap ? *esc_count : esc_cap;
-  for (;;) {
-    if (tid == 0) L.item = (int)atomicAdd(&queues[1], 1u);
-    __syncthreads();
-    const uint32_t e = (uint32_t)L.item;
-    __syncthreads();
-    if (e >= ne) break;
-    const uint64_t code = esc_list[e];
-    const int cell = (int)(code >> 32);
-    const uint32_t rep = (uint32_t)code;
-    const DevCell c = cells[cell];
-    if (cell != loaded) {
-      load_cell_tables(L.T, L.guide, tables + (size_t)cell * kH,
-                       guides + (size_t)cell * (kGuide + 1), c, tid, 64 * kHeavyWaves);
-      loaded = cell;
-      __syncthreads();
-    }
-    if (wave == 0) heavy_replicate(&L.w[0], L.T, L.guide, c, rep, gov, lv, lc, ln, out);
-    __syncthreads();
-  }
 }
 
 }  // namespace zpl
@@ -1828,7 +1621,7 @@ __global__ __launch_bounds__(64 * kFitWaves) void k_fit_block(
     return;
   }
   Summary sm;
-  [[clang::always_inline]] sm = build_list(W.hist, kHeavyHist, gov, oc, lv, lc, lane, ln, n, false);
+  [[clang::always_inline]] sm = build_list(W.hist, kHeavyHist, gov, oc, lv, lc, lane, ln, n);
   wave_sync_global();
   double a = 0.0, D = 0.0;
   uint32_t flags = 0;
@@ -1886,11 +1679,8 @@ __global__ __launch_bounds__(64) void k_fit_scan(const int64_t* __restrict__ x, 
     };
     double a = 0.0, D = 0.0;
     uint32_t flags = 0;
-    uint64_t fp;
-    int64_t xmax;
     bool ok;
-    heavy_core<true>(&W, (int64_t)cnt, fill, gov, lv, lc, ln, 0u, false, a, D, flags, fp, xmax, ok,
-               xmin);
+    heavy_core(&W, (int64_t)cnt, fill, gov, lv, lc, ln, 0u, a, D, flags, ok, xmin);
     if (lane == 0) {
       ahat_out[cand] = a;
       D_out[cand] = D;
@@ -1922,10 +1712,8 @@ __global__ __launch_bounds__(64) void k_fit(const int64_t* const* __restrict__ x
     };
     double a = 0.0, D = 0.0;
     uint32_t flags = 0;
-    uint64_t fp;
-    int64_t xmax;
     bool ok;
-    heavy_core<true>(&W, n, fill, gov, lv, lc, ln, K, false, a, D, flags, fp, xmax, ok);
+    heavy_core(&W, n, fill, gov, lv, lc, ln, K, a, D, flags, ok);
     if (lane == 0) {
       ahat_out[set] = a;
       D_out[set] = D;
@@ -2055,6 +1843,13 @@ __global__ void k_ln_table(double* ln) {
   const double l = k == 0 ? 0.0 : log((double)k);
   ln[k] = l;
   reinterpret_cast<uint64_t*>(ln + kH + 2)[k] = (uint64_t)(l * 0x1p53);
+}
+
+// The MLE's start table.
+__global__ __launch_bounds__(64) void k_mle_guess(const double* __restrict__ ln,
+                                                  double* __restrict__ guess) {
+  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i < kGuessN) mle_guess_entry(i, ln, guess + 2 * i);
 }
 
 __global__ void k_fill_u32(uint32_t* p, int n, uint32_t v) {
@@ -2676,6 +2471,9 @@ namespace zpl {
 
 hipError_t launch_ln_table(double* ln, hipStream_t s) {
   k_ln_table<<<(kH + 2 + 255) / 256, 256, 0, s>>>(ln);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_mle_guess<<<(kGuessN + 63) / 64, 64, 0, s>>>(ln, ln + 2 * (kH + 2));
   return hipGetLastError();
 }
 
@@ -2703,43 +2501,38 @@ hipError_t launch_tables(DevCell* cells, int n_cells, double* tables, uint16_t* 
 
 static_assert(sizeof(WaveSlot) == kWaveSlotBytes, "WaveSlot layout");
 
-hipError_t launch_simulate(int grid, const DevCell* cells, const double* tables,
-                           const uint16_t* guides, const double* ln, const Unit* units,
-                           int n_units, uint32_t* queue, Outputs out, uint64_t* esc_list,
-                           uint32_t* esc_count, uint32_t esc_cap, int64_t* list_v,
-                           uint32_t* list_c, void* wslots, uint32_t* err, hipStream_t s) {
-  if (n_units <= 0 || grid <= 0) return hipSuccess;
-  k_simulate<<<grid, kBlock, 0, s>>>(cells, tables, guides, ln, units, n_units, queue, out,
-                                     esc_list, esc_count, esc_cap, list_v, list_c,
-                                     (WaveSlot*)wslots, err);
+hipError_t launch_simulate(const SimGrid& g, const DevCell* cells, const double* tables,
+                           const uint16_t* guides, const double* ln, const Unit* lane_units,
+                           int n_lane, const Unit* batch_units, int n_batch, uint32_t* lane_queue,
+                           uint32_t* batch_queue, Outputs out, uint64_t* esc_list,
+                           uint32_t* esc_count, uint32_t esc_cap, int64_t* slots,
+                           int64_t* scratch, uint32_t* err, hipStream_t s) {
+  if (g.grid <= 0) return hipSuccess;
+  k_simulate<<<g.grid, kBlock, 0, s>>>(g, cells, tables, guides, ln, lane_units, n_lane,
+                                       batch_units, n_batch, lane_queue, batch_queue, out,
+                                       esc_list, esc_count, esc_cap, slots, scratch, err);
   return hipGetLastError();
 }
 
-hipError_t launch_heavy(int grid, const DevCell* cells, const double* tables,
-                        const uint16_t* guides, const double* ln, const Unit* units,
-                        int n_units, const uint64_t* esc_list, const uint32_t* esc_count,
-                        uint32_t esc_cap, uint32_t* queues, Outputs out, int64_t* scratch,
-                        int64_t stride, hipStream_t s) {
+hipError_t launch_escalated(int grid, const DevCell* cells, const double* tables,
+                            const uint16_t* guides, const double* ln, uint32_t* queue, Outputs out,
+                            uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap,
+                            int64_t* scratch, int64_t stride, uint32_t* err, hipStream_t s) {
   if (grid <= 0) return hipSuccess;
-  k_heavy<<<grid, 64 * kHeavyWaves, 0, s>>>(cells, tables, guides, ln, units, n_units, esc_list, esc_count,
-                              esc_cap, queues, out, scratch, stride);
+  k_escalated<<<grid, 64 * kEscWaves, 0, s>>>(cells, tables, guides, ln, queue, out, esc_list,
+                                              esc_count, esc_cap, scratch, stride, err);
   return hipGetLastError();
 }
 
-hipError_t launch_batch(int grid, bool cut, const DevCell* cells, const double* tables,
-                        const uint16_t* guides, const double* ln, const Unit* units, int n_units,
-                        uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
-                        uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
-                        hipStream_t s) {
+hipError_t launch_cutoff(int grid, const DevCell* cells, const double* tables,
+                         const uint16_t* guides, const double* ln, const Unit* units, int n_units,
+                         uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
+                         uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
+                         hipStream_t s) {
   if (n_units <= 0 || grid <= 0) return hipSuccess;
-  if (cut)
-    k_batch<true, kBatchWavesCut><<<grid, 64 * kBatchWavesCut, 0, s>>>(
-        cells, tables, guides, ln, units, n_units, queue, out, esc_list, esc_count, esc_cap,
-        scratch, stride, err);
-  else
-    k_batch<false, kBatchWaves><<<grid, 64 * kBatchWaves, 0, s>>>(
-        cells, tables, guides, ln, units, n_units, queue, out, esc_list, esc_count, esc_cap,
-        scratch, stride, err);
+  k_cutoff<<<grid, 64 * kBatchWavesCut, 0, s>>>(cells, tables, guides, ln, units, n_units, queue,
+                                                out, esc_list, esc_count, esc_cap, scratch, stride,
+                                                err);
   return hipGetLastError();
 }
 

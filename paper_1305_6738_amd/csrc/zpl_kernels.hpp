@@ -26,33 +26,34 @@ constexpr int kGBits = 6;
 constexpr int kOctaves = 52;  // e in [2^-53, 1/2)
 constexpr int kGuide = kGA + (kOctaves << kGBits);
 
-// Simulation kernel geometry: 8 wave64 per workgroup share the CDF table and
+// Lane-form kernel geometry: twelve wave64 per workgroup share the CDF table and
 // the guide in LDS.
 constexpr int kWaves = 12;  // three per SIMD
 constexpr int kBlock = 64 * kWaves;
 // Lane form: one replicate per lane; per-lane histogram of values 1..kHLB
 // (16-bit counters packed two per dword) plus a per-lane list of up to
 // kLaneCap larger values in the wave's global scratch (a replicate with more
-// is redone by the heavy form).
+// is escalated).
 constexpr int kHLB = 48;
-constexpr int kLaneCap = 128;
-// Wave form: one replicate per wave at a time; histogram of values 1..kHW
-// plus up to kCW larger values in LDS; finishes run one replicate per lane.
+constexpr int kLaneCap = 224;
+// int64 of scratch per wave of the lane form: kLaneCap slots per lane, and as
+// many again for the finish.
+constexpr int kLaneScratch = 64 * 2 * kLaneCap;
+// Wave and heavy forms: one replicate per wave at a time, in batches that a
+// wave finishes together (k_batch): histogram of values 1..kHW in LDS, larger
+// ones in the wave's global scratch.  Waves per workgroup (one workgroup per
+// compute unit) without and with a lower cutoff: three waves per SIMD are
+// better for the former (heavy tails of 10,000 draws: 5.81 against 6.16 ms at
+// two), two for the latter, whose survival values take more registers (1,000
+// draws: 7.18 against 7.90 ms at three).
 constexpr int kHW = 1024;
-constexpr int kCW = 248;
-// Compact (value, count) list capacity per wave for deferred finishes.
-constexpr int kListCap = 16 * (kHW + kCW);
-// Heavy form: 4 wave64 per workgroup, values above kHeavyHist in per-wave
-// global scratch (sorted there).
-constexpr int kHeavyWaves = 4;
-constexpr int kHeavyHist = 1024;
-// Batched heavy form: wave64 per workgroup (one workgroup per compute unit),
-// for cells without and with a lower cutoff.  Three waves per SIMD are better
-// for the former (heavy tails of 10,000 draws: 5.81 against 6.16 ms at two),
-// two for the latter, whose survival values take more registers (1,000 draws:
-// 7.18 against 7.90 ms at three).
 constexpr int kBatchWaves = 12;
 constexpr int kBatchWavesCut = 8;
+// Waves per workgroup that run escalated replicates (whole replicates of
+// scratch each, so few).
+constexpr int kEscWaves = 4;
+// Dataset fits: histogram of the values 1..kHeavyHist in LDS.
+constexpr int kHeavyHist = 1024;
 // Allocation-free fit: the overflow values and the compact list of one
 // dataset of up to kNoAllocMaxN values live in a fixed device array of
 // kNoAllocStride int64 (the heavy layout's stride for that n:
@@ -64,8 +65,7 @@ constexpr int64_t kNoAllocStride = 2 * (2 * ((int64_t)kHeavyHist + kNoAllocMaxN)
 // bracket gather scratch.
 constexpr int kSelQ = 4;
 constexpr int64_t kSelGather = 32768;
-// Size of the per-replicate record of a wave-form batch (global scratch,
-// 64 per wave).
+// Size of the per-replicate record of a batch (global scratch, 64 per wave).
 constexpr int kWaveSlotBytes = 48;
 
 enum Mode : uint32_t { kModeLane = 0, kModeWave = 1, kModeHeavy = 2 };
@@ -84,6 +84,10 @@ struct DevCell {
   uint32_t K;       // 0: the pure law; else the truncated law on 1..K
   uint32_t gsh;     // guide refinement: 2^(kGBits + gsh) bins per octave of 1 - U
   int64_t xmin;     // lower cutoff of the pure law (1: none); values >= xmin
+  // wave and heavy forms: scratch kept free for a replicate's values above the
+  // histogram before it is begun (n: all it can have)
+  uint32_t room;
+  uint32_t pad;
 };
 
 struct Unit {
@@ -92,12 +96,19 @@ struct Unit {
   int64_t r0;     // first replicate
 };
 
+// Launch shape of the simulation kernel: workgroups 0 .. lane_wgs - 1 take
+// lane-form units (of at most 64 lane_waves replicates), the last batch_wgs
+// wave- and heavy-form ones, with `stride` int64 of scratch per wave.
+struct SimGrid {
+  int32_t grid, lane_wgs, lane_waves, batch_wgs;
+  int64_t stride;
+};
+
 struct Outputs {
   double* D;
   double* ahat;
   uint32_t* flags;
   uint64_t* fp;
-  int64_t* xmax;
 };
 
 // Error bits written by kernels into the context's error word.

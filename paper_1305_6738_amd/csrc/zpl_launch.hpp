@@ -7,7 +7,8 @@
 
 namespace zpl {
 
-// ln k for k = 0..kH+1 (doubles), then ln k 2^53 as integers (uint64).
+// The context's constants: ln k for k = 0..kH+1 (doubles), ln k 2^53 as
+// integers (uint64), then the MLE's start table (2 kGuessN doubles).
 hipError_t launch_ln_table(double* ln, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t s);
 // CDF tables (the truncated law's only when any_trunc: a cell with K > 0)
@@ -15,24 +16,28 @@ hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t s);
 hipError_t launch_tables(DevCell* cells, int n_cells, double* tables, uint16_t* guides,
                          const double* ln, hipStream_t s, bool any_trunc = true,
                          uint32_t* zero = nullptr, int n_zero = 0);
-hipError_t launch_simulate(int grid, const DevCell* cells, const double* tables,
-                           const uint16_t* guides, const double* ln, const Unit* units,
-                           int n_units, uint32_t* queue, Outputs out, uint64_t* esc_list,
-                           uint32_t* esc_count, uint32_t esc_cap, int64_t* list_v,
-                           uint32_t* list_c, void* wslots, uint32_t* err, hipStream_t s);
-hipError_t launch_heavy(int grid, const DevCell* cells, const double* tables,
-                        const uint16_t* guides, const double* ln, const Unit* units,
-                        int n_units, const uint64_t* esc_list, const uint32_t* esc_count,
-                        uint32_t esc_cap, uint32_t* queues, Outputs out, int64_t* scratch,
-                        int64_t stride, hipStream_t s);
-// Batched heavy-form units of pure-law cells (cut = false) or of cells with a
-// lower cutoff (cut = true); scratch: an area of `stride` int64 for each wave
-// of the grid (kBatchWaves or kBatchWavesCut per workgroup).
-hipError_t launch_batch(int grid, bool cut, const DevCell* cells, const double* tables,
-                        const uint16_t* guides, const double* ln, const Unit* units, int n_units,
-                        uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
-                        uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
-                        hipStream_t s);
+// Lane-form units and wave- and heavy-form ones in one launch; slots: lane_wgs
+// * lane_waves areas of kLaneScratch int64, scratch: batch_wgs * kBatchWaves of
+// g.stride.
+hipError_t launch_simulate(const SimGrid& g, const DevCell* cells, const double* tables,
+                           const uint16_t* guides, const double* ln, const Unit* lane_units,
+                           int n_lane, const Unit* batch_units, int n_batch, uint32_t* lane_queue,
+                           uint32_t* batch_queue, Outputs out, uint64_t* esc_list,
+                           uint32_t* esc_count, uint32_t esc_cap, int64_t* slots,
+                           int64_t* scratch, uint32_t* err, hipStream_t s);
+// The escalated replicates (none: a few empty workgroups); scratch: grid *
+// kEscWaves areas of `stride` int64, each for a replicate's every draw.
+hipError_t launch_escalated(int grid, const DevCell* cells, const double* tables,
+                            const uint16_t* guides, const double* ln, uint32_t* queue, Outputs out,
+                            uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap,
+                            int64_t* scratch, int64_t stride, uint32_t* err, hipStream_t s);
+// The units of cells with a lower cutoff; scratch: grid * kBatchWavesCut areas of
+// `stride` int64.
+hipError_t launch_cutoff(int grid, const DevCell* cells, const double* tables,
+                         const uint16_t* guides, const double* ln, const Unit* units, int n_units,
+                         uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
+                         uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
+                         hipStream_t s);
 hipError_t launch_fit(int grid, const int64_t* const* xs, const int64_t* ns, int n_sets,
                       const double* ln, int64_t* scratch, int64_t stride, double* ahat,
                       double* D, uint32_t* flags, uint32_t* status, uint32_t K, hipStream_t s);

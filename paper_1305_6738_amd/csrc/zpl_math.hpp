@@ -294,6 +294,88 @@ ZPL_HD double mle_alpha(double m, const double* __restrict__ ln, uint32_t* flags
   return a;
 }
 
+// ---------------------------------------------------------------------------
+// The same root from a tabulated start.  y(t) = ln(alpha - 1) at m = e^t is
+// smooth over the means of logarithms that samples can have (t from ln(ln 2 /
+// 2^31), one 2 among 2^31 ones, to ln ln 2^63), so a cubic through values and
+// slopes on a grid of 1/32 starts Newton within about 1e-8 of alpha - 1, and
+// its first step ends at the rounding of mu.  Newton doubles the correct
+// digits: after a step of at most 2^-26 (alpha - 1) what is left is below
+// 2^-52 (alpha - 1), so one evaluation of the zeta sums is enough where the
+// start of mle_alpha took two to five.  Means outside the table start as there;
+// the bracket and its bisection are mle_alpha's.
+// guess: kGuessN pairs (y, dy/dt / 32), at t = kGuessLo + i / 32.
+// ---------------------------------------------------------------------------
+constexpr int kGuessPerUnit = 32;
+constexpr double kGuessLo = -22.25;
+constexpr int kGuessN = 835;  // to t = 3.8125
+
+// The table's entry i.
+ZPL_HD void mle_guess_entry(int i, const double* __restrict__ ln, double out[2]) {
+  const double m = exp(kGuessLo + (double)i / kGuessPerUnit);
+  uint32_t fl = 0;
+  const double a = mle_alpha(m, ln, &fl);
+  const Z3 z = zeta3(a, ln);
+  const double mu = -z.z1 / z.z0;
+  const double var = fma(-mu, mu, z.z2 / z.z0);
+  out[0] = log(a - 1.0);
+  out[1] = -m / (var * (a - 1.0)) / kGuessPerUnit;
+}
+
+ZPL_HD double mle_alpha_start(double m, const double* __restrict__ ln,
+                              const double* __restrict__ guess, uint32_t* flags,
+                              int* iters = nullptr) {
+  const double lm = log(m);
+  const double u = (lm - kGuessLo) * kGuessPerUnit;
+  double a;
+  if (u >= 0.0 && u < (double)(kGuessN - 1)) {
+    const int i = (int)u;
+    const double f = u - (double)i;
+    const double y0 = guess[2 * i], d0 = guess[2 * i + 1];
+    const double y1 = guess[2 * i + 2], d1 = guess[2 * i + 3];
+    const double dy = y1 - y0;
+    // y0 + f (d0 + f (3 dy - 2 d0 - d1 + f (d0 + d1 - 2 dy)))
+    const double c3 = d0 + d1 - 2.0 * dy, c2 = 3.0 * dy - 2.0 * d0 - d1;
+    a = 1.0 + exp(fma(f, fma(f, fma(f, c3, c2), d0), y0));
+  } else {  // the start of mle_alpha
+    const double a1 = 1.0 + 1.0 / (m + 0.5772156649015329);
+    const double a2 = (-0.36651292058166433 - lm) / ln[2];  // log2(ln 2 / m)
+    a = a1 > a2 ? a1 : a2;
+  }
+  double lo = 1.0 + 0x1p-20, hi = 64.0;
+  if (!(a > lo && a < hi)) a = 0.5 * (lo + hi);
+  const double im = 1.0 / m;
+  double gl = 0.0;  // the last residual of eq. 2
+  int it = 0;
+  for (; it < kMleCap; ++it) {
+    const Z3 z = zeta3(a, ln);
+    const double iz = 1.0 / z.z0;
+    const double mu = -z.z1 * iz;
+    if (mu == m) break;
+    gl = mu - m;
+    if (mu > m)
+      lo = a;
+    else
+      hi = a;
+    const double var = fma(-mu, mu, z.z2 * iz);
+    const double x = gl * im;
+    // ln(mu/m): past the first step the quadratic series is exact to rounding
+    const double l = fabs(x) < 0x1p-16 ? x * fma(-0.5, x, 1.0) : log(mu) - lm;
+    const double step = l * (mu / var);
+    double an = a + step;
+    if (!(an >= lo && an <= hi)) {
+      an = 0.5 * (lo + hi);
+      *flags |= kFlagBisect;
+    }
+    const bool done = fabs(an - a) <= 0x1p-26 * (an - 1.0);
+    a = an;
+    if (done) break;
+  }
+  if (iters) *iters = it < kMleCap ? it + 1 : it;
+  if (it == kMleCap && !(fabs(gl) <= 0x1p-44 * m)) *flags |= kFlagNoConv;
+  return a;
+}
+
 // ln of an integer value: from the table for v <= kH + 1, else computed.
 ZPL_HD double ln_value(int64_t v, const double* __restrict__ ln) {
   return v <= (int64_t)(kH + 1) ? ln[v] : log((double)v);
@@ -436,16 +518,49 @@ ZPL_HD double mle_alpha_hz(double m, int64_t xmin, const double* __restrict__ ln
 // Truncated law on 1..K (Sect. 1 with a finite upper limit): Z_K(s) =
 // sum_{k<=K} k^-s and its first two s-derivatives by direct summation, index
 // K down to 1.  Defined for every real s; |s| <= 64 and K <= 4097 keep every
-// term below 2^768.
+// term below 2^768.  The powers up to 16 come from those of the six primes
+// there (direct_powers).
 // ---------------------------------------------------------------------------
+constexpr int kDirect = 16;
+
+// k^-s for k = 2..min(K, 16): one exponential per prime, products in a fixed
+// order for the others.  pw[k] for k = 0..16 (pw[0] unused; 0 above K's primes
+// is never read: a composite's factors are below it).
+ZPL_HD void direct_powers(double s, uint32_t K, const double* __restrict__ ln,
+                          double (&pw)[kDirect + 1]) {
+  pw[0] = 0.0;
+  pw[1] = 1.0;
+#pragma unroll
+  for (int k = 2; k <= kDirect; ++k) {
+    int f = k;  // the smallest factor of k
+    for (int d = 2; d * d <= k; ++d)
+      if (k % d == 0) {
+        f = d;
+        break;
+      }
+    pw[k] = f < k ? pw[f] * pw[k / f] : ((uint32_t)k <= K ? pow_neg(s, ln[k]) : 0.0);
+  }
+}
+
 ZPL_HD Z3 zeta3_trunc(double s, uint32_t K, const double* __restrict__ ln) {
   double z0 = 0.0, z1 = 0.0, z2 = 0.0;
-  for (int k = (int)K; k >= 2; --k) {
+  for (int k = (int)K; k > kDirect; --k) {
     const double l = ln[k];
     const double t = pow_neg(s, l);
     z0 += t;
     z1 = fma(-l, t, z1);
     z2 = fma(l * l, t, z2);
+  }
+  double pw[kDirect + 1];
+  direct_powers(s, K, ln, pw);
+#pragma unroll
+  for (int k = kDirect; k >= 2; --k) {
+    if ((uint32_t)k <= K) {
+      const double l = ln[k], t = pw[k];
+      z0 += t;
+      z1 = fma(-l, t, z1);
+      z2 = fma(l * l, t, z2);
+    }
   }
   z0 += 1.0;
   return Z3{z0, z1, z2};
@@ -615,7 +730,9 @@ ZPL_HD double mle_alpha_trunc(double m, uint32_t K, const double* __restrict__ l
       *flags |= kFlagBisect;
     }
     const double scale = fabs(a) > 1.0 ? fabs(a) : 1.0;
-    const bool done = fabs(an - a) <= 0x1p-40 * scale;
+    // away from the edge m -> ln K the steps shrink quadratically, and what is
+    // left after one of 2^-27 is below 2^-50
+    const bool done = fabs(an - a) <= (m < 0.875 * ln[K] ? 0x1p-27 : 0x1p-40) * scale;
     a = an;
     if (done) break;
   }
@@ -638,6 +755,57 @@ ZPL_HD double mle_alpha_trunc(double m, uint32_t K, const double* __restrict__ l
     }
   }
   return a;
+}
+
+// ---------------------------------------------------------------------------
+// Survival sums of the truncated law, sum_{t < k <= K} k^-s for t >= 16, where
+// zeta3_trunc_em applies (trunc_em): Euler-Maclaurin between q = t + 1 and K,
+//   q^-s [q (e^{uL} - 1)/u + 1/2 + sum_i k_i q^-(2i-1)] + end,
+// u = 1 - s, L = ln(K/q), k_i the factors of EmCoef (finite for every real s)
+// and end = K^-s [1/2 - sum_i k_i K^-(2i-1)] the same for every t.  One power
+// and one expm1 for any t, where a running sum takes a power per support value.
+// At q = 17 the eight Bernoulli terms leave an error that is negligible against
+// the normaliser (s > 0: as for zeta(s); s < 0: K^-s outweighs 17^-s, K being
+// 48 or more above em_start(|s|)).
+// ---------------------------------------------------------------------------
+struct TruncEnd {
+  double u, iu, lnK, end;
+  int64_t K;
+};
+ZPL_HD bool trunc_em(double s, uint32_t K) { return (int64_t)K >= em_start(fabs(s)) + 48; }
+ZPL_HD double em_poly(const EmCoef& E, double iq) {
+  const double iq2 = iq * iq;
+  double acc = E.k[7];
+#pragma unroll
+  for (int i = 6; i >= 0; --i) acc = fma(acc, iq2, E.k[i]);
+  return acc * iq;
+}
+ZPL_HD TruncEnd trunc_end(const EmCoef& E, uint32_t K, const double* __restrict__ ln) {
+  TruncEnd e;
+  e.u = 1.0 - E.s;
+  e.iu = e.u == 0.0 ? 0.0 : 1.0 / e.u;
+  e.lnK = ln[K];
+  e.end = pow_neg(E.s, e.lnK) * (0.5 - em_poly(E, recip((double)K)));
+  e.K = (int64_t)K;
+  return e;
+}
+// The sum over t < k <= K; lnq = ln(t + 1).
+ZPL_HD double trunc_tail(const EmCoef& E, const TruncEnd& e, int64_t t, double lnq) {
+  if (t >= e.K) return 0.0;
+  const double q = (double)(t + 1);
+  const double L = e.lnK - lnq;
+  const double g = e.u == 0.0 ? L : expm1(e.u * L) * e.iu;
+  return pow_neg(E.s, lnq) * (fma(q, g, 0.5) + em_poly(E, recip(q))) + e.end;
+}
+// suf[t] = the sum over t < k <= K, t = 0..16.
+ZPL_HD void survival_head_trunc(const EmCoef& E, const TruncEnd& e, const double* __restrict__ ln,
+                                double suf[17]) {
+  double pw[17];
+  small_powers(E.s, ln, pw);
+  suf[16] = trunc_tail(E, e, 16, ln[17]);
+#pragma unroll
+  for (int t = 15; t >= 1; --t) suf[t] = suf[t + 1] + pw[t + 1];
+  suf[0] = suf[1] + 1.0;
 }
 
 // ---------------------------------------------------------------------------
