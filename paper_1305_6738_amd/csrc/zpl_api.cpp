@@ -984,39 +984,25 @@ zpl_status autotune_grid(zpl_ctx* c, const double* alphas, int na, const int64_t
 
 zpl_status fit_device(zpl_ctx* c, const int64_t* xd, int64_t n, hipStream_t s, double* ahat,
                       double* D, uint32_t* flags, uint32_t* status, uint32_t K = 0) {
-  const int64_t stride = heavy_stride(n);
-  ZPL_TRY(ensure(c, c->fit_ptrs, sizeof(int64_t*)));
-  ZPL_TRY(ensure(c, c->fit_ns, sizeof(int64_t)));
-  ZPL_TRY(ensure(c, c->fit_out, sizeof(double) * 2 + sizeof(uint32_t) * 2));
-  ZPL_TRY(ensure(c, c->fit_st, sizeof(uint32_t) * 2));
-  ZPL_TRY(ensure(c, c->heavy, grow_size(sizeof(int64_t) * (size_t)stride)));
+  struct Out {
+    double a, D;
+    uint32_t flags, status;
+  } out;
+  ZPL_TRY(ensure(c, c->fit_out, sizeof(Out)));
+  ZPL_TRY(ensure(c, c->heavy, grow_size(sizeof(int64_t) * (size_t)heavy_stride(n))));
   ZPL_TRY(ensure_pinned(c, 64));
+  Out* o = (Out*)c->fit_out.p;
+  HIP_TRY(launch_fit_one(xd, n, c->ln, (int64_t*)c->heavy.p, &o->a, &o->D, &o->flags, &o->status, K,
+                         s));
+  HIP_TRY(hipMemcpyAsync(c->pin, o, sizeof(Out), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  int64_t* pin = (int64_t*)c->pin;
-  pin[0] = (int64_t)(intptr_t)xd;
-  pin[1] = n;
-  HIP_TRY(hipMemcpyAsync(c->fit_ptrs.p, &pin[0], sizeof(int64_t), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(c->fit_ns.p, &pin[1], sizeof(int64_t), hipMemcpyHostToDevice, s));
-  double* o = (double*)c->fit_out.p;
-  uint32_t* of = (uint32_t*)(o + 2);
-  // a large dataset is read, histogrammed and sorted by a whole workgroup
-  // (the same list and finish, so the same bits as the one-wave kernel)
-  if (n >= kFitBlockMin)
-    HIP_TRY(launch_fit_block(xd, n, c->ln, (int64_t*)c->heavy.p, stride, o, o + 1, of,
-                             (uint32_t*)c->fit_st.p, K, s));
-  else
-    HIP_TRY(launch_fit(1, (const int64_t* const*)c->fit_ptrs.p, (const int64_t*)c->fit_ns.p, 1,
-                       c->ln, (int64_t*)c->heavy.p, stride, o, o + 1, of,
-                       (uint32_t*)c->fit_st.p, K, s));
-  char* hp = (char*)c->pin + 16;
-  HIP_TRY(hipMemcpyAsync(hp, o, sizeof(double) * 2, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(hp + 16, of, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(hp + 20, c->fit_st.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  std::memcpy(ahat, hp, sizeof(double));
-  std::memcpy(D, hp + 8, sizeof(double));
-  std::memcpy(flags, hp + 16, sizeof(uint32_t));
-  std::memcpy(status, hp + 20, sizeof(uint32_t));
+  std::memcpy(&out, c->pin, sizeof(Out));
+  *status = out.status;
+  if (out.status == 0u) {
+    *ahat = out.a;
+    *D = out.D;
+    *flags = out.flags;
+  }
   return ZPL_OK;
 }
 
@@ -1262,14 +1248,14 @@ zpl_status Server::fit_fresh(std::vector<Req*>& fresh) {
                            hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(c->fit_ns.p, pns, sizeof(int64_t) * ns_small, hipMemcpyHostToDevice, s));
     HIP_TRY(launch_fit(grid, (const int64_t* const*)c->fit_ptrs.p, (const int64_t*)c->fit_ns.p,
-                       ns_small, c->ln, (int64_t*)c->heavy.p, sstride, fa, fd, ff, fs, 0u, s));
+                       ns_small, c->ln, (int64_t*)c->heavy.p, sstride, fa, fd, ff, fs, s));
   }
   // large ones after the small ones' outputs, sharing one scratch area
   for (size_t k = 0; k < large.size(); ++k) {
     const int o = ns_small + (int)k;
     const int i = large[k];
-    HIP_TRY(launch_fit_block(fx + xoff[i], fresh[i]->n, c->ln, (int64_t*)c->heavy.p,
-                             heavy_stride(fresh[i]->n), fa + o, fd + o, ff + o, fs + o, 0u, s));
+    HIP_TRY(launch_fit_one(fx + xoff[i], fresh[i]->n, c->ln, (int64_t*)c->heavy.p, fa + o, fd + o,
+                           ff + o, fs + o, 0u, s));
   }
   double* ha = (double*)(pns + nb);
   double* hd = ha + nb;
@@ -1738,9 +1724,8 @@ zpl_status zpl_fit_noalloc(zpl_ctx* c, const int64_t* x_dev, int64_t n, uint32_t
     return fail(ZPL_EINVAL, "dataset of %lld values needs %lld scratch words, more than the "
                 "fixed %lld", (long long)n, (long long)stride, (long long)kNoAllocStride);
   HIP_TRY(hipSetDevice(c->device));
-  // the workgroup fit gives the same bits as the one-wave fit at every n
-  HIP_TRY(launch_fit_block(x_dev, n, c->ln, c->noalloc_scratch, stride, alpha_hat_dev, D_dev,
-                           flags_dev, status_dev, kmax, (hipStream_t)stream));
+  HIP_TRY(launch_fit_one(x_dev, n, c->ln, c->noalloc_scratch, alpha_hat_dev, D_dev, flags_dev,
+                         status_dev, kmax, (hipStream_t)stream));
   return ZPL_OK;
 }
 
@@ -1760,13 +1745,8 @@ zpl_status zpl_fit_scan(zpl_ctx* c, const int64_t* x, int64_t n, int32_t x_on_de
   hipStream_t s = (hipStream_t)stream;
   const int64_t* xd;
   ZPL_TRY(stage_x(c, x, n, x_on_device, s, &xd));
-  // one wave per candidate; each wave keeps its overflow and list areas in
-  // the heavy scratch, so the grid is what a quarter of the budget holds
-  const int64_t stride = heavy_stride(n);
-  int grid = std::min(n_xmin, 4 * c->n_cu);
-  while (grid > 1 && (uint64_t)grid * stride * 8 > c->budget / 4) grid /= 2;
   const size_t nc = (size_t)n_xmin;
-  ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)stride * grid));
+  ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)heavy_stride(n)));
   ZPL_TRY(ensure(c, c->scan, nc * (sizeof(int64_t) + 2 * sizeof(double) + sizeof(int64_t) +
                                    2 * sizeof(uint32_t))));
   const size_t host_bytes = nc * (2 * sizeof(double) + sizeof(int64_t) + 2 * sizeof(uint32_t));
@@ -1781,8 +1761,8 @@ zpl_status zpl_fit_scan(zpl_ctx* c, const int64_t* x, int64_t n, int32_t x_on_de
   uint32_t* d_fl = (uint32_t*)(d_nt + nc);
   uint32_t* d_st = d_fl + nc;
   HIP_TRY(hipMemcpyAsync(d_xmins, c->pin, nc * sizeof(int64_t), hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_fit_scan(grid, xd, n, d_xmins, n_xmin, c->ln, (int64_t*)c->heavy.p, stride,
-                          d_a, d_D, d_nt, d_fl, d_st, s));
+  HIP_TRY(launch_fit_scan(xd, n, d_xmins, n_xmin, c->ln, (int64_t*)c->heavy.p, d_a, d_D, d_nt, d_fl,
+                          d_st, s));
   // results: alpha_hat, D, n_tail, flags, status are contiguous on the device
   HIP_TRY(hipMemcpyAsync(c->pin, d_a, host_bytes, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));

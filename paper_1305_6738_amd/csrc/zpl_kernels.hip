@@ -44,19 +44,6 @@ __device__ __forceinline__ uint32_t wave_or_u32(uint32_t v) {
   for (int m = 32; m > 0; m >>= 1) v |= shfl_xor_u32(v, m);
   return v;
 }
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) v += shfl_xor_u64(v, m);
-  return v;
-}
-__device__ __forceinline__ int64_t wave_max_i64(int64_t v) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) {
-    const int64_t o = (int64_t)shfl_xor_u64((uint64_t)v, m);
-    v = o > v ? o : v;
-  }
-  return v;
-}
 __device__ __forceinline__ U128 wave_sum_u128(U128 v) {
 #pragma unroll
   for (int m = 32; m > 0; m >>= 1) {
@@ -367,65 +354,6 @@ struct LaneSrc {
   }
 };
 
-// A compact ascending (value, count) list in global memory.  The entry after
-// the one being consumed is loaded ahead, so its latency overlaps the FP64
-// work of the current value.
-struct ListSrc {
-  const int64_t* vals;
-  const uint32_t* cnts;
-  int len;
-  int p;  // index of the entry held in (nv, nc)
-  int64_t nv;
-  uint32_t nc;
-  __device__ __forceinline__ ListSrc(const int64_t* v, const uint32_t* c, int l)
-      : vals(v), cnts(c), len(l), p(0), nv(0), nc(0u) {
-    if (len > 0) {
-      nv = vals[0];
-      nc = cnts[0];
-    }
-  }
-  __device__ __forceinline__ void advance() {
-    ++p;
-    if (p < len) {
-      nv = vals[p];
-      nc = cnts[p];
-    }
-  }
-  __device__ __forceinline__ uint32_t small(int v) {
-    if (p < len && nv == (int64_t)v) {
-      const uint32_t c = nc;
-      advance();
-      return c;
-    }
-    return 0u;
-  }
-  __device__ __forceinline__ bool next_large(int64_t& v, uint32_t& c) {
-    if (p >= len) return false;
-    v = nv;
-    c = nc;
-    advance();
-    return true;
-  }
-};
-
-// ks_distance over a compact ascending list in global memory, by a whole
-// wave: the values <= 16 are taken by every lane as in ks_distance, the rest
-// is cut into 64 contiguous chunks, one per lane.  A wave prefix sum gives
-// each chunk its count C of draws below it, and a chunk whose first value v
-// follows its predecessor (v - 1 = previous value) recomputes the same
-// zeta(a, v) the sequential loop would have carried over, so every term, and
-// hence the maximum, is bit-identical to ks_distance.  Returns D on every lane.
-__device__ __forceinline__ uint64_t wave_excl_scan_u64(uint64_t v, int lane) {
-  uint64_t x = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t lo = (uint32_t)__shfl_up((int)(uint32_t)x, d, 64);
-    const uint32_t hi = (uint32_t)__shfl_up((int)(uint32_t)(x >> 32), d, 64);
-    if (lane >= d) x += ((uint64_t)hi << 32) | lo;
-  }
-  return x - v;
-}
-
 __device__ __forceinline__ double wave_max_f64(double v) {
 #pragma unroll
   for (int m = 32; m > 0; m >>= 1) {
@@ -435,132 +363,8 @@ __device__ __forceinline__ double wave_max_f64(double v) {
   return v;
 }
 
-// iz = 1/zeta(a, xmin): F(t) = 1 - zeta(a, t+1) iz for t >= xmin - 1 (the
-// first distinct value's lower term is then zero).  cut: the law with a lower
-// cutoff, whose survival values above 16 come from survival_next_cut (there
-// they are the normaliser's own scale, not a tail of zeta(a)); xrel > 0: a
-// cutoff xrel above 17, every survival value (and iz) taken relative to
-// xrel^-a (survival_rel).
-__device__ double ks_distance_wave(const int64_t* __restrict__ lv, const uint32_t* __restrict__ lc,
-                                   int len, const EmCoef& E, const double (&suf)[17], int64_t n,
-                                   const double* __restrict__ ln, int lane, double iz,
-                                   bool cut = false, int64_t xrel = 0) {
-  const double idn = 1.0 / (double)n;
-  int64_t C = 0;
-  double D = 0.0;
-  int p = 0;
-  // the list's first 64 entries, one per lane, in one round of loads; the
-  // values <= 16 (at most the first 16 entries) are then read across lanes
-  // instead of by a chain of dependent global loads
-  const int64_t hv = lane < len ? lv[lane] : INT64_MAX;
-  const uint32_t hc = lane < len ? lc[lane] : 0u;
-#pragma unroll
-  for (int v = 1; v <= 16; ++v) {
-    const int64_t pv = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(uint32_t)(hv >> 32), p, 64) << 32) |
-                                 (uint32_t)__shfl((int)(uint32_t)hv, p, 64));
-    if (p < len && pv == (int64_t)v) {
-      const double t2 = fabs(fma(suf[v - 1], iz, -(double)(n - C) * idn));
-      C += (uint32_t)__shfl((int)hc, p, 64);
-      const double t1 = fabs(fma(suf[v], iz, -(double)(n - C) * idn));
-      D = fmax(D, fmax(t1, t2));
-      ++p;
-    }
-  }
-  const int p16 = p;
-  const int chunk = (len - p16 + 63) / 64;
-  const int q0 = p16 + lane * chunk;
-  const int q1 = min(q0 + chunk, len);
-  uint64_t cs = 0;
-  for (int q = q0; q < q1; ++q) cs += lc[q];
-  C += (int64_t)wave_excl_scan_u64(cs, lane);
-  if (q0 < q1) {
-    int64_t vprev = q0 == p16 ? 16 : lv[q0 - 1];
-    double zprev = suf[16];
-    bool have = q0 == p16;  // zprev is zeta(a, vprev + 1)
-    // the next entry is loaded before this one's arithmetic, so the load's
-    // latency overlaps it
-    int64_t v = lv[q0];
-    uint32_t cv = lc[q0];
-    for (int q = q0; q < q1; ++q) {
-      const int qn = q + 1 < q1 ? q + 1 : q;
-      const int64_t vn = lv[qn];
-      const uint32_t cn = lc[qn];
-      const double zv = xrel ? survival_rel(E, v, xrel)
-                             : (cut ? survival_next_cut(E, v, ln) : survival_next(E, v, ln));
-      double zv1;
-      if (v - 1 == vprev)
-        zv1 = have ? zprev
-                   : (xrel ? survival_rel(E, vprev, xrel)
-                           : (cut ? survival_next_cut(E, vprev, ln) : survival_next(E, vprev, ln)));
-      else
-        zv1 = zv + (xrel ? pow_rel(E.s, v, xrel) : pow_neg(E.s, ln_value(v, ln)));
-      const double t2 = fabs(fma(zv1, iz, -(double)(n - C) * idn));
-      C += cv;
-      const double t1 = fabs(fma(zv, iz, -(double)(n - C) * idn));
-      D = fmax(D, fmax(t1, t2));
-      zprev = zv;
-      vprev = v;
-      have = true;
-      v = vn;
-      cv = cn;
-    }
-  }
-  return wave_max_f64(D);
-}
-
-// finish_replicate by a whole wave over a global list (heavy form, fit):
-// every lane solves the same MLE; the KS is split over the lanes.
-__device__ __forceinline__ void finish_replicate_wave(const int64_t* lv, const uint32_t* lc, int len,
-                                                      const U128& S, int64_t n, uint32_t fl,
-                                                      const double* __restrict__ ln, int lane,
-                                                      uint32_t K, double& ahat, double& D,
-                                                      uint32_t& flags, int64_t xmin = 1) {
-  if (K) {  // O(K) per replicate either way: every lane runs the same sequence
-    ListSrc src(lv, lc, len);
-    finish_replicate(src, S, n, fl, ln, K, ahat, D, flags);
-    return;
-  }
-  if (xmin > 1) {  // the law with a lower cutoff (every value >= xmin)
-    U128 Sx = S;
-    if (len == 1 && lv[0] == xmin) {  // every value at the cutoff: one counts as xmin + 1
-      Sx = U128{0, 0};
-      u128_add_mul(Sx, (uint64_t)(n - 1), ln_fixed(xmin, ln));
-      u128_add(Sx, ln_fixed(xmin + 1, ln), 0);
-      fl |= kFlagAllOnes;
-    }
-    const double a = mle_alpha_hz(u128_to_S(Sx) / (double)n, xmin, ln, &fl);
-    const EmCoef E = em_coef(a);
-    double suf[17];
-    survival_head_cut(E, ln, suf);
-    double zx = 0.0;  // zeta(a, xmin) = suf[xmin - 1] (static indices: no scratch)
-#pragma unroll
-    for (int t = 1; t <= 16; ++t)
-      if (xmin - 1 == t) zx = suf[t];
-    // above 17 every value is: survival values relative to xmin^-a
-    if (xmin > 17) zx = survival_rel(E, xmin - 1, xmin);
-    D = ks_distance_wave(lv, lc, len, E, suf, n, ln, lane, 1.0 / zx, true, xmin > 17 ? xmin : 0);
-    ahat = a;
-    flags = fl;
-    return;
-  }
-  double Sd;
-  if (S.lo == 0 && S.hi == 0) {
-    Sd = ln[2];
-    fl |= kFlagAllOnes;
-  } else {
-    Sd = u128_to_S(S);
-  }
-  const double a = mle_alpha_start(Sd / (double)n, ln, mle_guess_table(ln), &fl);
-  const EmCoef E = em_coef(a);
-  double suf[17];
-  survival_head(E, ln, suf);
-  D = ks_distance_wave(lv, lc, len, E, suf, n, ln, lane, 1.0 / suf[0]);
-  ahat = a;
-  flags = fl;
-}
-
 // ---------------------------------------------------------------------------
-// Wave-cooperative helpers for the wave and heavy forms.
+// Wave-cooperative helpers.
 // ---------------------------------------------------------------------------
 // Ordering of one wave's global-memory stores before its later loads.
 __device__ __forceinline__ void wave_sync_global() {
@@ -569,315 +373,10 @@ __device__ __forceinline__ void wave_sync_global() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// Builds the compact (value, count) list of one replicate from a histogram
-// of values 1..nbins (hist[v-1]) and a sorted overflow array ov[0..oc),
-// appending at lv/lc (length returned).  Also returns, identical on every
-// lane, the exact 128-bit sum of ln x.  The histogram is consumed: when every
-// count fits in 21 bits (n < 2^21) its nonzero bins are also packed as
-// (v << 21 | count) into hist[0..) in list order, so the sums read them from
-// LDS instead of reading the global list back.
-struct Summary {
-  U128 S;
-  int len;
-};
-
-__device__ Summary build_list(uint32_t* hist, int nbins, const int64_t* ov, int oc, int64_t* lv,
-                              uint32_t* lc, int lane, const double* __restrict__ ln, int64_t n) {
-  const uint64_t below = lanes_below(lane);
-  const bool packed = n < ((int64_t)1 << 21);
-  U128 S = {0, 0};
-  int len = 0;
-  // 1. non-zero histogram bins, four per lane per step (16-byte LDS reads;
-  //    nbins is a multiple of 256), compacted in ascending order.  A bin's
-  //    list position never exceeds its own index, so the packed copy only
-  //    overwrites bins that have been read.
-  for (int b0 = 0; b0 < nbins; b0 += 256) {
-    const uint4 h = *reinterpret_cast<const uint4*>(hist + b0 + 4 * lane);
-    const uint32_t nz = (h.x != 0u) + (h.y != 0u) + (h.z != 0u) + (h.w != 0u);
-    const uint64_t m0 = __ballot(nz & 1u), m1 = __ballot(nz & 2u), m2 = __ballot(nz & 4u);
-    int pos = len + __popcll(m0 & below) + 2 * __popcll(m1 & below) + 4 * __popcll(m2 & below);
-    const uint32_t v0 = (uint32_t)(b0 + 4 * lane + 1);
-    const uint32_t cs[4] = {h.x, h.y, h.z, h.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (cs[k]) {
-        lv[pos] = (int64_t)(v0 + k);
-        lc[pos] = cs[k];
-        if (packed) hist[pos] = ((v0 + k) << 21) | cs[k];
-        ++pos;
-      }
-    }
-    len += __popcll(m0) + 2 * __popcll(m1) + 4 * __popcll(m2);
-  }
-  const int hlen = len;
-  // 2. runs of equal values in the sorted overflow array; the last lane of a
-  //    run adds the run's terms.  A run starts at the last start position at
-  //    or below its end: in this chunk (ballot of starts), else the carried
-  //    start of a run that began in an earlier chunk.
-  int run0 = 0;  // start of the run open at the chunk boundary (wave-uniform)
-  for (int p0 = 0; p0 < oc; p0 += 64) {
-    const int p = p0 + lane;
-    const bool valid = p < oc;
-    const int64_t v = valid ? ov[p] : 0;
-    // neighbours read at clamped indices (always inside ov[0..oc))
-    const int64_t vn = ov[p + 1 < oc ? p + 1 : oc - 1];
-    const int64_t vp = ov[p > 0 ? (p - 1 < oc ? p - 1 : oc - 1) : 0];
-    const bool end = valid && ((p == oc - 1) || (vn != v));
-    const bool start = valid && ((p == 0) || (vp != v));
-    const uint64_t m = __ballot(end);
-    const uint64_t sm = __ballot(start);
-    if (end) {
-      const int pos = len + __popcll(m & below);
-      const uint64_t sb = sm & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
-      const int first = sb ? p0 + 63 - __clzll((long long)sb) : run0;
-      const uint32_t cnt = (uint32_t)(p + 1 - first);
-      lv[pos] = v;
-      lc[pos] = cnt;
-      u128_add_mul(S, cnt, ln_fixed(v, ln));
-    }
-    len += __popcll(m);
-    if (sm) run0 = p0 + 63 - __clzll((long long)sm);
-  }
-  // 3. exact S over the histogram part of the list
-  if (packed) {
-    wave_sync();
-    for (int q = lane; q < hlen; q += 64) {
-      const uint32_t e = hist[q];
-      const int64_t v = (int64_t)(e >> 21);
-      const uint32_t c = e & ((1u << 21) - 1u);
-      u128_add_mul(S, c, ln_fixed(v, ln));
-    }
-  } else {
-    wave_sync_global();  // the list is in global memory
-    for (int q = lane; q < hlen; q += 64) {
-      const int64_t v = lv[q];
-      const uint32_t c = lc[q];
-      u128_add_mul(S, c, ln_fixed(v, ln));
-    }
-  }
-  Summary s;
-  s.S = wave_sum_u128(S);
-  s.len = len;
-  return s;
-}
-
-// Ascending sort of up to 64 values held one per lane (unused lanes hold
-// INT64_MAX): a bitonic network over lane shuffles, no memory traffic.
-__device__ __forceinline__ int64_t wave_sort64(int64_t v, int lane) {
-#pragma unroll
-  for (int k = 2; k <= 64; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const int64_t o = (int64_t)shfl_xor_u64((uint64_t)v, j);
-      const bool up = (lane & k) == 0;
-      const bool lower = (lane & j) == 0;
-      const int64_t lo = o < v ? o : v, hi = o < v ? v : o;
-      v = (lower == up) ? lo : hi;
-    }
-  }
-  return v;
-}
-
 __device__ __forceinline__ int next_pow2(int v) {
   int p = 1;
   while (p < v) p <<= 1;
   return p;
-}
-
-// Compare-exchange of a (the lower index) and b: the smaller value goes to a
-// when the block holding them sorts ascending (up), the larger otherwise.
-__device__ __forceinline__ void cmpx(int64_t& a, int64_t& b, bool up) {
-  const int64_t lo = a < b ? a : b, hi = a < b ? b : a;
-  a = up ? lo : hi;
-  b = up ? hi : lo;
-}
-
-// Passes j = jtop..1 of bitonic stage k on a block of 64 E elements held E
-// per lane: element t of this lane has index base + lane + 64 t.  Passes with
-// j >= 64 pair registers t and t | j/64 of the same lane; passes with j < 64
-// pair lanes (shuffles).  Every index is a compile-time register number.
-template <int E>
-__device__ __forceinline__ void block_passes(int64_t (&v)[E], int base, int k, int jtop,
-                                             int lane) {
-#pragma unroll
-  for (int tj = E / 2; tj >= 1; tj >>= 1) {
-    if ((tj << 6) <= jtop) {
-#pragma unroll
-      for (int t = 0; t < E; ++t)
-        if ((t & tj) == 0) cmpx(v[t], v[t | tj], ((base + lane + 64 * t) & k) == 0);
-    }
-  }
-#pragma unroll
-  for (int j = 32; j > 0; j >>= 1) {
-    if (j <= jtop) {
-      const bool lower = (lane & j) == 0;
-#pragma unroll
-      for (int t = 0; t < E; ++t) {
-        const bool up = ((base + lane + 64 * t) & k) == 0;
-        const int64_t o = (int64_t)shfl_xor_u64((uint64_t)v[t], j);
-        const int64_t lo = o < v[t] ? o : v[t], hi = o < v[t] ? v[t] : o;
-        v[t] = (lower == up) ? lo : hi;
-      }
-    }
-  }
-}
-
-// Every stage k <= 64 E of a block (a full bitonic sort when the block is the
-// whole array; else a sort whose direction alternates with the block index,
-// as the network's first stages leave it).
-template <int E>
-__device__ __forceinline__ void block_sort(int64_t (&v)[E], int base, int lane) {
-  for (int k = 2; k <= 64 * E; k <<= 1) block_passes<E>(v, base, k, k >> 1, lane);
-}
-
-template <int E>
-__device__ __forceinline__ void block_load(int64_t (&v)[E], const int64_t* a, int lane) {
-#pragma unroll
-  for (int t = 0; t < E; ++t) v[t] = a[lane + 64 * t];
-}
-template <int E>
-__device__ __forceinline__ void block_store(const int64_t (&v)[E], int64_t* a, int lane) {
-#pragma unroll
-  for (int t = 0; t < E; ++t) a[lane + 64 * t] = v[t];
-}
-
-// Ascending bitonic sort of a[0..P) (P a power of two, 128..512) by one wave,
-// entirely in registers (P / 64 values per lane); a is LDS or global memory,
-// read once and written once by the calling wave.
-__device__ __forceinline__ void wave_sort_small(int64_t* a, int P, int lane) {
-  if (P == 128) {
-    int64_t v[2];
-    block_load<2>(v, a, lane);
-    block_sort<2>(v, 0, lane);
-    block_store<2>(v, a, lane);
-  } else if (P == 256) {
-    int64_t v[4];
-    block_load<4>(v, a, lane);
-    block_sort<4>(v, 0, lane);
-    block_store<4>(v, a, lane);
-  } else {
-    int64_t v[8];
-    block_load<8>(v, a, lane);
-    block_sort<8>(v, 0, lane);
-    block_store<8>(v, a, lane);
-  }
-}
-
-// The same for a[0..nv) padded to P: positions from nv on count as INT64_MAX
-// and are neither read nor written (the wave form's LDS area holds fewer
-// than P entries).
-template <int E>
-__device__ __forceinline__ void block_load_n(int64_t (&v)[E], const int64_t* a, int nv, int lane) {
-#pragma unroll
-  for (int t = 0; t < E; ++t) v[t] = lane + 64 * t < nv ? a[lane + 64 * t] : INT64_MAX;
-}
-template <int E>
-__device__ __forceinline__ void block_store_n(const int64_t (&v)[E], int64_t* a, int nv, int lane) {
-#pragma unroll
-  for (int t = 0; t < E; ++t)
-    if (lane + 64 * t < nv) a[lane + 64 * t] = v[t];
-}
-__device__ __forceinline__ void wave_sort_small_n(int64_t* a, int P, int nv, int lane) {
-  if (P == 128) {
-    int64_t v[2];
-    block_load_n<2>(v, a, nv, lane);
-    block_sort<2>(v, 0, lane);
-    block_store_n<2>(v, a, nv, lane);
-  } else {
-    int64_t v[4];
-    block_load_n<4>(v, a, nv, lane);
-    block_sort<4>(v, 0, lane);
-    block_store_n<4>(v, a, nv, lane);
-  }
-}
-
-// G consecutive passes j1, j1/2, ..., j1 >> (G-1) (all >= 512) of bitonic
-// stage k over g[0..P) in one round trip: each group of 2^G elements differing
-// only in those index bits is loaded into registers, put through the G passes
-// and stored back.  The block direction (index & k) is the same for a whole
-// group, since k is above every bit that varies in it.
-template <int G>
-__device__ __forceinline__ void mem_group(int64_t* g, int P, int k, int j1, int lane) {
-  constexpr int NE = 1 << G;
-  const int p = 31 - __builtin_clz((unsigned)j1);
-  const int low = p - G + 1;
-  const int lowmask = (1 << low) - 1;
-  // two groups per lane per step (P >> G is a multiple of 128 for P >= 1024),
-  // all their loads in flight before the compare-exchanges
-  for (int q = lane; q < (P >> G); q += 128) {
-    int b[2];
-    int64_t v[2][NE];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int qq = q + 64 * h;
-      b[h] = ((qq >> low) << (p + 1)) | (qq & lowmask);
-#pragma unroll
-      for (int e = 0; e < NE; ++e) v[h][e] = g[b[h] + (e << low)];
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const bool up = (b[h] & k) == 0;
-#pragma unroll
-      for (int sft = G - 1; sft >= 0; --sft) {
-#pragma unroll
-        for (int e = 0; e < NE; ++e)
-          if ((e & (1 << sft)) == 0) cmpx(v[h][e], v[h][e | (1 << sft)], up);
-      }
-#pragma unroll
-      for (int e = 0; e < NE; ++e) g[b[h] + (e << low)] = v[h][e];
-    }
-  }
-}
-
-// Ascending bitonic sort of the global array g[0..P) (P a power of two, at
-// least 128) by one wave.  Arrays of up to 512 values are sorted in registers.
-// Larger ones: every 512-value block is first sorted in registers (the
-// network's stages up to 512); each later stage k runs its passes with
-// j >= 512 through memory, up to three per round trip (mem_group), and its
-// passes with j <= 256 on 512-value blocks in registers.  A 4,096-value
-// array takes 7 round trips through memory instead of 78 passes.
-__device__ void wave_sort_global(int64_t* g, int P, int lane) {
-  if (P <= 512) {
-    wave_sort_small(g, P, lane);
-    wave_sync_global();
-    return;
-  }
-  // two 512-value blocks per step (P >= 1024 holds an even number), both
-  // blocks' loads in flight together
-  for (int base = 0; base < P; base += 1024) {
-    int64_t v[8], w[8];
-    block_load<8>(v, g + base, lane);
-    block_load<8>(w, g + base + 512, lane);
-    block_sort<8>(v, base, lane);
-    block_sort<8>(w, base + 512, lane);
-    block_store<8>(v, g + base, lane);
-    block_store<8>(w, g + base + 512, lane);
-  }
-  wave_sync_global();
-  for (int k = 1024; k <= P; k <<= 1) {
-    int j = k >> 1;
-    while (j >= 512) {
-      const int G = min(3, 31 - __builtin_clz((unsigned)j) - 8);
-      if (G == 3)
-        mem_group<3>(g, P, k, j, lane);
-      else if (G == 2)
-        mem_group<2>(g, P, k, j, lane);
-      else
-        mem_group<1>(g, P, k, j, lane);
-      wave_sync_global();
-      j >>= G;
-    }
-    for (int base = 0; base < P; base += 1024) {
-      int64_t v[8], w[8];
-      block_load<8>(v, g + base, lane);
-      block_load<8>(w, g + base + 512, lane);
-      block_passes<8>(v, base, k, 256, lane);
-      block_passes<8>(w, base + 512, k, 256, lane);
-      block_store<8>(v, g + base, lane);
-      block_store<8>(w, g + base + 512, lane);
-    }
-    wave_sync_global();
-  }
 }
 
 // Ring of deferred draws (lane form).  Before an iteration's
@@ -1442,75 +941,6 @@ __device__ __forceinline__ void lane_wave(const DevCell* cells, int32_t cell_id,
   if (ok) write_outputs(out, c.out_off + rep0 + lane, o.D, o.a, o.flags, o.fp);
 }
 
-// ---------------------------------------------------------------------------
-// One dataset by one wave (the fits): values above kHeavyHist in global scratch,
-// sorted there.
-// ---------------------------------------------------------------------------
-struct alignas(16) HeavyWave {
-  uint32_t hist[kHeavyHist];  // values 1..kHeavyHist
-  uint32_t ones[64];  // per-lane count of values equal to 1 (the most frequent value)
-  uint32_t ovc;
-};
-
-// Histogram/overflow fill, sort, compact list and finish of one replicate by
-// one wave.  fill(sink, flags) calls sink(x) for every value.
-// K = 0: the pure law; K > 0: the truncated law on 1..K (values above K are
-// invalid, like values below 1).  The list build is inlined (out of line, with
-// the histogram reached through a flat pointer, a fit has been seen to return
-// a wrong estimate).
-template <class Fill>
-__device__ void heavy_core(HeavyWave* W, int64_t n, Fill fill, int64_t* gov, int64_t* lv,
-                           uint32_t* lc, const double* __restrict__ ln, uint32_t K, double& a, double& D,
-                           uint32_t& flags, bool& ok, int64_t xmin = 1) {
-  const int lane = lane_id();
-  for (int k = lane; k < kHeavyHist; k += 64) W->hist[k] = 0u;
-  W->ones[lane] = 0u;
-  if (lane == 0) W->ovc = 0u;
-  wave_sync_global();
-  uint32_t fl = 0;
-  bool bad = false;
-  const int64_t xhi = K ? (int64_t)K : INT64_MAX;
-  // sink runs in divergent code (partial draw blocks, deferred draws): the
-  // ones go to the lane's own LDS counter (no contention on bin 1), summed
-  // from LDS once every lane is back
-  auto sink = [&](int64_t x) {
-    if (x < 1 || x > xhi) {
-      bad = true;
-    } else if (x == 1) {
-      atomicAdd(&W->ones[lane], 1u);
-    } else if (x <= kHeavyHist) {
-      atomicAdd(&W->hist[x - 1], 1u);
-    } else {
-      const uint32_t idx = atomicAdd(&W->ovc, 1u);
-      gov[idx] = x;
-    }
-  };
-  fill(sink, fl);
-  wave_sync();
-  const uint32_t c1 = wave_sum_u32(W->ones[lane]);
-  fl = wave_or_u32(fl);
-  const uint32_t anybad = wave_or_u32(bad ? 1u : 0u);
-  if (lane == 0) W->hist[0] += c1;
-  wave_sync_global();
-  ok = (anybad == 0u);
-  if (!ok) return;
-  const int oc = (int)W->ovc;
-  if (oc > 1 && oc <= 64) {
-    const int64_t v = wave_sort64(lane < oc ? gov[lane] : INT64_MAX, lane);
-    if (lane < oc) gov[lane] = v;
-    wave_sync_global();
-  } else if (oc > 64) {
-    const int P = next_pow2(oc);
-    for (int k = oc + lane; k < P; k += 64) gov[k] = INT64_MAX;
-    wave_sync_global();
-    wave_sort_global(gov, P, lane);
-  }
-  Summary s;
-  [[clang::always_inline]] s = build_list(W->hist, kHeavyHist, gov, oc, lv, lc, lane, ln, n);
-  wave_sync_global();
-  finish_replicate_wave(lv, lc, s.len, s.S, n, fl, ln, lane, K, a, D, flags, xmin);
-}
-
 // Resolves a deferred draw of a cell with a lower cutoff (xmin = 1 for the
 // pure law): the table index j is the value xmin - 1 + j, the tail starts at
 // xmin + kH.
@@ -1527,202 +957,9 @@ __device__ __forceinline__ int64_t resolve_entry_cut(uint64_t e, uint32_t rep, c
 }  // namespace zpl
 
 #include "zpl_batch.hpp"
+#include "zpl_fit.hpp"
 
 namespace zpl {
-
-// ---------------------------------------------------------------------------
-// Dataset fit: S, alpha_hat and D of caller data x[0..n) (one wave per
-// dataset).  Same histogram/list/finish arithmetic as the simulated
-// replicates, so identical multisets give bit-identical results.
-// ---------------------------------------------------------------------------
-// Bitonic sort of buf[0..P) (P a power of two) by the nthreads threads of
-// one workgroup; buf is LDS or global memory (a workgroup shares its CU's
-// caches, so the barrier orders the passes either way).
-__device__ __forceinline__ void block_bitonic(int64_t* buf, int P, int tid, int nthreads) {
-  for (int k = 2; k <= P; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = tid; i < P; i += nthreads) {
-        const int ixj = i ^ j;
-        if (ixj > i) {
-          const int64_t a = buf[i], b = buf[ixj];
-          const bool asc = (i & k) == 0;
-          if ((a > b) == asc) {
-            buf[i] = b;
-            buf[ixj] = a;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// Fit of one large dataset (eq. 2 and eq. 3) by a whole workgroup: all
-// kFitWaves waves fill the LDS histogram (values 1..kHeavyHist) and the
-// global overflow list and sort the overflow (in LDS when it fits); wave 0
-// then builds the (value, count) list and finishes as k_fit does, so the
-// result has k_fit's bits.
-constexpr int kFitWaves = 8;
-constexpr int kFitSortLds = 4096;
-__global__ __launch_bounds__(64 * kFitWaves) void k_fit_block(
-    const int64_t* __restrict__ x, int64_t n, const double* __restrict__ ln, int64_t* scratch,
-    int64_t scratch_stride, double* ahat_out, double* D_out, uint32_t* flags_out,
-    uint32_t* status_out, uint32_t K) {
-  __shared__ HeavyWave W;
-  __shared__ int64_t sbuf[kFitSortLds];
-  __shared__ uint32_t sbad;
-  const int tid = (int)threadIdx.x;
-  const int nt = (int)blockDim.x;
-  const int lane = tid & 63;
-  int64_t* gov = scratch;
-  const int64_t half = scratch_stride / 2;
-  int64_t* lv = gov + half;
-  uint32_t* lc = reinterpret_cast<uint32_t*>(lv + half / 2);
-  for (int k = tid; k < kHeavyHist; k += nt) W.hist[k] = 0u;
-  if (tid == 0) {
-    W.ovc = 0u;
-    sbad = 0u;
-  }
-  __syncthreads();
-  const int64_t xhi = K ? (int64_t)K : INT64_MAX;
-  uint32_t bad = 0u;
-  for (int64_t i = tid; i < n; i += nt) {
-    const int64_t v = x[i];
-    if (v < 1 || v > xhi) {
-      bad = 1u;
-    } else if (v <= kHeavyHist) {
-      atomicAdd(&W.hist[v - 1], 1u);
-    } else {
-      const uint32_t idx = atomicAdd(&W.ovc, 1u);
-      gov[idx] = v;
-    }
-  }
-  if (bad) atomicOr(&sbad, 1u);
-  __syncthreads();
-  const bool ok = sbad == 0u;
-  const int oc = (int)W.ovc;
-  if (ok && oc > 1) {
-    const int P = next_pow2(oc);
-    if (P <= kFitSortLds) {
-      for (int k = tid; k < P; k += nt) sbuf[k] = k < oc ? gov[k] : INT64_MAX;
-      __syncthreads();
-      block_bitonic(sbuf, P, tid, nt);
-      for (int k = tid; k < oc; k += nt) gov[k] = sbuf[k];
-    } else {
-      for (int k = oc + tid; k < P; k += nt) gov[k] = INT64_MAX;
-      __syncthreads();
-      block_bitonic(gov, P, tid, nt);
-    }
-    __syncthreads();
-  }
-  if (tid >= 64) return;
-  if (!ok) {
-    if (lane == 0) status_out[0] = kErrBadValue;
-    return;
-  }
-  Summary sm;
-  [[clang::always_inline]] sm = build_list(W.hist, kHeavyHist, gov, oc, lv, lc, lane, ln, n);
-  wave_sync_global();
-  double a = 0.0, D = 0.0;
-  uint32_t flags = 0;
-  finish_replicate_wave(lv, lc, sm.len, sm.S, n, 0u, ln, lane, K, a, D, flags);
-  if (lane == 0) {
-    ahat_out[0] = a;
-    D_out[0] = D;
-    flags_out[0] = flags;
-    status_out[0] = 0u;
-  }
-}
-
-// The KS-minimising choice of a lower cutoff (the practice the paper cites
-// for fitting data): for each candidate xmin one wave fits the values >= xmin
-// of the same dataset (the law with cutoff xmin, eq. 2 and eq. 3 with the
-// Hurwitz zeta).  A candidate above every value gets D = +inf and status
-// kErrNoTail; any value below 1 sets kErrBadValue.
-__global__ __launch_bounds__(64) void k_fit_scan(const int64_t* __restrict__ x, int64_t n,
-                                                const int64_t* __restrict__ xmins, int n_cand,
-                                                const double* __restrict__ ln, int64_t* scratch,
-                                                int64_t scratch_stride, double* ahat_out,
-                                                double* D_out, int64_t* ntail_out,
-                                                uint32_t* flags_out, uint32_t* status_out) {
-  __shared__ HeavyWave W;
-  int64_t* gov = scratch + (int64_t)blockIdx.x * scratch_stride;
-  const int64_t half = scratch_stride / 2;
-  int64_t* lv = gov + half;
-  uint32_t* lc = reinterpret_cast<uint32_t*>(lv + half / 2);
-  const int lane = lane_id();
-  for (int cand = (int)blockIdx.x; cand < n_cand; cand += (int)gridDim.x) {
-    const int64_t xmin = xmins[cand];
-    uint32_t cnt = 0, bad = 0;
-    for (int64_t i = lane; i < n; i += 64) {
-      const int64_t v = x[i];
-      bad |= v < 1 ? 1u : 0u;
-      cnt += v >= xmin ? 1u : 0u;
-    }
-    cnt = wave_sum_u32(cnt);
-    bad = wave_or_u32(bad);
-    if (bad != 0u || cnt == 0u) {
-      if (lane == 0) {
-        ahat_out[cand] = 0.0;
-        D_out[cand] = __builtin_inf();
-        ntail_out[cand] = (int64_t)cnt;
-        flags_out[cand] = 0u;
-        status_out[cand] = bad != 0u ? kErrBadValue : kErrNoTail;
-      }
-      continue;
-    }
-    auto fill = [&](auto sink, uint32_t&) {
-      for (int64_t i = lane; i < n; i += 64) {
-        const int64_t v = x[i];
-        if (v >= xmin) sink(v);
-      }
-    };
-    double a = 0.0, D = 0.0;
-    uint32_t flags = 0;
-    bool ok;
-    heavy_core(&W, (int64_t)cnt, fill, gov, lv, lc, ln, 0u, a, D, flags, ok, xmin);
-    if (lane == 0) {
-      ahat_out[cand] = a;
-      D_out[cand] = D;
-      ntail_out[cand] = (int64_t)cnt;
-      flags_out[cand] = flags;
-      status_out[cand] = ok ? 0u : kErrBadValue;
-    }
-    wave_sync_global();
-  }
-}
-
-__global__ __launch_bounds__(64) void k_fit(const int64_t* const* __restrict__ xs,
-                                           const int64_t* __restrict__ ns, int n_sets,
-                                           const double* __restrict__ ln, int64_t* scratch,
-                                           int64_t scratch_stride, double* ahat_out,
-                                           double* D_out, uint32_t* flags_out,
-                                           uint32_t* status_out, uint32_t K) {
-  __shared__ HeavyWave W;
-  int64_t* gov = scratch + (int64_t)blockIdx.x * scratch_stride;
-  const int64_t half = scratch_stride / 2;
-  int64_t* lv = gov + half;
-  uint32_t* lc = reinterpret_cast<uint32_t*>(lv + half / 2);
-  const int lane = lane_id();
-  for (int set = (int)blockIdx.x; set < n_sets; set += (int)gridDim.x) {
-    const int64_t* x = xs[set];
-    const int64_t n = ns[set];
-    auto fill = [&](auto sink, uint32_t&) {
-      for (int64_t i = lane; i < n; i += 64) sink(x[i]);
-    };
-    double a = 0.0, D = 0.0;
-    uint32_t flags = 0;
-    bool ok;
-    heavy_core(&W, n, fill, gov, lv, lc, ln, K, a, D, flags, ok);
-    if (lane == 0) {
-      ahat_out[set] = a;
-      D_out[set] = D;
-      flags_out[set] = flags;
-      status_out[set] = ok ? 0u : kErrBadValue;
-    }
-    wave_sync_global();
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Table build: T[k] = F(k; alpha) = 1 - zeta(alpha, k+1)/zeta(alpha), the
@@ -2538,16 +1775,52 @@ hipError_t launch_cutoff(int grid, const DevCell* cells, const double* tables,
 
 hipError_t launch_fit(int grid, const int64_t* const* xs, const int64_t* ns, int n_sets,
                       const double* ln, int64_t* scratch, int64_t stride, double* ahat,
-                      double* D, uint32_t* flags, uint32_t* status, uint32_t K, hipStream_t s) {
+                      double* D, uint32_t* flags, uint32_t* status, hipStream_t s) {
   if (n_sets <= 0) return hipSuccess;
-  k_fit<<<grid, 64, 0, s>>>(xs, ns, n_sets, ln, scratch, stride, ahat, D, flags, status, K);
+  k_fit_block<false><<<grid, kFitThreads, 0, s>>>(xs, ns, n_sets, nullptr, 0, ln, scratch, stride,
+                                                  ahat, D, flags, status, 0u);
   return hipGetLastError();
 }
 
-hipError_t launch_fit_block(const int64_t* x, int64_t n, const double* ln, int64_t* scratch,
-                            int64_t stride, double* ahat, double* D, uint32_t* flags,
-                            uint32_t* status, uint32_t K, hipStream_t s) {
-  k_fit_block<<<1, 64 * kFitWaves, 0, s>>>(x, n, ln, scratch, stride, ahat, D, flags, status, K);
+// Counts and sorts a dataset into fit_view(scratch, n, *groups).
+static hipError_t launch_fit_prepare(const int64_t* x, int64_t n, uint32_t K, const double* ln,
+                                     int64_t* scratch, int* groups, hipStream_t s) {
+  if (n < kFitGridMin) {
+    *groups = 0;
+    k_fit_block<true><<<1, kFitThreads, 0, s>>>(nullptr, nullptr, 1, x, n, ln, scratch, 0, nullptr,
+                                                nullptr, nullptr, nullptr, K);
+    return hipGetLastError();
+  }
+  int64_t g = n / kFitChunkMin;
+  if (g > kFitGroups) g = kFitGroups;
+  const int64_t chunk = (n + g - 1) / g;
+  g = (n + chunk - 1) / chunk;
+  *groups = (int)g;
+  k_fit_count<<<(int)g, kFitCountThreads, 0, s>>>(x, n, chunk, K, ln, scratch);
+  const int64_t runs = (n + kFitRun - 1) / kFitRun;
+  const int most = runs < kFitGroups ? (int)runs : kFitGroups;
+  k_fit_merge<<<most < kFitBins / 64 ? kFitBins / 64 : most, kFitThreads, 0, s>>>(n, chunk, (int)g,
+                                                                                 scratch);
+  int pass = 0;
+  if (K == 0u)  // (up to K <= kFitBins every value has its bin)
+    for (int64_t run = kFitRun; run < n; run *= kFitFan)
+      k_fit_runs<<<most, 256, 0, s>>>(n, (int)g, run, pass++, scratch);
+  return hipGetLastError();
+}
+
+hipError_t launch_fit_one(const int64_t* x, int64_t n, const double* ln, int64_t* scratch,
+                          double* ahat, double* D, uint32_t* flags, uint32_t* status, uint32_t K,
+                          hipStream_t s) {
+  if (n < kFitGridMin) {
+    k_fit_block<false><<<1, kFitThreads, 0, s>>>(nullptr, nullptr, 1, x, n, ln, scratch, 0, ahat, D,
+                                                 flags, status, K);
+    return hipGetLastError();
+  }
+  int groups = 0;
+  const hipError_t e = launch_fit_prepare(x, n, K, ln, scratch, &groups, s);
+  if (e != hipSuccess) return e;
+  k_fit_cand<<<kFitShares, kFitCandThreads, 0, s>>>(n, groups, scratch, nullptr, kFitShares, K, ln,
+                                                    ahat, D, nullptr, flags, status);
   return hipGetLastError();
 }
 
@@ -2561,13 +1834,20 @@ hipError_t noalloc_scratch_address(int64_t** p) {
   return hipGetSymbolAddress((void**)p, HIP_SYMBOL(zpl_noalloc_scratch));
 }
 
-hipError_t launch_fit_scan(int grid, const int64_t* x, int64_t n, const int64_t* xmins,
-                           int n_cand, const double* ln, int64_t* scratch, int64_t stride,
-                           double* ahat, double* D, int64_t* ntail, uint32_t* flags,
-                           uint32_t* status, hipStream_t s) {
-  if (n_cand <= 0 || grid <= 0) return hipSuccess;
-  k_fit_scan<<<grid, 64, 0, s>>>(x, n, xmins, n_cand, ln, scratch, stride, ahat, D, ntail,
-                                 flags, status);
+hipError_t launch_fit_scan(const int64_t* x, int64_t n, const int64_t* xmins, int n_cand,
+                           const double* ln, int64_t* scratch, double* ahat, double* D,
+                           int64_t* ntail, uint32_t* flags, uint32_t* status, hipStream_t s) {
+  if (n_cand <= 0) return hipSuccess;
+  int groups = 0;
+  const hipError_t e = launch_fit_prepare(x, n, 0u, ln, scratch, &groups, s);
+  if (e != hipSuccess) return e;
+  // few candidates: several workgroups share a distance (about one per compute
+  // unit in all; a small dataset has no more to share than a few of them take)
+  const int most = n < kFitGridMin ? 8 : kFitShares;
+  int wgs = n_cand <= kFitAcc ? 256 / n_cand : 1;
+  if (wgs > most) wgs = most;
+  k_fit_cand<<<n_cand * wgs, kFitCandThreads, 0, s>>>(n, groups, scratch, xmins, wgs, 0u, ln, ahat,
+                                                      D, ntail, flags, status);
   return hipGetLastError();
 }
 

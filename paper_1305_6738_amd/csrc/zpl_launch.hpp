@@ -38,19 +38,22 @@ hipError_t launch_cutoff(int grid, const DevCell* cells, const double* tables,
                          uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
                          uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
                          hipStream_t s);
+// Datasets of a batch, a workgroup each; scratch: grid areas of `stride` int64
+// (heavy_stride of the largest).
 hipError_t launch_fit(int grid, const int64_t* const* xs, const int64_t* ns, int n_sets,
                       const double* ln, int64_t* scratch, int64_t stride, double* ahat,
-                      double* D, uint32_t* flags, uint32_t* status, uint32_t K, hipStream_t s);
-hipError_t launch_fit_block(const int64_t* x, int64_t n, const double* ln, int64_t* scratch,
-                            int64_t stride, double* ahat, double* D, uint32_t* flags,
-                            uint32_t* status, uint32_t K, hipStream_t s);
+                      double* D, uint32_t* flags, uint32_t* status, hipStream_t s);
+// One dataset (the truncated law on 1..K, or K = 0), or its fits with each of
+// n_cand lower cutoffs; scratch: heavy_stride(n) int64.
+hipError_t launch_fit_one(const int64_t* x, int64_t n, const double* ln, int64_t* scratch,
+                          double* ahat, double* D, uint32_t* flags, uint32_t* status, uint32_t K,
+                          hipStream_t s);
+hipError_t launch_fit_scan(const int64_t* x, int64_t n, const int64_t* xmins, int n_cand,
+                           const double* ln, int64_t* scratch, double* ahat, double* D,
+                           int64_t* ntail, uint32_t* flags, uint32_t* status, hipStream_t s);
 // Device address of the fixed scratch array of the allocation-free fit
 // (kNoAllocStride int64) on the current device.
 hipError_t noalloc_scratch_address(int64_t** p);
-hipError_t launch_fit_scan(int grid, const int64_t* x, int64_t n, const int64_t* xmins,
-                           int n_cand, const double* ln, int64_t* scratch, int64_t stride,
-                           double* ahat, double* D, int64_t* ntail, uint32_t* flags,
-                           uint32_t* status, hipStream_t s);
 // gather: n_cells * kSelQ * gcap values, then n_cells * kSelQ * 32 bytes of
 // per-(cell, quantile) state; maxR bounds every cell's R.
 hipError_t launch_select(const double* D, const DevCell* cells, int n_cells, int n_q,
