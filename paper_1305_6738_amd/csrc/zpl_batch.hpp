@@ -250,9 +250,9 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
   const double idn = 1.0 / (double)n_;
   const int hi = __builtin_amdgcn_readfirstlane(hi_);
   const uint32_t oc = (uint32_t)__builtin_amdgcn_readfirstlane((int)oc_);
-  const int64_t* __restrict__ ov = reinterpret_cast<const int64_t*>(uniform64((int64_t)ov_));
-  const double* __restrict__ ln = reinterpret_cast<const double*>(uniform64((int64_t)ln_));
-  const CountView cv{reinterpret_cast<const uint32_t*>(uniform64((int64_t)counts)),
+  const int64_t* __restrict__ ov = as_global(reinterpret_cast<const int64_t*>(uniform64((int64_t)ov_)));
+  const double* __restrict__ ln = as_global(reinterpret_cast<const double*>(uniform64((int64_t)ln_)));
+  const CountView cv{as_global(reinterpret_cast<const uint32_t*>(uniform64((int64_t)counts))),
                      __builtin_amdgcn_readfirstlane((int)wide_) != 0};
   KsLaw<kLaw> w;
   w.E = em_coef(a);
@@ -572,18 +572,20 @@ struct DrawOut {
   uint32_t fl, ovn;
   int hi;
 };
-template <bool kCut>
+// (kKernel only tells the kernels' copies apart: each then has its own tables'
+// LDS addresses as constants.)
+template <bool kCut, int kKernel>
 static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint32_t rep_,
                                                       LdsU32* hist, LdsU64* ring, LdsU64* hard,
                                                       int64_t* top_, uint32_t room_,
-                                                      const LdsU64* T, const LdsU32* guide,
+                                                      const LdsU32* T, const LdsU32* guide,
                                                       int hi_) {
   const int lane = lane_id();
   const uint64_t below = lanes_below(lane);
-  const DevCell& c = *reinterpret_cast<const DevCell*>(uniform64((int64_t)cell));
+  const DevCell& c = *as_global(reinterpret_cast<const DevCell*>(uniform64((int64_t)cell)));
   const uint32_t rep = (uint32_t)__builtin_amdgcn_readfirstlane((int)rep_);
   const uint32_t room = (uint32_t)__builtin_amdgcn_readfirstlane((int)room_);
-  int64_t* __restrict__ top = reinterpret_cast<int64_t*>(uniform64((int64_t)top_));
+  int64_t* __restrict__ top = as_global(reinterpret_cast<int64_t*>(uniform64((int64_t)top_)));
   const int hi0 = __builtin_amdgcn_readfirstlane(hi_);
   for (int k = lane; k < hi0; k += 64) hist[k] = 0u;
 #pragma unroll
@@ -613,68 +615,81 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
       ovn += (uint32_t)__popcll(mb);
     }
   };
-  auto gen = [&](uint32_t j0, uint64_t (&Uo)[2 * kWaveBlocks]) {
+  auto gen = [&](uint32_t j0, uint32_t (&ho)[4], uint32_t (&lo)[4]) {
     uint32_t k0 = ck0, k1 = ck1;  // round keys per block (see lane_wave)
     asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
     for (int b = 0; b < kWaveBlocks; ++b) {
       const Words4 w =
           philox4x32_10(j0 + 64u * (uint32_t)b + (uint32_t)lane, rep, cs, 0u, k0, k1);
-      Uo[2 * b] = m53(w.w0, w.w1);
-      Uo[2 * b + 1] = m53(w.w2, w.w3);
+      ho[2 * b] = w.w0;
+      lo[2 * b] = w.w1;
+      ho[2 * b + 1] = w.w2;
+      lo[2 * b + 1] = w.w3;
     }
   };
-  uint64_t U[2 * kWaveBlocks];
-  int gi[2 * kWaveBlocks];
-  gen(0u, U);
+  const GuideRule rule = guide_rule(sh);
+  uint32_t wh[4], wl[4];  // the words of the uniforms
+  int gi[4];
+  gen(0u, wh, wl);
 #pragma unroll
-  for (int d = 0; d < 2 * kWaveBlocks; ++d) gi[d] = guide_index(U[d], sh);
+  for (int d = 0; d < 4; ++d) gi[d] = guide_index32(wh[d], rule);
   for (uint32_t j0 = 0;;) {
-    uint32_t gg[2 * kWaveBlocks];
+    uint32_t gg[4];
 #pragma unroll
-    for (int d = 0; d < 2 * kWaveBlocks; ++d) gg[d] = guide[gi[d]];
-    uint64_t Un[2 * kWaveBlocks] = {1ull, 1ull, 1ull, 1ull};
+    for (int d = 0; d < 4; ++d) gg[d] = guide[gi[d]];
+    uint32_t nh[4], nl[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) asm volatile("" : "=v"(nh[d]), "=v"(nl[d]));  // any (see more)
     const bool more = j0 + 64u * kWaveBlocks < nblk;
-    if (more) gen(j0 + 64u * kWaveBlocks, Un);  // none past the end
-    asm volatile("" : "+v"(Un[0]), "+v"(Un[1]), "+v"(Un[2]), "+v"(Un[3]));  // made here
-    uint64_t t[2 * kWaveBlocks];
+    if (more) gen(j0 + 64u * kWaveBlocks, nh, nl);  // none past the end
+    asm volatile("" : "+v"(nh[0]), "+v"(nh[1]), "+v"(nh[2]), "+v"(nh[3]));  // made here
+    uint32_t t[4];
 #pragma unroll
-    for (int d = 0; d < 2 * kWaveBlocks; ++d) t[d] = T[(int)(gg[d] & 0xffffu) - 1];
+    for (int d = 0; d < 4; ++d) t[d] = T[(gg[d] & 0xffffu) >> 2];
     __builtin_amdgcn_sched_barrier(0);  // the table reads issue before the index math
 #pragma unroll
-    for (int d = 0; d < 2 * kWaveBlocks; ++d) gi[d] = guide_index(Un[d], sh);
+    for (int d = 0; d < 4; ++d) gi[d] = guide_index32(nh[d], rule);
     asm volatile("" : "+v"(gi[0]), "+v"(gi[1]), "+v"(gi[2]), "+v"(gi[3]));  // made here
     asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));  // reads stay unconditional
-    int x[2 * kWaveBlocks];
-    bool def[2 * kWaveBlocks];
+    int z[4];
+    bool def[4];
+    fast_offsets(wh, gg, t, rule, [](int) { return true; }, z, def);
+    if (n32 - 2u * j0 < 4u * 64u) {  // the last ones
+      // draw d of the lane is number 2 lane + (d & 1) of the wave's 128 from
+      // 2 j0 + 128 (d >> 1) on
+      const int left = (int)(n32 - 2u * j0);
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        if (2 * lane >= left - 128 * (d >> 1) - (d & 1)) {
+          z[d] = -1;
+          def[d] = false;
+        }
+      }
+    }
     bool big = false;
 #pragma unroll
-    for (int d = 0; d < 2 * kWaveBlocks; ++d) {
-      const int xd = fast_select(gg[d], t[d], U[d]);
-      const uint32_t i =
-          2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1);
-      const bool valid = i < n32;
-      const bool drawn = xd < kDeferred;
-      x[d] = valid && drawn ? xd : -1;
-      def[d] = valid && !drawn;
-      big = big || x[d] > kHW;
-      const uint32_t xm1 = (uint32_t)(x[d] - 1);
-      const int slot = xm1 < 3u ? kWaveOwn + (int)xm1 * 64 + lane
-                                : (xm1 < (uint32_t)kHW ? (int)xm1 : kWavePad + lane);
-      lds_inc(&hist[slot]);
-      xm = max(xm, x[d]);  // values above kHW are clamped once, below
+    for (int d = 0; d < 4; ++d) {
+      big = big || z[d] >= 4 * kHW;
+      // values 1..3 into the lane's own counters, those above kHW (and none)
+      // into the pad
+      const uint32_t zd = (uint32_t)z[d];
+      const uint32_t at = zd < 12u ? (zd << 6) + 4u * (uint32_t)(kWaveOwn + lane)
+                                   : (zd < 4u * (uint32_t)kHW ? zd : 4u * (uint32_t)(kWavePad + lane));
+      lds_inc((LdsU32*)((LdsU8*)hist + at));
+      xm = max(xm, z[d]);  // an offset; values above kHW are clamped once, below
     }
     if (__ballot(big) != 0ull) {
 #pragma unroll
-      for (int d = 0; d < 2 * kWaveBlocks; ++d) put_big((int64_t)x[d]);
+      for (int d = 0; d < 4; ++d) put_big((int64_t)((z[d] >> 2) + 1));
     }
     // deferred draws into the first ring: positions from a prefix sum of the
     // lanes' counts (three ballots of its bits)
     {
-      uint32_t nd = 0;
+      if (__ballot(def[0] || def[1] || def[2] || def[3]) != 0ull) {
+        uint32_t nd = 0;
 #pragma unroll
-      for (int d = 0; d < 2 * kWaveBlocks; ++d) nd += def[d] ? 1u : 0u;
-      if (__ballot(nd != 0u) != 0ull) {
+        for (int d = 0; d < 4; ++d) nd += def[d] ? 1u : 0u;
         const uint64_t b0 = __ballot(nd & 1u), b1 = __ballot(nd & 2u), b2 = __ballot(nd & 4u);
         uint32_t pos = qh + qn + (uint32_t)(__popcll(b0 & below) + 2 * __popcll(b1 & below) +
                                             4 * __popcll(b2 & below));
@@ -683,7 +698,7 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
           if (def[d]) {
             const uint32_t i =
                 2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1);
-            ring[wrap(pos, kBatchRing)] = defer_entry(U[d], timax, i, 0);
+            ring[wrap(pos, kBatchRing)] = defer_entry(m53(wh[d], wl[d]), timax, i, 0);
             ++pos;
           }
         }
@@ -735,19 +750,22 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
       if (code != kTailTaken) j = 0;
       if (j >= 1 && j <= kHW) {
         lds_inc(&hist[j - 1]);
-        xm = max(xm, (int)j);
+        xm = max(xm, 4 * (int)j - 4);
       }
       put_big(j);
     }
     if (!more) break;
     j0 += 64u * kWaveBlocks;
 #pragma unroll
-    for (int d = 0; d < 2 * kWaveBlocks; ++d) U[d] = Un[d];
+    for (int d = 0; d < 4; ++d) {
+      wh[d] = nh[d];
+      wl[d] = nl[d];
+    }
   }
   DrawOut o;
   o.fl = dpp_or_u32(fl);
   o.ovn = ovn;
-  const int hi = ((int)min(dpp_max_u32((uint32_t)xm), (uint32_t)kHW) + 255) & ~255;
+  const int hi = ((int)min((dpp_max_u32((uint32_t)xm) >> 2) + 1u, (uint32_t)kHW) + 255) & ~255;
   o.hi = hi < 256 ? 256 : hi;
   wave_sync();
   const uint32_t c1 = dpp_sum_u32(hist[kWaveOwn + lane]);
@@ -778,9 +796,9 @@ static __device__ __noinline__ SumOut sum_replicate(const LdsU32* hist, int hi_,
   const int64_t off = uniform64(off_);
   const bool wide = __builtin_amdgcn_readfirstlane((int)wide_) != 0;
   const bool want_fp = __builtin_amdgcn_readfirstlane((int)want_fp_) != 0;
-  uint32_t* __restrict__ cp = reinterpret_cast<uint32_t*>(uniform64((int64_t)cp_));
-  const int64_t* __restrict__ ov = reinterpret_cast<const int64_t*>(uniform64((int64_t)ov_));
-  const double* __restrict__ ln = reinterpret_cast<const double*>(uniform64((int64_t)ln_));
+  uint32_t* __restrict__ cp = as_global(reinterpret_cast<uint32_t*>(uniform64((int64_t)cp_)));
+  const int64_t* __restrict__ ov = as_global(reinterpret_cast<const int64_t*>(uniform64((int64_t)ov_)));
+  const double* __restrict__ ln = as_global(reinterpret_cast<const double*>(uniform64((int64_t)ln_)));
   uint64_t slo = 0, shi = 0, fp = 0;
   for (int b0 = 0; b0 < hi; b0 += 256) {
     uint32_t cs[4];
@@ -846,8 +864,10 @@ struct CountSrc {
 };
 template <int kLaw>
 static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin, uint32_t K,
-                                                 const uint32_t* counts, bool wide,
-                                                 uint32_t flags, const double* __restrict__ ln) {
+                                                 const uint32_t* counts_, bool wide,
+                                                 uint32_t flags, const double* ln_) {
+  const uint32_t* counts = as_global(counts_);
+  const double* __restrict__ ln = as_global(ln_);
   HeadOut o;
   o.flags = flags;
   o.done = 0u;
@@ -930,11 +950,11 @@ static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin
 // c.room of those still fit (all n of them, or what the cell's replicates
 // hardly ever exceed); one that exceeds the rest after all is drawn again as
 // the first of the next batch, or goes to the escalation list if it was.
-template <bool kCut>
+template <bool kCut, int kKernel>
 __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t cell_id,
                                                 int64_t r0, int nrep, BatchLds* L, int64_t* scratch,
                                                 int64_t stride, int lane,
-                                                const uint64_t* __restrict__ T,
+                                                const uint32_t* __restrict__ T,
                                                 const uint32_t* __restrict__ guide,
                                                 const double* __restrict__ ln, const Outputs& out,
                                                 uint64_t* esc_list, uint32_t* esc_count,
@@ -958,9 +978,9 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
            (q == 0 || top - (kRecords + (q + 1) * cw) >= (int64_t)c.room)) {
       const uint32_t rep = (uint32_t)(r0 + done + q);
       const uint32_t room = (uint32_t)min(top - (kRecords + (q + 1) * cw), n);
-      const DrawOut dr = draw_replicate<kCut>(&c, rep, (LdsU32*)L->hist, (LdsU64*)L->ring,
+      const DrawOut dr = draw_replicate<kCut, kKernel>(&c, rep, (LdsU32*)L->hist, (LdsU64*)L->ring,
                                               (LdsU64*)L->hard, scratch + top, room,
-                                              (const LdsU64*)T, (const LdsU32*)guide, hi);
+                                              (const LdsU32*)T, (const LdsU32*)guide, hi);
       hi = dr.hi;
       full = dr.ovn > room;
       if (full && q > 0) break;
@@ -1052,7 +1072,7 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
 // The cell's table and guide, and a region per wave.
 template <class Region, int kWavesPer>
 struct KernelLds {
-  alignas(16) uint64_t T[kH];  // floor(F(k) 2^53)
+  alignas(16) uint32_t T[2 * kH];  // floor(F(k) 2^53): threshold_hi, then threshold_lo
   uint32_t guide[kGuide];
   Region w[kWavesPer];
   int unit;
@@ -1125,7 +1145,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_simulate(
       const int share = (un.count + kBatchWaves - 1) / kBatchWaves;
       const int first = wave * share;
       if (first < un.count)
-        replicate_batch<false>(cells, un.cell, un.r0 + first,
+        replicate_batch<false, 0>(cells, un.cell, un.r0 + first,
                                un.count - first < share ? un.count - first : share,
                                &L.w[wave].batch, mine, g.stride, lane, L.T, L.guide, ln, out,
                                esc_list, esc_count, esc_cap, err);
@@ -1151,7 +1171,7 @@ __global__ __launch_bounds__(64 * kBatchWavesCut, kBatchWavesCut / 4) void k_cut
     const int share = (un.count + kBatchWavesCut - 1) / kBatchWavesCut;
     const int first = wave * share;
     if (first < un.count)
-      replicate_batch<true>(cells, un.cell, un.r0 + first,
+      replicate_batch<true, 1>(cells, un.cell, un.r0 + first,
                             un.count - first < share ? un.count - first : share, &L.w[wave], mine,
                             stride, lane, L.T, L.guide, ln, out, esc_list, esc_count, esc_cap, err);
   }
@@ -1190,10 +1210,15 @@ __global__ __launch_bounds__(64 * kEscWaves, kEscWaves / 4) void k_escalated(
         loaded = cell;
         __syncthreads();
       }
-      if ((uint32_t)wave < same)
-        replicate_batch<false>(cells, cell, (int64_t)(uint32_t)esc_list[e + (uint32_t)wave], 1,
-                               &L.w[wave], mine, stride, lane, L.T, L.guide, ln, out, esc_list,
-                               esc_count, 0u, err);
+      if ((uint32_t)wave < same) {
+        const int64_t r0 = (int64_t)(uint32_t)esc_list[e + (uint32_t)wave];
+        if (c.xmin > 1)
+          replicate_batch<true, 2>(cells, cell, r0, 1, &L.w[wave], mine, stride, lane, L.T, L.guide,
+                                   ln, out, esc_list, esc_count, 0u, err);
+        else
+          replicate_batch<false, 2>(cells, cell, r0, 1, &L.w[wave], mine, stride, lane, L.T,
+                                    L.guide, ln, out, esc_list, esc_count, 0u, err);
+      }
       e += same;
     }
     __syncthreads();

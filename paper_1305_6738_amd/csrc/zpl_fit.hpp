@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_block(
   int64_t* base = scratch + (int64_t)blockIdx.x * stride;
   const int64_t xhi = K ? (int64_t)K : INT64_MAX;
   for (int set = (int)blockIdx.x; set < n_sets; set += (int)gridDim.x) {
-    const int64_t* x = xs ? xs[set] : x1;
+    const int64_t* x = as_global(xs ? xs[set] : x1);
     const int64_t n = xs ? ns[set] : n1;
     for (int k = tid; k < kFitBins; k += kFitThreads) hist[k] = 0u;
     if (tid == 0) ovc = sbad = 0u;

@@ -401,19 +401,24 @@ struct alignas(16) LaneRegion {
 // registers from their hot loops.
 static __device__ __noinline__ uint32_t guide_pack_dev(const uint16_t* g, int b, int sh,
                                                        uint64_t timax) {
-  return guide_pack(g, b, sh, timax);
+  return guide_pack(as_global(g), b, sh, timax);
 }
 
-// Stages the cell's table, as integers floor(F(k) 2^53), and packed guide
-// (guide_pack) into LDS.
-__device__ __forceinline__ void load_cell_tables(uint64_t* T, uint32_t* guide,
+// Stages the cell's table, as the words of the integers floor(F(k) 2^53)
+// (threshold_hi, then threshold_lo), and packed guide (guide_offsets) into LDS.
+__device__ __forceinline__ void load_cell_tables(uint32_t* T, uint32_t* guide,
                                                  const double* __restrict__ Tg,
                                                  const uint16_t* __restrict__ g,
                                                  const DevCell& c, int tid, int nthreads) {
-  for (int k = tid; k < kH; k += nthreads) T[k] = table_int(Tg[k]);
+  for (int k = tid; k < kH; k += nthreads) {
+    const uint64_t t = table_int(Tg[k]);
+    T[k] = threshold_hi(t);
+    T[kH + k] = threshold_lo(t);
+  }
   const uint64_t timax = table_int(c.tmax);
   const int sh = (int)c.gsh;
-  for (int b = tid; b < kGuide; b += nthreads) guide[b] = guide_pack_dev(g, b, sh, timax);
+  for (int b = tid; b < kGuide; b += nthreads)
+    guide[b] = guide_offsets(guide_pack_dev(g, b, sh, timax));
 }
 
 // ---------------------------------------------------------------------------
@@ -455,9 +460,11 @@ struct LaneOut {
   uint64_t fp;
   uint32_t flags;
 };
-static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slots, int myc, int od,
+static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slots_, int myc, int od,
                                                    bool ok, int64_t n, uint32_t fl, bool want_fp,
-                                                   const double* __restrict__ ln) {
+                                                   const double* ln_) {
+  int64_t* slots = as_global(slots_);
+  const double* __restrict__ ln = as_global(ln_);
   LaneOut o;
   o.fp = 0;
   const int lane = lane_id();
@@ -670,10 +677,12 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
 
 // The same under the truncated law, each lane by itself: its values above the
 // column (few: they are rare under the planner's rule) sorted by rank.
-static __device__ __noinline__ LaneOut lane_finish_trunc(const LdsU32* column, int64_t* slots,
+static __device__ __noinline__ LaneOut lane_finish_trunc(const LdsU32* column, int64_t* slots_,
                                                          int myc, int od, int64_t n, uint32_t fl,
                                                          uint32_t K, bool want_fp,
-                                                         const double* __restrict__ ln) {
+                                                         const double* ln_) {
+  int64_t* slots = as_global(slots_);
+  const double* __restrict__ ln = as_global(ln_);
   LaneOut o;
   o.fp = 0;
   const int oc = myc + od;
@@ -739,19 +748,43 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 __device__ __forceinline__ uint32_t uniform32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
-// slow_search through LDS pointers.
-__device__ __forceinline__ int lds_search(uint64_t m, const LdsU64* T, const LdsU32* guide,
+// slow_search in the staged tables.
+__device__ __forceinline__ int lds_search(uint64_t m, const LdsU32* T, const LdsU32* guide,
                                           int sh) {
   const uint32_t g = guide[guide_index(m, sh)];
-  int lo = (int)(g & 0xffffu), hi = (int)((g >> 16) & (kDeferred - 1));
+  int lo = (int)(g & 0xffffu) >> 2, hi = (int)((g >> 16) & (kDeferred - 1)) >> 2;
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
-    if (T[mid - 1] >= m)
+    if (threshold(T[mid], T[kH + mid]) >= m)
       hi = mid;
     else
       lo = mid + 1;
   }
-  return lo;
+  return lo + 1;
+}
+
+// The fast path of four draws in 32-bit steps: value offsets 4 (x - 1) of the
+// draws valid(d) that it decides, -1 for the others; def marks the valid ones
+// to search in full (a wide bracket, a tail uniform, a first word that equals
+// the threshold's or whose bin needs more bits).
+template <class Valid>
+__device__ __forceinline__ void fast_offsets(const uint32_t (&w0)[4], const uint32_t (&gg)[4],
+                                             uint32_t (&t)[4], const GuideRule& rule, Valid valid,
+                                             int (&z)[4], bool (&def)[4]) {
+  const uint32_t wm = max(max(w0[0], w0[1]), max(w0[2], w0[3]));
+  if (__ballot(wm > rule.last) != 0ull) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+      if (w0[d] > rule.last) t[d] = w0[d];
+  }
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const uint32_t zd = w0[d] < t[d] ? (gg[d] & 0xffffu) : (gg[d] >> 16);
+    const bool drawn = zd < (uint32_t)kDeferred && w0[d] != t[d];
+    const bool v = valid(d);
+    z[d] = v && drawn ? (int)zd : -1;
+    def[d] = v && !drawn;
+  }
 }
 
 // Draw blocks per iteration of the lane form's loop (two draws each).
@@ -767,14 +800,15 @@ static_assert(kLaneBlocks == 2, "the draw loop keeps four table reads in flight"
 // slots 0, 1, ... (the count returned), the resolved ones slots kLaneCap - 1,
 // kLaneCap - 2, ... (counted in L.ovc; either may exceed the room).
 static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_, int count_,
-                                              LdsU32* region, int64_t* spill_, const LdsU64* T,
+                                              LdsU32* region, int64_t* spill_, const LdsU32* T,
                                               const LdsU32* guide) {
   const int lane = lane_id();
-  const DevCell& c = *reinterpret_cast<const DevCell*>(uniform64((int64_t)cell));
+  const DevCell& c = *as_global(reinterpret_cast<const DevCell*>(uniform64((int64_t)cell)));
   const uint32_t rep0 = uniform32((uint32_t)rep0_);
   const bool active = lane < count_;
-  int64_t* __restrict__ spill = reinterpret_cast<int64_t*>(uniform64((int64_t)spill_));
+  int64_t* __restrict__ spill = as_global(reinterpret_cast<int64_t*>(uniform64((int64_t)spill_)));
   LdsU32* hist = region + lane;
+  const uint32_t column = (uint32_t)(uintptr_t)hist;
   LdsU64* ring = (LdsU64*)(region + offsetof(LaneRegion, ring) / 4);
   LdsU32* ovc = region + offsetof(LaneRegion, ovc) / 4;
   LdsU32* lfl = region + offsetof(LaneRegion, fl) / 4;
@@ -797,7 +831,7 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
   // its uniforms, generates the next iteration's uniforms while they are in
   // flight, issues the table reads, and computes the next guide indexes while
   // those are in flight (one extra block of uniforms is generated at the end).
-  auto gen = [&](uint32_t j, uint64_t (&Uo)[2 * kLaneBlocks]) {
+  auto gen = [&](uint32_t j, uint32_t (&ho)[4], uint32_t (&lo)[4]) {
     // the round keys are recomputed per block with scalar adds rather than
     // kept live across the loop (where they would be spilled)
     uint32_t k0 = ck0, k1 = ck1;
@@ -805,59 +839,61 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
 #pragma unroll
     for (int b = 0; b < kLaneBlocks; ++b) {
       const Words4 w = philox4x32_10(j + (uint32_t)b, r, cs, 0u, k0, k1);
-      Uo[2 * b] = m53(w.w0, w.w1);
-      Uo[2 * b + 1] = m53(w.w2, w.w3);
+      ho[2 * b] = w.w0;
+      lo[2 * b] = w.w1;
+      ho[2 * b + 1] = w.w2;
+      lo[2 * b + 1] = w.w3;
     }
   };
-  uint64_t U[2 * kLaneBlocks];  // uniforms as 53-bit integers m
-  int gi[2 * kLaneBlocks];      // their guide bins
-  gen(0u, U);
+  const GuideRule rule = guide_rule(sh);
+  uint32_t wh[4], wl[4];  // the words of the uniforms
+  int gi[4];              // their guide bins
+  gen(0u, wh, wl);
 #pragma unroll
-  for (int d = 0; d < 2 * kLaneBlocks; ++d) gi[d] = guide_index(U[d], sh);
+  for (int d = 0; d < 4; ++d) gi[d] = guide_index32(wh[d], rule);
   for (uint32_t j = 0;;) {
-    uint32_t gg[2 * kLaneBlocks];
+    uint32_t gg[4];
 #pragma unroll
-    for (int d = 0; d < 2 * kLaneBlocks; ++d) gg[d] = guide[gi[d]];
-    uint64_t Un[2 * kLaneBlocks];
-    gen(j + (uint32_t)kLaneBlocks, Un);
-    asm volatile("" : "+v"(Un[0]), "+v"(Un[1]), "+v"(Un[2]), "+v"(Un[3]));  // made here
-    uint64_t t[2 * kLaneBlocks];
+    for (int d = 0; d < 4; ++d) gg[d] = guide[gi[d]];
+    uint32_t nh[4], nl[4];
+    gen(j + (uint32_t)kLaneBlocks, nh, nl);
+    asm volatile("" : "+v"(nh[0]), "+v"(nh[1]), "+v"(nh[2]), "+v"(nh[3]));  // made here
+    uint32_t t[4];
 #pragma unroll
-    for (int d = 0; d < 2 * kLaneBlocks; ++d) t[d] = T[(int)(gg[d] & 0xffffu) - 1];
+    for (int d = 0; d < 4; ++d) t[d] = T[(gg[d] & 0xffffu) >> 2];
     __builtin_amdgcn_sched_barrier(0);  // the table reads issue before the index math
 #pragma unroll
-    for (int d = 0; d < 2 * kLaneBlocks; ++d) gi[d] = guide_index(Un[d], sh);
+    for (int d = 0; d < 4; ++d) gi[d] = guide_index32(nh[d], rule);
     asm volatile("" : "+v"(gi[0]), "+v"(gi[1]), "+v"(gi[2]), "+v"(gi[3]));  // made here
     asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));  // reads stay unconditional
-    int x[2 * kLaneBlocks];
-    bool def[2 * kLaneBlocks];
+    int z[4];
+    bool def[4];
+    fast_offsets(wh, gg, t, rule,
+                 [&](int d) { return active && 2u * j + (uint32_t)d < n32; }, z, def);
     bool big = false;
-    uint32_t nd = 0;
 #pragma unroll
-    for (int d = 0; d < 2 * kLaneBlocks; ++d) {
-      const bool valid = active && 2u * j + (uint32_t)d < n32;
-      const int xd = fast_select(gg[d], t[d], U[d]);
-      const bool drawn = xd < kDeferred;
-      x[d] = valid && drawn ? xd : -1;
-      def[d] = valid && !drawn;
-      nd += def[d] ? 1u : 0u;
-      big = big || x[d] > kHLB;
+    for (int d = 0; d < 4; ++d) {
+      big = big || z[d] >= 4 * kHLB;
       // own column, no branch: values outside 1..kHLB count into the pad row
-      const uint32_t xm1 = (uint32_t)(x[d] - 1);
-      const uint32_t v = xm1 < (uint32_t)kHLB ? xm1 : (uint32_t)kHLB;
-      lds_add(&hist[(v >> 1) * 64], 1u << ((v & 1u) * 16u));
+      const uint32_t v = min((uint32_t)z[d], 4u * (uint32_t)kHLB);
+      uint32_t at;
+      asm("v_lshl_add_u32 %0, %1, 5, %2" : "=v"(at) : "v"(v & ~7u), "v"(column));
+      lds_add((LdsU32*)at, 1u << ((v << 2) & 31u));
     }
     if (__ballot(big) != 0ull) {  // values above the column, into the lane's own slots
 #pragma unroll
       for (int d = 0; d < 2 * kLaneBlocks; ++d) {
-        if (x[d] > kHLB) {
-          if (myc < kLaneCap) spill[myc * 64 + lane] = x[d];
+        if (z[d] >= 4 * kHLB) {
+          if (myc < kLaneCap) spill[myc * 64 + lane] = (z[d] >> 2) + 1;
           ++myc;
         }
       }
     }
     // deferred draws into the ring (positions from three ballots of the counts)
-    if (__ballot(nd != 0u) != 0ull) {
+    if (__ballot(def[0] || def[1] || def[2] || def[3]) != 0ull) {
+      uint32_t nd = 0;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) nd += def[d] ? 1u : 0u;
       const uint64_t b0 = __ballot(nd & 1u), b1 = __ballot(nd & 2u), b2 = __ballot(nd & 4u);
       uint32_t pos = qh + qn + (uint32_t)(__popcll(b0 & below) + 2 * __popcll(b1 & below) +
                                           4 * __popcll(b2 & below));
@@ -865,7 +901,7 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
       for (int d = 0; d < 2 * kLaneBlocks; ++d) {
         if (def[d]) {
           ring[pos >= (uint32_t)kRing ? pos - (uint32_t)kRing : pos] =
-              defer_entry(U[d], timax, 2u * j + (uint32_t)d, lane);
+              defer_entry(m53(wh[d], wl[d]), timax, 2u * j + (uint32_t)d, lane);
           ++pos;
         }
       }
@@ -903,21 +939,24 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
     }
     if (!more) break;
 #pragma unroll
-    for (int d = 0; d < 2 * kLaneBlocks; ++d) U[d] = Un[d];
+    for (int d = 0; d < 4; ++d) {
+      wh[d] = nh[d];
+      wl[d] = nl[d];
+    }
   }
   wave_sync_global();  // other lanes wrote to this lane's slots
   return myc;
 }
 
 __device__ __forceinline__ void lane_wave(const DevCell* cells, int32_t cell_id, int64_t rep0,
-                                          int count, LaneRegion* L, int lane, const uint64_t* T,
+                                          int count, LaneRegion* L, int lane, const uint32_t* T,
                                           const uint32_t* guide, const double* __restrict__ ln,
                                           const Outputs& out, uint64_t* esc_list,
                                           uint32_t* esc_count, uint32_t esc_cap, uint32_t* err,
                                           int64_t* spill) {
   const DevCell& c = cells[cell_id];
   LdsU32* region = (LdsU32*)L->hist;
-  int myc = lane_draws(&c, rep0, count, region, spill, (const LdsU64*)T, (const LdsU32*)guide);
+  int myc = lane_draws(&c, rep0, count, region, spill, (const LdsU32*)T, (const LdsU32*)guide);
   int od = (int)L->ovc[lane];
   const uint32_t fl = L->fl[lane];
   bool ok = lane < count;
@@ -1677,7 +1716,9 @@ __global__ __launch_bounds__(256) void k_draws(const DevCell* __restrict__ cells
   __shared__ uint64_t T[kH];
   __shared__ uint32_t guide[kGuide];
   const DevCell c = cells[0];
-  load_cell_tables(T, guide, tables, guides, c, (int)threadIdx.x, 256);
+  for (int k = (int)threadIdx.x; k < kH; k += 256) T[k] = table_int(tables[k]);
+  for (int b = (int)threadIdx.x; b < kGuide; b += 256)
+    guide[b] = guide_pack_dev(guides, b, (int)c.gsh, table_int(c.tmax));
   __syncthreads();
   const int64_t total = count * c.n;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;

@@ -128,6 +128,19 @@ ZPL_HD double recip(double x) {
 #endif
 }
 
+// A pointer known to be to global memory.  Functions that are called, not
+// inlined, see generic pointers otherwise, and a flat access holds up the LDS
+// ones behind it (both count as outstanding in one counter).
+template <class T>
+ZPL_HD T* as_global(T* p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  // (by way of an integer: the two casts alone would cancel)
+  return (T*)(__attribute__((address_space(1))) T*)(uint64_t)p;
+#else
+  return p;
+#endif
+}
+
 // q^-s = exp(-s ln q) with the product s ln q kept exact (p + e), so the
 // product's rounding (up to s ln q ulps of relative error) is not amplified.
 ZPL_HD double pow_neg(double s, double lnq) {
@@ -621,7 +634,8 @@ ZPL_HD void moments012(double z, double& m0, double& m1, double& m2) {
 // Out of line: it is long, and inlined into every finish it would crowd the
 // registers of the draw loops around them.
 __host__ __device__ __noinline__ static Z3 zeta3_trunc_em(double s, uint32_t K,
-                                                          const double* __restrict__ ln) {
+                                                          const double* ln_) {
+  const double* __restrict__ ln = as_global(ln_);
   const int64_t q0 = em_start(fabs(s));
   const double c[8] = {1.0 / 12.0,         -1.0 / 720.0,
                        1.0 / 30240.0,      -1.0 / 1209600.0,
@@ -842,7 +856,8 @@ ZPL_HD double survival_next(double a, int64_t v, const double* __restrict__ ln) 
 // Out of line: only large exponents take it, and inlined it would crowd the
 // registers of the KS loops that call it.
 static __host__ __device__ __noinline__ double survival_cut_direct(double s, int64_t v, int64_t q0,
-                                                                   const double* __restrict__ ln) {
+                                                                   const double* ln_) {
+  const double* __restrict__ ln = as_global(ln_);
   double z = hurwitz_tail(em_coef(s), (double)q0, ln[q0]);
   for (int64_t k = q0 - 1; k > v; --k) z += pow_neg(s, ln[k]);
   return z;
@@ -1065,6 +1080,46 @@ ZPL_HD int guide_index(uint64_t m, int sh) {
   return mh < lim ? ia : ibc;
 }
 
+// guide_index from the uniform's first word w0 (the top 32 bits of m) alone,
+// in 32-bit steps: the words of the table's upper half are w0 >> 23 (or 21) as
+// before, and with c = ~w0 the top 32 bits of e are c, so the octave and the
+// top nb mantissa bits of e are those of c, which a double holds exactly.  That
+// needs c >= 2^nb: a uniform with w0 > `last` (below 2^-20 of them) has to take
+// the full search.
+struct GuideRule {
+  uint32_t half;  // w0 <= half: the linear bins, by w0 >> sa
+  int sa, sq, top;
+  uint32_t last;
+};
+ZPL_HD GuideRule guide_rule(int sh) {
+  const bool uni = sh == kGuideUniform;
+  const int nb = kGBits + (uni ? 0 : sh);
+  GuideRule r;
+  r.half = uni ? 0xffffffffu : 0x7fffffffu;
+  r.sa = uni ? 21 : 23;
+  r.sq = 20 - nb;
+  r.top = kGA + ((1074 << nb) + ((1 << nb) - 1)) - (21 << nb);  // E of c is 21 below e's
+  r.last = 0xffffffffu - (1u << nb);
+  return r;
+}
+ZPL_HD int guide_index32(uint32_t w0, const GuideRule& r) {
+  const int ia = (int)(w0 >> r.sa);
+  const double c = (double)(~w0);
+  const int q = (int)((uint32_t)(__builtin_bit_cast(uint64_t, c) >> 32) >> r.sq);
+  const int ib = r.top - q;
+  const int ibc = ib < kGuide - 1 ? ib : kGuide - 1;
+  return w0 <= r.half ? ia : ibc;
+}
+
+// A table threshold floor(F 2^53) (at most 2^53) as the 32 bits compared with
+// w0 and the rest, t = hi 2^21 + lo: w0 < hi means t >= m and w0 > hi means
+// t < m; a draw with w0 = hi takes the full search.
+ZPL_HD uint32_t threshold_hi(uint64_t t) {
+  return t >> 53 ? 0xffffffffu : (uint32_t)(t >> 21);
+}
+ZPL_HD uint32_t threshold_lo(uint64_t t) { return (uint32_t)(t - ((uint64_t)threshold_hi(t) << 21)); }
+ZPL_HD uint64_t threshold(uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 21) + lo; }
+
 // The refinement of a cell's log-scale guide: the largest sh <= kGuideShMax
 // whose 52 >> sh octaves of e still reach the octave of the table's end
 // (e = 2^53 - timax, rounded to the next odd m: conservative), so that every
@@ -1139,6 +1194,14 @@ ZPL_HD uint32_t guide_pack(const uint16_t* g, int b, int sh, uint64_t timax) {
   const uint32_t hw = (hi == lo + 1 && !tail) ? hi : ((uint32_t)kDeferred | hi);
   return lo | (hw << 16);
 }
+
+// The same with both bounds as 4 (v - 1), the byte offsets that the draw loops
+// use for a value throughout (its threshold, its bin).
+ZPL_HD uint32_t guide_offsets(uint32_t gg) {
+  const uint32_t lo = gg & 0xffffu, hi = (gg >> 16) & (uint32_t)(kDeferred - 1);
+  return 4u * (lo - 1u) | (4u * (hi - 1u)) << 16 | (gg & ((uint32_t)kDeferred << 16));
+}
+static_assert(4 * kH < kDeferred, "offsets fit below the deferral mark");
 
 // ---------------------------------------------------------------------------
 // Tail sampler for U > T[kH].  Target on k >= m = kH + 1: p(k) ~ k^-a.
