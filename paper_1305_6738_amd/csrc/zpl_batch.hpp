@@ -295,8 +295,8 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
       zl = 1.0;
       sl = 1.0;
     }
-    const bool need = sum != 0u && 16 * (lane + 1) > jh &&
-                      fmax(zl - s, sl - z) > Dlow - kPruneMargin;
+    const double bound = fmax(zl - s, sl - z);
+    const bool need = sum != 0u && 16 * (lane + 1) > jh && bound > Dlow - kPruneMargin;
     uint64_t mask = __ballot(need);
     // four chunks per round, one value per lane
     while (mask != 0ull) {
@@ -306,7 +306,8 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
       const uint32_t cnt = p < 0 ? 0u : cv.at(b);
       const uint32_t Ca = (uint32_t)__shfl((int)Cl, pc, 64) + row_incl_scan_u32(cnt);
       const int64_t v = off + b + 1;
-      const double zv = w.survival(v, ln);
+      // (values up to 16 are in D0: below a cutoff's direct sums)
+      const double zv = w.survival(kLaw == kCutoff && v < 17 ? 17 : v, ln);
       double zp = prev_lane_f64(zv);
       uint32_t cp = prev_lane_u32(cnt);
       const double zq = shfl_f64(zr, pc > 0 ? pc - 1 : 0);
@@ -320,6 +321,11 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
         cp = 1u;
       }
       if (cnt != 0u && b >= jh) terms(zv, cp != 0u ? zp : zv + w.point(v, ln), Ca - cnt, cnt);
+      // What a round found may rule out the rest.  Worth a maximum over the wave
+      // only where the sums cost as much as with a cutoff (1,000 draws: 5.69
+      // against 5.89 ms; the truncated law's K = 1,000 6.92 against 6.72).
+      if constexpr (kLaw == kCutoff)
+        if (mask != 0ull) mask &= __ballot(bound > dpp_max_f64(D) - kPruneMargin);
     }
     D = dpp_max_f64(D);
   }

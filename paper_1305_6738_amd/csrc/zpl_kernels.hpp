@@ -42,13 +42,12 @@ constexpr int kLaneScratch = 64 * 2 * kLaneCap;
 // Wave and heavy forms: one replicate per wave at a time, in batches that a
 // wave finishes together (k_batch): histogram of values 1..kHW in LDS, larger
 // ones in the wave's global scratch.  Waves per workgroup (one workgroup per
-// compute unit) without and with a lower cutoff: three waves per SIMD are
-// better for the former (heavy tails of 10,000 draws: 5.81 against 6.16 ms at
-// two), two for the latter, whose survival values take more registers (1,000
-// draws: 7.18 against 7.90 ms at three).
+// compute unit) without and with a lower cutoff: three per SIMD are better than
+// two (heavy tails of 10,000 draws: 5.81 against 6.16 ms; cutoffs, 1,000 draws:
+// 5.69 against 6.45 ms).
 constexpr int kHW = 1024;
 constexpr int kBatchWaves = 12;
-constexpr int kBatchWavesCut = 8;
+constexpr int kBatchWavesCut = 12;
 // Waves per workgroup that run escalated replicates (whole replicates of
 // scratch each, so few).
 constexpr int kEscWaves = 4;

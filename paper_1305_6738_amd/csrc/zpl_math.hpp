@@ -442,22 +442,23 @@ ZPL_HD Z3 hurwitz3(double s, int64_t xmin, const double* __restrict__ ln) {
                        1.0 / 30240.0,      -1.0 / 1209600.0,
                        1.0 / 47900160.0,   -691.0 / 1307674368000.0,
                        1.0 / 74724249600.0, -3617.0 / 10670622842880000.0};
-  // full-precision reciprocals: with a large cutoff the variance of ln X is
-  // small and eq. (2) amplifies any error in zeta'/zeta
-  const double is = recip(s);
-  double P = s, sg1 = is, sg2 = is * is, E = iq;
+  // s (s + 1) ... (s + 2 i) and its two s-derivatives, a factor at a time (all
+  // positive: nothing cancels)
+  double P = s, P1 = 1.0, P2 = 0.0, E = iq;
   double Q0 = 0.0, Q1 = 0.0, Q2 = 0.0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const double ce = c[i] * E;
     Q0 = fma(ce, P, Q0);
-    Q1 = fma(ce, P * sg1, Q1);
-    Q2 = fma(ce, P * fma(sg1, sg1, -sg2), Q2);
-    const double u = s + (double)(2 * i + 1), v = s + (double)(2 * i + 2);
-    const double iu = recip(u), iv = recip(v);
-    P *= u * v;
-    sg1 += iu + iv;
-    sg2 += iu * iu + iv * iv;
+    Q1 = fma(ce, P1, Q1);
+    Q2 = fma(ce, P2, Q2);
+#pragma unroll
+    for (int k = 1; k <= 2; ++k) {
+      const double f = s + (double)(2 * i + k);
+      P2 = fma(P2, f, 2.0 * P1);
+      P1 = fma(P1, f, P);
+      P *= f;
+    }
     E *= iq2;
   }
   const double sm1 = s - 1.0, ism1 = 1.0 / sm1;
@@ -482,22 +483,53 @@ ZPL_HD Z3 hurwitz3(double s, int64_t xmin, const double* __restrict__ ln) {
 
 // MLE of eq. (2) with the Hurwitz zeta: mu(a) = -zeta'(a,xmin)/zeta(a,xmin)
 // = E_a[ln X] decreases from +inf (a -> 1) to ln xmin (a -> inf).  Newton on
-// mu(a) - m in the bracket [1 + 2^-20, 64] with a bisection safeguard, from
-// the continuous-Pareto guess a = 1 + 1/(m - ln(xmin - 1/2)); stops after a
-// step of at most 2^-40 a.  A root above 64 (m <= mu(64), a sample close to
-// a large cutoff) gives 64 with kFlagNoConv.  xmin >= 2.
+// mu(a) - m in the bracket [1 + 2^-20, 64] with a bisection safeguard; stops
+// after a step of at most 2^-40 a.  A root above 64 (m <= mu(64), a sample
+// close to a large cutoff) gives 64 with kFlagNoConv.  xmin >= 2.
+//
+// Away from that edge, m - ln xmin > 1/32 (mu(64) - ln xmin < 1/63: the mean
+// of ln(X/xmin) under the law lies below the continuous one's, 1/(a - 1)), the
+// edge need not be looked at, the steps shrink quadratically, with what is
+// left after one of 2^-27 min(a - 1, 1) below 2^-53 of it, and the start comes
+// from mu without the terms of order xmin^-4 (mle_hz_start).
+//
+// The start: with y = a - 1 and q = xmin, zeta(a, q) q^a is
+// q/y + 1/2 + (y + 1)/(12 q) up to order q^-3, so mu - ln q is
+// (q/y^2 - 1/(12 q)) / that.  Its reciprocal is nearly linear in y: two Newton
+// steps on it from the continuous guess 1/(m - ln(q - 1/2)).
+ZPL_HD double mle_hz_start(double t, double q, double y) {
+  const double it = 1.0 / t, i12 = 1.0 / (12.0 * q);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const double iy = 1.0 / y;
+    const double N = fma(q * iy, iy, -i12), D = fma(q, iy, fma(y + 1.0, i12, 0.5));
+    const double N1 = -2.0 * q * iy * iy * iy, D1 = fma(-q * iy, iy, i12);
+    // (D / N - 1 / t) / (D / N)'
+    const double step = N * (D - N * it) / (D1 * N - D * N1);
+    y -= step;
+  }
+  return y;
+}
+
 ZPL_HD double mle_alpha_hz(double m, int64_t xmin, const double* __restrict__ ln,
                            uint32_t* flags, int* iters = nullptr) {
   if (iters) *iters = 0;
   double lo = 1.0 + 0x1p-20, hi = 64.0;
-  {
+  const double x = (double)xmin;
+  const double t = m - ln_value(xmin, ln);  // E ln(X / xmin)
+  const bool far = t > 0.03125;
+  if (!far) {
     const Z3 z = hurwitz3(hi, xmin, ln);
     if (!(m > -z.z1 / z.z0)) {
       *flags |= kFlagNoConv;
       return hi;
     }
   }
-  double a = 1.0 + 1.0 / (m - log((double)xmin - 0.5));
+  double a = 1.0 + 1.0 / (m - log(x - 0.5));
+  if (far && a - 1.0 < 0.5 * x) {  // (the expansion needs y below q)
+    const double b = 1.0 + mle_hz_start(t, x, a - 1.0);
+    if (fabs(b - a) < 0.25 * (a - 1.0)) a = b;
+  }
   if (!(a > lo && a < hi)) a = 0.5 * (lo + hi);
   double gl = 0.0;  // the last residual of eq. 2
   for (int it = 0; it < kMleCap; ++it) {
@@ -517,7 +549,8 @@ ZPL_HD double mle_alpha_hz(double m, int64_t xmin, const double* __restrict__ ln
       an = 0.5 * (lo + hi);
       *flags |= kFlagBisect;
     }
-    if (fabs(an - a) <= 0x1p-40 * a) return an;
+    const double tol = far ? 0x1p-27 * (an < 2.0 ? an - 1.0 : 1.0) : 0x1p-40 * a;
+    if (fabs(an - a) <= tol) return an;
     a = an;
   }
   // Near the edge m -> ln xmin eq. 2 fixes the root only to about
@@ -718,12 +751,32 @@ ZPL_HD Z3 zeta3_trunc_fast(double s, uint32_t K, const double* __restrict__ ln) 
 // iteration as mle_alpha on [-64, 64]; an iterate ending at the bracket edge
 // is checked against mu at the edge, and when m has no root inside the
 // bracket the edge is returned with kFlagNoConv.
+//
+// The start: for steep laws that of the pure law's; for flat ones (below 1.25,
+// where the end at K tells) the exponent of the continuous law on 1/2..K + 1/2
+// with that mean logarithm.  There ln X has the density e^{z u}, u uniform on
+// [0, 1], z = (1 - a) W, W = ln(2 K + 1), whose mean is
+// (1 + coth(z/2) - 2/z) / 2: the inverse of the Langevin function, by the
+// rational form of M. Kroeger (J. Non-Newton. Fluid Mech. 223, 2015, within
+// 0.3 %).
+constexpr double kTruncFlat = 1.25;
+ZPL_HD double mle_trunc_start(double m, uint32_t K, const double* __restrict__ ln) {
+  const double a1 = 1.0 + 1.0 / (m + 0.5772156649015329);
+  const double a2 = log2(ln[2] / m);
+  const double a = a1 > a2 ? a1 : a2;
+  const double W = log((double)(2 * K + 1));
+  const double x = 2.0 * (m + 0.6931471805599453) / W - 1.0;
+  if (!(x > -1.0 && x < 1.0)) return a;
+  const double x2 = x * x;
+  const double y = x * (3.0 - 0.2 * x2 * (6.0 + x2 * (1.0 - 2.0 * x2))) / (1.0 - x2);
+  const double b = 1.0 - 2.0 * y / W;
+  return b < kTruncFlat ? b : a;
+}
+
 ZPL_HD double mle_alpha_trunc(double m, uint32_t K, const double* __restrict__ ln,
                               uint32_t* flags, int* iters = nullptr) {
   double lo = -64.0, hi = 64.0;
-  double a1 = 1.0 + 1.0 / (m + 0.5772156649015329);
-  double a2 = log2(ln[2] / m);
-  double a = a1 > a2 ? a1 : a2;
+  double a = mle_trunc_start(m, K, ln);
   if (!(a > lo && a < hi)) a = 0.0;
   const double lm = log(m);
   double gl = 0.0;  // the last residual of eq. 2
