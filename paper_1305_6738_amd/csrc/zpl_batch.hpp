@@ -85,15 +85,20 @@ __device__ __forceinline__ uint32_t dpp_incl_scan_u32(uint32_t v) {
 // without a cutoff): 1..kHW in the LDS histogram, larger ones in the wave's
 // global scratch.
 //
-// Deferred draws wait in two rings and are resolved 64 at a time.  A tail draw
-// makes one proposal per pass; a rejected one goes back into the ring with its
-// next attempt, one that needs a double-double floor into the second ring, so
-// that a wave runs that long path with all its lanes (at alpha = 1.2 one
-// proposal in 80 needs it, which was half of all passes).  The first ring
-// holds fewer than 64 entries before an iteration's at most 256, and a pass
-// of either ring puts back at most what it takes out, but for at most 64 that
-// come from the second: 384.
-constexpr int kBatchRing = 384;
+// Deferred draws wait in rings and are resolved 64 at a time.  A tail draw makes
+// one proposal per pass; a rejected one waits in the second ring with its next
+// attempt, one that needs a double-double floor in the third, so that a wave
+// runs that long path with all its lanes (at alpha = 1.2 one proposal in 80
+// needs it, which was half of all passes).  The first ring holds the draws'
+// numbers: four stores and a few steps of positions per iteration, where
+// keeping the uniforms and composing their entries took 25 instructions per
+// draw at times (an uneven batch, 256 cells: 66.9 against 69.0 ms); a
+// pass draws its 64 uniforms again.  It holds fewer than 64 entries before an
+// iteration's at most 256.  A pass of it begins with fewer than 64 in each of
+// the others and adds at most 64 in all, a pass of another moves entries or
+// removes them and takes no more than the third has room for: both hold at
+// most 190 together, 128 each.
+constexpr int kBatchRing = 512;
 constexpr int kHardRing = 128;
 // Histogram layout: bins of j = 1..kHW, one pad slot per lane (the draw loop's
 // no-op counts, never read), then three rows of per-lane counts of j = 1, 2 and
@@ -107,7 +112,8 @@ static_assert(kWaveBlocks == 2, "the draw loop keeps four table reads in flight"
 struct alignas(16) BatchLds {
   // during the KS the bin table of the larger draws
   uint32_t hist[kHW + 64 + 3 * 64];
-  uint64_t ring[kBatchRing];  // deferred draws; the gathered draws during the KS
+  uint32_t ring[kBatchRing];  // deferred draws; the gathered draws during the KS
+  uint64_t retry[kHardRing];  // tail draws whose proposals so far were rejected
   uint64_t hard[kHardRing];   // tail proposals whose floor FP64 does not decide
 };
 
@@ -582,12 +588,12 @@ struct DrawOut {
 // LDS addresses as constants.)
 template <bool kCut, int kKernel>
 static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint32_t rep_,
-                                                      LdsU32* hist, LdsU64* ring, LdsU64* hard,
+                                                      LdsU32* hist, LdsU32* ring, LdsU64* retry,
+                                                      LdsU64* hard,
                                                       int64_t* top_, uint32_t room_,
                                                       const LdsU32* T, const LdsU32* guide,
                                                       int hi_) {
   const int lane = lane_id();
-  const uint64_t below = lanes_below(lane);
   const DevCell& c = *as_global(reinterpret_cast<const DevCell*>(uniform64((int64_t)cell)));
   const uint32_t rep = (uint32_t)__builtin_amdgcn_readfirstlane((int)rep_);
   const uint32_t room = (uint32_t)__builtin_amdgcn_readfirstlane((int)room_);
@@ -609,19 +615,19 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
   const int64_t off = kCut ? uniform64(c.xmin) - 1 : 0;
   int xm = 0;
   uint32_t fl = 0, ovn = 0;
-  uint32_t qh = 0, qn = 0;  // the first ring, wave-uniform
-  uint32_t hh = 0, hn = 0;  // the second
-  auto wrap = [](uint32_t p, int size) { return p >= (uint32_t)size ? p - (uint32_t)size : p; };
+  // first places and lengths of the rings (wave-uniform)
+  uint32_t qh = 0, qn = 0, rh = 0, rn = 0, hh = 0, hn = 0;
   // larger draws (j > kHW) of the lanes that have one, in converged code
   auto put_big = [&](int64_t j) {
     const uint64_t mb = __ballot(j > kHW);
     if (mb != 0ull) {
-      const uint32_t pos = ovn + (uint32_t)__popcll(mb & below);
+      const uint32_t pos = ovn + place_below(mb);
       if (j > kHW && pos < room) top[-1 - (int64_t)pos] = j;
       ovn += (uint32_t)__popcll(mb);
     }
   };
-  auto gen = [&](uint32_t j0, uint32_t (&ho)[4], uint32_t (&lo)[4]) {
+  // the uniforms' first words
+  auto gen = [&](uint32_t j0, uint32_t (&ho)[4]) {
     uint32_t k0 = ck0, k1 = ck1;  // round keys per block (see lane_wave)
     asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
@@ -629,26 +635,24 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
       const Words4 w =
           philox4x32_10(j0 + 64u * (uint32_t)b + (uint32_t)lane, rep, cs, 0u, k0, k1);
       ho[2 * b] = w.w0;
-      lo[2 * b] = w.w1;
       ho[2 * b + 1] = w.w2;
-      lo[2 * b + 1] = w.w3;
     }
   };
   const GuideRule rule = guide_rule(sh);
-  uint32_t wh[4], wl[4];  // the words of the uniforms
+  uint32_t wh[4];
   int gi[4];
-  gen(0u, wh, wl);
+  gen(0u, wh);
 #pragma unroll
   for (int d = 0; d < 4; ++d) gi[d] = guide_index32(wh[d], rule);
   for (uint32_t j0 = 0;;) {
     uint32_t gg[4];
 #pragma unroll
     for (int d = 0; d < 4; ++d) gg[d] = guide[gi[d]];
-    uint32_t nh[4], nl[4];
+    uint32_t nh[4];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) asm volatile("" : "=v"(nh[d]), "=v"(nl[d]));  // any (see more)
+    for (int d = 0; d < 4; ++d) asm volatile("" : "=v"(nh[d]));  // any (see more)
     const bool more = j0 + 64u * kWaveBlocks < nblk;
-    if (more) gen(j0 + 64u * kWaveBlocks, nh, nl);  // none past the end
+    if (more) gen(j0 + 64u * kWaveBlocks, nh);  // none past the end
     asm volatile("" : "+v"(nh[0]), "+v"(nh[1]), "+v"(nh[2]), "+v"(nh[3]));  // made here
     uint32_t t[4];
 #pragma unroll
@@ -689,68 +693,74 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
 #pragma unroll
       for (int d = 0; d < 4; ++d) put_big((int64_t)((z[d] >> 2) + 1));
     }
-    // deferred draws into the first ring: positions from a prefix sum of the
-    // lanes' counts (three ballots of its bits)
-    {
-      if (__ballot(def[0] || def[1] || def[2] || def[3]) != 0ull) {
-        uint32_t nd = 0;
+    // deferred draws into the first ring, by their number (their uniform is
+    // drawn again when they are resolved)
+    if (__ballot(def[0] || def[1] || def[2] || def[3]) != 0ull) {
 #pragma unroll
-        for (int d = 0; d < 4; ++d) nd += def[d] ? 1u : 0u;
-        const uint64_t b0 = __ballot(nd & 1u), b1 = __ballot(nd & 2u), b2 = __ballot(nd & 4u);
-        uint32_t pos = qh + qn + (uint32_t)(__popcll(b0 & below) + 2 * __popcll(b1 & below) +
-                                            4 * __popcll(b2 & below));
-#pragma unroll
-        for (int d = 0; d < 2 * kWaveBlocks; ++d) {
-          if (def[d]) {
-            const uint32_t i =
-                2u * (j0 + 64u * (uint32_t)(d >> 1) + (uint32_t)lane) + (uint32_t)(d & 1);
-            ring[wrap(pos, kBatchRing)] = defer_entry(m53(wh[d], wl[d]), timax, i, 0);
-            ++pos;
-          }
-        }
-        qn += (uint32_t)(__popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2));
+      for (int d = 0; d < 4; ++d) {
+        const uint64_t md = __ballot(def[d]);
+        const uint32_t pos = place_below(md, qh + qn) & (uint32_t)(kBatchRing - 1);
+        if (def[d])
+          ring[pos] = 2u * (j0 + 64u * (uint32_t)(d >> 1)) + (uint32_t)(d & 1) + 2u * (uint32_t)lane;
+        qn += (uint32_t)__popcll(md);
       }
     }
     // resolve 64 entries (one per lane) at a time, at the end the rest
-    while (qn >= 64u || hn >= 64u || (!more && (qn | hn) != 0u)) {
-      const bool second = hn >= 64u || qn == 0u;
-      const uint32_t m = min(second ? hn : qn, 64u);
+    while (qn >= 64u || rn >= 64u || hn >= 64u || (!more && (qn | rn | hn) != 0u)) {
+      // (whole passes first; hard ones last, as they are few and long)
+      const int which = hn >= 64u || rn >= 64u ? (hn > rn ? 2 : 1) : qn != 0u ? 0 : rn != 0u ? 1 : 2;
+      const uint32_t m = which == 0 ? min(qn, 64u)
+                         : which == 1 ? min(min(rn, 64u), (uint32_t)kHardRing - hn)
+                                      : min(min(hn, 64u), (uint32_t)kHardRing - rn);
       wave_sync();
       int64_t j = 0;
       uint32_t code = kTailTaken;
-      uint64_t e = 0;
+      uint64_t e = 0;  // the draw's number, the attempt from bit 32 on
       if ((uint32_t)lane < m) {
-        e = second ? hard[wrap(hh + (uint32_t)lane, kHardRing)]
-                   : ring[wrap(qh + (uint32_t)lane, kBatchRing)];
-        if (e >> 63) {
-          const uint32_t attempt = (uint32_t)(e >> 32) & kTailAttempts;
-          const TailTry t = second ? tail_hard(m0, beta, gm, ck0, ck1, (uint32_t)e, rep, cs, attempt)
-                                   : tail_try(m0, beta, gm, ck0, ck1, (uint32_t)e, rep, cs, attempt);
+        bool tail = true;
+        uint64_t mu = 0;
+        if (which == 0) {
+          const uint32_t i = ring[(qh + (uint32_t)lane) & (uint32_t)(kBatchRing - 1)];
+          const Words4 w = philox4x32_10(i >> 1, rep, cs, 0u, ck0, ck1);
+          mu = (i & 1u) ? m53(w.w2, w.w3) : m53(w.w0, w.w1);
+          tail = mu > timax;
+          e = i;
+        } else {
+          const uint32_t p = ((which == 2 ? hh : rh) + (uint32_t)lane) & (uint32_t)(kHardRing - 1);
+          e = which == 2 ? hard[p] : retry[p];
+        }
+        if (tail) {
+          const uint32_t attempt = (uint32_t)(e >> 32);
+          const TailTry t = which == 2
+                                ? tail_hard(m0, beta, gm, ck0, ck1, (uint32_t)e, rep, cs, attempt)
+                                : tail_try(m0, beta, gm, ck0, ck1, (uint32_t)e, rep, cs, attempt);
           code = t.code;
           j = t.X - off;
           if (code == kTailCapped) fl |= kFlagTailCapped;
         } else {
-          j = (int64_t)lds_search(e & ((1ull << 53) - 1), T, guide, sh);
+          j = (int64_t)lds_search(mu, T, guide, sh);
         }
       }
-      if (second) {
-        hh = wrap(hh + m, kHardRing);
+      if (which == 2) {
+        hh += m;
         hn -= m;
+      } else if (which == 1) {
+        rh += m;
+        rn -= m;
       } else {
-        qh = wrap(qh + m, kBatchRing);
+        qh += m;
         qn -= m;
       }
       const uint64_t mr = __ballot(code == kTailRejected || code == kTailCapped);
       if (mr != 0ull) {
-        if ((mr >> lane) & 1ull)
-          ring[wrap(wrap(qh + qn, kBatchRing) + (uint32_t)__popcll(mr & below), kBatchRing)] =
-              e + (1ull << 32);
-        qn += (uint32_t)__popcll(mr);
+        const uint32_t p = place_below(mr, rh + rn) & (uint32_t)(kHardRing - 1);
+        if ((mr >> lane) & 1ull) retry[p] = e + (1ull << 32);
+        rn += (uint32_t)__popcll(mr);
       }
       const uint64_t mh = __ballot(code == kTailHard);
       if (mh != 0ull) {
-        if (code == kTailHard)
-          hard[wrap(wrap(hh + hn, kHardRing) + (uint32_t)__popcll(mh & below), kHardRing)] = e;
+        const uint32_t p = place_below(mh, hh + hn) & (uint32_t)(kHardRing - 1);
+        if (code == kTailHard) hard[p] = e;
         hn += (uint32_t)__popcll(mh);
       }
       if (code != kTailTaken) j = 0;
@@ -763,10 +773,7 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
     if (!more) break;
     j0 += 64u * kWaveBlocks;
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      wh[d] = nh[d];
-      wl[d] = nl[d];
-    }
+    for (int d = 0; d < 4; ++d) wh[d] = nh[d];
   }
   DrawOut o;
   o.fl = dpp_or_u32(fl);
@@ -984,8 +991,8 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
            (q == 0 || top - (kRecords + (q + 1) * cw) >= (int64_t)c.room)) {
       const uint32_t rep = (uint32_t)(r0 + done + q);
       const uint32_t room = (uint32_t)min(top - (kRecords + (q + 1) * cw), n);
-      const DrawOut dr = draw_replicate<kCut, kKernel>(&c, rep, (LdsU32*)L->hist, (LdsU64*)L->ring,
-                                              (LdsU64*)L->hard, scratch + top, room,
+      const DrawOut dr = draw_replicate<kCut, kKernel>(&c, rep, (LdsU32*)L->hist, (LdsU32*)L->ring,
+                                              (LdsU64*)L->retry, (LdsU64*)L->hard, scratch + top, room,
                                               (const LdsU32*)T, (const LdsU32*)guide, hi);
       hi = dr.hi;
       full = dr.ovn > room;

@@ -57,6 +57,12 @@ __device__ __forceinline__ uint64_t lanes_below(int lane) {
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
+// base plus the number of mask's lanes below this one.
+__device__ __forceinline__ uint32_t place_below(uint64_t mask, uint32_t base = 0u) {
+  return (uint32_t)__builtin_amdgcn_mbcnt_hi(
+      (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
+}
+
 // ---------------------------------------------------------------------------
 // Inverse-CDF sampling: x = min{k in 1..kH : T[k] >= U} (the ">=" rule of
 // the paper's sampler).  U = m 2^-53 with m = (w >> 11) | 1 an odd 53-bit
@@ -379,10 +385,10 @@ __device__ __forceinline__ int next_pow2(int v) {
   return p;
 }
 
-// Ring of deferred draws (lane form).  Before an iteration's
-// appends (at most 64 lanes x 4 draws) it holds fewer than 64 entries, so
-// 320 entries never overflow.
-constexpr int kRing = 320;
+// Ring of deferred draws (lane form), by number and lane.  Before an
+// iteration's appends (at most 64 lanes x 4 draws) it holds fewer than 64
+// entries, so it never overflows; a power of two for its places.
+constexpr int kRing = 512;
 
 // ---------------------------------------------------------------------------
 // A wave's LDS in the lane form.
@@ -392,7 +398,7 @@ struct alignas(16) LaneRegion {
   // dword b of lane l at hist[b * 64 + l]; row kHLB / 2 is a pad that takes
   // the draw loop's no-op counts (never read)
   uint32_t hist[(kHLB / 2 + 1) * 64];
-  uint64_t ring[kRing];          // deferred draws
+  uint32_t ring[kRing];          // deferred draws
   uint32_t ovc[64];  // values the drains added to a lane's list (may exceed its room)
   uint32_t fl[64];   // flags per lane
 };
@@ -809,7 +815,7 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
   int64_t* __restrict__ spill = as_global(reinterpret_cast<int64_t*>(uniform64((int64_t)spill_)));
   LdsU32* hist = region + lane;
   const uint32_t column = (uint32_t)(uintptr_t)hist;
-  LdsU64* ring = (LdsU64*)(region + offsetof(LaneRegion, ring) / 4);
+  LdsU32* ring = region + offsetof(LaneRegion, ring) / 4;
   LdsU32* ovc = region + offsetof(LaneRegion, ovc) / 4;
   LdsU32* lfl = region + offsetof(LaneRegion, fl) / 4;
 #pragma unroll
@@ -831,7 +837,7 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
   // its uniforms, generates the next iteration's uniforms while they are in
   // flight, issues the table reads, and computes the next guide indexes while
   // those are in flight (one extra block of uniforms is generated at the end).
-  auto gen = [&](uint32_t j, uint32_t (&ho)[4], uint32_t (&lo)[4]) {
+  auto gen = [&](uint32_t j, uint32_t (&ho)[4]) {  // the uniforms' first words
     // the round keys are recomputed per block with scalar adds rather than
     // kept live across the loop (where they would be spilled)
     uint32_t k0 = ck0, k1 = ck1;
@@ -840,23 +846,21 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
     for (int b = 0; b < kLaneBlocks; ++b) {
       const Words4 w = philox4x32_10(j + (uint32_t)b, r, cs, 0u, k0, k1);
       ho[2 * b] = w.w0;
-      lo[2 * b] = w.w1;
       ho[2 * b + 1] = w.w2;
-      lo[2 * b + 1] = w.w3;
     }
   };
   const GuideRule rule = guide_rule(sh);
-  uint32_t wh[4], wl[4];  // the words of the uniforms
-  int gi[4];              // their guide bins
-  gen(0u, wh, wl);
+  uint32_t wh[4];
+  int gi[4];  // their guide bins
+  gen(0u, wh);
 #pragma unroll
   for (int d = 0; d < 4; ++d) gi[d] = guide_index32(wh[d], rule);
   for (uint32_t j = 0;;) {
     uint32_t gg[4];
 #pragma unroll
     for (int d = 0; d < 4; ++d) gg[d] = guide[gi[d]];
-    uint32_t nh[4], nl[4];
-    gen(j + (uint32_t)kLaneBlocks, nh, nl);
+    uint32_t nh[4];
+    gen(j + (uint32_t)kLaneBlocks, nh);
     asm volatile("" : "+v"(nh[0]), "+v"(nh[1]), "+v"(nh[2]), "+v"(nh[3]));  // made here
     uint32_t t[4];
 #pragma unroll
@@ -889,23 +893,16 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
         }
       }
     }
-    // deferred draws into the ring (positions from three ballots of the counts)
+    // deferred draws into the ring, by number and lane (their uniform is drawn
+    // again when they are resolved)
     if (__ballot(def[0] || def[1] || def[2] || def[3]) != 0ull) {
-      uint32_t nd = 0;
 #pragma unroll
-      for (int d = 0; d < 4; ++d) nd += def[d] ? 1u : 0u;
-      const uint64_t b0 = __ballot(nd & 1u), b1 = __ballot(nd & 2u), b2 = __ballot(nd & 4u);
-      uint32_t pos = qh + qn + (uint32_t)(__popcll(b0 & below) + 2 * __popcll(b1 & below) +
-                                          4 * __popcll(b2 & below));
-#pragma unroll
-      for (int d = 0; d < 2 * kLaneBlocks; ++d) {
-        if (def[d]) {
-          ring[pos >= (uint32_t)kRing ? pos - (uint32_t)kRing : pos] =
-              defer_entry(m53(wh[d], wl[d]), timax, 2u * j + (uint32_t)d, lane);
-          ++pos;
-        }
+      for (int d = 0; d < 4; ++d) {
+        const uint64_t md = __ballot(def[d]);
+        const uint32_t pos = place_below(md, qh + qn) & (uint32_t)(kRing - 1);
+        if (def[d]) ring[pos] = (2u * j + (uint32_t)d) * 64u + (uint32_t)lane;
+        qn += (uint32_t)__popcll(md);
       }
-      qn += (uint32_t)(__popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2));
     }
     j += (uint32_t)kLaneBlocks;
     const bool more = j < nblk;
@@ -913,16 +910,17 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
       const uint32_t m = min(qn, 64u);
       wave_sync();
       if ((uint32_t)lane < m) {
-        const uint32_t p = qh + (uint32_t)lane;
-        const uint64_t e = ring[p >= (uint32_t)kRing ? p - (uint32_t)kRing : p];
-        const uint32_t owner = (uint32_t)(e >> 53) & 63u;
+        const uint32_t e = ring[(qh + (uint32_t)lane) & (uint32_t)(kRing - 1)];
+        const uint32_t owner = e & 63u, i = e >> 6;
+        const Words4 w = philox4x32_10(i >> 1, rep0 + owner, cs, 0u, ck0, ck1);
+        const uint64_t mu = (i & 1u) ? m53(w.w2, w.w3) : m53(w.w0, w.w1);
         int64_t v;
-        if (e >> 63) {
-          const TailDraw td = tail_draw_call(beta, gm, ck0, ck1, (uint32_t)e, rep0 + owner, cs);
+        if (mu > timax) {
+          const TailDraw td = tail_draw_call(beta, gm, ck0, ck1, i, rep0 + owner, cs);
           v = td.X;
           if (td.fl) lds_or(&lfl[owner], td.fl);
         } else {
-          v = (int64_t)lds_search(e & ((1ull << 53) - 1), T, guide, sh);
+          v = (int64_t)lds_search(mu, T, guide, sh);
         }
         if (v <= kHLB) {
           const uint32_t b = (uint32_t)v - 1u;
@@ -934,15 +932,12 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
             spill[(kLaneCap - 1 - (int)s) * 64 + (int)owner] = v;
         }
       }
-      qh = qh + m >= (uint32_t)kRing ? qh + m - (uint32_t)kRing : qh + m;
+      qh += m;
       qn -= m;
     }
     if (!more) break;
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      wh[d] = nh[d];
-      wl[d] = nl[d];
-    }
+    for (int d = 0; d < 4; ++d) wh[d] = nh[d];
   }
   wave_sync_global();  // other lanes wrote to this lane's slots
   return myc;
