@@ -613,7 +613,10 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
   const double m0 = kCut ? (double)(c.xmin + kH) : kTailM;
   const double beta = c.beta, gm = c.gm;
   const int64_t off = kCut ? uniform64(c.xmin) - 1 : 0;
-  int xm = 0;
+  // LDS addresses of the bins and of the lane's own counters
+  const uint32_t bins = (uint32_t)(uintptr_t)hist;
+  const uint32_t own = bins + 4u * (uint32_t)(kWaveOwn + lane);
+  uint32_t xm = 0;  // largest offset drawn (16 bits), values above kHW included
   uint32_t fl = 0, ovn = 0;
   // first places and lengths of the rings (wave-uniform)
   uint32_t qh = 0, qn = 0, rh = 0, rn = 0, hh = 0, hn = 0;
@@ -662,45 +665,40 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
     for (int d = 0; d < 4; ++d) gi[d] = guide_index32(nh[d], rule);
     asm volatile("" : "+v"(gi[0]), "+v"(gi[1]), "+v"(gi[2]), "+v"(gi[3]));  // made here
     asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));  // reads stay unconditional
-    int z[4];
-    bool def[4];
-    fast_offsets(wh, gg, t, rule, [](int) { return true; }, z, def);
+    uint32_t z[4];
+    fast_offsets(wh, gg, t, rule, z);
     if (n32 - 2u * j0 < 4u * 64u) {  // the last ones
       // draw d of the lane is number 2 lane + (d & 1) of the wave's 128 from
       // 2 j0 + 128 (d >> 1) on
       const int left = (int)(n32 - 2u * j0);
 #pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        if (2 * lane >= left - 128 * (d >> 1) - (d & 1)) {
-          z[d] = -1;
-          def[d] = false;
-        }
-      }
+      for (int d = 0; d < 4; ++d)
+        if (2 * lane >= left - 128 * (d >> 1) - (d & 1)) z[d] = kNoDraw;
     }
-    bool big = false;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      big = big || z[d] >= 4 * kHW;
-      // values 1..3 into the lane's own counters, those above kHW (and none)
-      // into the pad
-      const uint32_t zd = (uint32_t)z[d];
-      const uint32_t at = zd < 12u ? (zd << 6) + 4u * (uint32_t)(kWaveOwn + lane)
-                                   : (zd < 4u * (uint32_t)kHW ? zd : 4u * (uint32_t)(kWavePad + lane));
-      lds_inc((LdsU32*)((LdsU8*)hist + at));
-      xm = max(xm, z[d]);  // an offset; values above kHW are clamped once, below
+      // values 1..3 into the lane's own counters, what is above 1..kHW into the
+      // pad
+      const uint32_t at = z[d] < 12u ? (z[d] << 6) + own : min(z[d], 4u * (uint32_t)kWavePad) + bins;
+      lds_inc((LdsU32*)at);
+      // the largest offset, marks left out: they are negative in 16 bits
+      asm("v_max_i16 %0, %0, %1" : "+v"(xm) : "v"(z[d]));
     }
-    if (__ballot(big) != 0ull) {
-#pragma unroll
-      for (int d = 0; d < 4; ++d) put_big((int64_t)((z[d] >> 2) + 1));
-    }
-    // deferred draws into the first ring, by their number (their uniform is
-    // drawn again when they are resolved)
-    if (__ballot(def[0] || def[1] || def[2] || def[3]) != 0ull) {
+    if (__ballot(max(max(z[0], z[1]), max(z[2], z[3])) >= 4u * (uint32_t)kHW) != 0ull) {
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
-        const uint64_t md = __ballot(def[d]);
+        const bool bg = z[d] >= 4u * (uint32_t)kHW && z[d] < (uint32_t)kDeferred;
+        const uint64_t mb = __ballot(bg);
+        if (mb != 0ull) {
+          const uint32_t at = ovn + place_below(mb);
+          if (bg && at < room) top[-1 - (int64_t)at] = (int64_t)((z[d] >> 2) + 1u);
+          ovn += (uint32_t)__popcll(mb);
+        }
+        // deferred draws into the first ring, by their number (their uniform is
+        // drawn again when they are resolved)
+        const uint64_t md = __ballot(deferred(z[d]));
         const uint32_t pos = place_below(md, qh + qn) & (uint32_t)(kBatchRing - 1);
-        if (def[d])
+        if ((md >> lane) & 1ull)
           ring[pos] = 2u * (j0 + 64u * (uint32_t)(d >> 1)) + (uint32_t)(d & 1) + 2u * (uint32_t)lane;
         qn += (uint32_t)__popcll(md);
       }
@@ -766,7 +764,7 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
       if (code != kTailTaken) j = 0;
       if (j >= 1 && j <= kHW) {
         lds_inc(&hist[j - 1]);
-        xm = max(xm, 4 * (int)j - 4);
+        xm = max(xm, 4u * (uint32_t)j - 4u);
       }
       put_big(j);
     }
@@ -778,7 +776,7 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
   DrawOut o;
   o.fl = dpp_or_u32(fl);
   o.ovn = ovn;
-  const int hi = ((int)min((dpp_max_u32((uint32_t)xm) >> 2) + 1u, (uint32_t)kHW) + 255) & ~255;
+  const int hi = ((int)min((dpp_max_u32(xm) >> 2) + 1u, (uint32_t)kHW) + 255) & ~255;
   o.hi = hi < 256 ? 256 : hi;
   wave_sync();
   const uint32_t c1 = dpp_sum_u32(hist[kWaveOwn + lane]);

@@ -769,28 +769,30 @@ __device__ __forceinline__ int lds_search(uint64_t m, const LdsU32* T, const Lds
   return lo + 1;
 }
 
-// The fast path of four draws in 32-bit steps: value offsets 4 (x - 1) of the
-// draws valid(d) that it decides, -1 for the others; def marks the valid ones
-// to search in full (a wide bracket, a tail uniform, a first word that equals
-// the threshold's or whose bin needs more bits).
-template <class Valid>
+// The fast path of four draws in 32-bit steps: z is the offset 4 (x - 1) of a
+// draw that it decides, else kDeferred or more: a draw to search in full (a
+// wide bracket, a tail uniform, a first word that equals the threshold's or
+// whose bin needs more bits).  A counter's place is then a minimum away, with
+// no look at what a draw is; the loops look when the largest z says so.
+constexpr uint32_t kNoDraw = 0xffffu;  // z of a draw that does not exist
 __device__ __forceinline__ void fast_offsets(const uint32_t (&w0)[4], const uint32_t (&gg)[4],
-                                             uint32_t (&t)[4], const GuideRule& rule, Valid valid,
-                                             int (&z)[4], bool (&def)[4]) {
+                                             const uint32_t (&t)[4], const GuideRule& rule,
+                                             uint32_t (&z)[4]) {
   const uint32_t wm = max(max(w0[0], w0[1]), max(w0[2], w0[3]));
-  if (__ballot(wm > rule.last) != 0ull) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d)
-      if (w0[d] > rule.last) t[d] = w0[d];
-  }
+  bool odd = wm > rule.last;
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
-    const uint32_t zd = w0[d] < t[d] ? (gg[d] & 0xffffu) : (gg[d] >> 16);
-    const bool drawn = zd < (uint32_t)kDeferred && w0[d] != t[d];
-    const bool v = valid(d);
-    z[d] = v && drawn ? (int)zd : -1;
-    def[d] = v && !drawn;
+    z[d] = w0[d] < t[d] ? (gg[d] & 0xffffu) : (gg[d] >> 16);
+    odd = odd || w0[d] == t[d];
   }
+  if (__ballot(odd) != 0ull) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+      if (w0[d] == t[d] || w0[d] > rule.last) z[d] = (uint32_t)kDeferred;
+  }
+}
+__device__ __forceinline__ bool deferred(uint32_t z) {
+  return z >= (uint32_t)kDeferred && z != kNoDraw;
 }
 
 // Draw blocks per iteration of the lane form's loop (two draws each).
@@ -812,6 +814,7 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
   const DevCell& c = *as_global(reinterpret_cast<const DevCell*>(uniform64((int64_t)cell)));
   const uint32_t rep0 = uniform32((uint32_t)rep0_);
   const bool active = lane < count_;
+  const bool idle = __builtin_amdgcn_readfirstlane(count_) < 64;
   int64_t* __restrict__ spill = as_global(reinterpret_cast<int64_t*>(uniform64((int64_t)spill_)));
   LdsU32* hist = region + lane;
   const uint32_t column = (uint32_t)(uintptr_t)hist;
@@ -870,37 +873,34 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
     for (int d = 0; d < 4; ++d) gi[d] = guide_index32(nh[d], rule);
     asm volatile("" : "+v"(gi[0]), "+v"(gi[1]), "+v"(gi[2]), "+v"(gi[3]));  // made here
     asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));  // reads stay unconditional
-    int z[4];
-    bool def[4];
-    fast_offsets(wh, gg, t, rule,
-                 [&](int d) { return active && 2u * j + (uint32_t)d < n32; }, z, def);
-    bool big = false;
+    uint32_t z[4];
+    fast_offsets(wh, gg, t, rule, z);
+    if (2u * j + 4u > n32 || idle) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+        if (!active || 2u * j + (uint32_t)d >= n32) z[d] = kNoDraw;
+    }
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      big = big || z[d] >= 4 * kHLB;
-      // own column, no branch: values outside 1..kHLB count into the pad row
-      const uint32_t v = min((uint32_t)z[d], 4u * (uint32_t)kHLB);
+      // own column, no branch: what is above 1..kHLB counts into the pad row
+      const uint32_t v = min(z[d], 4u * (uint32_t)kHLB);
       uint32_t at;
       asm("v_lshl_add_u32 %0, %1, 5, %2" : "=v"(at) : "v"(v & ~7u), "v"(column));
       lds_add((LdsU32*)at, 1u << ((v << 2) & 31u));
     }
-    if (__ballot(big) != 0ull) {  // values above the column, into the lane's own slots
-#pragma unroll
-      for (int d = 0; d < 2 * kLaneBlocks; ++d) {
-        if (z[d] >= 4 * kHLB) {
-          if (myc < kLaneCap) spill[myc * 64 + lane] = (z[d] >> 2) + 1;
-          ++myc;
-        }
-      }
-    }
-    // deferred draws into the ring, by number and lane (their uniform is drawn
-    // again when they are resolved)
-    if (__ballot(def[0] || def[1] || def[2] || def[3]) != 0ull) {
+    if (__ballot(max(max(z[0], z[1]), max(z[2], z[3])) >= 4u * (uint32_t)kHLB) != 0ull) {
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
-        const uint64_t md = __ballot(def[d]);
+        // values above the column, into the lane's own slots
+        if (z[d] >= 4u * (uint32_t)kHLB && z[d] < (uint32_t)kDeferred) {
+          if (myc < kLaneCap) spill[myc * 64 + lane] = (int64_t)(z[d] >> 2) + 1;
+          ++myc;
+        }
+        // deferred draws into the ring, by number and lane (their uniform is
+        // drawn again when they are resolved)
+        const uint64_t md = __ballot(deferred(z[d]));
         const uint32_t pos = place_below(md, qh + qn) & (uint32_t)(kRing - 1);
-        if (def[d]) ring[pos] = (2u * j + (uint32_t)d) * 64u + (uint32_t)lane;
+        if ((md >> lane) & 1ull) ring[pos] = (2u * j + (uint32_t)d) * 64u + (uint32_t)lane;
         qn += (uint32_t)__popcll(md);
       }
     }
