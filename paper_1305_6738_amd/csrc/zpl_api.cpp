@@ -353,6 +353,21 @@ bool form_eligible(uint32_t m, double alpha, int64_t n, uint32_t K = 0) {
 // measured on MI355X over the paper's sample sizes at K = 20 and K = 1000.
 double trunc_cost(int64_t n, uint32_t K) { return 2.2e-3 * ((double)n + 8.6 * (double)K); }
 
+// The truncated law by Euler-Maclaurin sums, more than a few values above the
+// lane's column: the lane form finishes 64 replicates at once, where the batch
+// takes them one by one, but each of a lane's values above the column costs as
+// many comparisons as there are.  ns per replicate with the device busy, lane
+// and batch, K = 1,000: alpha 1.0, 200 draws (81 above) 5.3 and 7.7, 400 (162)
+// 15.6 and 8.9; alpha 1.5, 1,000 draws (88) 7.9 and 8.5; alpha 2, 1,000 draws
+// (12) 5.2 and 7.6, 3,000 (36) 13.6 and 11.5.  A round of lanes takes about
+// 0.4 us per draw however few they are, the batch 12.5 ns per replicate of a
+// call with few: at R = 32 n they meet (1,000 draws, 30,000 replicates: 606 and
+// 618 us; 10,000: 552 and 298).  Cells of fewer than 16 draws stay in the wave
+// form, whose choice for them is part of the tested interface.
+bool lane_truncated(double alpha, int64_t n, uint32_t K, int64_t R) {
+  return n >= 16 && n <= 2000 && (double)n * tail_prob(alpha, kHLB, K) <= 84.0 && R >= 32 * n;
+}
+
 // Time for one cell alone under form f (tuned cost v ns per replicate with
 // the device busy): its work units (kBlock replicates per workgroup for the
 // lane and wave forms; the heavy form's replicates spread over the device, in
@@ -404,6 +419,7 @@ uint32_t choose_form(double alpha, int64_t n, const Tuning* t, uint32_t K = 0, i
     }
   }
   if (n <= 65535 && (double)n * tail_prob(alpha, kHLB, K) <= 2.0) return kModeLane;
+  if (K >= kTruncEmK && lane_truncated(alpha, n, K, R)) return kModeLane;
   if (form_eligible(kModeWave, alpha, n, K)) return kModeWave;
   return kModeHeavy;
 }

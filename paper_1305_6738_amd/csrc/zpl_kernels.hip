@@ -466,9 +466,10 @@ struct LaneOut {
   uint64_t fp;
   uint32_t flags;
 };
+template <bool kTruncLaw>
 static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slots_, int myc, int od,
-                                                   bool ok, int64_t n, uint32_t fl, bool want_fp,
-                                                   const double* ln_) {
+                                                   bool ok, int64_t n, uint32_t fl, uint32_t K,
+                                                   bool want_fp, const double* ln_) {
   int64_t* slots = as_global(slots_);
   const double* __restrict__ ln = as_global(ln_);
   LaneOut o;
@@ -512,15 +513,28 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
   } else {
     Sd = u128_to_S(S);
   }
-  o.a = mle_alpha_start(Sd / (double)n, ln, mle_guess_table(ln), &o.flags);
+  // sum of k^-a over k > v (v >= 16)
+  auto survival = [&](const EmCoef& e, const TruncEnd& t, int64_t v) -> double {
+    if constexpr (kTruncLaw) return trunc_tail(e, t, v, ln[v <= (int64_t)kH ? v + 1 : 0]);
+    return survival_next(e, v, ln);
+  };
+  if constexpr (kTruncLaw)
+    o.a = mle_alpha_trunc(Sd / (double)n, K, ln, &o.flags);
+  else
+    o.a = mle_alpha_start(Sd / (double)n, ln, mle_guess_table(ln), &o.flags);
   const EmCoef E = em_coef(o.a);
+  TruncEnd te = {};
+  if constexpr (kTruncLaw) te = trunc_end(E, K, ln);
   const double idn = 1.0 / (double)n;
   const uint32_t nu = (uint32_t)n;  // lane form: n <= 65535
   double D = 0.0, iz, zprev;
   uint32_t C = 0;
   {
     double suf[17];
-    survival_head(E, ln, suf);
+    if constexpr (kTruncLaw)
+      survival_head_trunc(E, te, ln, suf);
+    else
+      survival_head(E, ln, suf);
     iz = 1.0 / suf[0];
 #pragma unroll
     for (int v = 1; v <= 16; ++v) {
@@ -542,7 +556,7 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
       const uint32_t wv = column[((v - 1) >> 1) * 64];
       const uint32_t c = (v & 1) ? (wv & 0xffffu) : (wv >> 16);
       if (c) {
-        const double zv = hurwitz_tail(E, (double)(v + 1), ln[v + 1]);
+        const double zv = survival(E, te, v);
         const double zv1 = prev ? zprev : zv + pow_neg(E.s, ln[v]);
         const double t2 = fabs(fma(zv1, iz, -(double)(nu - C) * idn));
         C += c;
@@ -552,7 +566,7 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
       }
       prev = c != 0u;
     }
-    if (!prev) zprev = hurwitz_tail(E, (double)(kHLB + 1), ln[kHLB + 1]);
+    if (!prev) zprev = survival(E, te, kHLB);
     live = oc > 0 && fmax(zprev * iz, (double)oc * idn) > D - kPruneMargin;
   }
   if (__ballot(live) == 0ull) {
@@ -585,7 +599,7 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
       lower += c;
       const double sr = (double)((uint32_t)oc - lower) * idn;
       const double zr = nb < kLaneBuckets - 1
-                            ? iz * survival_next(E, (int64_t)lane_bucket_start(nb + 1) - 1, ln)
+                            ? iz * survival(E, te, (int64_t)lane_bucket_start(nb + 1) - 1)
                             : 0.0;
       more[64 * nb] = __double_as_longlong(c ? fmax(zl - sr, sl - zr) : 0.0);
       Dlow = fmax(Dlow, fabs(zr - sr));
@@ -665,9 +679,11 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
         }
         const uint32_t Cb = nu - (io & 0xffffu) + cum[64 * b + owner] + lt;
         const EmCoef Eo = em_coef(as);
-        const double zv = survival_next(Eo, v, ln);
+        TruncEnd to = {};
+        if constexpr (kTruncLaw) to = trunc_end(Eo, K, ln);
+        const double zv = survival(Eo, to, v);
         const double zv1 =
-            pres ? survival_next(Eo, v - 1, ln) : zv + pow_neg(as, ln_value(v, ln));
+            pres ? survival(Eo, to, v - 1) : zv + pow_neg(as, ln_value(v, ln));
         const double t2 = fabs(fma(zv1, izo, -(double)(nu - Cb) * idn));
         const double t1 = fabs(fma(zv, izo, -(double)(nu - Cb - eq) * idn));
         __hip_atomic_fetch_max(&dmax[owner], (uint64_t)__double_as_longlong(fmax(t1, t2)),
@@ -966,11 +982,13 @@ __device__ __forceinline__ void lane_wave(const DevCell* cells, int32_t cell_id,
   if (!ok) myc = od = 0;
   const bool want_fp = out.fp != nullptr;
   LaneOut o;
-  if (c.K) {
+  if (c.K >= kTruncEmK) {
+    o = lane_finish<true>(region, spill + lane, myc, od, ok, c.n, fl, c.K, want_fp, ln);
+  } else if (c.K) {
     if (ok)
       o = lane_finish_trunc(region + lane, spill + lane, myc, od, c.n, fl, c.K, want_fp, ln);
   } else {
-    o = lane_finish(region, spill + lane, myc, od, ok, c.n, fl, want_fp, ln);
+    o = lane_finish<false>(region, spill + lane, myc, od, ok, c.n, fl, 0u, want_fp, ln);
   }
   if (ok) write_outputs(out, c.out_off + rep0 + lane, o.D, o.a, o.flags, o.fp);
 }

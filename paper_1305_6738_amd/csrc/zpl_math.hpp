@@ -839,6 +839,8 @@ struct TruncEnd {
   double u, iu, lnK, end;
   int64_t K;
 };
+// From this K on it applies at every exponent in [-64, 64] (em_start(64) = 113).
+constexpr uint32_t kTruncEmK = 113 + 48;
 ZPL_HD bool trunc_em(double s, uint32_t K) { return (int64_t)K >= em_start(fabs(s)) + 48; }
 ZPL_HD double em_poly(const EmCoef& E, double iq) {
   const double iq2 = iq * iq;
