@@ -85,7 +85,7 @@ def progress(msg):
 
 
 PROFILE = ROOT / "profiles" / "k_simulate_table_n1000.md"
-HEAVY_PROFILE = ROOT / "profiles" / "k_heavy_heavy_tail.md"
+HEAVY_PROFILE = ROOT / "profiles" / "k_simulate_heavy_tail.md"
 # the device code's sources and the build script (its compiler flags)
 KERNEL_SOURCES = ["paper_1305_6738_amd/csrc/zpl_kernels.hip", "paper_1305_6738_amd/csrc/zpl_batch.hpp",
                   "paper_1305_6738_amd/csrc/zpl_fit.hpp",
@@ -286,13 +286,13 @@ def config_runs(ctx, stream, torch):
 def heavy_roofline(cells, tm):
     """Roofline of the heavy-tail configuration: the heavy_ops model over
     every replicate against the simulation launches' time (HIP events: the
-    lane/wave launch plus the heavy launch, which runs most of these cells),
-    and the counters of the committed k_heavy profile while it is current."""
+    simulation kernel, which runs these cells, plus the escalations'), and the
+    counters of the committed heavy-tail profile while it is current."""
     ops = sum(R * heavy_ops(a, n) for (a, n, R, s, st) in cells)
     sec = (tm["simulate"] + tm["heavy"]) / 1e3
     r = {"bound": "alu", "achieved": ops / sec / 1e12, "peak": PEAK_OPS / 1e12,
-         "unit": "Tops/s", "frac": ops / sec / PEAK_OPS, "kernel": "k_heavy",
-         "kernel_ms": tm["heavy"], "simulate_ms": tm["simulate"], "ops_per_launch": ops,
+         "unit": "Tops/s", "frac": ops / sec / PEAK_OPS, "kernel": "k_simulate",
+         "kernel_ms": tm["simulate"], "simulate_ms": tm["simulate"], "ops_per_launch": ops,
          "traffic": profiled_traffic(HEAVY_PROFILE),
          "traffic_unit": "bytes per launch (HBM, rocprofv3 FETCH_SIZE + WRITE_SIZE)"}
     r.update(profiled_counters(HEAVY_PROFILE))
@@ -398,7 +398,7 @@ def main(argv=None):
     ap.add_argument("--tune-out", default=None, help="save the measured tuning table here")
     ap.add_argument("--workload", default="table_n1000", choices=["table_n1000", "heavy_tail"],
                     help="cells of the timed region: the headline n = 1000 table slice, or "
-                         "the heavy tails (alpha 1.2..1.5, n = 10,000; for profiling k_heavy)")
+                         "the heavy tails (alpha 1.2..1.5, n = 10,000; for profiling its batches)")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
                     help="first copy this many MiB device-to-device once (a kernel of known "
                          "traffic that scales the profiler's FETCH_SIZE / WRITE_SIZE)")

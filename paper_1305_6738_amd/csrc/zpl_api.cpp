@@ -73,7 +73,8 @@ const HostLn& host_ln() {
 // exponents are never below about 1.023: mean ln x < ln 2^63.)
 constexpr double kMinAlpha = 1.01;
 constexpr int64_t kMaxXmin = (int64_t)1 << 40;
-// Datasets at least this long are fitted by a whole workgroup.
+// Datasets of a serving batch below this length share one launch and its
+// scratch areas; longer ones are fitted one after another.
 constexpr int64_t kFitBlockMin = 2048;
 // Host datasets up to this many bytes go through pinned staging.
 constexpr size_t kPinStageMax = (size_t)64 << 20;
@@ -318,6 +319,7 @@ struct Plan {
   int64_t batch_R = 0;          // their replicates
   int64_t max_room = 0;         // largest DevCell::room among their cells
   bool bounded = false;         // some cell's room is less than its n
+  int64_t lane_n = 0;    // most draws of a lane-form replicate
   // what the form of each cell alone sizes the scratch by: units of kBlock
   // lane- and wave-form replicates, and of 8 heavy-form ones
   int64_t sim_units = 0, heavy8 = 0;
@@ -598,6 +600,7 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
       if (v > 0.0) w = v;
     }
     runs.push_back({w, i, 0, d.R});
+    P.lane_n = std::max(P.lane_n, d.n);
     lane_R += d.R;
     lane_work += (double)d.R * ((double)d.n + 200.0);
   }
@@ -739,7 +742,8 @@ zpl_status prepare(zpl_ctx* c, const Plan& P, int n_q, bool need_dbuf, Launch& L
   L.sim.grid = std::min(L.sim.lane_wgs + L.sim.batch_wgs, c->n_cu);
   share(P.n_bcut, kBatchWavesCut, P.max_room, L.cut_grid, L.cstride);
   L.esc_grid = 0;
-  if (!P.units.empty() || P.bounded)
+  // (a replicate of at most kLaneCap draws cannot leave its lane)
+  if (P.lane_n > kLaneCap || P.bounded)
     share(64, kEscWaves, P.max_n, L.esc_grid, L.estride);
   if (need_dbuf) ZPL_TRY(ensure(c, c->dbuf, sizeof(double) * (size_t)P.total_R));
   // bracket gather: at most ~12% of a cell's replicates fall in a bracket

@@ -7,8 +7,8 @@
 // between two points l < r of the support every |F - S_n| is at most
 // max(F(r) - S_n(l), S_n(r) - F(l)), so an interval whose bound does not reach
 // a distance already found elsewhere holds no maximum and its values are not
-// looked at.  What remains is evaluated exactly as the list walk of
-// ks_distance does (the same terms, hence the same D bit for bit).
+// looked at.  What remains is evaluated by the same expressions as everywhere
+// (hence the same D bit for bit).
 //
 // Included by zpl_kernels.hip after the helpers it uses.
 #pragma once
@@ -854,7 +854,7 @@ struct HeadOut {
   double a, iz, z16, D;
   uint32_t flags, done;
 };
-// The distinct values of stored counts 1..K, K <= kHW (see ListSrc).
+// The distinct values of stored counts 1..K, K <= kHW, as ks_distance_trunc takes them.
 struct CountSrc {
   CountView cv;
   uint32_t K;

@@ -39,11 +39,6 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   for (int m = 32; m > 0; m >>= 1) v += shfl_xor_u32(v, m);
   return v;
 }
-__device__ __forceinline__ uint32_t wave_or_u32(uint32_t v) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) v |= shfl_xor_u32(v, m);
-  return v;
-}
 __device__ __forceinline__ U128 wave_sum_u128(U128 v) {
 #pragma unroll
   for (int m = 32; m > 0; m >>= 1) {
@@ -130,63 +125,12 @@ __device__ __forceinline__ uint64_t defer_entry(uint64_t m, uint64_t timax, uint
 // suf[]; for larger ones Z(v) comes from the Euler-Maclaurin tail and
 // Z(v-1) = Z(v) + v^-a.  Src yields the distinct values: small(v) returns
 // the count of v for v = 1..16 in order, then next_large() returns the
-// remaining (value, count) pairs ascending.
-// ---------------------------------------------------------------------------
-template <class Src>
-__device__ __forceinline__ double ks_distance(Src& src, const EmCoef& E,
-                                              const double (&suf)[17], int64_t n,
-                                              const double* __restrict__ ln) {
-  const double iz = 1.0 / suf[0], idn = 1.0 / (double)n;
-  int64_t C = 0;
-  double D = 0.0;
-#pragma unroll
-  for (int v = 1; v <= 16; ++v) {
-    const uint32_t c = src.small(v);
-    if (c) {
-      const double t2 = fabs(fma(suf[v - 1], iz, -(double)(n - C) * idn));
-      C += c;
-      const double t1 = fabs(fma(suf[v], iz, -(double)(n - C) * idn));
-      D = fmax(D, fmax(t1, t2));
-    }
-  }
-  double zprev = suf[16];
-  int64_t vprev = 16;
-  // The table logarithms ln v and ln(v + 1) of each entry are read one entry
-  // ahead (at indexes clamped into the table; values past it take log), so
-  // their latency overlaps the previous entry's arithmetic.
-  constexpr int64_t kLnTop = (int64_t)kH + 1;
-  int64_t v = 0;
-  uint32_t c = 0;
-  bool have = src.next_large(v, c);
-  double lv = ln[v < kLnTop ? v : kLnTop], lv1 = ln[v < kLnTop ? v + 1 : kLnTop];
-  while (have) {
-    int64_t vn = 0;
-    uint32_t cn = 0;
-    const bool haven = src.next_large(vn, cn);
-    const double lvn = ln[vn < kLnTop ? vn : kLnTop];
-    const double lvn1 = ln[vn < kLnTop ? vn + 1 : kLnTop];
-    // survival_next and ln_value with the logarithms read ahead
-    const double q = (double)v + 1.0;
-    const double zv = hurwitz_tail(E, q, v < kLnTop ? lv1 : log(q));
-    const double zv1 =
-        (v - 1 == vprev) ? zprev : zv + pow_neg(E.s, v <= kLnTop ? lv : log((double)v));
-    const double t2 = fabs(fma(zv1, iz, -(double)(n - C) * idn));
-    C += c;
-    const double t1 = fabs(fma(zv, iz, -(double)(n - C) * idn));
-    D = fmax(D, fmax(t1, t2));
-    zprev = zv;
-    vprev = v;
-    v = vn;
-    c = cn;
-    lv = lvn;
-    lv1 = lvn1;
-    have = haven;
-  }
-  return D;
-}
-
+// remaining (value, count) pairs ascending.  Every kernel evaluates the terms
+// by these expressions, in whatever order and for whichever values can reach
+// the maximum, so all give the same D bit for bit.
+//
 // KS distance (eq. 3) under the truncated law on 1..K.  Where its sums go by
-// Euler-Maclaurin (trunc_em), as ks_distance with the survival sums of
+// Euler-Maclaurin (trunc_em), as described, with the survival sums of
 // trunc_tail.  Else (K < 161) F(t) = P(t)/Z with P(t) = sum_{k<=t} k^-a
 // accumulated in ascending k as the distinct values are visited, and Z the K
 // terms from K down.  The terms are |F(v) - C(v)/n| and |F(v-1) - C(v-1)/n|
@@ -278,13 +222,12 @@ __device__ __forceinline__ uint64_t ln_fixed_at(int64_t v, const double* __restr
 // far above the rounding of a bound (a few 2^-53), far below any distance.
 constexpr double kPruneMargin = 1e-12;
 
-// S (with the paper's all-ones rule), alpha_hat (eq. 2) and D (eq. 3), for
-// the pure law (K = 0) or the truncated law on 1..K.
+// S (with the paper's all-ones rule), alpha_hat (eq. 2) and D (eq. 3) for the
+// truncated law on 1..K, by one lane.
 template <class Src>
-__device__ __forceinline__ void finish_replicate(Src& src, const U128& S, int64_t n,
-                                                 uint32_t fl, const double* __restrict__ ln,
-                                                 uint32_t K, double& ahat, double& D,
-                                                 uint32_t& flags) {
+__device__ __forceinline__ void finish_truncated(Src& src, const U128& S, int64_t n, uint32_t fl,
+                                                 const double* __restrict__ ln, uint32_t K,
+                                                 double& ahat, double& D, uint32_t& flags) {
   double Sd;
   if (S.lo == 0 && S.hi == 0) {  // every draw was 1: S := ln 2
     Sd = ln[2];
@@ -292,18 +235,8 @@ __device__ __forceinline__ void finish_replicate(Src& src, const U128& S, int64_
   } else {
     Sd = u128_to_S(S);
   }
-  if (K) {
-    const double a = mle_alpha_trunc(Sd / (double)n, K, ln, &fl);
-    D = ks_distance_trunc(src, a, K, n, ln);
-    ahat = a;
-  } else {
-    const double a = mle_alpha_start(Sd / (double)n, ln, mle_guess_table(ln), &fl);
-    const EmCoef E = em_coef(a);
-    double suf[17];
-    survival_head(E, ln, suf);
-    D = ks_distance(src, E, suf, n, ln);
-    ahat = a;
-  }
+  ahat = mle_alpha_trunc(Sd / (double)n, K, ln, &fl);
+  D = ks_distance_trunc(src, ahat, K, n, ln);
   flags = fl;
 }
 
@@ -735,7 +668,7 @@ static __device__ __noinline__ LaneOut lane_finish_trunc(const LdsU32* column, i
     }
   }
   LaneSrc src{column, more, oc, 17, 0};
-  finish_replicate(src, S, n, fl, ln, K, o.a, o.D, o.flags);
+  finish_truncated(src, S, n, fl, ln, K, o.a, o.D, o.flags);
   return o;
 }
 
@@ -1172,7 +1105,7 @@ __global__ void k_fill_u32(uint32_t* p, int n, uint32_t v) {
 constexpr int kSelSample = 4096;
 constexpr int kSelUnroll = 8;
 constexpr int kSelRegs = 24;  // gathered values per thread of a quantile group held in registers
-static_assert(kHW % 256 == 0 && kHeavyHist % 256 == 0, "build_list reads 256 bins per step");
+static_assert(kHW % 256 == 0, "sum_replicate reads 256 bins per step");
 
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v, int lane) {
 #pragma unroll
@@ -2096,8 +2029,8 @@ hipError_t launch_fit_one(const int64_t* x, int64_t n, const double* ln, int64_t
   return hipGetLastError();
 }
 
-// Scratch of the allocation-free fit (overflow values and compact list of
-// one dataset, the heavy layout), one copy per GPU for the life of the
+// Scratch of the allocation-free fit (a dataset's larger values and counts,
+// fit_view), one copy per GPU for the life of the
 // process.  Host code never passes this name to a kernel: it stands for the
 // host-side shadow; the device address comes from noalloc_scratch_address.
 static __device__ __align__(256) int64_t zpl_noalloc_scratch[kNoAllocStride];

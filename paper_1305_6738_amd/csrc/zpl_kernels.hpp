@@ -40,7 +40,7 @@ constexpr int kLaneCap = 224;
 // many again for the finish.
 constexpr int kLaneScratch = 64 * 2 * kLaneCap;
 // Wave and heavy forms: one replicate per wave at a time, in batches that a
-// wave finishes together (k_batch): histogram of values 1..kHW in LDS, larger
+// wave finishes together (replicate_batch): histogram of values 1..kHW in LDS, larger
 // ones in the wave's global scratch.  Waves per workgroup (one workgroup per
 // compute unit) without and with a lower cutoff: three per SIMD are better than
 // two (heavy tails of 10,000 draws: 5.81 against 6.16 ms; cutoffs, 1,000 draws:
@@ -51,11 +51,11 @@ constexpr int kBatchWavesCut = 12;
 // Waves per workgroup that run escalated replicates (whole replicates of
 // scratch each, so few).
 constexpr int kEscWaves = 4;
-// Dataset fits: histogram of the values 1..kHeavyHist in LDS.
+// Part of a dataset's scratch that does not grow with it (heavy_stride).
 constexpr int kHeavyHist = 1024;
-// Allocation-free fit: the overflow values and the compact list of one
-// dataset of up to kNoAllocMaxN values live in a fixed device array of
-// kNoAllocStride int64 (the heavy layout's stride for that n:
+// Allocation-free fit: the larger values and the counts of one dataset of up to
+// kNoAllocMaxN values (fit_view) live in a fixed device array of
+// kNoAllocStride int64 (heavy_stride of that n:
 // 2 * max(2^20, 2 * (kHeavyHist + 2^20))).
 constexpr int64_t kNoAllocMaxN = (int64_t)1 << 20;
 constexpr int64_t kNoAllocStride = 2 * (2 * ((int64_t)kHeavyHist + kNoAllocMaxN));

@@ -8,8 +8,8 @@
 # The shipped tuning table is loaded so that no autotuning probe launches mix
 # into the statistics.
 #   profile.sh [OUT_DIR] [table_n1000|heavy_tail]
-# table_n1000 (default) profiles k_simulate on the headline slice, heavy_tail
-# profiles k_heavy on the heavy-tail cells.  Output: OUT_DIR (default
+# Profiles k_simulate, on the headline slice (default) or on the heavy-tail
+# cells.  Output: OUT_DIR (default
 # profile_out/ at the root), summary in OUT_DIR/summary.md.
 set -o pipefail
 ROOT="$(cd "$(dirname "$0")/.." && pwd)"
@@ -19,7 +19,7 @@ mkdir -p "$OUT"
 cd /tmp && export TMPDIR=/tmp
 case "$WL" in
   table_n1000) KERNEL=k_simulate; TITLE="the n = 1000 table slice (9 cells x 100,000 replicates)";;
-  heavy_tail) KERNEL=k_heavy; TITLE="the heavy tails (alpha 1.2, 1.3, 1.4, 1.5 x n = 10,000 x 100,000 replicates)";;
+  heavy_tail) KERNEL=k_simulate; TITLE="the heavy tails (alpha 1.2, 1.3, 1.4, 1.5 x n = 10,000 x 100,000 replicates)";;
   *) echo "unknown workload $WL"; exit 2;;
 esac
 ARGS="--workload $WL --steps 5 --warmup 2 --no-extras --no-cpu-baseline --tune paper_1305_6738_amd/tuning/mi355x.json --copy-probe-mib 256"
