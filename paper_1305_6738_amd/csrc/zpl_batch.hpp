@@ -584,6 +584,37 @@ struct DrawOut {
   uint32_t fl, ovn;
   int hi;
 };
+// The first words of the two blocks' uniforms (w0 and w2 of each).  The blocks'
+// rounds are kept side by side: one block is two dependent chains, and three
+// waves need about four to fill the vector ALU's issue slots (an uneven batch,
+// 256 cells: 61.4 against 63.3 ms one block after the other; heavy tails 4.81
+// against 4.88).  The lane form keeps them apart: its slice of 9 cells gains 2 %,
+// but the truncated law's short replicates at K = 20 lose as much.
+__device__ __forceinline__ void philox_pair(uint32_t a0, uint32_t b0, uint32_t c1, uint32_t c2,
+                                            uint32_t k0, uint32_t k1, uint32_t (&w)[4]) {
+  uint32_t a1 = c1, a2 = c2, a3 = 0u, b1 = c1, b2 = c2, b3 = 0u;
+#pragma unroll
+  for (int r = 0; r < 10; ++r) {
+    const uint64_t pa0 = (uint64_t)0xD2511F53u * a0, pb0 = (uint64_t)0xD2511F53u * b0;
+    const uint64_t pa1 = (uint64_t)0xCD9E8D57u * a2, pb1 = (uint64_t)0xCD9E8D57u * b2;
+    a0 = xor3((uint32_t)(pa1 >> 32), a1, k0);
+    b0 = xor3((uint32_t)(pb1 >> 32), b1, k0);
+    a2 = xor3((uint32_t)(pa0 >> 32), a3, k1);
+    b2 = xor3((uint32_t)(pb0 >> 32), b3, k1);
+    a1 = (uint32_t)pa1;
+    b1 = (uint32_t)pb1;
+    a3 = (uint32_t)pa0;
+    b3 = (uint32_t)pb0;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+    __builtin_amdgcn_sched_barrier(0);  // a round of both at a time
+  }
+  w[0] = a0;
+  w[1] = a2;
+  w[2] = b0;
+  w[3] = b2;
+}
+
 // (kKernel only tells the kernels' copies apart: each then has its own tables'
 // LDS addresses as constants.)
 template <bool kCut, int kKernel>
@@ -631,15 +662,9 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
   };
   // the uniforms' first words
   auto gen = [&](uint32_t j0, uint32_t (&ho)[4]) {
-    uint32_t k0 = ck0, k1 = ck1;  // round keys per block (see lane_wave)
+    uint32_t k0 = ck0, k1 = ck1;  // round keys per pair (see lane_draws)
     asm volatile("" : "+s"(k0), "+s"(k1));
-#pragma unroll
-    for (int b = 0; b < kWaveBlocks; ++b) {
-      const Words4 w =
-          philox4x32_10(j0 + 64u * (uint32_t)b + (uint32_t)lane, rep, cs, 0u, k0, k1);
-      ho[2 * b] = w.w0;
-      ho[2 * b + 1] = w.w2;
-    }
+    philox_pair(j0 + (uint32_t)lane, j0 + 64u + (uint32_t)lane, rep, cs, k0, k1, ho);
   };
   const GuideRule rule = guide_rule(sh);
   uint32_t wh[4];

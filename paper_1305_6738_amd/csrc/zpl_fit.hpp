@@ -23,9 +23,10 @@ constexpr int kFitThreads = 512;    // k_fit_block, k_fit_merge
 constexpr int kFitCandThreads = 256;
 constexpr int kFitRun = 4096;       // values sorted in LDS at a time
 // From this size on many workgroups count and sort; at most kFitGroups, of at
-// least kFitChunkMin values each.  One workgroup reads some 50 GB/s: 31,490
-// values take 74 us on the host's way (102 with one wave finishing), while the
-// three launches more of the grid cost 7 us (85,647 values: 52 us).
+// least kFitChunkMin values each.  A fit by one workgroup and by the grid (us,
+// from the device): alpha 2.2, 32,768 values 41 and 49, 65,536 49 and 50,
+// 131,072 65 and 53; alpha 1.7, 55 and 56, 65 and 57, 95 and 64.  Heavier tails
+// cross earlier (more than kFitRun larger values leave LDS in the one).
 constexpr int64_t kFitGridMin = 32768;
 constexpr int64_t kFitChunkMin = 8192;
 constexpr int kFitGroups = 512;
