@@ -85,18 +85,19 @@ __device__ __forceinline__ uint32_t dpp_incl_scan_u32(uint32_t v) {
 // without a cutoff): 1..kHW in the LDS histogram, larger ones in the wave's
 // global scratch.
 //
-// Deferred draws wait in rings and are resolved 64 at a time.  A tail draw makes
-// one proposal per pass; a rejected one waits in the second ring with its next
-// attempt, one that needs a double-double floor in the third, so that a wave
-// runs that long path with all its lanes (at alpha = 1.2 one proposal in 80
-// needs it, which was half of all passes).  The first ring holds the draws'
-// numbers: four stores and a few steps of positions per iteration, where
-// keeping the uniforms and composing their entries took 25 instructions per
-// draw at times (an uneven batch, 256 cells: 66.9 against 69.0 ms); a
-// pass draws its 64 uniforms again.  It holds fewer than 64 entries before an
-// iteration's at most 256.  A pass of it begins with fewer than 64 in each of
-// the others and adds at most 64 in all, a pass of another moves entries or
-// removes them and takes no more than the third has room for: both hold at
+// Deferred draws wait by their number and are resolved 64 at a time: on two
+// stacks that share an array, body draws to search in full and tail draws (by
+// the first word; mixed, each pass ran both paths: heavy tails of 10,000 draws 4.56
+// against 4.81 ms).  A tail draw makes one
+// proposal per pass; a rejected one waits in a ring with its next attempt, one
+// that needs a double-double floor in another, so that a wave runs that long
+// path with all its lanes (at alpha = 1.2 one proposal in 80 needs it, which
+// was half of all passes).  A pass over body draws draws their uniforms again:
+// cheaper than keeping and composing them (an uneven batch, 256 cells: 66.9
+// against 69.0 ms).  The stacks hold fewer than 64 entries each before an
+// iteration's at most 256 in all.  A pass of one begins with fewer than 64 in
+// each ring and adds at most 64 in all, a pass of a ring moves entries or
+// removes them and takes no more than the other has room for: both hold at
 // most 190 together, 128 each.
 constexpr int kBatchRing = 512;
 constexpr int kHardRing = 128;
@@ -540,7 +541,8 @@ struct WaveSlot {
 // as the sampler's last resort is (never reached: it would follow 2^21
 // rejections).
 constexpr uint32_t kTailAttempts = (1u << 21) - 1u;
-constexpr uint32_t kTailTaken = 0, kTailRejected = 1, kTailCapped = 2, kTailHard = 3;
+constexpr uint32_t kTailTaken = 0, kTailRejected = 1, kTailCapped = 2, kTailHard = 3,
+                   kTailFirst = 4;  // (no proposal made yet)
 struct TailTry {
   int64_t X;
   uint32_t code;
@@ -649,8 +651,9 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
   const uint32_t own = bins + 4u * (uint32_t)(kWaveOwn + lane);
   uint32_t xm = 0;  // largest offset drawn (16 bits), values above kHW included
   uint32_t fl = 0, ovn = 0;
-  // first places and lengths of the rings (wave-uniform)
-  uint32_t qh = 0, qn = 0, rh = 0, rn = 0, hh = 0, hn = 0;
+  // lengths of the stacks; first places and lengths of the rings (wave-uniform)
+  uint32_t qn = 0, tn = 0, rh = 0, rn = 0, hh = 0, hn = 0;
+  const uint32_t tailw = threshold_hi(timax);  // larger first words: tail uniforms
   // larger draws (j > kHW) of the lanes that have one, in converged code
   auto put_big = [&](int64_t j) {
     const uint64_t mb = __ballot(j > kHW);
@@ -719,20 +722,32 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
           if (bg && at < room) top[-1 - (int64_t)at] = (int64_t)((z[d] >> 2) + 1u);
           ovn += (uint32_t)__popcll(mb);
         }
-        // deferred draws into the first ring, by their number (their uniform is
-        // drawn again when they are resolved)
-        const uint64_t md = __ballot(deferred(z[d]));
-        const uint32_t pos = place_below(md, qh + qn) & (uint32_t)(kBatchRing - 1);
-        if ((md >> lane) & 1ull)
-          ring[pos] = 2u * (j0 + 64u * (uint32_t)(d >> 1)) + (uint32_t)(d & 1) + 2u * (uint32_t)lane;
-        qn += (uint32_t)__popcll(md);
+        // deferred draws onto the stacks, by their number (their uniform is drawn
+        // again when they are resolved): tail draws from the end
+        const uint64_t md = __ballot(deferred(z[d])), mt = md & __ballot(wh[d] > tailw);
+        if (md != 0ull) {
+          const bool tl = wh[d] > tailw;
+          const uint32_t pos = tl ? (uint32_t)kBatchRing - 1u - place_below(mt, tn)
+                                  : place_below(md & ~mt, qn);
+          if ((md >> lane) & 1ull)
+            ring[pos] = 2u * (j0 + 64u * (uint32_t)(d >> 1)) + (uint32_t)(d & 1) + 2u * (uint32_t)lane;
+          tn += (uint32_t)__popcll(mt);
+          qn += (uint32_t)__popcll(md & ~mt);
+        }
       }
     }
     // resolve 64 entries (one per lane) at a time, at the end the rest
-    while (qn >= 64u || rn >= 64u || hn >= 64u || (!more && (qn | rn | hn) != 0u)) {
+    while (qn >= 64u || tn >= 64u || rn >= 64u || hn >= 64u ||
+           (!more && (qn | tn | rn | hn) != 0u)) {
       // (whole passes first; hard ones last, as they are few and long)
-      const int which = hn >= 64u || rn >= 64u ? (hn > rn ? 2 : 1) : qn != 0u ? 0 : rn != 0u ? 1 : 2;
-      const uint32_t m = which == 0 ? min(qn, 64u)
+      const int which = hn >= 64u || rn >= 64u ? (hn > rn ? 2 : 1)
+                        : tn >= 64u            ? 3
+                        : qn != 0u             ? 0
+                        : tn != 0u             ? 3
+                        : rn != 0u             ? 1
+                                               : 2;
+      const uint32_t m = which == 0   ? min(qn, 64u)
+                         : which == 3 ? min(tn, 64u)
                          : which == 1 ? min(min(rn, 64u), (uint32_t)kHardRing - hn)
                                       : min(min(hn, 64u), (uint32_t)kHardRing - rn);
       wave_sync();
@@ -743,11 +758,13 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
         bool tail = true;
         uint64_t mu = 0;
         if (which == 0) {
-          const uint32_t i = ring[(qh + (uint32_t)lane) & (uint32_t)(kBatchRing - 1)];
+          const uint32_t i = ring[qn - 1u - (uint32_t)lane];
           const Words4 w = philox4x32_10(i >> 1, rep, cs, 0u, ck0, ck1);
           mu = (i & 1u) ? m53(w.w2, w.w3) : m53(w.w0, w.w1);
-          tail = mu > timax;
+          tail = false;
           e = i;
+        } else if (which == 3) {
+          e = ring[(uint32_t)kBatchRing - tn + (uint32_t)lane];
         } else {
           const uint32_t p = ((which == 2 ? hh : rh) + (uint32_t)lane) & (uint32_t)(kHardRing - 1);
           e = which == 2 ? hard[p] : retry[p];
@@ -760,6 +777,9 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
           code = t.code;
           j = t.X - off;
           if (code == kTailCapped) fl |= kFlagTailCapped;
+        } else if (mu > timax) {
+          // its first word is the last threshold's: a tail draw after all
+          code = kTailFirst;
         } else {
           j = (int64_t)lds_search(mu, T, guide, sh);
         }
@@ -770,14 +790,16 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
       } else if (which == 1) {
         rh += m;
         rn -= m;
+      } else if (which == 3) {
+        tn -= m;
       } else {
-        qh += m;
         qn -= m;
       }
-      const uint64_t mr = __ballot(code == kTailRejected || code == kTailCapped);
+      const uint64_t mr =
+          __ballot(code == kTailRejected || code == kTailCapped || code == kTailFirst);
       if (mr != 0ull) {
         const uint32_t p = place_below(mr, rh + rn) & (uint32_t)(kHardRing - 1);
-        if ((mr >> lane) & 1ull) retry[p] = e + (1ull << 32);
+        if ((mr >> lane) & 1ull) retry[p] = code == kTailFirst ? e : e + (1ull << 32);
         rn += (uint32_t)__popcll(mr);
       }
       const uint64_t mh = __ballot(code == kTailHard);
