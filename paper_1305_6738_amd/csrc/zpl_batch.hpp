@@ -341,6 +341,30 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
   if (oc == 0u || fmax(zE * w.iz, (double)oc * idn) <= D - kPruneMargin) return D;
   const bool has_top = __builtin_amdgcn_readlane((int)last, 63) != 0;  // j = kHW was drawn
   const uint32_t nbody = nu - oc;
+  // at most one per lane: every one is compared with all and evaluated, a third
+  // of the tables' work (a call of 83,710 replicates of 34 draws, cutoff 798: 0.91
+  // against 1.04 ms)
+  if (oc <= 64u) {
+    const bool valid = (uint32_t)lane < oc;
+    const uint64_t j = valid ? (uint64_t)ov[-1 - (int64_t)lane] : 0ull;
+    uint32_t lt = 0, eq = 0;
+    bool pres = j == (uint64_t)kHW + 1u && has_top;
+    for (int k = 0; k < (int)oc; ++k) {
+      const uint64_t x =
+          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)j, k) |
+          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(j >> 32), k) << 32;
+      lt += x < j ? 1u : 0u;
+      eq += x == j ? 1u : 0u;
+      pres = pres || x + 1u == j;
+    }
+    if (valid) {
+      const int64_t v = off + (int64_t)j;
+      const double zv = w.survival(v, ln);
+      const double zv1 = pres ? w.survival(v - 1, ln) : zv + w.point(v, ln);
+      terms(zv, zv1, nbody + lt, eq);
+    }
+    return dpp_max_f64(D);
+  }
   LdsU8* many = (LdsU8*)(tab + kHW);  // counts of the bins in reach, up to kManyDraws
   int depth = 0, next = 0;
   Bins B{(uint64_t)kHW, -1};
