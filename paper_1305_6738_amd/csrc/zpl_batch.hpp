@@ -126,7 +126,7 @@ constexpr int kBuckets = (63 - 10) << kBucketBits;  // octaves 10..62
 static_assert(kHW == 1024 && kBuckets <= kHW, "the bin table takes the histogram's place");
 // Draws gathered per pass (the ring's room, less the draws just below a bin),
 // and the count from which a bin is split instead.
-constexpr uint32_t kGather = 256;
+constexpr uint32_t kGather = 255;  // (places in bytes)
 constexpr uint32_t kManyDraws = 255;
 // A bin in reach keeps the number of larger draws below it (n <= 2^31), with
 // the mark for a draw just below its first value.
@@ -245,12 +245,14 @@ struct CountView {
 // those of j = 1..hi (hi a multiple of 256, zero above); ov[-1 - p], p < oc:
 // the draws above kHW, in any order.  tab, list, level: the wave's LDS
 // (kHW + 256 words, kBatchRing and kHardRing entries).
-template <int kLaw>
+// kLarge: there can be such draws (without them the function saves fewer
+// registers per call).
+template <int kLaw, bool kLarge = true>
 static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_, uint32_t K_,
                                               const uint32_t* counts, bool wide_, int hi_,
                                               const int64_t* ov_, uint32_t oc_, int64_t n_,
                                               double D0, double z16, LdsU32* tab, LdsU64* list,
-                                              LdsU64* level, const double* ln_) {
+                                              LdsU32* ends, LdsU64* level, const double* ln_) {
   // every argument is the wave's
   const int lane = lane_id();
   const uint32_t nu = (uint32_t)uniform64(n_);
@@ -336,6 +338,7 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
     }
     D = dpp_max_f64(D);
   }
+  if constexpr (!kLarge) return D;
   // 2. the larger draws: none can matter when their whole mass is below D
   const double zE = readlane_f64(zr, 63);
   if (oc == 0u || fmax(zE * w.iz, (double)oc * idn) <= D - kPruneMargin) return D;
@@ -473,7 +476,34 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
         const int b = B.of(j);
         return b >= wlo && b < whi && tab[b] != kNoBin && many[b] < kManyDraws;
       };
-      uint32_t m = 0;  // wave-uniform
+      // The list is grouped by bin, so that a draw is compared with its bin's
+      // only: each bin's first place, then (as its draws are placed) its end,
+      // in bytes.
+      uint32_t m = 0;  // draws of the window (wave-uniform)
+      {
+        auto count = [&](int b) {
+          const uint32_t n = many[b];
+          return b >= wlo && b < whi && tab[b] != kNoBin && n < kManyDraws ? n : 0u;
+        };
+        // (counted twice: kept, they would take registers from every call)
+        uint32_t cs16 = 0;
+#pragma unroll 1
+        for (int k = 0; k < 16; ++k) cs16 += count(16 * lane + k);
+        const uint32_t inc = dpp_incl_scan_u32(cs16);
+        m = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        uint32_t at = inc - cs16;
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {
+          uint32_t places = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            places |= at << (8 * i);
+            at += count(16 * lane + 4 * k + i);
+          }
+          ends[4 * lane + k] = places;
+        }
+        wave_sync();
+      }
       for (uint32_t p0 = 0; p0 < oc; p0 += 64u) {
         const uint32_t p = p0 + (uint32_t)lane;
         bool take = false;
@@ -484,11 +514,12 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
           if (wanted(j + 1u) && (j < B.lo || B.of(j) != B.of(j + 1u)))
             lds_or(&tab[B.of(j + 1u)], kBelowDrawn);
         }
-        const uint64_t mt = __ballot(take);
-        if (mt != 0ull) {
-          const uint32_t pos = m + (uint32_t)__popcll(mt & below);
-          if (take) list[pos] = j;  // at most kGather of them
-          m += (uint32_t)__popcll(mt);
+        if (take) {
+          const int b = B.of(j);
+          const uint32_t old = __hip_atomic_fetch_add(&ends[b >> 2], 1u << (8 * (b & 3)),
+                                                      __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+          list[(old >> (8 * (b & 3))) & 0xffu] = j;  // below m, at most kGather
         }
       }
       wave_sync();
@@ -496,14 +527,16 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
         const uint32_t i = i0 + (uint32_t)lane;
         const uint64_t j = i < m ? list[i] : 0ull;
         const bool valid = i < m;
-        const uint32_t entry = valid ? tab[B.of(j)] : 0u;
-        const uint64_t jlo = valid ? B.start(B.of(j)) : 0ull;
+        const int bj = valid ? B.of(j) : 0;
+        const uint32_t entry = valid ? tab[bj] : 0u;
+        const uint64_t jlo = valid ? B.start(bj) : 0ull;
+        const uint32_t k1 = valid ? (ends[bj >> 2] >> (8 * (bj & 3))) & 0xffu : 0u;
         uint32_t lt = 0, eq = 0;
         uint32_t pres = j == (uint64_t)kHW + 1u ? (has_top ? 1u : 0u)
                                                  : (j == jlo ? entry >> 31 : 0u);
-        for (uint32_t k = 0; k < m; ++k) {
+        for (uint32_t k = valid ? k1 - many[bj] : 0u; k < k1; ++k) {
           const uint64_t x = list[k];
-          lt += (x >= jlo && x < j) ? 1u : 0u;
+          lt += x < j ? 1u : 0u;
           eq += x == j ? 1u : 0u;
           pres |= x + 1u == j ? 1u : 0u;
         }
@@ -1120,14 +1153,15 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
                   reinterpret_cast<const uint32_t*>(counts + i * cw), wide,
                   __builtin_amdgcn_readlane((int)hib, i), scratch + tp,
                   (uint32_t)__builtin_amdgcn_readlane((int)oc, i), n, readlane_f64(h.D, i),
-                  readlane_f64(h.z16, i), (LdsU32*)L->hist, (LdsU64*)L->ring, (LdsU64*)L->hard,
-                  ln);
+                  readlane_f64(h.z16, i), (LdsU32*)L->hist, (LdsU64*)L->ring, (LdsU32*)L->retry,
+                  (LdsU64*)L->hard, ln);
       };
       double Di;
       if constexpr (kCut)
         Di = rest([](auto... x) { return ks_rest<kCutoff>(x...); });
       else if (c.K)
-        Di = rest([](auto... x) { return ks_rest<kTrunc>(x...); });
+        Di = c.K <= (uint32_t)kHW ? rest([](auto... x) { return ks_rest<kTrunc, false>(x...); })
+                                  : rest([](auto... x) { return ks_rest<kTrunc>(x...); });
       else
         Di = rest([](auto... x) { return ks_rest<kPure>(x...); });
       if (lane == i) h.D = Di;
