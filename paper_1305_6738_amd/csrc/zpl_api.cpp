@@ -24,6 +24,7 @@
 #include "zpl_kernels.hpp"
 #include "zpl_launch.hpp"
 #include "zpl_math.hpp"
+#include "zpl_scratch.hpp"
 
 using namespace zpl;
 
@@ -78,9 +79,6 @@ constexpr int64_t kMaxXmin = (int64_t)1 << 40;
 constexpr int64_t kFitBlockMin = 2048;
 // Host datasets up to this many bytes go through pinned staging.
 constexpr size_t kPinStageMax = (size_t)64 << 20;
-// int64 of scratch that each wavefront's worth of a lane- or wave-form unit
-// brings in (its lane-form slots are taken from it).
-constexpr int64_t kFormScratch = 30912;
 // Escalation slots for heavy-form replicates.
 constexpr int64_t kHeavyEsc = 4096;
 
@@ -656,14 +654,6 @@ void plain_unit_order(Plan& P) {
   }
 }
 
-int64_t heavy_stride(int64_t max_n) {
-  int64_t p2 = 1;
-  while (p2 < max_n) p2 <<= 1;
-  int64_t half = std::max<int64_t>(p2, 2 * ((int64_t)kHeavyHist + max_n));
-  half = (half + 1) & ~(int64_t)1;
-  return 2 * half;
-}
-
 // Byte offsets of a simulation call's parts in the plan and ctr buffers.
 // plan: cells | units | heavy units | q_num | q_den, each part 256-byte
 // aligned.  ctr (32-bit words): the work queues (nc + 8, rounded up to even),
@@ -726,31 +716,27 @@ zpl_status prepare(zpl_ctx* c, const Plan& P, int n_q, bool need_dbuf, Launch& L
   // Scratch of the wave and heavy forms.  The least a wave of a batch kernel
   // works with is one replicate (records, counts, its room), an escalated one
   // needs all of its draws; the more there is, the more replicates a wave
-  // finishes together.  Its size follows the forms: 2.9 MiB for each workgroup
-  // of kBlock lane- and wave-form replicates less the lane form's slots, and
-  // four areas of a sorted replicate's size (heavy_stride) for each 8
-  // heavy-form ones, up to two per compute unit and a quarter of the budget.
-  const int64_t hstride = heavy_stride(P.max_n);
-  int64_t hg = std::min<int64_t>(P.heavy8 + 64, (int64_t)c->n_cu * 2);
-  while (hg > 1 && (uint64_t)hg * 4 * hstride * 8 > c->budget / 4) hg /= 2;
-  const int64_t sim_wgs = std::max<int64_t>(1, std::min<int64_t>(P.sim_units, c->n_cu));
-  const int64_t area = hg * 4 * hstride + sim_wgs * kWaves * kFormScratch -
-                       slots - (esc_R - P.lw_R);
+  // finishes together.
+  const int64_t area = batch_area(P.heavy8, P.sim_units, P.max_n, slots + (esc_R - P.lw_R),
+                                  c->budget, c->n_cu);
   ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)area));
-  const int64_t fixed = 64 * (kWaveSlotBytes / 8) + kHW / 2;
-  auto share = [&](int units, int waves, int64_t room, int& grid, int64_t& stride) {
-    int64_t g = std::min<int64_t>(units, c->n_cu);
-    while (g > 1 && area / (g * waves) < fixed + room) g = (g + 1) / 2;
-    grid = (int)g;
-    stride = g > 0 ? area / (g * waves) & ~(int64_t)31 : 0;
+  auto share = [&](int64_t units, int waves, int64_t room, int& grid, int64_t& stride) {
+    const Share sh = share_scratch(area, units, waves, room, c->n_cu);
+    grid = sh.grid;
+    stride = sh.stride;
+    if (units > 0 && grid == 0)
+      return fail(ZPL_ENOMEM, "scratch of %lld words does not hold replicates of %lld values",
+                  (long long)area, (long long)room);
+    return ZPL_OK;
   };
-  share(P.n_bpure, kBatchWaves, P.max_room, L.sim.batch_wgs, L.sim.stride);
+  ZPL_TRY(share(P.n_bpure, kBatchWaves, P.max_room, L.sim.batch_wgs, L.sim.stride));
   L.sim.grid = std::min(L.sim.lane_wgs + L.sim.batch_wgs, c->n_cu);
-  share(P.n_bcut, kBatchWavesCut, P.max_room, L.cut_grid, L.cstride);
+  ZPL_TRY(share(P.n_bcut, kBatchWavesCut, P.max_room, L.cut_grid, L.cstride));
+  // Replicates that may escalate: those of the lane form with more than kLaneCap
+  // draws, and those whose room is not all of their draws.
   L.esc_grid = 0;
-  // (a replicate of at most kLaneCap draws cannot leave its lane)
   if (P.lane_n > kLaneCap || P.bounded)
-    share(64, kEscWaves, P.max_n, L.esc_grid, L.estride);
+    ZPL_TRY(share(64, kEscWaves, P.max_n, L.esc_grid, L.estride));
   if (need_dbuf) ZPL_TRY(ensure(c, c->dbuf, sizeof(double) * (size_t)P.total_R));
   // bracket gather: at most ~12% of a cell's replicates fall in a bracket
   int64_t maxR = 1;
