@@ -128,7 +128,7 @@ struct zpl_ctx {
   // work queues, escalation count and error word, cleared by the table
   // kernel, then the quantile results, so that error word and quantiles come
   // back with one copy (layout: PlanLayout)
-  DevBuf plan, ctr, tables, guides, esc, slots, heavy, dbuf, gather, fit_x,
+  DevBuf plan, ctr, tables, guides, esc, heavy, dbuf, gather, fit_x,
       fit_ptrs, fit_ns, fit_out, fit_st, count, boot_d, scan;
   // pinned host staging
   void* pin = nullptr;
@@ -687,6 +687,7 @@ struct Launch {
   SimGrid sim = {0, 0, 0, 0, 0};
   int cut_grid = 0, esc_grid = 0;      // workgroups of the cutoff and escalation kernels
   int64_t cstride = 0, estride = 0;    // int64 of scratch per wave of each
+  int64_t slots = 0;                   // int64 of the lane form's slots, before the waves' scratch
   int64_t gcap = 0;
   int64_t maxR = 1;
   PlanLayout lay;
@@ -712,14 +713,17 @@ zpl_status prepare(zpl_ctx* c, const Plan& P, int n_q, bool need_dbuf, Launch& L
   L.sim.lane_wgs = (int)std::min<int64_t>((int64_t)P.units.size(), (int64_t)c->n_cu);
   L.sim.lane_waves = P.lane_block / 64;
   const int64_t slots = (int64_t)L.sim.lane_wgs * L.sim.lane_waves * kLaneScratch;
-  ZPL_TRY(ensure(c, c->slots, sizeof(int64_t) * (size_t)slots));
   // Scratch of the wave and heavy forms.  The least a wave of a batch kernel
   // works with is one replicate (records, counts, its room), an escalated one
   // needs all of its draws; the more there is, the more replicates a wave
-  // finishes together.
-  const int64_t area = batch_area(P.heavy8, P.sim_units, P.max_n, slots + (esc_R - P.lw_R),
-                                  c->budget, c->n_cu);
-  ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)area));
+  // finishes together.  The lane form's slots lie before it in the same buffer:
+  // calls of either form follow one another within a budget that holds the
+  // larger, where two grow-only buffers would need both.
+  const int64_t total = scratch_words(P.heavy8, P.sim_units, P.max_n, esc_R - P.lw_R, c->budget,
+                                      c->n_cu);
+  ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)total));
+  L.slots = slots;
+  const int64_t area = total - slots;
   auto share = [&](int64_t units, int waves, int64_t room, int& grid, int64_t& stride) {
     const Share sh = share_scratch(area, units, waves, room, c->n_cu);
     grid = sh.grid;
@@ -773,11 +777,12 @@ zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, O
   HIP_TRY(mark(1));
   const Unit* units = (const Unit*)(plan + L.lay.units);
   const Unit* hunits = (const Unit*)(plan + L.lay.hunits);
+  int64_t* slots = (int64_t*)c->heavy.p;
+  int64_t* scratch = slots + L.slots;
   auto simulate = [&](const SimGrid& g, const Unit* u, int nu, uint32_t* queue, int nb) {
     return launch_simulate(g, dcells, (const double*)c->tables.p, (const uint16_t*)c->guides.p,
                            c->ln, u, nu, hunits, nb, queue, queues + 2, out,
-                           (uint64_t*)c->esc.p, escc, c->esc_cap, (int64_t*)c->slots.p,
-                           (int64_t*)c->heavy.p, err, s);
+                           (uint64_t*)c->esc.p, escc, c->esc_cap, slots, scratch, err, s);
   };
   if (launch == ZPL_LAUNCH_PLAIN) {  // the lane-form cells one by one, then the others
     for (int i = 0; i < nc; ++i) {
@@ -797,11 +802,10 @@ zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, O
   HIP_TRY(launch_cutoff(L.cut_grid, dcells, (const double*)c->tables.p,
                         (const uint16_t*)c->guides.p, c->ln, hunits + P.n_bpure, P.n_bcut,
                         queues + 3, out, (uint64_t*)c->esc.p, escc, c->esc_cap,
-                        (int64_t*)c->heavy.p, L.cstride, err, s));
+                        scratch, L.cstride, err, s));
   HIP_TRY(launch_escalated(L.esc_grid, dcells, (const double*)c->tables.p,
                            (const uint16_t*)c->guides.p, c->ln, queues + 4, out,
-                           (uint64_t*)c->esc.p, escc, c->esc_cap, (int64_t*)c->heavy.p, L.estride,
-                           err, s));
+                           (uint64_t*)c->esc.p, escc, c->esc_cap, scratch, L.estride, err, s));
   HIP_TRY(mark(3));
   if (n_q > 0 && Dsel)
     HIP_TRY(launch_select(Dsel, dcells, nc, n_q, (const uint32_t*)(plan + L.lay.qnum),
@@ -1555,7 +1559,7 @@ void zpl_destroy(zpl_ctx* c) {
   (void)hipDeviceSynchronize();
   if (c->graph_valid) (void)hipGraphExecDestroy(c->graph_exec);
   DevBuf* bufs[] = {&c->plan,   &c->ctr,      &c->tables, &c->guides, &c->esc,
-                    &c->slots, &c->heavy,  &c->gather,
+                    &c->heavy,  &c->gather,
                     &c->dbuf,   &c->fit_x,    &c->fit_ptrs, &c->fit_ns, &c->fit_out,
                     &c->fit_st, &c->count,    &c->boot_d, &c->scan};
   for (DevBuf* b : bufs)

@@ -39,20 +39,21 @@ inline Share share_scratch(int64_t area, int64_t units, int waves, int64_t room,
   return Share{(int)g, stride(g)};
 }
 
-// int64 of scratch for a call's wave- and heavy-form replicates.  It follows the
-// forms: kFormScratch for each wave of a workgroup per kBlock lane- and wave-form
-// replicates (2.8 MiB a workgroup; sim_units of them), and four areas of a sorted
-// replicate's size for each 8 heavy-form ones (heavy8), up to two per compute
-// unit and a quarter of the budget; less what the lane form's slots and the
-// escalation list take.
+// int64 of scratch for a call's replicates: the lane form's slots, then what the
+// waves of the other forms share.  It follows the forms: kFormScratch for each
+// wave of a workgroup per kBlock lane- and wave-form replicates (2.8 MiB a
+// workgroup; sim_units of them), and four areas of a sorted replicate's size for
+// each 8 heavy-form ones (heavy8), up to two per compute unit and a quarter of
+// the budget; less what the escalation list takes for them (esc).
 constexpr int64_t kFormScratch = 30912;
-inline int64_t batch_area(int64_t heavy8, int64_t sim_units, int64_t max_n, int64_t taken,
-                          uint64_t budget, int n_cu) {
+static_assert(kLaneScratch <= kFormScratch, "a lane unit's slots are part of what it brings in");
+inline int64_t scratch_words(int64_t heavy8, int64_t sim_units, int64_t max_n, int64_t esc,
+                             uint64_t budget, int n_cu) {
   const int64_t hstride = heavy_stride(max_n);
   int64_t hg = std::min<int64_t>(heavy8 + 64, (int64_t)n_cu * 2);
   while (hg > 1 && (uint64_t)hg * 4 * hstride * 8 > budget / 4) hg /= 2;
   const int64_t sim_wgs = std::max<int64_t>(1, std::min<int64_t>(sim_units, n_cu));
-  return hg * 4 * hstride + sim_wgs * kWaves * kFormScratch - taken;
+  return hg * 4 * hstride + sim_wgs * kWaves * kFormScratch - esc;
 }
 
 }  // namespace zpl

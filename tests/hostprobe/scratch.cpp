@@ -4,9 +4,9 @@
 using namespace zpl;
 
 extern "C" {
-int64_t sc_area(int64_t heavy8, int64_t sim_units, int64_t max_n, int64_t taken, uint64_t budget,
+int64_t sc_area(int64_t heavy8, int64_t sim_units, int64_t max_n, int64_t esc, uint64_t budget,
                 int n_cu) {
-  return batch_area(heavy8, sim_units, max_n, taken, budget, n_cu);
+  return scratch_words(heavy8, sim_units, max_n, esc, budget, n_cu);
 }
 void sc_share(int64_t area, int64_t units, int waves, int64_t room, int n_cu, int64_t* out) {
   const Share s = share_scratch(area, units, waves, room, n_cu);
