@@ -315,7 +315,8 @@ struct Plan {
   std::vector<Unit> hunits;
   int n_bpure = 0, n_bcut = 0;  // lengths of the two parts
   int64_t batch_R = 0;          // their replicates
-  int64_t max_room = 0;         // largest DevCell::room among their cells
+  int64_t max_room[2] = {0, 0};  // largest DevCell::room of each part's cells
+  int unit_waves[2] = {1, 1};    // waves that the largest unit of each part gives work
   bool bounded = false;         // some cell's room is less than its n
   int64_t lane_n = 0;    // most draws of a lane-form replicate
   // what the form of each cell alone sizes the scratch by: units of kBlock
@@ -458,7 +459,8 @@ void plan_batch(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) 
     if (d.mode == kModeHeavy) P.heavy8 += (d.R + 7) / 8;
     const int64_t room = batch_room(d);
     d.room = (uint32_t)room;
-    P.max_room = std::max(P.max_room, room);
+    int64_t& most = P.max_room[d.xmin > 1];
+    most = std::max(most, room);
     P.bounded = P.bounded || room < d.n;
     P.batch_R += d.R;
     work += cost(d) * (double)d.R;
@@ -472,10 +474,12 @@ void plan_batch(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) 
       const int64_t per_wave =
           std::min<int64_t>(64, std::max<int64_t>(1, (int64_t)(unit_work / cost(d) / waves)));
       int64_t step = per_wave * waves;
-      // too few replicates for every wave of the device: spread over the
-      // compute units, so that the waves of a SIMD do not share its issue slots
+      // too few replicates for every wave of the device (counting the call's work
+      // in replicates of this size): spread over the compute units, so that the
+      // waves of a SIMD do not share its issue slots
       if (per_wave == 1)
-        step = std::min<int64_t>(waves, std::max<int64_t>(1, (P.batch_R + n_cu - 1) / n_cu));
+        step = std::min<int64_t>(waves, std::max<int64_t>(1, (int64_t)std::ceil(work / cost(d) / n_cu)));
+      P.unit_waves[cut] = std::max(P.unit_waves[cut], (int)std::min<int64_t>(step, waves));
       for (int64_t r = 0; r < d.R; r += step) {
         Unit u;
         u.cell = i;
@@ -684,17 +688,17 @@ PlanLayout plan_layout(const Plan& P, int n_q) {
 }
 
 struct Launch {
-  SimGrid sim = {0, 0, 0, 0, 0};
-  int cut_grid = 0, esc_grid = 0;      // workgroups of the cutoff and escalation kernels
-  int64_t cstride = 0, estride = 0;    // int64 of scratch per wave of each
+  SimGrid sim = {};
+  Share cut = {0, 0, 0}, esc = {0, 0, 0};  // of the cutoff and escalation kernels
   int64_t slots = 0;                   // int64 of the lane form's slots, before the waves' scratch
   int64_t gcap = 0;
   int64_t maxR = 1;
   PlanLayout lay;
 };
 
-// Grows every scratch buffer the plan needs.
-zpl_status prepare(zpl_ctx* c, const Plan& P, int n_q, bool need_dbuf, Launch& L) {
+// Grows every scratch buffer the plan needs, and shares it among the waves (where
+// their replicates differ much in size, the units of the larger come first).
+zpl_status prepare(zpl_ctx* c, Plan& P, int n_q, bool need_dbuf, Launch& L) {
   const int nc = (int)P.cells.size();
   L.lay = plan_layout(P, n_q);
   ZPL_TRY(ensure(c, c->plan, L.lay.plan_bytes));
@@ -724,23 +728,43 @@ zpl_status prepare(zpl_ctx* c, const Plan& P, int n_q, bool need_dbuf, Launch& L
   ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)total));
   L.slots = slots;
   const int64_t area = total - slots;
-  auto share = [&](int64_t units, int waves, int64_t room, int& grid, int64_t& stride) {
-    const Share sh = share_scratch(area, units, waves, room, c->n_cu);
-    grid = sh.grid;
-    stride = sh.stride;
-    if (units > 0 && grid == 0)
+  auto share = [&](int64_t words, int64_t units, int waves, int64_t room, Share& sh) {
+    sh = share_scratch(words, units, waves, room, c->n_cu);
+    if (units > 0 && sh.grid == 0)
       return fail(ZPL_ENOMEM, "scratch of %lld words does not hold replicates of %lld values",
-                  (long long)area, (long long)room);
+                  (long long)words, (long long)room);
     return ZPL_OK;
   };
-  ZPL_TRY(share(P.n_bpure, kBatchWaves, P.max_room, L.sim.batch_wgs, L.sim.stride));
+  // the wave and heavy forms, in two parts where the rooms differ that much
+  const int waves = P.unit_waves[0];
+  int64_t big_words = 0, small_room = P.max_room[0], limit = 0;
+  if (split_batch(area, P.n_bpure, waves, P.max_room[0], c->n_cu, limit)) {
+    auto is_big = [&](const Unit& u) { return (int64_t)P.cells[u.cell].room > limit; };
+    const auto end = P.hunits.begin() + P.n_bpure;
+    const int n = (int)(std::stable_partition(P.hunits.begin(), end, is_big) - P.hunits.begin());
+    if (n < P.n_bpure) {
+      small_room = 0;
+      for (int k = n; k < P.n_bpure; ++k)
+        small_room = std::max<int64_t>(small_room, P.cells[P.hunits[k].cell].room);
+      big_words = area - area / 4;
+      L.sim.n_big = n;
+    }
+  }
+  Share big, rest;
+  ZPL_TRY(share(big_words, L.sim.n_big, waves, P.max_room[0], big));
+  ZPL_TRY(share(area - big_words, std::min(P.n_bpure, c->n_cu) - big.grid, waves, small_room, rest));
+  L.sim.big_wgs = big.grid;
+  L.sim.big_waves = big.waves;
+  L.sim.big_stride = big.stride;
+  L.sim.big_area = big_words;
+  L.sim.waves = rest.waves;
+  L.sim.stride = rest.stride;
+  L.sim.batch_wgs = big.grid + rest.grid;
   L.sim.grid = std::min(L.sim.lane_wgs + L.sim.batch_wgs, c->n_cu);
-  ZPL_TRY(share(P.n_bcut, kBatchWavesCut, P.max_room, L.cut_grid, L.cstride));
+  ZPL_TRY(share(area, P.n_bcut, P.unit_waves[1], P.max_room[1], L.cut));
   // Replicates that may escalate: those of the lane form with more than kLaneCap
   // draws, and those whose room is not all of their draws.
-  L.esc_grid = 0;
-  if (P.lane_n > kLaneCap || P.bounded)
-    ZPL_TRY(share(64, kEscWaves, P.max_n, L.esc_grid, L.estride));
+  if (P.lane_n > kLaneCap || P.bounded) ZPL_TRY(share(area, 64, kEscWaves, P.max_n, L.esc));
   if (need_dbuf) ZPL_TRY(ensure(c, c->dbuf, sizeof(double) * (size_t)P.total_R));
   // bracket gather: at most ~12% of a cell's replicates fall in a bracket
   int64_t maxR = 1;
@@ -781,7 +805,7 @@ zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, O
   int64_t* scratch = slots + L.slots;
   auto simulate = [&](const SimGrid& g, const Unit* u, int nu, uint32_t* queue, int nb) {
     return launch_simulate(g, dcells, (const double*)c->tables.p, (const uint16_t*)c->guides.p,
-                           c->ln, u, nu, hunits, nb, queue, queues + 2, out,
+                           c->ln, u, nu, hunits, nb, queue, queues + 2, queues + 5, out,
                            (uint64_t*)c->esc.p, escc, c->esc_cap, slots, scratch, err, s);
   };
   if (launch == ZPL_LAUNCH_PLAIN) {  // the lane-form cells one by one, then the others
@@ -789,23 +813,29 @@ zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, O
       const int b = P.cell_unit_begin[i], e = P.cell_unit_end[i];
       if (e <= b) continue;
       const int grid = std::min(e - b, L.sim.lane_wgs);
-      HIP_TRY(simulate(SimGrid{grid, grid, L.sim.lane_waves, 0, 0}, units + b, e - b,
-                       queues + 8 + i, 0));
+      SimGrid g = {};
+      g.grid = g.lane_wgs = grid;
+      g.lane_waves = L.sim.lane_waves;
+      HIP_TRY(simulate(g, units + b, e - b, queues + 8 + i, 0));
     }
-    if (P.n_bpure > 0)
-      HIP_TRY(simulate(SimGrid{L.sim.batch_wgs, 0, 0, L.sim.batch_wgs, L.sim.stride}, units, 0,
-                       queues, P.n_bpure));
+    if (P.n_bpure > 0) {
+      SimGrid g = L.sim;
+      g.grid = g.batch_wgs;
+      g.lane_wgs = 0;
+      HIP_TRY(simulate(g, units, 0, queues, P.n_bpure));
+    }
   } else {
     HIP_TRY(simulate(L.sim, units, (int)P.units.size(), queues, P.n_bpure));
   }
   HIP_TRY(mark(2));
-  HIP_TRY(launch_cutoff(L.cut_grid, dcells, (const double*)c->tables.p,
+  HIP_TRY(launch_cutoff(L.cut.grid, dcells, (const double*)c->tables.p,
                         (const uint16_t*)c->guides.p, c->ln, hunits + P.n_bpure, P.n_bcut,
                         queues + 3, out, (uint64_t*)c->esc.p, escc, c->esc_cap,
-                        scratch, L.cstride, err, s));
-  HIP_TRY(launch_escalated(L.esc_grid, dcells, (const double*)c->tables.p,
+                        scratch, L.cut.waves, L.cut.stride, err, s));
+  HIP_TRY(launch_escalated(L.esc.grid, dcells, (const double*)c->tables.p,
                            (const uint16_t*)c->guides.p, c->ln, queues + 4, out,
-                           (uint64_t*)c->esc.p, escc, c->esc_cap, scratch, L.estride, err, s));
+                           (uint64_t*)c->esc.p, escc, c->esc_cap, scratch, L.esc.waves,
+                           L.esc.stride, err, s));
   HIP_TRY(mark(3));
   if (n_q > 0 && Dsel)
     HIP_TRY(launch_select(Dsel, dcells, nc, n_q, (const uint32_t*)(plan + L.lay.qnum),

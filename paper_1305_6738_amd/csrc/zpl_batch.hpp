@@ -1226,7 +1226,7 @@ __device__ __forceinline__ bool next_unit(Lds& L, uint32_t* queue, const Unit* _
 // Persistent simulation kernel: workgroups pull units from two queues, first
 // those of the lane form (up to kBlock replicates of a cell, one per lane;
 // workgroups 0 .. lane_wgs - 1), then those of the wave and heavy forms (each
-// wave a contiguous share; the last batch_wgs workgroups).  Both kinds in one
+// wave a contiguous share; the last batch_wgs workgroups, see SimGrid).  Both kinds in one
 // launch: one after the other each would end on a device that runs dry.
 // Three waves per SIMD: the twelve waves' LDS regions and the shared table
 // fit one workgroup per compute unit, and the register budget is 168 per lane.
@@ -1235,8 +1235,9 @@ __global__ __launch_bounds__(kBlock, 3) void k_simulate(
     SimGrid g, const DevCell* __restrict__ cells, const double* __restrict__ tables,
     const uint16_t* __restrict__ guides, const double* __restrict__ ln,
     const Unit* __restrict__ lane_units, int n_lane, const Unit* __restrict__ batch_units,
-    int n_batch, uint32_t* lane_queue, uint32_t* batch_queue, Outputs out, uint64_t* esc_list,
-    uint32_t* esc_count, uint32_t esc_cap, int64_t* slots, int64_t* scratch, uint32_t* err) {
+    int n_batch, uint32_t* lane_queue, uint32_t* batch_queue, uint32_t* big_queue, Outputs out,
+    uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* slots, int64_t* scratch,
+    uint32_t* err) {
   __shared__ KernelLds<SimRegion, kWaves> L;
   const int wave = (int)threadIdx.x >> 6;
   const int lane = lane_id();
@@ -1254,18 +1255,27 @@ __global__ __launch_bounds__(kBlock, 3) void k_simulate(
     }
   }
   const int b = (int)blockIdx.x - (g.grid - g.batch_wgs);
-  if (b >= 0) {
-    int64_t* mine = scratch + ((int64_t)b * kBatchWaves + wave) * g.stride;
-    while (next_unit(L, batch_queue, batch_units, n_batch, cells, tables, guides, loaded, un,
-                     kBlock)) {
-      const int share = (un.count + kBatchWaves - 1) / kBatchWaves;
-      const int first = wave * share;
-      if (first < un.count)
-        replicate_batch<false, 0>(cells, un.cell, un.r0 + first,
-                               un.count - first < share ? un.count - first : share,
-                               &L.w[wave].batch, mine, g.stride, lane, L.T, L.guide, ln, out,
-                               esc_list, esc_count, esc_cap, err);
+  if (b < 0) return;
+  // workgroups with scratch for the longest replicates take those first
+  bool big = b < g.big_wgs;
+  const int waves = big ? g.big_waves : g.waves;
+  const int64_t stride = big ? g.big_stride : g.stride;
+  int64_t* mine = scratch + (big ? 0 : g.big_area) +
+                  ((int64_t)(big ? b : b - g.big_wgs) * waves + wave) * stride;
+  for (;;) {
+    if (!next_unit(L, big ? big_queue : batch_queue, big ? batch_units : batch_units + g.n_big,
+                   big ? g.n_big : n_batch - g.n_big, cells, tables, guides, loaded, un, kBlock)) {
+      if (!big) return;
+      big = false;
+      continue;
     }
+    const int share = (un.count + waves - 1) / waves;
+    const int first = wave * share;
+    if (wave < waves && first < un.count)
+      replicate_batch<false, 0>(cells, un.cell, un.r0 + first,
+                             un.count - first < share ? un.count - first : share,
+                             &L.w[wave].batch, mine, stride, lane, L.T, L.guide, ln, out,
+                             esc_list, esc_count, esc_cap, err);
   }
 }
 
@@ -1274,19 +1284,19 @@ __global__ __launch_bounds__(64 * kBatchWavesCut, kBatchWavesCut / 4) void k_cut
     const DevCell* __restrict__ cells, const double* __restrict__ tables,
     const uint16_t* __restrict__ guides, const double* __restrict__ ln,
     const Unit* __restrict__ units, int n_units, uint32_t* queue, Outputs out,
-    uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* scratch, int64_t stride,
-    uint32_t* err) {
+    uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* scratch, int waves,
+    int64_t stride, uint32_t* err) {
   __shared__ KernelLds<BatchLds, kBatchWavesCut> L;
   const int wave = (int)threadIdx.x >> 6;
   const int lane = lane_id();
-  int64_t* mine = scratch + ((int64_t)blockIdx.x * kBatchWavesCut + wave) * stride;
+  int64_t* mine = scratch + ((int64_t)blockIdx.x * waves + wave) * stride;
   int loaded = -1;
   Unit un;
   while (next_unit(L, queue, units, n_units, cells, tables, guides, loaded, un,
                    64 * kBatchWavesCut)) {
-    const int share = (un.count + kBatchWavesCut - 1) / kBatchWavesCut;
+    const int share = (un.count + waves - 1) / waves;
     const int first = wave * share;
-    if (first < un.count)
+    if (wave < waves && first < un.count)
       replicate_batch<true, 1>(cells, un.cell, un.r0 + first,
                             un.count - first < share ? un.count - first : share, &L.w[wave], mine,
                             stride, lane, L.T, L.guide, ln, out, esc_list, esc_count, esc_cap, err);
@@ -1294,26 +1304,26 @@ __global__ __launch_bounds__(64 * kBatchWavesCut, kBatchWavesCut / 4) void k_cut
 }
 
 // The replicates on the escalation list, with scratch for a replicate's every
-// draw: a workgroup takes up to kEscWaves of them, those of the same cell side
-// by side.
+// draw: a workgroup takes `waves` of them at a time (at most kEscWaves), those of
+// the same cell side by side.
 __global__ __launch_bounds__(64 * kEscWaves, kEscWaves / 4) void k_escalated(
     const DevCell* __restrict__ cells, const double* __restrict__ tables,
     const uint16_t* __restrict__ guides, const double* __restrict__ ln, uint32_t* queue,
     Outputs out, uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* scratch,
-    int64_t stride, uint32_t* err) {
+    int waves, int64_t stride, uint32_t* err) {
   __shared__ KernelLds<BatchLds, kEscWaves> L;
   const int tid = (int)threadIdx.x;
   const int wave = tid >> 6;
   const int lane = tid & 63;
-  int64_t* mine = scratch + ((int64_t)blockIdx.x * kEscWaves + wave) * stride;
+  int64_t* mine = scratch + ((int64_t)blockIdx.x * waves + wave) * stride;
   const uint32_t ne = *esc_count < esc_cap ? *esc_count : esc_cap;
   int loaded = -1;
   for (;;) {
-    if (tid == 0) L.unit = (int)atomicAdd(queue, (uint32_t)kEscWaves);
+    if (tid == 0) L.unit = (int)atomicAdd(queue, (uint32_t)waves);
     __syncthreads();
     const uint32_t e0 = (uint32_t)L.unit;
     if (e0 >= ne) break;
-    const uint32_t e1 = e0 + kEscWaves < ne ? e0 + kEscWaves : ne;
+    const uint32_t e1 = e0 + (uint32_t)waves < ne ? e0 + (uint32_t)waves : ne;
     for (uint32_t e = e0; e < e1;) {
       const int cell = (int)(esc_list[e] >> 32);
       uint32_t same = 1;

@@ -1946,35 +1946,36 @@ static_assert(sizeof(WaveSlot) == kWaveSlotBytes, "WaveSlot layout");
 hipError_t launch_simulate(const SimGrid& g, const DevCell* cells, const double* tables,
                            const uint16_t* guides, const double* ln, const Unit* lane_units,
                            int n_lane, const Unit* batch_units, int n_batch, uint32_t* lane_queue,
-                           uint32_t* batch_queue, Outputs out, uint64_t* esc_list,
-                           uint32_t* esc_count, uint32_t esc_cap, int64_t* slots,
-                           int64_t* scratch, uint32_t* err, hipStream_t s) {
+                           uint32_t* batch_queue, uint32_t* big_queue, Outputs out,
+                           uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap,
+                           int64_t* slots, int64_t* scratch, uint32_t* err, hipStream_t s) {
   if (g.grid <= 0) return hipSuccess;
   k_simulate<<<g.grid, kBlock, 0, s>>>(g, cells, tables, guides, ln, lane_units, n_lane,
-                                       batch_units, n_batch, lane_queue, batch_queue, out,
-                                       esc_list, esc_count, esc_cap, slots, scratch, err);
+                                       batch_units, n_batch, lane_queue, batch_queue, big_queue,
+                                       out, esc_list, esc_count, esc_cap, slots, scratch, err);
   return hipGetLastError();
 }
 
 hipError_t launch_escalated(int grid, const DevCell* cells, const double* tables,
                             const uint16_t* guides, const double* ln, uint32_t* queue, Outputs out,
                             uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap,
-                            int64_t* scratch, int64_t stride, uint32_t* err, hipStream_t s) {
+                            int64_t* scratch, int waves, int64_t stride, uint32_t* err,
+                            hipStream_t s) {
   if (grid <= 0) return hipSuccess;
   k_escalated<<<grid, 64 * kEscWaves, 0, s>>>(cells, tables, guides, ln, queue, out, esc_list,
-                                              esc_count, esc_cap, scratch, stride, err);
+                                              esc_count, esc_cap, scratch, waves, stride, err);
   return hipGetLastError();
 }
 
 hipError_t launch_cutoff(int grid, const DevCell* cells, const double* tables,
                          const uint16_t* guides, const double* ln, const Unit* units, int n_units,
                          uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
-                         uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
-                         hipStream_t s) {
+                         uint32_t esc_cap, int64_t* scratch, int waves, int64_t stride,
+                         uint32_t* err, hipStream_t s) {
   if (n_units <= 0 || grid <= 0) return hipSuccess;
   k_cutoff<<<grid, 64 * kBatchWavesCut, 0, s>>>(cells, tables, guides, ln, units, n_units, queue,
-                                                out, esc_list, esc_count, esc_cap, scratch, stride,
-                                                err);
+                                                out, esc_list, esc_count, esc_cap, scratch, waves,
+                                                stride, err);
   return hipGetLastError();
 }
 

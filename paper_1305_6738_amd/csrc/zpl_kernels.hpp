@@ -97,10 +97,14 @@ struct Unit {
 
 // Launch shape of the simulation kernel: workgroups 0 .. lane_wgs - 1 take
 // lane-form units (of at most 64 lane_waves replicates), the last batch_wgs
-// wave- and heavy-form ones, with `stride` int64 of scratch per wave.
+// wave- and heavy-form ones.  Of those the first big_wgs take the first n_big
+// units before the others, by big_waves waves with big_stride int64 of scratch
+// each; the other workgroups' waves (`waves` of them, `stride` each) have theirs
+// from big_area on.
 struct SimGrid {
   int32_t grid, lane_wgs, lane_waves, batch_wgs;
-  int64_t stride;
+  int32_t n_big, big_wgs, big_waves, waves;
+  int64_t big_stride, big_area, stride;
 };
 
 struct Outputs {

@@ -17,27 +17,27 @@ hipError_t launch_tables(DevCell* cells, int n_cells, double* tables, uint16_t* 
                          const double* ln, hipStream_t s, bool any_trunc = true,
                          uint32_t* zero = nullptr, int n_zero = 0);
 // Lane-form units and wave- and heavy-form ones in one launch; slots: lane_wgs
-// * lane_waves areas of kLaneScratch int64, scratch: batch_wgs * kBatchWaves of
-// g.stride.
+// * lane_waves areas of kLaneScratch int64; scratch: the waves' areas (SimGrid).
 hipError_t launch_simulate(const SimGrid& g, const DevCell* cells, const double* tables,
                            const uint16_t* guides, const double* ln, const Unit* lane_units,
                            int n_lane, const Unit* batch_units, int n_batch, uint32_t* lane_queue,
-                           uint32_t* batch_queue, Outputs out, uint64_t* esc_list,
-                           uint32_t* esc_count, uint32_t esc_cap, int64_t* slots,
-                           int64_t* scratch, uint32_t* err, hipStream_t s);
-// The escalated replicates (none: a few empty workgroups); scratch: grid *
-// kEscWaves areas of `stride` int64, each for a replicate's every draw.
+                           uint32_t* batch_queue, uint32_t* big_queue, Outputs out,
+                           uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap,
+                           int64_t* slots, int64_t* scratch, uint32_t* err, hipStream_t s);
+// The escalated replicates; scratch: grid * waves areas (waves <= kEscWaves) of `stride`
+// int64, each for a replicate's every draw.  Grid 0 (no replicate can escalate): no launch.
 hipError_t launch_escalated(int grid, const DevCell* cells, const double* tables,
                             const uint16_t* guides, const double* ln, uint32_t* queue, Outputs out,
                             uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap,
-                            int64_t* scratch, int64_t stride, uint32_t* err, hipStream_t s);
-// The units of cells with a lower cutoff; scratch: grid * kBatchWavesCut areas of
-// `stride` int64.
+                            int64_t* scratch, int waves, int64_t stride, uint32_t* err,
+                            hipStream_t s);
+// The units of cells with a lower cutoff, `waves` waves of each workgroup at
+// work; scratch: grid * waves areas of `stride` int64.
 hipError_t launch_cutoff(int grid, const DevCell* cells, const double* tables,
                          const uint16_t* guides, const double* ln, const Unit* units, int n_units,
                          uint32_t* queue, Outputs out, uint64_t* esc_list, uint32_t* esc_count,
-                         uint32_t esc_cap, int64_t* scratch, int64_t stride, uint32_t* err,
-                         hipStream_t s);
+                         uint32_t esc_cap, int64_t* scratch, int waves, int64_t stride,
+                         uint32_t* err, hipStream_t s);
 // Datasets of a batch, a workgroup each; scratch: grid areas of `stride` int64
 // (heavy_stride of the largest).
 hipError_t launch_fit(int grid, const int64_t* const* xs, const int64_t* ns, int n_sets,

@@ -21,22 +21,40 @@ inline int64_t heavy_stride(int64_t max_n) {
 // records and one replicate's counts (the wider ones, of n >= 65536).
 constexpr int64_t kBatchFixed = 64 * (int64_t)kWaveSlotBytes / 8 + kHW / 2;
 
-// An area of int64 shared by `grid` workgroups, `stride` for each of their waves.
+// An area of int64 shared by `grid` workgroups, of which `waves` waves each work
+// on `stride` of it.
 struct Share {
-  int grid;
+  int grid, waves;
   int64_t stride;
 };
-// The most workgroups, up to `units` and one per compute unit, whose waves each
-// hold a replicate with `room` values above the histogram.  The strides are
-// multiples of 32, and it is the rounded one that has to hold it: a replicate
-// whose room is all of its n draws has nowhere else to go.  Grid 0: not even
-// one workgroup's do.
+// For `units` of up to `waves` waves each, one workgroup per compute unit at most,
+// whose waves each hold a replicate with `room` values above the histogram.
+// Where the area does not hold that many, fewer waves per workgroup, and then
+// fewer workgroups: waves on compute units of their own do not share issue
+// slots.  The strides are multiples of 32, and it is the rounded one that has to
+// hold a replicate: one whose room is all of its n draws has nowhere else to go.
+// Grid 0: no units, or not even one replicate fits.
 inline Share share_scratch(int64_t area, int64_t units, int waves, int64_t room, int n_cu) {
-  auto stride = [&](int64_t g) { return area / (g * waves) & ~(int64_t)31; };
-  int64_t g = std::min<int64_t>(units, n_cu);
-  while (g > 1 && stride(g) < kBatchFixed + room) g = (g + 1) / 2;
-  if (g < 1 || stride(g) < kBatchFixed + room) return Share{0, 0};
-  return Share{(int)g, stride(g)};
+  const int64_t need = (kBatchFixed + room + 31) & ~(int64_t)31;
+  const int64_t most = area / need;
+  const int64_t g = std::min<int64_t>(std::min<int64_t>(units, n_cu), most);
+  if (g < 1) return Share{0, 0, 0};
+  const int64_t w = std::min<int64_t>(waves, most / g);
+  return Share{(int)g, (int)w, area / (g * w) & ~(int64_t)31};
+}
+
+// Cells of one call may differ by orders of magnitude in their rooms, and a share
+// that holds the largest would leave the device to a few workgroups.  When it
+// does (the result is true), cells of rooms up to `limit` share a quarter of the
+// area among all workgroups, and the longer ones have the rest of it to
+// themselves: six cells of 20,000 draws beside ten replicates of 10^7 took 5.2 s
+// in the 32 workgroups that one share leaves, 1.5 s with a share of their own.
+inline bool split_batch(int64_t area, int64_t units, int waves, int64_t max_room, int n_cu,
+                        int64_t& limit) {
+  const Share all = share_scratch(area, units, waves, max_room, n_cu);
+  if (all.grid == std::min<int64_t>(units, n_cu) && all.waves == waves) return false;
+  limit = (area / 4 / ((int64_t)n_cu * waves) & ~(int64_t)31) - kBatchFixed;
+  return limit >= 0;
 }
 
 // int64 of scratch for a call's replicates: the lane form's slots, then what the

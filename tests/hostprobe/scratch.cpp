@@ -12,6 +12,10 @@ void sc_share(int64_t area, int64_t units, int waves, int64_t room, int n_cu, in
   const Share s = share_scratch(area, units, waves, room, n_cu);
   out[0] = s.grid;
   out[1] = s.stride;
+  out[2] = s.waves;
+}
+int sc_split(int64_t area, int64_t units, int waves, int64_t max_room, int n_cu, int64_t* limit) {
+  return split_batch(area, units, waves, max_room, n_cu, *limit) ? 1 : 0;
 }
 // Values above the histogram that the first replicate of a wave's batch has
 // place for, n draws of 32-bit (n >= 65536) or 16-bit counts: as the kernel

@@ -30,13 +30,16 @@ def sc(tmp_path_factory):
     L.sc_area.argtypes = [i64, i64, i64, i64, C.c_uint64, C.c_int]
     L.sc_share.argtypes = [i64, i64, C.c_int, i64, C.c_int, C.POINTER(i64)]
     L.sc_first_room.argtypes = [i64, i64]
+    L.sc_split.argtypes = [i64, i64, C.c_int, i64, C.c_int, C.POINTER(i64)]
     return L
 
 
 def share(sc, area, units, waves, room):
-    out = (C.c_int64 * 2)()
+    out = (C.c_int64 * 3)()
     sc.sc_share(area, units, waves, room, N_CU, out)
-    return out[0], out[1]
+    grid, stride, w = out
+    assert 0 <= grid <= N_CU and 0 <= w <= waves and grid * w * stride <= area
+    return grid, stride, w
 
 
 def first_room(sc, n, R, budget=BUDGET, waves=None):
@@ -44,8 +47,8 @@ def first_room(sc, n, R, budget=BUDGET, waves=None):
     waves = waves or sc.sc_waves_cut()
     area = sc.sc_area((R + 7) // 8, 0, n, 0, budget, N_CU)
     step = min(waves, max(1, (R + N_CU - 1) // N_CU))
-    grid, stride = share(sc, area, (R + step - 1) // step, waves, n)
-    assert 1 <= grid <= N_CU and grid * waves * stride <= area
+    grid, stride, w = share(sc, area, (R + step - 1) // step, step, n)
+    assert grid >= 1 and w >= 1
     return sc.sc_first_room(stride, n)
 
 
@@ -64,5 +67,29 @@ def test_whole_replicates_fit_over_the_range(sc, budget):
         assert first_room(sc, n, R, budget) >= n, (n, R)
         # an escalated replicate, whatever the call holds besides
         area = sc.sc_area((R + 7) // 8, 0, n, 4096, budget, N_CU)
-        grid, stride = share(sc, area, 64, sc.sc_esc_waves(), n)
+        grid, stride, _ = share(sc, area, 64, sc.sc_esc_waves(), n)
         assert grid >= 1 and sc.sc_first_room(stride, n) >= n, (n, R)
+
+
+@pytest.mark.parametrize("long_n", [10 ** 7, 3 * 10 ** 7, 10 ** 8])
+def test_a_long_cell_leaves_the_device_to_the_others(sc, long_n):
+    """24,000 replicates of 20,000 draws beside ten of long_n at alpha = 1.2 (a
+    quarter of their draws above the histogram): the short ones keep a
+    workgroup on every compute unit."""
+    waves, units, room, long_room = sc.sc_waves(), 2000, 400, long_n // 4
+    area = sc.sc_area(24000 // 8 + 2, 0, long_n, 4096, BUDGET, N_CU)
+    grid, _, w = share(sc, area, units + 10, waves, long_room)
+    assert grid * w < N_CU * waves // 2  # what one share for all would leave
+    limit = C.c_int64()
+    assert sc.sc_split(area, units + 10, waves, long_room, N_CU, C.byref(limit)) == 1
+    assert room <= limit.value < long_room
+    big, stride, _ = share(sc, area - area // 4, 10, waves, long_room)
+    assert 1 <= big <= 10 and sc.sc_first_room(stride, long_n) >= long_room
+    rest, stride, w = share(sc, area // 4, N_CU - big, waves, room)
+    assert big + rest == N_CU and w == waves and sc.sc_first_room(stride, 20000) >= room
+
+
+def test_equal_cells_are_not_split(sc):
+    limit = C.c_int64()
+    area = sc.sc_area(2500, 0, 10000, 4096, BUDGET, N_CU)
+    assert sc.sc_split(area, 1700, sc.sc_waves(), 2200, N_CU, C.byref(limit)) == 0
