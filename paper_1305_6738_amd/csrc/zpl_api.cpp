@@ -739,14 +739,14 @@ zpl_status prepare(zpl_ctx* c, Plan& P, int n_q, bool need_dbuf, Launch& L) {
   const int waves = P.unit_waves[0];
   int64_t big_words = 0, small_room = P.max_room[0], limit = 0;
   if (split_batch(area, P.n_bpure, waves, P.max_room[0], c->n_cu, limit)) {
-    auto is_big = [&](const Unit& u) { return (int64_t)P.cells[u.cell].room > limit; };
+    auto is_big = [&](const Unit& u) { return batch_need(P.cells[u.cell].room) > limit; };
     const auto end = P.hunits.begin() + P.n_bpure;
     const int n = (int)(std::stable_partition(P.hunits.begin(), end, is_big) - P.hunits.begin());
     if (n < P.n_bpure) {
       small_room = 0;
       for (int k = n; k < P.n_bpure; ++k)
         small_room = std::max<int64_t>(small_room, P.cells[P.hunits[k].cell].room);
-      big_words = area - area / 4;
+      big_words = (area - area / 4) & ~(int64_t)31;  // (whole records and counts stay aligned)
       L.sim.n_big = n;
     }
   }

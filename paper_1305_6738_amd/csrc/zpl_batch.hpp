@@ -584,6 +584,313 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
   return D;
 }
 
+// ks_rest's second part for a replicate with many larger draws.  Gathered window
+// by window, every window of 255 reads them all again: of 20,000 draws above the
+// histogram nearly all are in reach (D is about 0.005, a bin holds 0.003 of them),
+// and 80 passes over them took 18 ms where the whole replicate had taken 7.4.
+// Here the bins in reach are copied out in order once, those of up to 254 draws
+// first; a window is then a piece of the copy, and a bin with more is a
+// contiguous range with a table, a copy and bins of its own.
+// D0: the largest term over the values of the histogram.  work, words: the
+// scratch behind the batch's counts.  Negative: it does not hold the copies (the
+// caller takes the windows over all draws instead).
+template <int kLaw>
+static __device__ __noinline__ double ks_many(double a, double iz, int64_t xmin_, uint32_t K_,
+                                              bool has_top_, const int64_t* ov_, uint32_t oc_,
+                                              int64_t* work_, int64_t words_, int64_t n_, double D0,
+                                              LdsU32* tab, LdsU64* list, LdsU64* level,
+                                              const double* ln_) {
+  // every argument is the wave's
+  const int lane = lane_id();
+  const uint32_t nu = (uint32_t)uniform64(n_);
+  const double idn = 1.0 / (double)n_;
+  const uint32_t oc = uniform32(oc_);
+  const bool has_top = uniform32(has_top_) != 0u;
+  int64_t* work = as_global(reinterpret_cast<int64_t*>(uniform64((int64_t)work_)));
+  const int64_t words = uniform64(words_);
+  const double* __restrict__ ln = as_global(reinterpret_cast<const double*>(uniform64((int64_t)ln_)));
+  KsLaw<kLaw> w;
+  w.E = em_coef(a);
+  w.iz = iz;
+  w.xmin = kLaw == kCutoff ? uniform64(xmin_) : 1;
+  if constexpr (kLaw == kTrunc) w.te = trunc_end(w.E, uniform32(K_), ln);
+  const int64_t off = w.xmin - 1;
+  double D = D0;
+  const double zE = w.survival(off + kHW, ln);
+  if (fmax(zE * w.iz, (double)oc * idn) <= D - kPruneMargin) return D;
+  const uint32_t nbody = nu - oc;
+  auto terms = [&](double zv, double zv1, uint32_t Cb, uint32_t c) {
+    const double t2 = fabs(fma(zv1, w.iz, -(double)(nu - Cb) * idn));
+    const double t1 = fabs(fma(zv, w.iz, -(double)(nu - Cb - c) * idn));
+    D = fmax(D, fmax(t1, t2));
+  };
+  LdsU8* many = (LdsU8*)(tab + kHW);  // counts of the bins in reach, up to kManyDraws
+  // the range at hand: its bins and how many of them are in it, its draws, the
+  // larger draws below it, whether the value just below it was drawn, and the
+  // words of `work` in use
+  Bins B{(uint64_t)kHW, -1};
+  int nbins = kBuckets;
+  const int64_t* src = as_global(reinterpret_cast<const int64_t*>(uniform64((int64_t)ov_))) - oc;
+  uint32_t len = oc, lower = 0;
+  bool edge = false;
+  int64_t used = 0;
+  int depth = 0;
+  for (;;) {
+    if (B.sh != 0 && used + kPartLevel > words) return -1.0;
+    // of each bin in reach: its draws, its first place in the copy, the larger
+    // draws below it (with kBelowDrawn)
+    uint32_t* cnts = reinterpret_cast<uint32_t*>(work + used);
+    uint32_t* firsts = cnts + kHW;
+    uint32_t* belows = firsts + kHW;
+    int64_t* part = work + used + kPartLevel;
+    auto each = [&](auto fn) {  // fn of every draw, four loads in flight
+      uint32_t p = (uint32_t)lane;
+      for (; p + 192u < len; p += 256u) {
+        uint64_t j[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) j[k] = (uint64_t)src[p + 64u * k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) fn(j[k]);
+      }
+      for (; p < len; p += 64u) fn((uint64_t)src[p]);
+    };
+    wave_sync();
+    for (int k = lane; k < kHW; k += 64) tab[k] = 0u;
+    wave_sync();
+    each([&](uint64_t j) { lds_inc(&tab[B.of(j)]); });
+    wave_sync();
+    uint32_t cs = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) cs += tab[16 * lane + k];
+    const uint32_t cr = lower + dpp_incl_scan_u32(cs), cl = cr - cs;
+    auto right = [&](int b) {
+      return (int64_t)min((uint64_t)off + B.end(b), (uint64_t)INT64_MAX);
+    };
+    // (S_n is known at the edges of the range's own bins only)
+    const bool real = 16 * lane + 15 < nbins;
+    const double zo = w.survival(right(16 * lane < kBuckets || B.sh >= 0 ? 16 * lane + 15 : 15), ln);
+    const double zlo = B.sh >= 0 ? w.survival(off + (int64_t)B.lo - 1, ln) : zE;
+    double Dlow = fmax(D, dpp_max_f64(real ? fabs(zo * w.iz - (double)(oc - cr) * idn) : 0.0));
+    double zl = prev_lane_f64(zo);
+    if (lane == 0) zl = zlo;
+    const bool need = cs != 0u && fmax(zl * w.iz - (double)(oc - cr) * idn,
+                                       (double)(oc - cl) * idn - zo * w.iz) > Dlow - kPruneMargin;
+    if (!need && B.sh != 0) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) tab[16 * lane + k] = kNoBin;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        reinterpret_cast<uint4*>(cnts + 16 * lane)[k] = uint4{0u, 0u, 0u, 0u};
+    }
+    uint64_t mask = __ballot(need);
+    uint32_t small = 0, large = 0;
+    while (mask != 0ull) {  // 16 bins of four lanes per round
+      int p = -1;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int q = mask != 0ull ? __ffsll((long long)mask) - 1 : -1;
+        mask &= mask - 1ull;
+        if ((lane >> 4) == g) p = q;
+      }
+      const int pc = p < 0 ? 0 : p;
+      const int b = 16 * pc + (lane & 15);
+      const uint32_t cnt = p < 0 ? 0u : tab[b];
+      const uint32_t ca = (uint32_t)__shfl((int)cl, pc, 64) + row_incl_scan_u32(cnt);
+      const int64_t t = right(b);
+      const double zv = w.survival(t, ln);
+      double zp = prev_lane_f64(zv);
+      const double zq = shfl_f64(zl, pc);
+      if ((lane & 15) == 0) zp = zq;
+      if (B.sh == 0) {  // single values
+        const bool pres = B.lo + (uint64_t)b == (uint64_t)kHW + 1u
+                              ? has_top
+                              : (b > 0 ? tab[b - 1] != 0u : edge);
+        if (cnt != 0u) terms(zv, pres ? zp : zv + w.point(t, ln), nbody + ca - cnt, cnt);
+      } else {
+        const double sb = (double)(oc - ca) * idn;
+        Dlow = fmax(Dlow, dpp_max_f64(p < 0 ? 0.0 : fabs(zv * w.iz - sb)));
+        const bool in = cnt != 0u && fmax(zp * w.iz - sb, (double)(oc - (ca - cnt)) * idn -
+                                                              zv * w.iz) > Dlow - kPruneMargin;
+        if (p >= 0) {
+          tab[b] = in ? ca - cnt : kNoBin;
+          cnts[b] = in ? cnt : 0u;
+          many[b] = (uint8_t)(cnt < kManyDraws ? cnt : kManyDraws);
+        }
+        small += in && cnt < kManyDraws ? cnt : 0u;
+        large += in && cnt >= kManyDraws ? cnt : 0u;
+      }
+    }
+    small = dpp_sum_u32(small);
+    large = dpp_sum_u32(large);
+    const uint32_t m = small + large;
+    if (m != 0u) {
+      if (used + kPartLevel + (int64_t)m > words) return -1.0;
+      wave_sync_global();
+      // the places, 16 bins per lane; the table then counts them up
+      {
+        uint32_t c1 = 0, c2 = 0;
+#pragma unroll 4
+        for (int k = 0; k < 16; ++k) {
+          const int b = 16 * lane + k;
+          const uint32_t c = cnts[b];
+          c1 += c < kManyDraws ? c : 0u;
+          c2 += c < kManyDraws ? 0u : c;
+        }
+        uint32_t p1 = dpp_incl_scan_u32(c1) - c1, p2 = small + dpp_incl_scan_u32(c2) - c2;
+#pragma unroll 4
+        for (int k = 0; k < 16; ++k) {
+          const int b = 16 * lane + k;
+          const uint32_t c = cnts[b];
+          if (c == 0u) continue;
+          const uint32_t at = c < kManyDraws ? p1 : p2;
+          firsts[b] = at;
+          belows[b] = tab[b];
+          tab[b] = at | (b == 0 && edge ? kBelowDrawn : 0u);
+          p1 += c < kManyDraws ? c : 0u;
+          p2 += c < kManyDraws ? 0u : c;
+        }
+        wave_sync();
+      }
+      // a draw equal to the value just below another bin marks that bin's entry
+      const uint64_t last = B.sh >= 0 ? B.end(kHW - 1) : ~0ull;
+      each([&](uint64_t j) {
+        const int b = B.of(j);
+        if (tab[b] != kNoBin) {
+          const uint32_t at = __hip_atomic_fetch_add(&tab[b], 1u, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+          part[at & ~kBelowDrawn] = (int64_t)j;
+        }
+        if (j < last) {
+          const int b1 = B.of(j + 1u);
+          if (b1 != b && tab[b1] != kNoBin) lds_or(&tab[b1], kBelowDrawn);
+        }
+      });
+      wave_sync();
+#pragma unroll 4
+      for (int k = 0; k < 16; ++k) {  // marks, kept for the ranges of their own
+        const int b = 16 * lane + k;
+        if (tab[b] != kNoBin && (tab[b] & kBelowDrawn) != 0u) belows[b] |= kBelowDrawn;
+      }
+      wave_sync_global();
+      // the bins of up to 254 draws, whole bins of at most kGather draws at a time
+      uint32_t w0 = 0;
+      for (int lo = 0; w0 < small && lo < kHW;) {
+        const int b = lo + lane;
+        uint32_t c = 0;
+        if (b < kHW && tab[b] != kNoBin) c = many[b];
+        c = c < kManyDraws ? c : 0u;
+        const uint32_t inc = dpp_incl_scan_u32(c);
+        const uint64_t fit = __ballot(inc <= kGather);
+        const int take = fit == ~0ull ? 64 : __ffsll((long long)~fit) - 1;  // at least one
+        const uint32_t wn = (uint32_t)__builtin_amdgcn_readlane((int)inc, take - 1);
+        lo += take;
+        for (uint32_t i = (uint32_t)lane; i < wn; i += 64u) list[i] = (uint64_t)part[w0 + i];
+        wave_sync();
+        for (uint32_t i = (uint32_t)lane; i < wn; i += 64u) {
+          const uint64_t j = list[i];
+          const int bj = B.of(j);
+          const uint32_t entry = tab[bj];
+          const uint32_t k1 = (entry & ~kBelowDrawn) - w0;  // past the bin's last
+          uint32_t lt = 0, eq = 0;
+          uint32_t pres = j == (uint64_t)kHW + 1u ? (has_top ? 1u : 0u)
+                                                   : (j == B.start(bj) ? entry >> 31 : 0u);
+          for (uint32_t k = k1 - many[bj]; k < k1; ++k) {
+            const uint64_t x = list[k];
+            lt += x < j ? 1u : 0u;
+            eq += x == j ? 1u : 0u;
+            pres |= x + 1u == j ? 1u : 0u;
+          }
+          const int64_t v = off + (int64_t)j;
+          const double zv = w.survival(v, ln);
+          const double zv1 = pres ? w.survival(v - 1, ln) : zv + w.point(v, ln);
+          terms(zv, zv1, nbody + (belows[bj] & ~kBelowDrawn) + lt, eq);
+        }
+        wave_sync();
+        w0 += wn;
+      }
+    }
+    D = dpp_max_f64(D);
+    // the bins with more, one after another
+    if (large != 0u) {
+      if (lane == 0) {
+        level[5 * depth] = B.lo;
+        level[5 * depth + 1] = (uint64_t)(int64_t)B.sh;
+        level[5 * depth + 2] = (uint64_t)used;
+        level[5 * depth + 3] = (uint64_t)((m + 1u) & ~1u);  // (16-byte alignment)
+        level[5 * depth + 4] = 0u;
+      }
+      ++depth;
+    }
+    wave_sync();
+    for (;;) {
+      if (depth == 0) return D;
+      LdsU64* r = level + 5 * (depth - 1);
+      const Bins P{(uint64_t)uniform64((int64_t)r[0]), (int)uniform64((int64_t)r[1])};
+      const int64_t base = uniform64((int64_t)r[2]);
+      const int next = (int)uniform64((int64_t)r[4]);
+      const uint32_t* pc = reinterpret_cast<const uint32_t*>(work + base);
+      int child = -1;
+      for (int b0 = next & ~63; b0 < kHW && child < 0; b0 += 64) {
+        const uint64_t hit = __ballot(b0 + lane >= next && pc[b0 + lane] >= kManyDraws);
+        if (hit != 0ull) child = b0 + __ffsll((long long)hit) - 1;
+      }
+      if (child < 0) {
+        --depth;
+        continue;
+      }
+      used = base + kPartLevel + uniform64((int64_t)r[3]);
+      wave_sync();
+      if (lane == 0) r[4] = (uint64_t)(child + 1);
+      len = uniform32(pc[child]);
+      src = work + base + kPartLevel + uniform32(pc[kHW + child]);
+      const uint32_t bl = uniform32(pc[2 * kHW + child]);
+      lower = bl & ~kBelowDrawn;
+      edge = (bl & kBelowDrawn) != 0u;
+      const int bits = P.width_bits(child);
+      B = Bins{P.start(child), bits > 10 ? bits - 10 : 0};
+      nbins = 1 << (bits > 10 ? 10 : bits);
+      break;
+    }
+  }
+}
+
+// ks_rest for the replicates of a batch that have many larger draws (bits of
+// `left`; a, iz, D, z16, hi, oc and top are each lane's own replicate's, D comes
+// back).  One call outside the loop over the others, which keeps its registers.
+template <int kLaw>
+static __device__ __noinline__ double ks_parted(uint64_t left, double a, double iz, double D,
+                                                double z16, int hi, uint32_t oc, int64_t top,
+                                                int64_t xmin, uint32_t K, const uint32_t* counts,
+                                                int64_t cw, bool wide, const int64_t* scratch,
+                                                int64_t n, LdsU32* tab, LdsU64* list, LdsU32* ends,
+                                                LdsU64* level, const double* ln, int64_t* work,
+                                                int64_t words) {
+  const int lane = lane_id();
+  left = (uint64_t)uniform64((int64_t)left);
+  while (left != 0ull) {
+    const int i = __ffsll((long long)left) - 1;
+    left &= left - 1ull;
+    const uint32_t* ci = counts + 2 * i * uniform64(cw);
+    const int64_t* ov =
+        scratch + (((int64_t)__builtin_amdgcn_readlane((int)(top >> 32), i) << 32) |
+                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)top, i));
+    const uint32_t oi = (uint32_t)__builtin_amdgcn_readlane((int)oc, i);
+    auto rest = [&](auto fn) {
+      return fn(readlane_f64(a, i), readlane_f64(iz, i), xmin, K, ci, wide,
+                __builtin_amdgcn_readlane(hi, i), ov, oi, n, readlane_f64(D, i),
+                readlane_f64(z16, i), tab, list, ends, level, ln);
+    };
+    const CountView cv{as_global(ci), wide};
+    const bool has_top = __builtin_amdgcn_readlane(hi, i) == kHW && cv.at(kHW - 1) != 0u;
+    double Di = rest([](auto... x) { return ks_rest<kLaw, false>(x...); });
+    Di = ks_many<kLaw>(readlane_f64(a, i), readlane_f64(iz, i), xmin, K, has_top, ov, oi, work,
+                       words, n, Di, tab, list, level, ln);
+    if (Di < 0.0) Di = rest([](auto... x) { return ks_rest<kLaw>(x...); });
+    if (lane == i) D = Di;
+  }
+  return D;
+}
+
 // Record of one replicate of a batch.
 struct WaveSlot {
   U128 S;
@@ -1083,6 +1390,7 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
   int64_t* counts = scratch + kRecords;
   const int64_t off = kCut ? c.xmin - 1 : 0;
   const bool want_fp = out.fp != nullptr;
+  const int64_t want = (int64_t)c.room + part_words(c.room);
   int hi = kHW;  // the region's LDS held other data
   int done = 0;
   while (done < nrep) {
@@ -1090,7 +1398,7 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
     bool full = false;
     int64_t top = stride;  // the larger draws of the next replicate lie below it
     while (done + q < nrep && q < 64 && !full &&
-           (q == 0 || top - (kRecords + (q + 1) * cw) >= (int64_t)c.room)) {
+           (q == 0 || top - (kRecords + (q + 1) * cw) >= want)) {
       const uint32_t rep = (uint32_t)(r0 + done + q);
       const uint32_t room = (uint32_t)min(top - (kRecords + (q + 1) * cw), n);
       const DrawOut dr = draw_replicate<kCut, kKernel>(&c, rep, (LdsU32*)L->hist, (LdsU32*)L->ring,
@@ -1141,7 +1449,23 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
       }
     }
     // the rest of the KS, one replicate per wave
-    uint64_t left = __ballot(h.done == 0u);
+    const bool part = oc > (uint32_t)kPartMin;
+    const uint64_t parted = __ballot(h.done == 0u && part);
+    if (parted != 0ull) {
+      auto many = [&](auto fn) {
+        return fn(parted, h.a, h.iz, h.D, h.z16, (int)hib, oc, ovtop, c.xmin, c.K,
+                  reinterpret_cast<const uint32_t*>(counts), cw, wide, scratch, n,
+                  (LdsU32*)L->hist, (LdsU64*)L->ring, (LdsU32*)L->retry, (LdsU64*)L->hard, ln,
+                  counts + q * cw, top - (kRecords + q * cw));
+      };
+      if constexpr (kCut)
+        h.D = many([](auto... x) { return ks_parted<kCutoff>(x...); });
+      else if (c.K)
+        h.D = many([](auto... x) { return ks_parted<kTrunc>(x...); });
+      else
+        h.D = many([](auto... x) { return ks_parted<kPure>(x...); });
+    }
+    uint64_t left = __ballot(h.done == 0u && !part);
     while (left != 0ull) {
       const int i = __ffsll((long long)left) - 1;
       left &= left - 1ull;

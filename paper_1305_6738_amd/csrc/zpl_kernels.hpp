@@ -48,6 +48,18 @@ constexpr int kLaneScratch = 64 * 2 * kLaneCap;
 constexpr int kHW = 1024;
 constexpr int kBatchWaves = 12;
 constexpr int kBatchWavesCut = 12;
+// A replicate with more values above the histogram than kPartMin partitions them
+// by bin in the scratch that is left behind its counts (ks_many): kPartLevel
+// int64 for the bins of a level, a copy of the draws in reach, and as much again
+// for the ranges within a bin (an eighth of an octave at most).  Cutoff 1e6, so
+// that all draws are such: 10,000 replicates of 1,500 draws 1.25 ms by bins and
+// 1.14 in windows over all of them, of 2,500 2.08 and 2.35; 1,000 replicates of
+// 20,000 4.5 and 23.6; alpha 1.2, 10,000 draws (about 1,700 such): 2.0 and 2.3.
+constexpr int64_t kPartMin = 1536;
+constexpr int64_t kPartLevel = 3 * kHW / 2;
+constexpr int64_t part_words(int64_t room) {
+  return room > kPartMin ? room + room / 4 + 3 * kPartLevel : 0;
+}
 // Waves per workgroup that run escalated replicates (whole replicates of
 // scratch each, so few).
 constexpr int kEscWaves = 4;

@@ -34,9 +34,12 @@ struct Share {
 // slots.  The strides are multiples of 32, and it is the rounded one that has to
 // hold a replicate: one whose room is all of its n draws has nowhere else to go.
 // Grid 0: no units, or not even one replicate fits.
+inline int64_t batch_need(int64_t room) {  // with what its KS partitions its draws in
+  return (kBatchFixed + room + part_words(room) + 31) & ~(int64_t)31;
+}
 inline Share share_scratch(int64_t area, int64_t units, int waves, int64_t room, int n_cu) {
-  const int64_t need = (kBatchFixed + room + 31) & ~(int64_t)31;
-  const int64_t most = area / need;
+  int64_t most = area / batch_need(room);
+  if (most < 1) most = area / ((kBatchFixed + room + 31) & ~(int64_t)31);
   const int64_t g = std::min<int64_t>(std::min<int64_t>(units, n_cu), most);
   if (g < 1) return Share{0, 0, 0};
   const int64_t w = std::min<int64_t>(waves, most / g);
@@ -47,14 +50,14 @@ inline Share share_scratch(int64_t area, int64_t units, int waves, int64_t room,
 // that holds the largest would leave the device to a few workgroups.  When it
 // does (the result is true), cells of rooms up to `limit` share a quarter of the
 // area among all workgroups, and the longer ones have the rest of it to
-// themselves: six cells of 20,000 draws beside ten replicates of 10^7 took 5.2 s
-// in the 32 workgroups that one share leaves, 1.5 s with a share of their own.
+// themselves: six cells of 20,000 draws (1.15 ms alone) beside ten replicates of
+// 10^7 at alpha = 2 (28 ms) took 45 ms in the workgroups that one share leaves.
 inline bool split_batch(int64_t area, int64_t units, int waves, int64_t max_room, int n_cu,
                         int64_t& limit) {
   const Share all = share_scratch(area, units, waves, max_room, n_cu);
   if (all.grid == std::min<int64_t>(units, n_cu) && all.waves == waves) return false;
-  limit = (area / 4 / ((int64_t)n_cu * waves) & ~(int64_t)31) - kBatchFixed;
-  return limit >= 0;
+  limit = area / 4 / ((int64_t)n_cu * waves) & ~(int64_t)31;
+  return true;
 }
 
 // int64 of scratch for a call's replicates: the lane form's slots, then what the

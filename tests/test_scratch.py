@@ -26,7 +26,8 @@ def sc(tmp_path_factory):
                    check=True, capture_output=True)
     L = C.CDLL(str(out))
     i64 = C.c_int64
-    L.sc_area.restype = L.sc_first_room.restype = i64
+    L.sc_area.restype = L.sc_first_room.restype = L.sc_need.restype = i64
+    L.sc_need.argtypes = [i64]
     L.sc_area.argtypes = [i64, i64, i64, i64, C.c_uint64, C.c_int]
     L.sc_share.argtypes = [i64, i64, C.c_int, i64, C.c_int, C.POINTER(i64)]
     L.sc_first_room.argtypes = [i64, i64]
@@ -82,7 +83,7 @@ def test_a_long_cell_leaves_the_device_to_the_others(sc, long_n):
     assert grid * w < N_CU * waves // 2  # what one share for all would leave
     limit = C.c_int64()
     assert sc.sc_split(area, units + 10, waves, long_room, N_CU, C.byref(limit)) == 1
-    assert room <= limit.value < long_room
+    assert sc.sc_need(room) <= limit.value < sc.sc_need(long_room)
     big, stride, _ = share(sc, area - area // 4, 10, waves, long_room)
     assert 1 <= big <= 10 and sc.sc_first_room(stride, long_n) >= long_room
     rest, stride, w = share(sc, area // 4, N_CU - big, waves, room)
