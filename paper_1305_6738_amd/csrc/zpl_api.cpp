@@ -447,7 +447,8 @@ int64_t batch_room(const DevCell& d) {
 
 // Units of the wave- and heavy-form cells, longest replicates first.  A unit
 // holds the same number of replicates (up to 64) for each of the kernel's
-// waves, as many as leaves about eight units for each compute unit.
+// waves, as many as leaves about eight units for each compute unit, or more
+// where all cells are alike.
 void plan_batch(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) {
   // a replicate costs about its draws plus 2,000 draws' time for fit and KS
   auto cost = [](const DevCell& d) { return (double)d.n + 2000.0; };
@@ -466,13 +467,32 @@ void plan_batch(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) 
     work += cost(d) * (double)d.R;
   }
   const double unit_work = work / (8.0 * n_cu);
+  // Cells that differ only in their exponents need not be balanced so finely, and
+  // a wave's estimates cost as much for one replicate as for 64: a wave's part of
+  // the call in one batch, or in batches of about 33 where it is more than 64
+  // replicates (or in eighths, several cells of long replicates, whose exponents
+  // then tell).  us with eight units per compute unit and so: one cell of 10,000
+  // replicates, alpha 2.5, n = 300, 190 and 123; alpha 2, n = 10,000, 396 and
+  // 330; cutoff 2, alpha 3.5, n = 100, 644 and 263; six cutoff cells of 100,000 of
+  // n = 1000, 5,826 and 5,565; four of 20,000 of n = 10,000, alpha 1.2..1.5: 4,295
+  // and (in one batch) 5,731.
+  bool alike = true;
+  for (int i : cells)
+    alike = alike && P.cells[i].n == P.cells[cells[0]].n &&
+            (P.cells[i].xmin > 1) == (P.cells[cells[0]].xmin > 1);
+  auto whole = [&](const DevCell& d, double share) -> int64_t {  // share: replicates per wave
+    if (!alike || (cells.size() > 1 && d.n > 1000)) return 1;
+    if (share <= 64.0) return (int64_t)std::ceil(share);
+    return d.n <= 1000 ? (int64_t)std::ceil(share / std::ceil(share / 33.0)) : 1;
+  };
   for (int cut = 0; cut < 2; ++cut) {
     const int waves = cut ? kBatchWavesCut : kBatchWaves;
     for (int i : cells) {
       const DevCell& d = P.cells[i];
       if ((d.xmin > 1) != (cut != 0)) continue;
-      const int64_t per_wave =
-          std::min<int64_t>(64, std::max<int64_t>(1, (int64_t)(unit_work / cost(d) / waves)));
+      const int64_t per_wave = std::min<int64_t>(
+          64, std::max<int64_t>(whole(d, work / cost(d) / ((double)n_cu * waves)),
+                                (int64_t)(unit_work / cost(d) / waves)));
       int64_t step = per_wave * waves;
       // too few replicates for every wave of the device (counting the call's work
       // in replicates of this size): spread over the compute units, so that the
@@ -690,7 +710,6 @@ PlanLayout plan_layout(const Plan& P, int n_q) {
 struct Launch {
   SimGrid sim = {};
   Share cut = {0, 0, 0}, esc = {0, 0, 0};  // of the cutoff and escalation kernels
-  int64_t slots = 0;                   // int64 of the lane form's slots, before the waves' scratch
   int64_t gcap = 0;
   int64_t maxR = 1;
   PlanLayout lay;
@@ -720,24 +739,20 @@ zpl_status prepare(zpl_ctx* c, Plan& P, int n_q, bool need_dbuf, Launch& L) {
   // Scratch of the wave and heavy forms.  The least a wave of a batch kernel
   // works with is one replicate (records, counts, its room), an escalated one
   // needs all of its draws; the more there is, the more replicates a wave
-  // finishes together.  The lane form's slots lie before it in the same buffer:
-  // calls of either form follow one another within a budget that holds the
-  // larger, where two grow-only buffers would need both.
+  // finishes together.  The lane form's slots are in the same buffer: calls of
+  // either form follow one another within a budget that holds the larger, where
+  // two grow-only buffers would need both.
   const int64_t total = scratch_words(P.heavy8, P.sim_units, P.max_n, esc_R - P.lw_R, c->budget,
                                       c->n_cu);
   ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)total));
-  L.slots = slots;
-  const int64_t area = total - slots;
-  auto share = [&](int64_t words, int64_t units, int waves, int64_t room, Share& sh) {
-    sh = share_scratch(words, units, waves, room, c->n_cu);
-    if (units > 0 && sh.grid == 0)
-      return fail(ZPL_ENOMEM, "scratch of %lld words does not hold replicates of %lld values",
-                  (long long)words, (long long)room);
-    return ZPL_OK;
+  const int64_t area = total - slots;  // what the slots leave
+  auto none = [&](int64_t room) {
+    return fail(ZPL_ENOMEM, "scratch of %lld words does not hold replicates of %lld values",
+                (long long)total, (long long)room);
   };
   // the wave and heavy forms, in two parts where the rooms differ that much
   const int waves = P.unit_waves[0];
-  int64_t big_words = 0, small_room = P.max_room[0], limit = 0;
+  int64_t small_room = P.max_room[0], limit = 0;
   if (split_batch(area, P.n_bpure, waves, P.max_room[0], c->n_cu, limit)) {
     auto is_big = [&](const Unit& u) { return batch_need(P.cells[u.cell].room) > limit; };
     const auto end = P.hunits.begin() + P.n_bpure;
@@ -746,25 +761,20 @@ zpl_status prepare(zpl_ctx* c, Plan& P, int n_q, bool need_dbuf, Launch& L) {
       small_room = 0;
       for (int k = n; k < P.n_bpure; ++k)
         small_room = std::max<int64_t>(small_room, P.cells[P.hunits[k].cell].room);
-      big_words = (area - area / 4) & ~(int64_t)31;  // (whole records and counts stay aligned)
       L.sim.n_big = n;
     }
   }
-  Share big, rest;
-  ZPL_TRY(share(big_words, L.sim.n_big, waves, P.max_room[0], big));
-  ZPL_TRY(share(area - big_words, std::min(P.n_bpure, c->n_cu) - big.grid, waves, small_room, rest));
-  L.sim.big_wgs = big.grid;
-  L.sim.big_waves = big.waves;
-  L.sim.big_stride = big.stride;
-  L.sim.big_area = big_words;
-  L.sim.waves = rest.waves;
-  L.sim.stride = rest.stride;
-  L.sim.batch_wgs = big.grid + rest.grid;
-  L.sim.grid = std::min(L.sim.lane_wgs + L.sim.batch_wgs, c->n_cu);
-  ZPL_TRY(share(area, P.n_bcut, P.unit_waves[1], P.max_room[1], L.cut));
+  if (!place_sim(L.sim, total, P.n_bpure, waves, P.max_room[0], small_room, c->n_cu))
+    return none(P.max_room[0]);
+  // the other kernels run after it
+  L.cut = share_scratch(total, P.n_bcut, P.unit_waves[1], P.max_room[1], c->n_cu);
+  if (P.n_bcut > 0 && L.cut.grid == 0) return none(P.max_room[1]);
   // Replicates that may escalate: those of the lane form with more than kLaneCap
   // draws, and those whose room is not all of their draws.
-  if (P.lane_n > kLaneCap || P.bounded) ZPL_TRY(share(area, 64, kEscWaves, P.max_n, L.esc));
+  if (P.lane_n > kLaneCap || P.bounded) {
+    L.esc = share_scratch(total, 64, kEscWaves, P.max_n, c->n_cu);
+    if (L.esc.grid == 0) return none(P.max_n);
+  }
   if (need_dbuf) ZPL_TRY(ensure(c, c->dbuf, sizeof(double) * (size_t)P.total_R));
   // bracket gather: at most ~12% of a cell's replicates fall in a bracket
   int64_t maxR = 1;
@@ -801,12 +811,11 @@ zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, O
   HIP_TRY(mark(1));
   const Unit* units = (const Unit*)(plan + L.lay.units);
   const Unit* hunits = (const Unit*)(plan + L.lay.hunits);
-  int64_t* slots = (int64_t*)c->heavy.p;
-  int64_t* scratch = slots + L.slots;
+  int64_t* scratch = (int64_t*)c->heavy.p;
   auto simulate = [&](const SimGrid& g, const Unit* u, int nu, uint32_t* queue, int nb) {
     return launch_simulate(g, dcells, (const double*)c->tables.p, (const uint16_t*)c->guides.p,
                            c->ln, u, nu, hunits, nb, queue, queues + 2, queues + 5, out,
-                           (uint64_t*)c->esc.p, escc, c->esc_cap, slots, scratch, err, s);
+                           (uint64_t*)c->esc.p, escc, c->esc_cap, scratch, err, s);
   };
   if (launch == ZPL_LAUNCH_PLAIN) {  // the lane-form cells one by one, then the others
     for (int i = 0; i < nc; ++i) {
@@ -816,6 +825,7 @@ zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, O
       SimGrid g = {};
       g.grid = g.lane_wgs = grid;
       g.lane_waves = L.sim.lane_waves;
+      g.lane_area = L.sim.lane_area;
       HIP_TRY(simulate(g, units + b, e - b, queues + 8 + i, 0));
     }
     if (P.n_bpure > 0) {

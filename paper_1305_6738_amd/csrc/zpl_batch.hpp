@@ -1265,21 +1265,34 @@ struct HeadOut {
   double a, iz, z16, D;
   uint32_t flags, done;
 };
-// The distinct values of stored counts 1..K, K <= kHW, as ks_distance_trunc takes them.
+// The distinct values of stored counts 1..K, K <= kHW, as ks_distance_trunc takes
+// them.  Read 16 bytes at a time: the lanes' replicates lie 2 KiB apart, and a
+// load for every value took longer than the terms.
 struct CountSrc {
   CountView cv;
   uint32_t K;
-  uint32_t v;  // next value above 16
-  __device__ __forceinline__ uint32_t small(int x) const {
-    return (uint32_t)x <= K ? cv.at(x - 1) : 0u;
+  uint32_t v;      // next value above 16
+  uint64_t lo, hi;  // counts of v and up, as far as they are read
+  __device__ __forceinline__ void load(int b) {  // from bin b, a multiple of 8
+    const uint4 w = *reinterpret_cast<const uint4*>(cv.wide ? cv.p + b : cv.p + (b >> 1));
+    lo = (uint64_t)w.y << 32 | w.x;
+    hi = (uint64_t)w.w << 32 | w.z;
+  }
+  __device__ __forceinline__ uint32_t small(int x) {  // x = 1..16 in order
+    if (cv.wide) return (uint32_t)x <= K ? cv.at(x - 1) : 0u;
+    if ((x & 7) == 1) load(x - 1);
+    const uint32_t c = (uint32_t)((((x - 1) & 4) ? hi : lo) >> (16 * ((x - 1) & 3))) & 0xffffu;
+    return (uint32_t)x <= K ? c : 0u;
   }
   __device__ __forceinline__ bool next_large(int64_t& x, uint32_t& c) {
-    for (; v <= K; ++v) {
-      c = cv.at((int)v - 1);
-      if (c) {
-        x = (int64_t)v++;
-        return true;
-      }
+    const int bits = cv.wide ? 32 : 16;
+    while (v <= K) {
+      if (((v - 1u) & (cv.wide ? 3u : 7u)) == 0u) load((int)v - 1);
+      c = cv.wide ? (uint32_t)lo : (uint32_t)lo & 0xffffu;
+      lo = lo >> bits | hi << (64 - bits);
+      hi >>= bits;
+      x = (int64_t)v++;
+      if (c) return true;
     }
     return false;
   }
@@ -1324,7 +1337,7 @@ static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin
     if constexpr (kLaw == kTrunc) {
       o.a = mle_alpha_trunc(Sd / (double)n, K, ln, &o.flags);
       if (!trunc_em(o.a, K)) {
-        CountSrc src{cv, K, 17};
+        CountSrc src{cv, K, 17, 0, 0};
         o.D = ks_distance_trunc(src, o.a, K, n, ln);
         o.iz = 1.0;
         o.z16 = 0.0;
@@ -1560,15 +1573,14 @@ __global__ __launch_bounds__(kBlock, 3) void k_simulate(
     const uint16_t* __restrict__ guides, const double* __restrict__ ln,
     const Unit* __restrict__ lane_units, int n_lane, const Unit* __restrict__ batch_units,
     int n_batch, uint32_t* lane_queue, uint32_t* batch_queue, uint32_t* big_queue, Outputs out,
-    uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* slots, int64_t* scratch,
-    uint32_t* err) {
+    uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap, int64_t* scratch, uint32_t* err) {
   __shared__ KernelLds<SimRegion, kWaves> L;
   const int wave = (int)threadIdx.x >> 6;
   const int lane = lane_id();
   int loaded = -1;
   Unit un;
   if ((int)blockIdx.x < g.lane_wgs) {
-    int64_t* mine = slots + ((int64_t)blockIdx.x * g.lane_waves + wave) * kLaneScratch;
+    int64_t* mine = scratch + (int64_t)blockIdx.x * g.lane_area + (int64_t)wave * kLaneScratch;
     while (next_unit(L, lane_queue, lane_units, n_lane, cells, tables, guides, loaded, un,
                      kBlock)) {
       const int first = wave * 64;
@@ -1584,8 +1596,9 @@ __global__ __launch_bounds__(kBlock, 3) void k_simulate(
   bool big = b < g.big_wgs;
   const int waves = big ? g.big_waves : g.waves;
   const int64_t stride = big ? g.big_stride : g.stride;
-  int64_t* mine = scratch + (big ? 0 : g.big_area) +
-                  ((int64_t)(big ? b : b - g.big_wgs) * waves + wave) * stride;
+  int64_t* mine = scratch + wave * stride +
+                  (big ? g.big_area + (int64_t)b * waves * stride
+                       : g.rest + (int64_t)(b - g.big_wgs) * g.area);
   for (;;) {
     if (!next_unit(L, big ? big_queue : batch_queue, big ? batch_units : batch_units + g.n_big,
                    big ? g.n_big : n_batch - g.n_big, cells, tables, guides, loaded, un, kBlock)) {

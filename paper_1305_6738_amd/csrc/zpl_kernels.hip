@@ -1948,11 +1948,11 @@ hipError_t launch_simulate(const SimGrid& g, const DevCell* cells, const double*
                            int n_lane, const Unit* batch_units, int n_batch, uint32_t* lane_queue,
                            uint32_t* batch_queue, uint32_t* big_queue, Outputs out,
                            uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap,
-                           int64_t* slots, int64_t* scratch, uint32_t* err, hipStream_t s) {
+                           int64_t* scratch, uint32_t* err, hipStream_t s) {
   if (g.grid <= 0) return hipSuccess;
   k_simulate<<<g.grid, kBlock, 0, s>>>(g, cells, tables, guides, ln, lane_units, n_lane,
                                        batch_units, n_batch, lane_queue, batch_queue, big_queue,
-                                       out, esc_list, esc_count, esc_cap, slots, scratch, err);
+                                       out, esc_list, esc_count, esc_cap, scratch, err);
   return hipGetLastError();
 }
 

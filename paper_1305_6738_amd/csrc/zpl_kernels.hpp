@@ -111,12 +111,15 @@ struct Unit {
 // lane-form units (of at most 64 lane_waves replicates), the last batch_wgs
 // wave- and heavy-form ones.  Of those the first big_wgs take the first n_big
 // units before the others, by big_waves waves with big_stride int64 of scratch
-// each; the other workgroups' waves (`waves` of them, `stride` each) have theirs
-// from big_area on.
+// each; in the other workgroups it is `waves` with `stride` each.  Workgroup g of
+// the lane form has its slots at lane_area g of the scratch, workgroup b of the
+// others its waves' scratch at big_area + big_waves big_stride b, or at rest +
+// area (b - big_wgs).  (A workgroup that takes both kinds may have both at one place: it
+// ends the one before it begins the other.)
 struct SimGrid {
   int32_t grid, lane_wgs, lane_waves, batch_wgs;
   int32_t n_big, big_wgs, big_waves, waves;
-  int64_t big_stride, big_area, stride;
+  int64_t lane_area, big_area, big_stride, rest, area, stride;
 };
 
 struct Outputs {

@@ -16,14 +16,15 @@ hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t s);
 hipError_t launch_tables(DevCell* cells, int n_cells, double* tables, uint16_t* guides,
                          const double* ln, hipStream_t s, bool any_trunc = true,
                          uint32_t* zero = nullptr, int n_zero = 0);
-// Lane-form units and wave- and heavy-form ones in one launch; slots: lane_wgs
-// * lane_waves areas of kLaneScratch int64; scratch: the waves' areas (SimGrid).
+// Lane-form units and wave- and heavy-form ones in one launch; scratch: the lane
+// form's slots (kLaneScratch int64 a wave) and the other waves' areas, as SimGrid
+// places them.
 hipError_t launch_simulate(const SimGrid& g, const DevCell* cells, const double* tables,
                            const uint16_t* guides, const double* ln, const Unit* lane_units,
                            int n_lane, const Unit* batch_units, int n_batch, uint32_t* lane_queue,
                            uint32_t* batch_queue, uint32_t* big_queue, Outputs out,
                            uint64_t* esc_list, uint32_t* esc_count, uint32_t esc_cap,
-                           int64_t* slots, int64_t* scratch, uint32_t* err, hipStream_t s);
+                           int64_t* scratch, uint32_t* err, hipStream_t s);
 // The escalated replicates; scratch: grid * waves areas (waves <= kEscWaves) of `stride`
 // int64, each for a replicate's every draw.  Grid 0 (no replicate can escalate): no launch.
 hipError_t launch_escalated(int grid, const DevCell* cells, const double* tables,

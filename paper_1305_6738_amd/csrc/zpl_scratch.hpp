@@ -60,6 +60,47 @@ inline bool split_batch(int64_t area, int64_t units, int waves, int64_t max_room
   return true;
 }
 
+// The simulation kernel's scratch of `total` int64: g's lane_wgs, lane_waves and
+// n_big given, `units` units of the wave and heavy forms of up to `waves` waves
+// each, the first n_big of rooms up to max_room and the others of up to small_room.
+// False when a replicate does not fit.
+inline bool place_sim(SimGrid& g, int64_t total, int64_t units, int waves, int64_t max_room,
+                      int64_t small_room, int n_cu) {
+  const int64_t slots = (int64_t)g.lane_wgs * g.lane_waves * kLaneScratch, area = total - slots;
+  // (multiples of 32, so that whole records and counts stay aligned)
+  const int64_t big_words = g.n_big > 0 ? (area - area / 4) & ~(int64_t)31 : 0;
+  const Share big = share_scratch(big_words, g.n_big, waves, max_room, n_cu);
+  const int64_t others = units > g.n_big ? std::min<int64_t>(units, n_cu) - big.grid : 0;
+  const Share rest = share_scratch(area - big_words, others, waves, small_room, n_cu);
+  if ((g.n_big > 0 && big.grid == 0) || (others > 0 && rest.grid == 0)) return false;
+  g.lane_area = (int64_t)g.lane_waves * kLaneScratch;
+  g.big_wgs = big.grid;
+  g.big_waves = big.waves;
+  g.big_stride = big.stride;
+  g.big_area = slots;
+  g.waves = rest.waves;
+  g.stride = rest.stride;
+  g.rest = slots + big_words;
+  g.area = rest.waves * rest.stride;
+  g.batch_wgs = big.grid + rest.grid;
+  g.grid = std::min(g.lane_wgs + g.batch_wgs, n_cu);
+  // Where workgroups take units of both kinds, one after the other, each has an
+  // equal part of all the scratch for both: beside them the slots leave a wave 8
+  // replicates at a time (K = 50, n = 100, 12 exponents of which two are in the
+  // wave form: 1.61 ms, 0.92 with whole batches).
+  if (big.grid == 0 && rest.grid > 0 && g.lane_wgs + rest.grid > g.grid) {
+    const int64_t part = total / g.grid & ~(int64_t)31;
+    const Share one = share_scratch(part, 1, waves, small_room, n_cu);
+    if (part >= g.lane_area && one.waves >= rest.waves && one.stride > rest.stride) {
+      g.lane_area = g.area = part;
+      g.rest = (int64_t)(g.grid - rest.grid) * part;
+      g.waves = one.waves;
+      g.stride = one.stride;
+    }
+  }
+  return true;
+}
+
 // int64 of scratch for a call's replicates: the lane form's slots, then what the
 // waves of the other forms share.  It follows the forms: kFormScratch for each
 // wave of a workgroup per kBlock lane- and wave-form replicates (2.8 MiB a

@@ -31,6 +31,8 @@ def sc(tmp_path_factory):
     L.sc_area.argtypes = [i64, i64, i64, i64, C.c_uint64, C.c_int]
     L.sc_share.argtypes = [i64, i64, C.c_int, i64, C.c_int, C.POINTER(i64)]
     L.sc_first_room.argtypes = [i64, i64]
+    L.sc_place.argtypes = [i64, C.c_int, C.c_int, i64, i64, C.c_int, i64, i64, C.c_int,
+                           C.POINTER(i64)]
     L.sc_split.argtypes = [i64, i64, C.c_int, i64, C.c_int, C.POINTER(i64)]
     return L
 
@@ -94,3 +96,47 @@ def test_equal_cells_are_not_split(sc):
     limit = C.c_int64()
     area = sc.sc_area(2500, 0, 10000, 4096, BUDGET, N_CU)
     assert sc.sc_split(area, 1700, sc.sc_waves(), 2200, N_CU, C.byref(limit)) == 0
+
+
+def place(sc, total, lane_wgs, lane_waves, units, n_big, waves, max_room, small_room):
+    stride = C.c_int64()
+    r = sc.sc_place(total, lane_wgs, lane_waves, units, n_big, waves, max_room, small_room, N_CU,
+                    C.byref(stride))
+    return r, stride.value
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_places_do_not_overlap(sc, seed):
+    """Lane units, long and short units of the other forms in every mixture."""
+    rng = random.Random(seed)
+    for _ in range(3000):
+        n = int(10 ** rng.uniform(1, 8))
+        lane_R = rng.choice([0, int(10 ** rng.uniform(0, 6))])
+        block = rng.choice([64, 128, 192, 256, 384, 768])
+        lane_wgs = min(N_CU, -(-lane_R // block))
+        wave_R = rng.choice([0, int(10 ** rng.uniform(0, 6))])
+        heavy_R = rng.choice([0, int(10 ** rng.uniform(0, 5))])
+        sim_units = -(-lane_R // 768) + -(-wave_R // 768)
+        if lane_wgs * block // 64 > max(1, min(sim_units, N_CU)) * 12:
+            continue  # (the planner's lane units never outnumber what they bring in)
+        total = sc.sc_area((heavy_R + 7) // 8, sim_units, n, 4096 if heavy_R else 0, BUDGET, N_CU)
+        step = rng.randint(1, 12)
+        units = -(-(wave_R + heavy_R) // step)
+        n_big = rng.choice([0, 0, rng.randint(0, units)])
+        room = rng.randint(1, n)
+        small = room if n_big == 0 else min(room, rng.randint(1, 400))
+        if n_big == units:
+            small, n_big = room, 0
+        r, _ = place(sc, total, lane_wgs, block // 64, units, n_big, step, room, small)
+        if n_big == 0 and lane_wgs == 0:
+            assert r == 0
+        assert r in (0, 1), (seed, n, lane_wgs, block, units, n_big, step, room, small)
+
+
+def test_both_kinds_share_a_place(sc):
+    """A table of 12 exponents, 50,000 replicates of 100 draws each, ten in the
+    lane form and two in the wave form: whole batches of 64 (384 words of records
+    and 256 of counts a replicate)."""
+    total = sc.sc_area(0, 792, 100, 0, BUDGET, N_CU)
+    r, stride = place(sc, total, N_CU, 12, 1000, 0, sc.sc_waves(), 100, 100)
+    assert r == 0 and stride >= 384 + 64 * 256 + 100
