@@ -375,6 +375,10 @@ __device__ __forceinline__ uint64_t lane_bucket_start(int b) {
   return (uint64_t)(8 + ((b + 4) & 7)) << (2 + ((b + 4) >> 3));
 }
 
+// Lanes with up to this many such values do without the buckets, whose edges take
+// up to 63 survival sums a lane: 100,000 replicates of 10 draws at alpha = 1.2 took
+// 271 us with them, 201 without.
+constexpr int kLaneFew = 12;
 // The finish's use of the wave's LDS region once the columns are read.
 typedef __attribute__((address_space(3))) uint8_t LdsU8;
 typedef __attribute__((address_space(3))) uint64_t LdsU64;
@@ -512,11 +516,15 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
   LdsU32* ends = region + 16 * kLaneBuckets;       // 64 inclusive counts
   LdsU64* dmax = (LdsU64*)(ends + 64);             // 64 distances
   LdsU64* pairs = dmax + 64;                       // kLanePairs values
+  // few values in every lane: all are in reach of one bucket from kHLB + 1 on
+  const bool few = __ballot(live && oc > kLaneFew) == 0ull;
+  uint64_t um = few && live ? ~0ull : 0ull;  // buckets in reach
+  if (!few) {
 #pragma unroll 4
-  for (int k = lane; k < 16 * kLaneBuckets; k += 64) region[k] = 0u;
-  wave_sync();
-  uint64_t um = 0ull;  // buckets in reach
-  if (live) {
+    for (int k = lane; k < 16 * kLaneBuckets; k += 64) region[k] = 0u;
+    wave_sync();
+  }
+  if (live && !few) {
     for (int q = 0; q < oc; ++q) {
       LdsU8* c = cum + 64 * lane_bucket((uint64_t)ov(q)) + lane;
       *c = (uint8_t)(*c + 1u);
@@ -546,8 +554,8 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
       if (__longlong_as_double(more[64 * b]) > Dlow - kPruneMargin) um |= 1ull << b;
   }
   uint64_t pm = 0ull;  // buckets whose first value's predecessor was drawn
-  uint32_t cnt = 0;
-  if (um != 0ull) {
+  uint32_t cnt = few && live ? (uint32_t)oc : 0u;
+  if (um != 0ull && !few) {
 #pragma unroll 4
     for (int q = 0; q < oc; ++q) {
       const uint64_t v = (uint64_t)ov(q);
@@ -600,8 +608,8 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
       const uint32_t io = (uint32_t)__shfl((int)info, owner, 64);
       if (valid) {
         const int64_t v = (int64_t)pairs[f - done];
-        const int b = lane_bucket((uint64_t)v);
-        const int64_t start = (int64_t)lane_bucket_start(b);
+        const int b = few ? 0 : lane_bucket((uint64_t)v);
+        const int64_t start = few ? kHLB + 1 : (int64_t)lane_bucket_start(b);
         uint32_t lt = 0, eq = 0;
         bool pres = v == kHLB + 1 ? (io >> 16) != 0u : (v == start && ((pmo >> b) & 1ull) != 0ull);
         for (uint32_t k = e0 - done; k < e1 - done; ++k) {
@@ -610,7 +618,7 @@ static __device__ __noinline__ LaneOut lane_finish(LdsU32* region, int64_t* slot
           eq += x == v ? 1u : 0u;
           pres = pres || (x == v - 1 && x >= start);
         }
-        const uint32_t Cb = nu - (io & 0xffffu) + cum[64 * b + owner] + lt;
+        const uint32_t Cb = nu - (io & 0xffffu) + (few ? 0u : (uint32_t)cum[64 * b + owner]) + lt;
         const EmCoef Eo = em_coef(as);
         TruncEnd to = {};
         if constexpr (kTruncLaw) to = trunc_end(Eo, K, ln);
