@@ -635,14 +635,19 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
   for (int i : batch_cells)
     batch_work += (double)P.cells[i].R * ((double)P.cells[i].n + 2000.0);
   // A lane-form unit is kBlock replicates when there are enough to give the
-  // compute units that the lane form's share of the work comes to one each;
-  // else fewer, down to one wave's (of the sizes that divide kBlock), so that
-  // they all have one: 10,000 replicates of 100 draws alone measured 96 us in
-  // 14 workgroups and 42 us in 157.
+  // compute units that the lane form's share of the work comes to one each; else
+  // fewer, down to one wave's, so that they all have one: 10,000 replicates of 100
+  // draws alone measured 96 us in 14 workgroups and 42 us in 157; 100,000 of 30
+  // draws at alpha = 1.2 342 us in 131 and 292 in 224.  (Units whose slots would
+  // exceed what kBlock-sized ones bring in are not taken.)
   const double cus = std::max(1.0, n_cu * lane_work / std::max(lane_work + batch_work, 1.0));
-  for (int b : {64, 128, 192, 256, 384, kBlock}) {
+  for (int b = 64; b <= kBlock; b += 64) {
     P.lane_block = b;
-    if ((double)lane_R <= cus * b) break;
+    int64_t units = 0;
+    for (const Run& g : runs) units += (g.r_end + b - 1) / b;
+    if ((double)units <= cus &&
+        units * (b / 64) * kLaneScratch <= std::min<int64_t>(P.sim_units, n_cu) * kWaves * kFormScratch)
+      break;
   }
   for (const Run& g : runs)
     n_units += (size_t)((g.r_end + P.lane_block - 1) / P.lane_block);
