@@ -350,23 +350,33 @@ bool form_eligible(uint32_t m, double alpha, int64_t n, uint32_t K = 0) {
 
 // Estimated cost (ns per replicate, device busy) of a replicate of the
 // truncated law on 1..K with n draws, in the lane or wave form: about 2.2 ps
-// per draw and 19 ps per support value (sums of the MLE and the KS distance),
-// measured on MI355X over the paper's sample sizes at K = 20 and K = 1000.
-double trunc_cost(int64_t n, uint32_t K) { return 2.2e-3 * ((double)n + 8.6 * (double)K); }
+// per draw, and 19 ps per support value where the MLE's and the KS's sums have K
+// terms (K = 20), or 4.5 ns from the K on that takes Euler-Maclaurin sums
+// (K = 1,000: 200 draws 5.3, 1,000 draws 5.2 to 7.9).
+double trunc_cost(int64_t n, uint32_t K) {
+  return 2.2e-3 * (double)n + (K >= kTruncEmK ? 4.5 : 0.019 * (double)K);
+}
 
 // The truncated law by Euler-Maclaurin sums, more than a few values above the
 // lane's column: the lane form finishes 64 replicates at once, where the batch
 // takes them one by one, but each of a lane's values above the column costs as
-// many comparisons as there are.  ns per replicate with the device busy, lane
-// and batch, K = 1,000: alpha 1.0, 200 draws (81 above) 5.3 and 7.7, 400 (162)
-// 15.6 and 8.9; alpha 1.5, 1,000 draws (88) 7.9 and 8.5; alpha 2, 1,000 draws
-// (12) 5.2 and 7.6, 3,000 (36) 13.6 and 11.5.  A round of lanes takes about
-// 0.4 us per draw however few they are, the batch 12.5 ns per replicate of a
-// call with few: at R = 32 n they meet (1,000 draws, 30,000 replicates: 606 and
-// 618 us; 10,000: 552 and 298).  Cells of fewer than 16 draws stay in the wave
-// form, whose choice for them is part of the tested interface.
+// many comparisons as there are, and a round of lanes takes as long for few
+// replicates as for many.
+// Replicates of the call at which the two meet, by values above the column (and
+// draws): 10 (24) 6,000; 20 (21) 10,000; 40 (98) 20,000, (42) 60,000, (455) 50,000;
+// 84 (956) 100,000, (207) 170,000, (84) more than 200,000: about 100 per draw and
+// 56 per pair of values times the part of the draws that they are.
+// The most values that pay on a full device, from tables of 12 exponents, 50,000
+// replicates, with lanes for up to 40, 64 and 84: K = 161, n = 100 1,013, 912, 910 us,
+// n = 200 1,382, 1,237, 1,403; K = 500, n = 200 1,592, 1,594, 1,463; K = 1,000, n = 100
+// 1,606, 1,258, 1,227.  Cells of up to 10 draws stay in the wave form: the choice for
+// 10 is part of the tested interface (it costs a column of K = 1,000, 50,000
+// replicates, 341 us instead of 153).
 bool lane_truncated(double alpha, int64_t n, uint32_t K, int64_t R) {
-  return n >= 16 && n <= 2000 && (double)n * tail_prob(alpha, kHLB, K) <= 84.0 && R >= 32 * n;
+  if (n <= 10 || n > 2000) return false;
+  const double p = tail_prob(alpha, kHLB, K), above = (double)n * p;
+  return above <= (K < 300 ? 64.0 : 84.0) &&
+         (double)R >= 100.0 * (double)n + 56.0 * above * above * p;
 }
 
 // Time for one cell alone under form f (tuned cost v ns per replicate with
@@ -388,13 +398,12 @@ double cell_makespan(int f, double v, int64_t R, int n_cu) {
 // (no table, or the truncated law): the lane form when a replicate's values
 // above its column are few, else the wave form when its overflow area holds
 // them, else the heavy form.
-uint32_t choose_form(double alpha, int64_t n, const Tuning* t, uint32_t K = 0, int64_t R = 0,
-                     int n_cu = 256, double horizon = -1.0, double* cost = nullptr) {
+uint32_t choose_form(double alpha, int64_t n, const Tuning* t, uint32_t K, int64_t R,
+                     int64_t trunc_R, int n_cu, double horizon, double* cost = nullptr) {
   if (cost) *cost = 0.0;
   if (K > 0) {
     // the table measures the pure law; the truncated law's cost is mostly
-    // its finite sums (K terms per MLE step), which the heavy form runs one
-    // replicate per wave: the built-in rule below, with an estimated cost
+    // its sums: the built-in rule below, with an estimated cost
     if (cost && t && !t->empty()) *cost = trunc_cost(n, K) * (double)R;
   } else if (t && !t->empty()) {
     int best = -1, fast = -1;
@@ -424,11 +433,11 @@ uint32_t choose_form(double alpha, int64_t n, const Tuning* t, uint32_t K = 0, i
   // 10,000 draws at alpha 3.5: 2,525 us and 94, 320,000 5,695 and 5,657; 12 columns
   // of K = 20, n = 50,000 with 333: 12,479 and 599.  Shorter ones keep the lanes: the choice there
   // is part of the tested interface.)
-  const bool rounds = R >= 32 * n;
+  const bool rounds = (K ? trunc_R : R) >= 32 * n;
   if (n <= 65535 && (double)n * tail_prob(alpha, kHLB, K) <= 2.0 &&
       (n <= (K ? 5000 : 1000) || rounds))
     return kModeLane;
-  if (K >= kTruncEmK && lane_truncated(alpha, n, K, R)) return kModeLane;
+  if (K >= kTruncEmK && lane_truncated(alpha, n, K, trunc_R)) return kModeLane;
   // The pure law without a table: the lane form wherever its slots hold the
   // values and there are enough replicates for a round of lanes (as above).  ns
   // per replicate, lane and batch: alpha 1.5, 1,000 draws 5.5 and 8.7; 2.0, 3,000
@@ -534,6 +543,11 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
   // the batch's work with every cell in its cheapest form: a cell that alone
   // would outlast it is given the form that finishes it soonest instead
   double horizon = -1.0;
+  int64_t trunc_R = 0;  // replicates of truncated cells
+  for (int i = 0; i < n_cells; ++i)
+    if (cells[i].kmax != 0 && cells[i].replicates > 0 &&
+        cells[i].replicates <= ((int64_t)1 << 32))
+      trunc_R += cells[i].replicates;
   if (form == ZPL_FORM_AUTO && tune && !tune->empty()) {
     horizon = 0.0;
     for (int i = 0; i < n_cells; ++i) {
@@ -544,7 +558,7 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
                                         z.alpha >= -64.0 && z.alpha <= 64.0);
       // (invalid cells are rejected below; cutoff cells run in the heavy form)
       if (valid && z.n >= 1 && z.replicates >= 1 && (z.xmin == 0 || z.xmin == 1))
-        (void)choose_form(z.alpha, z.n, tune, z.kmax, z.replicates, n_cu, -1.0, &c);
+        (void)choose_form(z.alpha, z.n, tune, z.kmax, z.replicates, trunc_R, n_cu, -1.0, &c);
       horizon += c;
     }
   }
@@ -591,7 +605,7 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
         break;
       case ZPL_FORM_WAVE: m = kModeWave; break;
       case ZPL_FORM_HEAVY: m = kModeHeavy; break;
-      default: m = choose_form(z.alpha, z.n, tune, z.kmax, z.replicates, n_cu, horizon);
+      default: m = choose_form(z.alpha, z.n, tune, z.kmax, z.replicates, trunc_R, n_cu, horizon);
     }
     // the lane and wave forms histogram values from 1; a cutoff law runs in
     // the heavy form, whose histogram and overflow list take any values
@@ -1181,7 +1195,7 @@ size_t fit_bytes(int64_t total_n, int n_sets, int64_t max_small, int n_small, in
 // fit to MI355X's tuned costs over the table's exponents and sizes).
 double replicate_cost(const zpl_ctx* c, double alpha, int64_t n) {
   double v;
-  (void)choose_form(alpha, n, &c->tune, 0, 1, c->n_cu, -1.0, &v);
+  (void)choose_form(alpha, n, &c->tune, 0, 1, 0, c->n_cu, -1.0, &v);
   if (v > 0.0) return v;
   return 2.2e-3 * (double)n * (1.0 + 90.0 * tail_prob(alpha, kHW)) + 2.5;
 }
