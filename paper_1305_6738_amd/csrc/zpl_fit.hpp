@@ -31,6 +31,12 @@ constexpr int64_t kFitGridMin = 32768;
 constexpr int64_t kFitChunkMin = 8192;
 constexpr int kFitGroups = 512;
 static_assert(kFitGroups <= kFitThreads, "k_fit_merge: a thread per group");
+// Datasets of up to kFitSmall values are counted and sorted by the workgroup of each
+// of up to kFitAlone candidates, two to a compute unit: one launch instead of two
+// (1,000 values, one candidate 46.5 and 41.2 us, 128 of them 79.7 and 75.1; 1,000
+// candidates take as long either way).
+constexpr int kFitSmall = 1024;
+constexpr int kFitAlone = 512;
 constexpr int kFitShares = 64;      // workgroups that share one distance, at most
 constexpr int kFitAcc = 128;        // candidates that may be shared
 constexpr int kFitFan = 16;         // runs merged per pass
@@ -608,33 +614,64 @@ __global__ __launch_bounds__(256) void k_fit_runs(int64_t n, int groups, int64_t
 
 // The fit with each candidate cutoff (xmins; without them the one fit from 1
 // on, with or without the upper limit K) from the counts and the sorted larger
-// values, `wgs` workgroups per candidate.  A candidate above every value gets
+// values, `wgs` workgroups per candidate.  kCount: of a dataset of up to kFitSmall
+// values, which each candidate's one workgroup counts and sorts itself.  A candidate above every value gets
 // D = +inf and status kErrNoTail; any value below 1 sets kErrBadValue.
 // One wave solves eq. 2 (latency: a chain of Newton steps), all share the
 // distance.  Registers for four workgroups per compute unit: 1,000 candidates
 // over 100,000 values take 77 us so, 86 us with two.
-__global__ __launch_bounds__(kFitCandThreads, 4) void k_fit_cand(
-    int64_t n, int groups, int64_t* scratch, const int64_t* __restrict__ xmins, int wgs, uint32_t K,
-    const double* __restrict__ ln, double* ahat_out, double* D_out, int64_t* ntail_out,
+template <bool kCount>
+__global__ __launch_bounds__(kCount ? kFitThreads : kFitCandThreads, 4) void k_fit_cand(
+    const int64_t* x, int64_t n, int groups, int64_t* scratch, const int64_t* __restrict__ xmins,
+    int wgs, uint32_t K, const double* __restrict__ ln, double* ahat_out, double* D_out, int64_t* ntail_out,
     uint32_t* flags_out, uint32_t* status_out) {
+  constexpr int kThreads = kCount ? kFitThreads : kFitCandThreads;
   __shared__ __align__(16) uint32_t hist[kFitBins];
   __shared__ uint32_t cum[kFitBins + 1];
   __shared__ FitSolved f;
-  __shared__ U128 part[kFitCandThreads / 64];
-  __shared__ uint32_t upart[kFitCandThreads / 64];
-  __shared__ double dpart[kFitCandThreads / 64];
+  __shared__ U128 part[kThreads / 64];
+  __shared__ uint32_t upart[kThreads / 64];
+  __shared__ double dpart[kThreads / 64];
   const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  constexpr int kWaves = kFitCandThreads / 64;
+  constexpr int kWaves = kThreads / 64;
+  __shared__ int64_t larger[kCount ? kFitSmall : 1];
+  __shared__ uint32_t ovc, sbad;
   const int cand = (int)blockIdx.x / wgs, share = (int)blockIdx.x % wgs;
   const FitView v = fit_view(scratch, n, groups);
   const int64_t xmin = xmins ? xmins[cand] : 1;
-  const int64_t oc = (int64_t)v.ctl[0];
-  const bool bad = v.ctl[1] != 0u;
-  const int64_t* ov = v.ctl[2] ? v.g0 : v.g1;
-  for (int k = 4 * tid; k < kFitBins; k += 4 * kFitCandThreads)
-    *reinterpret_cast<uint4*>(hist + k) = *reinterpret_cast<const uint4*>(v.hist + k);
+  U128 So = {0, 0};  // this thread's part of the larger values' sum of logarithms
+  int64_t oc;
+  bool bad;
+  const int64_t* ov;
+  if constexpr (kCount) {
+    for (int k = tid; k < kFitBins; k += kThreads) hist[k] = 0u;
+    if (tid == 0) ovc = sbad = 0u;
+    __syncthreads();
+    const FitCount r = fit_count<kThreads>(as_global(x), 0, n, K ? (int64_t)K : INT64_MAX,
+                                                  hist, &ovc, larger, ln);
+    if (r.bad) atomicOr(&sbad, 1u);
+    So = r.S;
+    __syncthreads();
+    oc = (int64_t)ovc;
+    bad = sbad != 0u;
+    ov = larger;
+    if (oc > 1) {
+      const int P = next_pow2((int)oc);
+      for (int k = (int)oc + tid; k < P; k += kThreads) larger[k] = INT64_MAX;
+      block_sort_pow2(larger, P, tid, kThreads);
+    }
+  } else {
+    oc = (int64_t)v.ctl[0];
+    bad = v.ctl[1] != 0u;
+    ov = v.ctl[2] ? v.g0 : v.g1;
+    if (tid == 0)
+      So = U128{(uint64_t)v.ctl[4] | (uint64_t)v.ctl[5] << 32,
+                (uint64_t)v.ctl[6] | (uint64_t)v.ctl[7] << 32};
+    for (int k = 4 * tid; k < kFitBins; k += 4 * kThreads)
+      *reinterpret_cast<uint4*>(hist + k) = *reinterpret_cast<const uint4*>(v.hist + k);
+  }
   __syncthreads();
-  fit_prefix<kFitCandThreads>(hist, cum, upart);
+  fit_prefix<kThreads>(hist, cum, upart);
   const int64_t p0 = xmin > kFitBins + 1 && !bad ? lower_bound_i64(ov, 0, oc, xmin) : 0;
   const int64_t nt = xmin > kFitBins + 1 ? oc - p0
                                          : (int64_t)cum[kFitBins] - (int64_t)cum[xmin - 1] + oc;
@@ -651,14 +688,13 @@ __global__ __launch_bounds__(kFitCandThreads, 4) void k_fit_cand(
     return;
   }
   U128 S = {0, 0};
-  if (xmin <= kFitBins) S = fit_bin_sum<kFitCandThreads>(hist, xmin, ln);
+  if (xmin <= kFitBins) S = fit_bin_sum<kThreads>(hist, xmin, ln);
   if (xmin > kFitBins + 1) {
-    for (int64_t p = p0 + tid; p < oc; p += kFitCandThreads) u128_add(S, ln_fixed(ov[p], ln), 0);
-  } else if (tid == 0) {
-    u128_add(S, (uint64_t)v.ctl[4] | (uint64_t)v.ctl[5] << 32,
-             (uint64_t)v.ctl[6] | (uint64_t)v.ctl[7] << 32);
+    for (int64_t p = p0 + tid; p < oc; p += kThreads) u128_add(S, ln_fixed(ov[p], ln), 0);
+  } else {
+    u128_add(S, So.lo, So.hi);
   }
-  S = block_sum_u128<kFitCandThreads>(S, part);
+  S = block_sum_u128<kThreads>(S, part);
   if (wave == 0) {
     bool atmin;
     if (xmin <= kFitBins)

@@ -2053,8 +2053,9 @@ hipError_t launch_fit_one(const int64_t* x, int64_t n, const double* ln, int64_t
   int groups = 0;
   const hipError_t e = launch_fit_prepare(x, n, K, ln, scratch, &groups, s);
   if (e != hipSuccess) return e;
-  k_fit_cand<<<kFitShares, kFitCandThreads, 0, s>>>(n, groups, scratch, nullptr, kFitShares, K, ln,
-                                                    ahat, D, nullptr, flags, status);
+  k_fit_cand<false><<<kFitShares, kFitCandThreads, 0, s>>>(nullptr, n, groups, scratch, nullptr,
+                                                           kFitShares, K, ln, ahat, D, nullptr,
+                                                           flags, status);
   return hipGetLastError();
 }
 
@@ -2072,6 +2073,11 @@ hipError_t launch_fit_scan(const int64_t* x, int64_t n, const int64_t* xmins, in
                            const double* ln, int64_t* scratch, double* ahat, double* D,
                            int64_t* ntail, uint32_t* flags, uint32_t* status, hipStream_t s) {
   if (n_cand <= 0) return hipSuccess;
+  if (n <= kFitSmall && n_cand <= kFitAlone) {
+    k_fit_cand<true><<<n_cand, kFitThreads, 0, s>>>(x, n, 0, scratch, xmins, 1, 0u, ln, ahat, D,
+                                                        ntail, flags, status);
+    return hipGetLastError();
+  }
   int groups = 0;
   const hipError_t e = launch_fit_prepare(x, n, 0u, ln, scratch, &groups, s);
   if (e != hipSuccess) return e;
@@ -2080,8 +2086,8 @@ hipError_t launch_fit_scan(const int64_t* x, int64_t n, const int64_t* xmins, in
   const int most = n < kFitGridMin ? 8 : kFitShares;
   int wgs = n_cand <= kFitAcc ? 256 / n_cand : 1;
   if (wgs > most) wgs = most;
-  k_fit_cand<<<n_cand * wgs, kFitCandThreads, 0, s>>>(n, groups, scratch, xmins, wgs, 0u, ln, ahat,
-                                                      D, ntail, flags, status);
+  k_fit_cand<false><<<n_cand * wgs, kFitCandThreads, 0, s>>>(nullptr, n, groups, scratch, xmins, wgs,
+                                                             0u, ln, ahat, D, ntail, flags, status);
   return hipGetLastError();
 }
 
