@@ -634,7 +634,6 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
   std::vector<Run> runs;
   std::vector<int> batch_cells;
   size_t n_units = 0;
-  int64_t lane_R = 0;
   double lane_work = 0.0, batch_work = 0.0;
   for (int i = 0; i < n_cells; ++i) {
     const DevCell& d = P.cells[i];
@@ -651,7 +650,6 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
     }
     runs.push_back({w, i, 0, d.R});
     P.lane_n = std::max(P.lane_n, d.n);
-    lane_R += d.R;
     lane_work += (double)d.R * ((double)d.n + 200.0);
   }
   for (int i : batch_cells)
@@ -2092,7 +2090,7 @@ zpl_status zpl_sample_draws(zpl_ctx* c, double alpha, uint32_t kmax, int64_t xmi
   HIP_TRY(launch_fill_u32(flags_out, (int)count, 0u, s));
   HIP_TRY(launch_draws((const DevCell*)c->plan.p, (const double*)c->tables.p,
                        (const uint16_t*)c->guides.p, rep_lo, count, x_out, flags_out,
-                       count * n, s));
+                       count * ((n + 3) / 4 * 4), s));
   return ZPL_OK;
 }
 

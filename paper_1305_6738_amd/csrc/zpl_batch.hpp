@@ -271,7 +271,6 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
     w.te = trunc_end(w.E, (uint32_t)__builtin_amdgcn_readfirstlane((int)K_), ln);
   const int64_t off = w.xmin - 1;
   const int jh = off < 16 ? 16 - (int)off : 0;  // values up to 16
-  const uint64_t below = lanes_below(lane);
   double D = D0;  // the lane's largest term
   // the two terms of a sample value v: zv and zv1 the survival sums past v and
   // past v - 1, Cb draws below v, c equal to it
@@ -401,7 +400,8 @@ static __device__ __noinline__ double ks_rest(double a, double iz, int64_t xmin_
     const uint32_t cr = lower + dpp_incl_scan_u32(cs), cl = cr - cs;
     const bool real = B.sh >= 0 || lane < (kBuckets >> kBucketBits);
     auto right = [&](int b) {
-      return (int64_t)min((uint64_t)off + B.end(b), (uint64_t)INT64_MAX);
+      const uint64_t e = (uint64_t)off + B.end(b);
+      return e < (uint64_t)INT64_MAX ? (int64_t)e : INT64_MAX;
     };
     const double zo = w.survival(right(real ? 16 * lane + 15 : 15), ln);
     const double zlo = B.sh >= 0 && B.lo > (uint64_t)kHW
@@ -664,7 +664,8 @@ static __device__ __noinline__ double ks_many(double a, double iz, int64_t xmin_
     for (int k = 0; k < 16; ++k) cs += tab[16 * lane + k];
     const uint32_t cr = lower + dpp_incl_scan_u32(cs), cl = cr - cs;
     auto right = [&](int b) {
-      return (int64_t)min((uint64_t)off + B.end(b), (uint64_t)INT64_MAX);
+      const uint64_t e = (uint64_t)off + B.end(b);
+      return e < (uint64_t)INT64_MAX ? (int64_t)e : INT64_MAX;
     };
     // (S_n is known at the edges of the range's own bins only)
     const bool real = 16 * lane + 15 < nbins;
@@ -1072,7 +1073,7 @@ static __device__ __noinline__ DrawOut draw_replicate(const DevCell* cell, uint3
       // values 1..3 into the lane's own counters, what is above 1..kHW into the
       // pad
       const uint32_t at = z[d] < 12u ? (z[d] << 6) + own : min(z[d], 4u * (uint32_t)kWavePad) + bins;
-      lds_inc((LdsU32*)at);
+      lds_inc((LdsU32*)(uintptr_t)at);
       // the largest offset, marks left out: they are negative in 16 bits
       asm("v_max_i16 %0, %0, %1" : "+v"(xm) : "v"(z[d]));
     }

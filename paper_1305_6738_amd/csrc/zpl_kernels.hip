@@ -62,58 +62,14 @@ __device__ __forceinline__ uint32_t place_below(uint64_t mask, uint32_t base = 0
 // Inverse-CDF sampling: x = min{k in 1..kH : T[k] >= U} (the ">=" rule of
 // the paper's sampler).  U = m 2^-53 with m = (w >> 11) | 1 an odd 53-bit
 // integer, and the LDS copy of the table holds TI[k] = floor(T[k] 2^53), so
-// T[k] >= U exactly when TI[k] >= m: every comparison is a 64-bit integer
-// one and U is never formed.  The guide brackets the answer in
-// [g[b], g[b+1]]; most brackets are one or two values wide, resolved with at
-// most one table probe ("fast path").  Wider brackets and U > T[kH] (the
-// tail) are deferred and resolved 64 at a time.
+// T[k] >= U exactly when TI[k] >= m, and U is never formed.  The guide brackets
+// the answer in [g[b], g[b+1]]; most brackets are one or two values wide, decided
+// by one comparison of first words (fast_offsets).  Wider brackets, equal words
+// and U > T[kH] (the tail) are deferred and resolved 64 at a time.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t m53(uint32_t hi, uint32_t lo) {
   return ((((uint64_t)hi) << 32 | (uint64_t)lo) >> 11) | 1ull;
 }
-
-// Packed guide entry (guide_pack): the draw is lo when TI[lo] >= m (a
-// bracket [lo, lo] always has it); otherwise the high half, which is hi when
-// that is the answer, else >= kDeferred: the draw is deferred (a wider
-// bracket, or a tail uniform m > TI[kH], which never has TI[lo] >= m).
-// Every m indexes a valid guide entry and 1 <= lo <= kH.
-__device__ __forceinline__ int fast_select(uint32_t gg, uint64_t ti, uint64_t m) {
-  return ti >= m ? (int)(gg & 0xffffu) : (int)(gg >> 16);
-}
-
-__device__ __forceinline__ int fast_draw(uint64_t m, const uint64_t* __restrict__ T,
-                                         const uint32_t* __restrict__ guide, int sh) {
-  const uint32_t gg = guide[guide_index(m, sh)];
-  uint64_t ti = T[(int)(gg & 0xffffu) - 1];
-  asm volatile("" : "+v"(ti));  // keep the read unconditional (no divergent branch)
-  return fast_select(gg, ti, m);
-}
-
-// Full search of a deferred body draw.
-__device__ __forceinline__ int slow_search(uint64_t m, const uint64_t* __restrict__ T,
-                                           const uint32_t* __restrict__ guide, int sh) {
-  const uint32_t gg = guide[guide_index(m, sh)];
-  int lo = (int)(gg & 0xffffu), hi = (int)((gg >> 16) & (kDeferred - 1));
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (T[mid - 1] >= m)
-      hi = mid;
-    else
-      lo = mid + 1;
-  }
-  return lo;
-}
-
-
-// Deferred draw of the lane and wave forms in 8 bytes.  Bit 63 clear: a body
-// draw, bits 0..52 = m.  Bit 63 set: a tail draw, bits 0..31 = its index in
-// the replicate.  Bits 53..58: the lane that owns the replicate (lane form).
-__device__ __forceinline__ uint64_t defer_entry(uint64_t m, uint64_t timax, uint32_t i, int owner) {
-  const uint64_t o = (uint64_t)owner << 53;
-  return m > timax ? ((1ull << 63) | o | i) : (o | m);
-}
-
-
 
 // ---------------------------------------------------------------------------
 // KS distance (eq. 3) over the distinct values of one replicate, in
@@ -731,7 +687,7 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 __device__ __forceinline__ uint32_t uniform32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
-// slow_search in the staged tables.
+// Full search of a deferred body draw in the staged tables.
 __device__ __forceinline__ int lds_search(uint64_t m, const LdsU32* T, const LdsU32* guide,
                                           int sh) {
   const uint32_t g = guide[guide_index(m, sh)];
@@ -810,7 +766,6 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
   const int sh = (int)uniform32(c.gsh);
   const uint32_t ck0 = uniform32(c.k0), ck1 = uniform32(c.k1), cs = uniform32(c.stream);
   const double beta = c.beta, gm = c.gm;
-  const uint64_t below = lanes_below(lane);
   uint32_t qh = 0, qn = 0;
   int myc = 0;  // the lane's own values above the column
   // The loop is software-pipelined: an iteration issues the guide reads of
@@ -863,7 +818,7 @@ static __device__ __noinline__ int lane_draws(const DevCell* cell, int64_t rep0_
       const uint32_t v = min(z[d], 4u * (uint32_t)kHLB);
       uint32_t at;
       asm("v_lshl_add_u32 %0, %1, 5, %2" : "=v"(at) : "v"(v & ~7u), "v"(column));
-      lds_add((LdsU32*)at, 1u << ((v << 2) & 31u));
+      lds_add((LdsU32*)(uintptr_t)at, 1u << ((v << 2) & 31u));
     }
     if (__ballot(max(max(z[0], z[1]), max(z[2], z[3])) >= 4u * (uint32_t)kHLB) != 0ull) {
 #pragma unroll
@@ -952,19 +907,6 @@ __device__ __forceinline__ void lane_wave(const DevCell* cells, int32_t cell_id,
     o = lane_finish<false>(region, spill + lane, myc, od, ok, c.n, fl, 0u, want_fp, ln);
   }
   if (ok) write_outputs(out, c.out_off + rep0 + lane, o.D, o.a, o.flags, o.fp);
-}
-
-// Resolves a deferred draw of a cell with a lower cutoff (xmin = 1 for the
-// pure law): the table index j is the value xmin - 1 + j, the tail starts at
-// xmin + kH.
-__device__ __forceinline__ int64_t resolve_entry_cut(uint64_t e, uint32_t rep, const DevCell& c,
-                                                     const uint64_t* __restrict__ T,
-                                                     const uint32_t* __restrict__ guide,
-                                                     uint32_t& fl) {
-  if (e >> 63)  // inline: heavy tails resolve thousands per replicate
-    return tail_draw_from((double)(c.xmin + kH), c.beta, c.gm, c.k0, c.k1, (uint32_t)e, rep,
-                          c.stream, &fl);
-  return (c.xmin - 1) + (int64_t)slow_search(e & ((1ull << 53) - 1), T, guide, (int)c.gsh);
 }
 
 }  // namespace zpl
@@ -1898,36 +1840,68 @@ __global__ __launch_bounds__(256) void k_count_cells(const double* __restrict__ 
 }
 
 // Raw draws of replicates rep_lo.. in draw order (parity checks of the
-// sampler), through the same fast path and resolution as the simulation.
+// sampler), by the steps of the simulation: the fast path of four draws from
+// their first words, the search in the staged tables, and a tail proposal at a
+// time.  A thread takes four draws of a replicate.
 __global__ __launch_bounds__(256) void k_draws(const DevCell* __restrict__ cells,
                                               const double* __restrict__ tables,
                                               const uint16_t* __restrict__ guides,
                                               int64_t rep_lo, int64_t count,
                                               int64_t* __restrict__ x,
                                               uint32_t* __restrict__ flags) {
-  __shared__ uint64_t T[kH];
+  __shared__ uint32_t T[2 * kH];
   __shared__ uint32_t guide[kGuide];
   const DevCell c = cells[0];
-  for (int k = (int)threadIdx.x; k < kH; k += 256) T[k] = table_int(tables[k]);
-  for (int b = (int)threadIdx.x; b < kGuide; b += 256)
-    guide[b] = guide_pack_dev(guides, b, (int)c.gsh, table_int(c.tmax));
+  load_cell_tables(T, guide, tables, guides, c, (int)threadIdx.x, 256);
   __syncthreads();
-  const int64_t total = count * c.n;
+  const uint64_t timax = table_int(c.tmax);
+  const int sh = (int)c.gsh;
+  const GuideRule rule = guide_rule(sh);
+  const int64_t off = c.xmin - 1, quads = (c.n + 3) / 4, total = count * quads;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
        t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t rr = t / c.n;
-    const uint32_t i = (uint32_t)(t - rr * c.n);
+    const int64_t rr = t / quads;
+    const uint32_t i0 = 4u * (uint32_t)(t - rr * quads);
     const uint32_t rep = (uint32_t)(rep_lo + rr);
-    const Words4 w = philox4x32_10(i >> 1, rep, c.stream, 0u, c.k0, c.k1);
-    const uint64_t m = (i & 1u) ? m53(w.w2, w.w3) : m53(w.w0, w.w1);
-    const uint64_t timax = table_int(c.tmax);
+    Words4 w[2];
+    uint32_t wh[4], gg[4], th[4], z[4];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      w[b] = philox4x32_10((i0 >> 1) + (uint32_t)b, rep, c.stream, 0u, c.k0, c.k1);
+      wh[2 * b] = w[b].w0;
+      wh[2 * b + 1] = w[b].w2;
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      gg[d] = guide[guide_index32(wh[d], rule)];
+      th[d] = T[(gg[d] & 0xffffu) >> 2];
+    }
+    fast_offsets(wh, gg, th, rule, z);
     uint32_t fl = 0;
-    int64_t v = fast_draw(m, T, guide, (int)c.gsh);
-    if (v < kDeferred)
-      v += c.xmin - 1;
-    else
-      v = resolve_entry_cut(defer_entry(m, timax, i, 0), rep, c, T, guide, fl);
-    x[t] = v;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const uint32_t i = i0 + (uint32_t)d;
+      if ((int64_t)i >= c.n) continue;
+      int64_t v = off + (int64_t)(z[d] >> 2) + 1;
+      if (deferred(z[d])) {
+        const Words4& p = w[d >> 1];
+        const uint64_t m = (d & 1) ? m53(p.w2, p.w3) : m53(p.w0, p.w1);
+        if (m <= timax) {
+          v = off + lds_search(m, (const LdsU32*)T, (const LdsU32*)guide, sh);
+        } else {
+          const double m0 = (double)(c.xmin + kH);
+          TailTry y{0, kTailFirst};
+          for (uint32_t attempt = 0; y.code != kTailTaken; ++attempt) {
+            y = tail_try(m0, c.beta, c.gm, c.k0, c.k1, i, rep, c.stream, attempt);
+            if (y.code == kTailHard)
+              y = tail_hard(m0, c.beta, c.gm, c.k0, c.k1, i, rep, c.stream, attempt);
+            if (y.code == kTailCapped) fl |= kFlagTailCapped;
+          }
+          v = y.X;
+        }
+      }
+      x[rr * c.n + i] = v;
+    }
     if (fl) atomicOr(&flags[rr], fl);
   }
 }
@@ -2152,7 +2126,7 @@ hipError_t launch_draws(const DevCell* cell, const double* table, const uint16_t
                         int64_t rep_lo, int64_t count, int64_t* x, uint32_t* flags,
                         int64_t total, hipStream_t s) {
   if (total <= 0) return hipSuccess;
-  int64_t g = (total + 255) / 256;
+  int64_t g = (total + 1023) / 1024;  // four draws a thread
   int grid = (int)(g > 4096 ? 4096 : g);
   k_draws<<<grid, 256, 0, s>>>(cell, table, guide, rep_lo, count, x, flags);
   return hipGetLastError();
