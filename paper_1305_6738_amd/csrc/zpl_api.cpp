@@ -363,9 +363,10 @@ double trunc_cost(int64_t n, uint32_t K) {
 // many comparisons as there are, and a round of lanes takes as long for few
 // replicates as for many.
 // Replicates of the call at which the two meet, by values above the column (and
-// draws): 10 (24) 6,000; 20 (21) 10,000; 40 (98) 20,000, (42) 60,000, (455) 50,000;
-// 84 (956) 100,000, (207) 170,000, (84) more than 200,000: about 100 per draw and
-// 56 per pair of values times the part of the draws that they are.
+// draws): K = 1,000, 20 (21) 10,000; 40 (98) 20,000, (42) 50,000, (455) 50,000; 60
+// (148) 45,000; 84 (956) 100,000, (207) 170,000; K = 161, 40 (83) 100,000; K = 4,096,
+// 40 (44) 18,000, 84 (93) 80,000, (168) 36,000: about 80 per draw, and 710 / sqrt(K)
+// per pair of values times the part of the draws that they are.
 // The most values that pay on a full device, from tables of 12 exponents, 50,000
 // replicates, with lanes for up to 40, 64 and 84: K = 161, n = 100 1,013, 912, 910 us,
 // n = 200 1,382, 1,237, 1,403; K = 500, n = 200 1,592, 1,594, 1,463; K = 1,000, n = 100
@@ -376,7 +377,7 @@ bool lane_truncated(double alpha, int64_t n, uint32_t K, int64_t R) {
   if (n <= 10 || n > 2000) return false;
   const double p = tail_prob(alpha, kHLB, K), above = (double)n * p;
   return above <= (K < 300 ? 64.0 : 84.0) &&
-         (double)R >= 100.0 * (double)n + 56.0 * above * above * p;
+         (double)R >= 80.0 * (double)n + 710.0 / std::sqrt((double)K) * above * above * p;
 }
 
 // Time for one cell alone under form f (tuned cost v ns per replicate with

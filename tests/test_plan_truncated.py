@@ -24,7 +24,7 @@ def test_values_above_the_column(K, most, alpha):
 @pytest.mark.parametrize("alpha,n,K", [(0.25, 20, 1000), (1.5, 500, 1000), (1.0, 98, 161)])
 def test_replicates_of_the_call(alpha, n, K):
     a = above(alpha, n, K)
-    R = int(np.ceil(100 * n + 56 * a * a * a / n)) + 1
+    R = int(np.ceil(80 * n + 710 / K ** 0.5 * a * a * a / n)) + 1
     assert plan_forms([(alpha, n, R, 1, 0, K)]) == ["lane"]
     assert plan_forms([(alpha, n, R - 2, 1, 0, K)]) == ["wave"]
     # the call's replicates count, not the cell's
