@@ -855,43 +855,6 @@ static __device__ __noinline__ double ks_many(double a, double iz, int64_t xmin_
   }
 }
 
-// ks_rest for the replicates of a batch that have many larger draws (bits of
-// `left`; a, iz, D, z16, hi, oc and top are each lane's own replicate's, D comes
-// back).  One call outside the loop over the others, which keeps its registers.
-template <int kLaw>
-static __device__ __noinline__ double ks_parted(uint64_t left, double a, double iz, double D,
-                                                double z16, int hi, uint32_t oc, int64_t top,
-                                                int64_t xmin, uint32_t K, const uint32_t* counts,
-                                                int64_t cw, bool wide, const int64_t* scratch,
-                                                int64_t n, LdsU32* tab, LdsU64* list, LdsU32* ends,
-                                                LdsU64* level, const double* ln, int64_t* work,
-                                                int64_t words) {
-  const int lane = lane_id();
-  left = (uint64_t)uniform64((int64_t)left);
-  while (left != 0ull) {
-    const int i = __ffsll((long long)left) - 1;
-    left &= left - 1ull;
-    const uint32_t* ci = counts + 2 * i * uniform64(cw);
-    const int64_t* ov =
-        scratch + (((int64_t)__builtin_amdgcn_readlane((int)(top >> 32), i) << 32) |
-                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)top, i));
-    const uint32_t oi = (uint32_t)__builtin_amdgcn_readlane((int)oc, i);
-    auto rest = [&](auto fn) {
-      return fn(readlane_f64(a, i), readlane_f64(iz, i), xmin, K, ci, wide,
-                __builtin_amdgcn_readlane(hi, i), ov, oi, n, readlane_f64(D, i),
-                readlane_f64(z16, i), tab, list, ends, level, ln);
-    };
-    const CountView cv{as_global(ci), wide};
-    const bool has_top = __builtin_amdgcn_readlane(hi, i) == kHW && cv.at(kHW - 1) != 0u;
-    double Di = rest([](auto... x) { return ks_rest<kLaw, false>(x...); });
-    Di = ks_many<kLaw>(readlane_f64(a, i), readlane_f64(iz, i), xmin, K, has_top, ov, oi, work,
-                       words, n, Di, tab, list, level, ln);
-    if (Di < 0.0) Di = rest([](auto... x) { return ks_rest<kLaw>(x...); });
-    if (lane == i) D = Di;
-  }
-  return D;
-}
-
 // Record of one replicate of a batch.
 struct WaveSlot {
   U128 S;
@@ -899,6 +862,64 @@ struct WaveSlot {
   int64_t top;  // its larger draws lie below this offset of the scratch
   uint32_t hi, len, flags, esc;
 };
+
+// The places of a wave's scratch: records, counts of each replicate, then free
+// space and the draws above kHW from the end.
+constexpr int64_t kBatchRecords = 64 * (int64_t)kWaveSlotBytes / 8;
+__device__ __forceinline__ int64_t count_words(int64_t n) {  // int64 per replicate's counts
+  return n >= 65536 ? kHW / 2 : kHW / 4;
+}
+
+// ks_rest for the replicates of a batch that have many larger draws (bits of
+// `left`; a, iz, D and z16 are each lane's own replicate's, D comes back), the
+// batch's q replicates in scratch, their draws from `top` on.  One call outside the
+// loop over the others, with few arguments: in the batch's own body it took
+// registers from every replicate (six cutoff cells of 1,000 draws: 5.91 against
+// 5.78 ms).
+template <int kLaw>
+static __device__ __noinline__ double ks_parted(uint64_t left, double a, double iz, double D,
+                                                double z16, const DevCell* cell,
+                                                int64_t* scratch_, int q, int64_t top_,
+                                                LdsU32* lds, const double* ln) {
+  const int lane = lane_id();
+  const DevCell& c = *as_global(reinterpret_cast<const DevCell*>(uniform64((int64_t)cell)));
+  int64_t* scratch = as_global(reinterpret_cast<int64_t*>(uniform64((int64_t)scratch_)));
+  const int64_t n = uniform64(c.n), cw = count_words(n);
+  const bool wide = n >= 65536;
+  int64_t* counts = scratch + kBatchRecords;
+  int64_t* work = counts + uniform32((uint32_t)q) * cw;
+  const int64_t words = scratch + uniform64(top_) - work;
+  LdsU64* list = (LdsU64*)(lds + offsetof(BatchLds, ring) / 4);
+  LdsU32* ends = lds + offsetof(BatchLds, retry) / 4;
+  LdsU64* level = (LdsU64*)(lds + offsetof(BatchLds, hard) / 4);
+  left = (uint64_t)uniform64((int64_t)left);
+  while (left != 0ull) {
+    const int i = __ffsll((long long)left) - 1;
+    left &= left - 1ull;
+    const WaveSlot& sl = reinterpret_cast<const WaveSlot*>(scratch)[i];
+    const int hi = (int)uniform32(sl.hi);
+    const uint32_t oc = uniform32(sl.len);
+    const int64_t* ov = scratch + uniform64(sl.top);
+    const CountView cv{reinterpret_cast<const uint32_t*>(counts + i * cw), wide};
+    const double ai = readlane_f64(a, i), izi = readlane_f64(iz, i);
+    // the histogram alone (as without larger draws), then those by bin or, where
+    // their copies do not fit, in windows
+    double Di = readlane_f64(D, i);
+    for (uint32_t large = 0u;; large = oc) {
+      Di = ks_rest<kLaw>(ai, izi, c.xmin, c.K, cv.p, wide, hi, ov, large, n, Di,
+                         readlane_f64(z16, i), lds, list, ends, level, ln);
+      if (large != 0u) break;
+      const double r = ks_many<kLaw>(ai, izi, c.xmin, c.K, hi == kHW && cv.at(kHW - 1) != 0u, ov,
+                                     oc, work, words, n, Di, lds, list, level, ln);
+      if (r >= 0.0) {
+        Di = r;
+        break;
+      }
+    }
+    if (lane == i) D = Di;
+  }
+  return D;
+}
 
 // One proposal of the tail sampler (tail_draw_from): taken (X), rejected,
 // rejected above 2^63, or undecided in FP64 (tail_hard repeats it with the
@@ -1402,8 +1423,8 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
   const DevCell& c = cells[cell_id];
   const int64_t n = c.n;
   const bool wide = n >= 65536;
-  const int64_t cw = wide ? kHW / 2 : kHW / 4;  // int64 per replicate's counts
-  constexpr int64_t kRecords = 64 * (int64_t)kWaveSlotBytes / 8;
+  const int64_t cw = count_words(n);
+  constexpr int64_t kRecords = kBatchRecords;
   WaveSlot* slots = reinterpret_cast<WaveSlot*>(scratch);
   int64_t* counts = scratch + kRecords;
   const int64_t off = kCut ? c.xmin - 1 : 0;
@@ -1471,10 +1492,7 @@ __device__ __forceinline__ void replicate_batch(const DevCell* cells, int32_t ce
     const uint64_t parted = __ballot(h.done == 0u && part);
     if (parted != 0ull) {
       auto many = [&](auto fn) {
-        return fn(parted, h.a, h.iz, h.D, h.z16, (int)hib, oc, ovtop, c.xmin, c.K,
-                  reinterpret_cast<const uint32_t*>(counts), cw, wide, scratch, n,
-                  (LdsU32*)L->hist, (LdsU64*)L->ring, (LdsU32*)L->retry, (LdsU64*)L->hard, ln,
-                  counts + q * cw, top - (kRecords + q * cw));
+        return fn(parted, h.a, h.iz, h.D, h.z16, &c, scratch, q, top, (LdsU32*)L->hist, ln);
       };
       if constexpr (kCut)
         h.D = many([](auto... x) { return ks_parted<kCutoff>(x...); });
