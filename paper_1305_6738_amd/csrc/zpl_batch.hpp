@@ -1319,7 +1319,6 @@ struct CountSrc {
     return false;
   }
 };
-constexpr uint32_t kTruncLaneK = 100;
 template <int kLaw>
 static __device__ __noinline__ HeadOut head_lane(U128 S, int64_t n, int64_t xmin, uint32_t K,
                                                  const uint32_t* counts_, bool wide,

@@ -60,6 +60,9 @@ constexpr int64_t kPartLevel = 3 * kHW / 2;
 constexpr int64_t part_words(int64_t room) {
   return room > kPartMin ? room + room / 4 + 3 * kPartLevel : 0;
 }
+// Truncated law: up to this K the lanes of a batch of 16 replicates and more walk
+// the support themselves for the KS distance (head_lane).
+constexpr uint32_t kTruncLaneK = 100;
 // Waves per workgroup that run escalated replicates (whole replicates of
 // scratch each, so few).
 constexpr int kEscWaves = 4;
