@@ -398,9 +398,9 @@ double cell_makespan(int f, double v, int64_t R, int n_cu) {
 // a few workgroups), the form that finishes the cell soonest.  Otherwise
 // (no table, or the truncated law): the lane form when a replicate's values
 // above its column are few, else the wave form when its overflow area holds
-// them, else the heavy form.
+// them, else the heavy form.  like_R: replicates of the call's cells of this kind.
 uint32_t choose_form(double alpha, int64_t n, const Tuning* t, uint32_t K, int64_t R,
-                     int64_t trunc_R, int n_cu, double horizon, double* cost = nullptr) {
+                     int64_t like_R, int n_cu, double horizon, double* cost = nullptr) {
   if (cost) *cost = 0.0;
   if (K > 0) {
     // the table measures the pure law; the truncated law's cost is mostly
@@ -434,11 +434,11 @@ uint32_t choose_form(double alpha, int64_t n, const Tuning* t, uint32_t K, int64
   // 10,000 draws at alpha 3.5: 2,525 us and 94, 320,000 5,695 and 5,657; 12 columns
   // of K = 20, n = 50,000 with 333: 12,479 and 599.  Shorter ones keep the lanes: the choice there
   // is part of the tested interface.)
-  const bool rounds = (K ? trunc_R : R) >= 32 * n;
+  const bool rounds = like_R >= 32 * n;
   if (n <= 65535 && (double)n * tail_prob(alpha, kHLB, K) <= 2.0 &&
       (n <= (K ? 5000 : 1000) || rounds))
     return kModeLane;
-  if (K >= kTruncEmK && lane_truncated(alpha, n, K, trunc_R)) return kModeLane;
+  if (K >= kTruncEmK && lane_truncated(alpha, n, K, like_R)) return kModeLane;
   // The pure law without a table: the lane form wherever its slots hold the
   // values and there are enough replicates for a round of lanes (as above).  ns
   // per replicate, lane and batch: alpha 1.5, 1,000 draws 5.5 and 8.7; 2.0, 3,000
@@ -466,8 +466,8 @@ int64_t batch_room(const DevCell& d) {
 // Units of the wave- and heavy-form cells, longest replicates first.  A unit
 // holds the same number of replicates (up to 64) for each of the kernel's
 // waves, as many as leaves about eight units for each compute unit, or more
-// where all cells are alike.
-void plan_batch(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) {
+// where all cells are alike.  lanes: there are lane-form cells beside them.
+void plan_batch(Plan& P, std::vector<int>& cells, bool lanes, const int64_t* rlo, int n_cu) {
   // a replicate costs about its draws plus 2,000 draws' time for fit and KS
   auto cost = [](const DevCell& d) { return (double)d.n + 2000.0; };
   std::stable_sort(cells.begin(), cells.end(),
@@ -485,35 +485,38 @@ void plan_batch(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) 
     work += cost(d) * (double)d.R;
   }
   const double unit_work = work / (8.0 * n_cu);
-  // Cells that differ only in their exponents need not be balanced so finely, and
-  // a wave's estimates cost as much for one replicate as for 64: a wave's part of
-  // the call in one batch, or in batches of about 33 where it is more than 64
-  // replicates (or in eighths, several cells of long replicates, whose exponents
-  // then tell).  us with eight units per compute unit and so: one cell of 10,000
-  // replicates, alpha 2.5, n = 300, 190 and 123; alpha 2, n = 10,000, 396 and
-  // 330; cutoff 2, alpha 3.5, n = 100, 644 and 263; six cutoff cells of 100,000 of
-  // n = 1000, 5,826 and 5,565; four of 20,000 of n = 10,000, alpha 1.2..1.5: 4,295
-  // and (in one batch) 5,731.
-  bool alike = true;
-  for (int i : cells)
-    alike = alike && P.cells[i].n == P.cells[cells[0]].n &&
-            (P.cells[i].xmin > 1) == (P.cells[cells[0]].xmin > 1);
-  // Several cutoff cells above 17, whose estimates are cheap beside their
-  // distances, in three rounds (nine of 1,000 replicates, n = 1000, xmin 5..500: 340
-  // us in one, 312 in three).  A short truncated support in batches of up to 32
-  // whatever else there is: its estimates are K powers a step, and 16 lanes and more
-  // walk it side by side (kTruncLaneK).  K = 60, 12 exponents, n = 500 and 600, 3,000
-  // replicates: 1,809 us in eighths, 518 so.
-  bool high = false;
-  for (int i : cells) high = high || P.cells[i].xmin > 17;
+  // A wave's estimates cost as much for one replicate as for 64.  Cells of one size
+  // need not be balanced so finely: one cell alone in one batch per wave (or about 33
+  // replicates at a time), several in one round where the estimates are dear beside
+  // the rest (a truncated law, few draws, cutoffs up to 17), else in three, and in
+  // six where a wave's part is more than 64 replicates.  Beside lane-form cells, whose
+  // workgroups are free at different times, in three at least.
+  // us in eight rounds and so: one cell of 10,000 replicates, alpha 2.5, n = 300,
+  // 190 and 123; alpha 2, n = 10,000, 396 and 330; cutoff 2, alpha 3.5, n = 100, 644
+  // and 263; six cutoff cells of 100,000 of n = 1000, 5,826 and 5,565; nine of 1,000
+  // (xmin 5..500) 307 and 312, in one round 340; 16 of 20,678 of n = 743, alpha
+  // 1.3..3.8, 1,481 and, in four rounds, 1,711.
+  // A short truncated support goes in batches as large whatever else there is: its
+  // estimates are K powers a step, and 16 lanes and more walk it side by side
+  // (kTruncLaneK).  K = 60, 12 exponents, n = 500 and 600, 3,000 replicates: 1,809 us
+  // in eight rounds, 518 so.
+  const DevCell& first = P.cells[cells[0]];
+  bool alike = true, low = true;
+  for (int i : cells) {
+    const DevCell& d = P.cells[i];
+    alike = alike && d.n == first.n && (d.xmin > 1) == (first.xmin > 1);
+    low = low && d.xmin <= 17;
+  }
+  const bool one = cells.size() == 1;
   auto whole = [&](const DevCell& d, double share) -> int64_t {  // share: replicates per wave
-    const int64_t part = (int64_t)std::ceil(share);
-    if (alike && cells.size() > 1 && high && share <= 64.0) return (int64_t)std::ceil(share / 3.0);
-    if (alike && (cells.size() == 1 || d.n <= 1000)) {
-      if (share <= 64.0) return part;
-      if (d.n <= 1000) return (int64_t)std::ceil(share / std::ceil(share / 33.0));
-    }
-    return d.K != 0 && d.K <= kTruncLaneK ? std::min<int64_t>(32, part) : 1;
+    auto in = [&](double rounds) { return (int64_t)std::ceil(share / rounds); };
+    const double r33 = std::ceil(share / 33.0);
+    if (d.K != 0 && d.K <= kTruncLaneK) return in(share <= 64.0 ? 1.0 : r33);
+    if (!alike || (d.n > 1000 && !(one && share <= 64.0))) return 1;
+    const bool dear = d.K != 0 || (d.xmin > 1 ? low : d.n <= 200);
+    double rounds = one || dear ? 1.0 : 3.0;
+    if (share > 64.0) rounds = one || d.K != 0 ? r33 : std::max(6.0, r33);
+    return in(lanes ? std::max(3.0, rounds) : rounds);
   };
   for (int cut = 0; cut < 2; ++cut) {
     const int waves = cut ? kBatchWavesCut : kBatchWaves;
@@ -546,9 +549,10 @@ void plan_batch(Plan& P, std::vector<int>& cells, const int64_t* rlo, int n_cu) 
 // (a window of a longer cell, as the serving scheduler runs them); its
 // outputs still start at the cell's prefix position in the per-replicate
 // arrays.  Without it every cell covers replicates 0 .. replicates - 1.
+// together: the cells share launches, and so a round of lanes.
 zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
                      const Tuning* tune = nullptr, int n_cu = 256,
-                     const int64_t* rlo = nullptr) {
+                     const int64_t* rlo = nullptr, bool together = true) {
   P = Plan();
   P.cells.resize(n_cells);
   P.cell_unit_begin.assign(n_cells, 0);
@@ -556,11 +560,15 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
   // the batch's work with every cell in its cheapest form: a cell that alone
   // would outlast it is given the form that finishes it soonest instead
   double horizon = -1.0;
-  int64_t trunc_R = 0;  // replicates of truncated cells
+  // the call's replicates of the pure law, of the truncated law on short supports and
+  // on the others
+  int64_t like_R[3] = {0, 0, 0};
+  auto kind = [](const zpl_cell& z) { return z.kmax == 0 ? 0 : z.kmax < kTruncEmK ? 1 : 2; };
   for (int i = 0; i < n_cells; ++i)
-    if (cells[i].kmax != 0 && cells[i].replicates > 0 &&
+    if (cells[i].xmin <= 1 && cells[i].replicates > 0 &&
         cells[i].replicates <= ((int64_t)1 << 32))
-      trunc_R += cells[i].replicates;
+      like_R[kind(cells[i])] += cells[i].replicates;
+  auto like = [&](const zpl_cell& z) { return together ? like_R[kind(z)] : z.replicates; };
   if (form == ZPL_FORM_AUTO && tune && !tune->empty()) {
     horizon = 0.0;
     for (int i = 0; i < n_cells; ++i) {
@@ -571,7 +579,7 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
                                         z.alpha >= -64.0 && z.alpha <= 64.0);
       // (invalid cells are rejected below; cutoff cells run in the heavy form)
       if (valid && z.n >= 1 && z.replicates >= 1 && (z.xmin == 0 || z.xmin == 1))
-        (void)choose_form(z.alpha, z.n, tune, z.kmax, z.replicates, trunc_R, n_cu, -1.0, &c);
+        (void)choose_form(z.alpha, z.n, tune, z.kmax, z.replicates, like(z), n_cu, -1.0, &c);
       horizon += c;
     }
   }
@@ -618,7 +626,7 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
         break;
       case ZPL_FORM_WAVE: m = kModeWave; break;
       case ZPL_FORM_HEAVY: m = kModeHeavy; break;
-      default: m = choose_form(z.alpha, z.n, tune, z.kmax, z.replicates, trunc_R, n_cu, horizon);
+      default: m = choose_form(z.alpha, z.n, tune, z.kmax, z.replicates, like(z), n_cu, horizon);
     }
     // the lane and wave forms histogram values from 1; a cutoff law runs in
     // the heavy form, whose histogram and overflow list take any values
@@ -701,7 +709,7 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
       P.units.push_back(u);
     }
   }
-  if (!batch_cells.empty()) plan_batch(P, batch_cells, rlo, n_cu);
+  if (!batch_cells.empty()) plan_batch(P, batch_cells, !runs.empty(), rlo, n_cu);
   return ZPL_OK;
 }
 
@@ -926,7 +934,8 @@ zpl_status run_cells(zpl_ctx* c, const zpl_cell* cells, int n_cells, const uint3
   if (rlo && (o.use_graph || n_q > 0))
     return fail(ZPL_EINVAL, "replicate windows run without graphs or quantiles");
   Plan P;
-  ZPL_TRY(make_plan(cells, n_cells, o.form, P, &c->tune, c->n_cu, rlo));
+  ZPL_TRY(make_plan(cells, n_cells, o.form, P, &c->tune, c->n_cu, rlo,
+                    o.launch != ZPL_LAUNCH_PLAIN));
   if (o.launch == ZPL_LAUNCH_PLAIN) plain_unit_order(P);
   const bool need_sel = quantiles && n_q > 0;
   const bool need_dbuf = need_sel && out.D == nullptr;

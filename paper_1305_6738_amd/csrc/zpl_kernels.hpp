@@ -50,15 +50,18 @@ constexpr int kBatchWaves = 12;
 constexpr int kBatchWavesCut = 12;
 // A replicate with more values above the histogram than kPartMin partitions them
 // by bin in the scratch that is left behind its counts (ks_many): kPartLevel
-// int64 for the bins of a level, a copy of the draws in reach, and as much again
-// for the ranges within a bin (an eighth of an octave at most).  Cutoff 1e6, so
-// that all draws are such: 10,000 replicates of 1,500 draws 1.25 ms by bins and
-// 1.14 in windows over all of them, of 2,500 2.08 and 2.35; 1,000 replicates of
-// 20,000 4.5 and 23.6; alpha 1.2, 10,000 draws (about 1,700 such): 2.0 and 2.3.
+// int64 for the bins of a level and a copy of the draws in reach, and the same for
+// the ranges within a bin (an eighth of the draws or less, and for the longest
+// replicates ranges within those).  Cutoff 1e6, so that all draws are such: 10,000
+// replicates of 1,500 draws 1.25 ms by bins and 1.14 in windows over all of them, of
+// 2,500 1.36 and 2.35; 1,000 replicates of 20,000 4.2 and 23.6; alpha 1.2, 10,000
+// draws (about 1,700 such): 1.9 and 2.3.
 constexpr int64_t kPartMin = 1536;
 constexpr int64_t kPartLevel = 3 * kHW / 2;
 constexpr int64_t part_words(int64_t room) {
-  return room > kPartMin ? room + room / 4 + 3 * kPartLevel : 0;
+  return room <= kPartMin ? 0
+         : room < 65536   ? room + room / 8 + 2 * kPartLevel
+                          : room + room / 4 + 3 * kPartLevel;
 }
 // Truncated law: up to this K the lanes of a batch of 16 replicates and more walk
 // the support themselves for the KS distance (head_lane).
