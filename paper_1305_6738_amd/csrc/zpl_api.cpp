@@ -643,9 +643,9 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
   }
   // Lane-form units: up to kBlock replicates, one per lane (wave- and heavy-form
   // cells: plan_batch).  The longest-first order weighs a unit by its
-  // per-replicate cost (from the tuning table when there is one; the truncated
-  // law: draws plus its K-term sums, see trunc_cost): a unit's waves take that
-  // long however many of its lanes hold a replicate.  Sorted by cell, not by
+  // per-replicate cost (from the tuning table when there is one, else 2.2 ps per
+  // draw; the truncated law: trunc_cost): a unit's waves take that long however many
+  // of its lanes hold a replicate.  Sorted by cell, not by
   // unit: a cell's units follow one another with ascending replicates.
   struct Run {
     double w;
@@ -664,9 +664,9 @@ zpl_status make_plan(const zpl_cell* cells, int n_cells, int form, Plan& P,
       continue;
     }
     if (d.R <= 0) continue;
-    double w = d.K ? (double)d.n + 8.6 * (double)d.K : (double)d.n;
-    if (tune && !tune->empty()) {
-      const double v = d.K ? trunc_cost(d.n, d.K) : tuned_cost(*tune, (int)d.mode, d.alpha, d.n);
+    double w = d.K ? trunc_cost(d.n, d.K) : 2.2e-3 * (double)d.n;
+    if (d.K == 0 && tune && !tune->empty()) {
+      const double v = tuned_cost(*tune, (int)d.mode, d.alpha, d.n);
       if (v > 0.0) w = v;
     }
     runs.push_back({w, i, 0, d.R});
