@@ -110,8 +110,8 @@ typedef struct zpl_cell {
 /* Per-cell execution form (the planner's choice unless forced). */
 #define ZPL_FORM_AUTO 0
 #define ZPL_FORM_LANE 1  /* one replicate per lane                     */
-#define ZPL_FORM_WAVE 2  /* one replicate per wave, finishes per lane  */
-#define ZPL_FORM_HEAVY 3 /* one replicate per wave, global overflow    */
+#define ZPL_FORM_WAVE 2  /* one replicate per wave, few values > 1,024 */
+#define ZPL_FORM_HEAVY 3 /* one replicate per wave, any number of them */
 
 typedef struct zpl_sim_opts {
   int32_t launch;    /* ZPL_LAUNCH_*                                     */
@@ -181,12 +181,14 @@ zpl_status zpl_critical_table(zpl_ctx *ctx, const double *gammas, int32_t n_gamm
  * Autotuning of the execution form (the batched launch of Sect. 3's
  * simulations over cells of uneven n).  Every form computes the same bits;
  * the choice only changes speed.  The lane form runs one replicate per lane
- * and suits short replicates with light tails; the wave form runs one
- * replicate per wavefront with per-lane finishes; the heavy form keeps large
- * values in global memory.  A tuning table holds the measured cost of each
- * form on a grid of (alpha, n); with one installed, the planner gives every
- * cell the cheapest form eligible there (cost interpolated bilinearly in
- * alpha and ln n) and orders the work units by measured cost.
+ * and suits short replicates with light tails; the wave and heavy forms run
+ * one replicate per wavefront, in one kernel, and differ in where they are
+ * eligible (the wave form where few values lie above 1,024) and in the number
+ * of replicates they are probed with (768 and 48 per compute unit).  A tuning
+ * table holds the measured cost of each form on a grid of (alpha, n); with one
+ * installed, the planner gives every cell the cheapest form eligible there
+ * (cost interpolated bilinearly in alpha and ln n) and orders the lane form's
+ * work units by measured cost.
  * ------------------------------------------------------------------------ */
 typedef struct zpl_tune_entry {
   double alpha;
@@ -200,8 +202,8 @@ typedef struct zpl_tune_entry {
  * alpha in [1.01, 64], n in [1, 2^20], at most 64 values per axis) on the
  * context's device and install the table in the context.  table_out (host,
  * [n_alpha * n_n], alpha-major: entry ia * n_n + in) receives it, or NULL.
- * Each eligible (point, form) runs a probe cell sized to give every compute
- * unit one unit of work, twice; the probes are synchronous on `stream`. */
+ * Each eligible (point, form) runs a probe cell of 768 (heavy form: 48)
+ * replicates per compute unit, twice; the probes are synchronous on `stream`. */
 zpl_status zpl_autotune(zpl_ctx *ctx, const double *alphas, int32_t n_alpha,
                         const int64_t *ns, int32_t n_n, zpl_tune_entry *table_out,
                         void *stream);
@@ -221,8 +223,8 @@ zpl_status zpl_plan_forms(const zpl_tune_entry *table, int32_t count, const zpl_
  * zpl_set_timing(ctx, 1) makes every later non-graph zpl_simulate_cells
  * record events around its kernels; zpl_get_timing then waits for the last
  * such call and writes ms4[0..3] = milliseconds spent in the table build,
- * the lane/wave simulation launches, the heavy/escalation launch and the
- * quantile selection.  ZPL_EINVAL if no timed call happened. */
+ * the simulation launches (every form), the cutoff cells' and the escalated
+ * replicates' launches and the quantile selection.  ZPL_EINVAL if no timed call happened. */
 zpl_status zpl_set_timing(zpl_ctx *ctx, int32_t enable);
 zpl_status zpl_get_timing(zpl_ctx *ctx, double *ms4);
 
@@ -245,8 +247,8 @@ zpl_status zpl_fit_truncated(zpl_ctx *ctx, const int64_t *x, int64_t n, int32_t 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): zpl_fit
  * (kmax = 0) or zpl_fit_truncated (kmax = K in 2..4096) of a device dataset
- * into device outputs.  The call enqueues one kernel on `stream` and returns:
- * it allocates nothing, copies nothing to the host and does not synchronise.
+ * into device outputs.  The call enqueues kernels only (one, up to five from
+ * 32,768 values on) on `stream` and returns: it allocates nothing, copies nothing to the host and does not synchronise.
  *   x_dev[n]        device int64; 1 <= n <= 2^20 (ZPL_EINVAL above that).
  *   alpha_hat_dev, D_dev    device double[1];  flags_dev device uint32[1]
  *                   (ZPL_FLAG_*; ZPL_FLAG_NOCONV where zpl_fit would return
@@ -365,7 +367,9 @@ zpl_status zpl_cdf_table(zpl_ctx *ctx, double alpha, uint32_t kmax, int64_t xmin
  * candidate whose fit has the smallest D.
  * ------------------------------------------------------------------------ */
 
-/* Fit for each candidate cutoff, one wavefront per candidate, in one launch.
+/* Fit for each candidate cutoff: the dataset is counted and sorted once (up
+ * to 1,024 values by each candidate's workgroup), then every candidate has a
+ * workgroup of one launch, or several where the candidates are few.
  *   x[n]            host (x_on_device = 0) or device int64, every x >= 1
  *                   (values below a candidate are ignored for that candidate).
  *   xmins[n_xmin]   host; each in [1, 2^40]; 1 <= n_xmin <= 65536.

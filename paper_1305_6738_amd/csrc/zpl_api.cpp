@@ -380,12 +380,14 @@ bool lane_truncated(double alpha, int64_t n, uint32_t K, int64_t R) {
          (double)R >= 80.0 * (double)n + 710.0 / std::sqrt((double)K) * above * above * p;
 }
 
-// Time for one cell alone under form f (tuned cost v ns per replicate with
-// the device busy): its work units (kBlock replicates per workgroup for the
-// lane and wave forms; the heavy form's replicates spread over the device, in
-// effect 8 for each of two workgroups per compute unit) run in rounds of as
-// many units as the device holds at once, and a unit takes v x (replicates the
-// device holds at once).
+// A price for one cell alone under form f (tuned cost v ns per replicate with
+// the device busy), to find the cells that outlast the rest of a call: rounds of
+// kBlock replicates per compute unit for the lane and wave forms, of 16 for the
+// heavy form, each of v x its replicates.  A coarse one: lane units are of any
+// whole number of waves (make_plan), and wave and heavy cells run in the same
+// kernel, their prices being those of its two probes (autotune_grid), many
+// replicates and few: a cell of few is priced nearer by the second, and which of
+// the two it is named changes only the scratch it brings in.
 double cell_makespan(int f, double v, int64_t R, int n_cu) {
   const double per = f == (int)kModeHeavy ? 8.0 : (double)kBlock;
   const double conc = f == (int)kModeHeavy ? 2.0 * n_cu : (double)n_cu;
@@ -835,7 +837,8 @@ zpl_status prepare(zpl_ctx* c, Plan& P, int n_q, bool need_dbuf, Launch& L) {
 }
 
 // Enqueue everything after the plan upload: counters, tables, simulation,
-// heavy pass, selection.  Kernel launches only (graph-capturable).
+// cutoff cells, escalated replicates, selection.  Kernel launches only
+// (graph-capturable).
 zpl_status enqueue_run(zpl_ctx* c, const Plan& P, int launch, const Launch& L, Outputs out,
                        const double* Dsel, int n_q, hipStream_t s, bool timed) {
   const int nc = (int)P.cells.size();
@@ -1034,10 +1037,9 @@ zpl_status run_cells(zpl_ctx* c, const zpl_cell* cells, int n_cells, const uint3
 }
 
 // Measures the cost of each eligible form at every grid point: a probe cell
-// with enough replicates to give every compute unit one unit of work (lane
-// and wave forms: kBlock replicates per workgroup; heavy form: 4 per
-// wavefront), timed with events around the simulation and heavy
-// launches (table build excluded), best of two runs.
+// of kBlock replicates per compute unit, or 4 per wavefront for the heavy form
+// (the wave form's kernel with few replicates), timed with events around the
+// simulation (table build and selection excluded), best of two runs.
 zpl_status autotune_grid(zpl_ctx* c, const double* alphas, int na, const int64_t* ns, int nn,
                          std::vector<zpl_tune_entry>& out, hipStream_t s) {
   out.assign((size_t)na * nn, zpl_tune_entry{});
@@ -1150,9 +1152,9 @@ zpl_status stage_x(zpl_ctx* c, const int64_t* x, int64_t n, int32_t on_dev, hipS
 //      their device memory fits the budget (the fit's dataset and scratch
 //      while it runs, and 8 bytes per bootstrap replicate until the request
 //      completes);
-//   2. fits the newly admitted datasets (eq. 2 and eq. 3) in one batched
-//      launch (one wavefront per dataset below 2,048 values, one workgroup per
-//      larger dataset);
+//   2. fits the newly admitted datasets (eq. 2 and eq. 3): one batched
+//      launch, a workgroup per dataset below 2,048 values, then the larger
+//      datasets one after another (one workgroup, from 32,768 values on many);
 //   3. runs one window of replicates of every active request's bootstrap, all
 //      of them as the cells of one batched simulation, the windows sized so
 //      that the launch holds about one time slice of work shared equally
@@ -1197,9 +1199,9 @@ struct Req {
 size_t held_bytes(const Req& r) { return (size_t)r.B * 8 + 4096; }
 
 // Transient device memory of fitting a set of datasets: the concatenated
-// data, the per-set descriptors and outputs, the one-wave fits' scratch
-// (one area per wavefront of the batched launch, each sized for the largest
-// small dataset) and one workgroup fit's scratch, reused by every large one.
+// data, the per-set descriptors and outputs, the small datasets' scratch (one
+// area per workgroup of the batched launch, each sized for the largest of them)
+// and one area for the large ones, which follow one another.
 size_t fit_bytes(int64_t total_n, int n_sets, int64_t max_small, int n_small, int64_t max_large,
                  int n_cu) {
   size_t b = (size_t)total_n * 8 + (size_t)n_sets * 64 + 4096;
@@ -1307,8 +1309,8 @@ zpl_status Server::fit_fresh(std::vector<Req*>& fresh) {
     HIP_TRY(hipMemcpyAsync(fx + start, px + start, sizeof(int64_t) * (size_t)run,
                            hipMemcpyHostToDevice, s));
   }
-  // 2. fits: small datasets one wavefront each in one launch, large ones a
-  //    workgroup each (the same bits as zpl_fit either way)
+  // 2. fits: small datasets a workgroup each in one launch, large ones one
+  //    after another (the same bits as zpl_fit either way)
   std::vector<int> small, large;
   int64_t max_small = 1, max_large = 0;
   for (int i = 0; i < nb; ++i) {

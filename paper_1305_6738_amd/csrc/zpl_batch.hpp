@@ -101,10 +101,10 @@ __device__ __forceinline__ uint32_t dpp_incl_scan_u32(uint32_t v) {
 // most 190 together, 128 each.
 constexpr int kBatchRing = 512;
 constexpr int kHardRing = 128;
-// Histogram layout: bins of j = 1..kHW, one pad slot per lane (the draw loop's
-// no-op counts, never read), then three rows of per-lane counts of j = 1, 2 and
-// 3 (most draws: a lane counting into its own slot never conflicts with
-// another lane).
+// Histogram layout: bins of j = 1..kHW, a row of 64 of which the first word takes
+// all lanes' no-op counts in the draw loop (never read), then three rows of
+// per-lane counts of j = 1, 2 and 3 (most draws: a lane counting into its own slot
+// never conflicts with another lane).  The KS keeps a byte per bin in the four rows.
 constexpr int kWavePad = kHW;
 constexpr int kWaveOwn = kHW + 64;
 // Draw blocks per lane per iteration of the draw loop.

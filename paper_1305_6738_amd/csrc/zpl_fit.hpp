@@ -8,10 +8,11 @@
 // replicates (the same expressions, hence the same bits), spread over all waves; their
 // maximum does not depend on the order.
 //
-// Small datasets take one workgroup from the data to the result (k_fit_block).
-// Larger ones and scans are counted and sorted once by many workgroups
-// (k_fit_count, k_fit_merge, k_fit_runs) and then finished per candidate
-// cutoff (k_fit_cand).
+// Small datasets take one workgroup from the data to the result (k_fit_block), or,
+// with few enough candidate cutoffs, one per candidate (k_fit_cand<true>).
+// Other scans are counted and sorted once, by one workgroup or, from kFitGridMin
+// values on, as larger fits are, by many (k_fit_count, k_fit_merge, k_fit_runs), and
+// then finished per candidate cutoff (k_fit_cand<false>).
 //
 // Included by zpl_kernels.hip after zpl_batch.hpp.
 #pragma once
@@ -615,8 +616,9 @@ __global__ __launch_bounds__(256) void k_fit_runs(int64_t n, int groups, int64_t
 // The fit with each candidate cutoff (xmins; without them the one fit from 1
 // on, with or without the upper limit K) from the counts and the sorted larger
 // values, `wgs` workgroups per candidate.  kCount: of a dataset of up to kFitSmall
-// values, which each candidate's one workgroup counts and sorts itself.  A candidate above every value gets
-// D = +inf and status kErrNoTail; any value below 1 sets kErrBadValue.
+// values, which each candidate's one workgroup counts and sorts itself.  A candidate
+// above every value gets D = +inf and status kErrNoTail; any value below 1 sets
+// kErrBadValue.
 // One wave solves eq. 2 (latency: a chain of Newton steps), all share the
 // distance.  Registers for four workgroups per compute unit: 1,000 candidates
 // over 100,000 values take 77 us so, 86 us with two.
