@@ -781,6 +781,16 @@ zpl_status prepare(zpl_ctx* c, Plan& P, int n_q, bool need_dbuf, Launch& L) {
   const uint32_t esc_cap = (uint32_t)std::min<int64_t>(std::max<int64_t>(esc_R, 64), (int64_t)1 << 31);
   ZPL_TRY(ensure(c, c->esc, sizeof(uint64_t) * esc_cap));
   c->esc_cap = esc_cap;
+  if (need_dbuf) ZPL_TRY(ensure(c, c->dbuf, sizeof(double) * (size_t)P.total_R));
+  // bracket gather: at most ~12% of a cell's replicates fall in a bracket
+  int64_t maxR = 1;
+  for (const DevCell& d : P.cells) maxR = std::max(maxR, d.R);
+  L.gcap = std::min<int64_t>(kSelGather, maxR * 3 / 20 + 1024);
+  L.maxR = maxR;
+  // gather areas, then 32 bytes of selection state per (cell, quantile)
+  if (n_q > 0)
+    ZPL_TRY(ensure(c, c->gather, sizeof(uint64_t) * (size_t)nc * kSelQ * L.gcap +
+                                     (size_t)32 * nc * kSelQ));
   L.sim.lane_wgs = (int)std::min<int64_t>((int64_t)P.units.size(), (int64_t)c->n_cu);
   L.sim.lane_waves = P.lane_block / 64;
   const int64_t slots = (int64_t)L.sim.lane_wgs * L.sim.lane_waves * kLaneScratch;
@@ -790,8 +800,15 @@ zpl_status prepare(zpl_ctx* c, Plan& P, int n_q, bool need_dbuf, Launch& L) {
   // finishes together.  The lane form's slots are in the same buffer: calls of
   // either form follow one another within a budget that holds the larger, where
   // two grow-only buffers would need both.
-  const int64_t total = scratch_words(P.heavy8, P.sim_units, P.max_n, esc_R - P.lw_R, c->budget,
-                                      c->n_cu);
+  int64_t total = scratch_words(P.heavy8, P.sim_units, P.max_n, esc_R - P.lw_R, c->budget,
+                                c->n_cu);
+  const int64_t parted = std::max<int64_t>(
+      slots + parted_words(P.n_bpure, P.unit_waves[0], P.max_room[0], c->budget, c->n_cu),
+      parted_words(P.n_bcut, P.unit_waves[1], P.max_room[1], c->budget, c->n_cu));
+  // (the last buffer to grow: a call that fits without the more fits)
+  if (parted > total &&
+      c->used - c->heavy.bytes + sizeof(int64_t) * (uint64_t)parted <= c->budget)
+    total = parted;
   ZPL_TRY(ensure(c, c->heavy, sizeof(int64_t) * (size_t)total));
   const int64_t area = total - slots;  // what the slots leave
   auto none = [&](int64_t room) {
@@ -823,16 +840,6 @@ zpl_status prepare(zpl_ctx* c, Plan& P, int n_q, bool need_dbuf, Launch& L) {
     L.esc = share_scratch(total, 64, kEscWaves, P.max_n, c->n_cu);
     if (L.esc.grid == 0) return none(P.max_n);
   }
-  if (need_dbuf) ZPL_TRY(ensure(c, c->dbuf, sizeof(double) * (size_t)P.total_R));
-  // bracket gather: at most ~12% of a cell's replicates fall in a bracket
-  int64_t maxR = 1;
-  for (const DevCell& d : P.cells) maxR = std::max(maxR, d.R);
-  L.gcap = std::min<int64_t>(kSelGather, maxR * 3 / 20 + 1024);
-  L.maxR = maxR;
-  // gather areas, then 32 bytes of selection state per (cell, quantile)
-  if (n_q > 0)
-    ZPL_TRY(ensure(c, c->gather, sizeof(uint64_t) * (size_t)nc * kSelQ * L.gcap +
-                                     (size_t)32 * nc * kSelQ));
   return ZPL_OK;
 }
 

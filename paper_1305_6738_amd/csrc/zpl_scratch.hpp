@@ -46,6 +46,18 @@ inline Share share_scratch(int64_t area, int64_t units, int waves, int64_t room,
   return Share{(int)g, (int)w, area / (g * w) & ~(int64_t)31};
 }
 
+// int64 with which all of the units' waves hold a replicate of `room` values and what
+// its KS partitions them in: scratch_words follows the replicates, and with fewer
+// waves than a unit has replicates, it takes a second pass (cutoffs 739, alpha 1.8 and
+// 3.43, 1,531 replicates each of n = 1975: 457 us by 11 waves of 12, 322 by all).  0
+// where the KS partitions nothing, and for the longest replicates, which pay with
+// fewer waves too; up to a sixteenth of the budget.
+inline int64_t parted_words(int64_t units, int waves, int64_t room, uint64_t budget, int n_cu) {
+  if (room <= kPartMin || room >= 65536) return 0;
+  const int64_t words = std::min<int64_t>(units, n_cu) * waves * batch_need(room);
+  return (uint64_t)words <= budget / 128 ? words : 0;
+}
+
 // Cells of one call may differ by orders of magnitude in their rooms, and a share
 // that holds the largest would leave the device to a few workgroups.  When it
 // does (the result is true), cells of rooms up to `limit` share a quarter of the

@@ -19,6 +19,9 @@ void sc_share(int64_t area, int64_t units, int waves, int64_t room, int n_cu, in
 int sc_split(int64_t area, int64_t units, int waves, int64_t max_room, int n_cu, int64_t* limit) {
   return split_batch(area, units, waves, max_room, n_cu, *limit) ? 1 : 0;
 }
+int64_t sc_parted(int64_t units, int waves, int64_t room, uint64_t budget, int n_cu) {
+  return parted_words(units, waves, room, budget, n_cu);
+}
 int64_t sc_need(int64_t room) { return batch_need(room); }
 // Values above the histogram that the first replicate of a wave's batch has
 // place for, n draws of 32-bit (n >= 65536) or 16-bit counts: as the kernel

@@ -28,6 +28,8 @@ def sc(tmp_path_factory):
     i64 = C.c_int64
     L.sc_area.restype = L.sc_first_room.restype = L.sc_need.restype = i64
     L.sc_need.argtypes = [i64]
+    L.sc_parted.restype = i64
+    L.sc_parted.argtypes = [i64, C.c_int, i64, C.c_uint64, C.c_int]
     L.sc_area.argtypes = [i64, i64, i64, i64, C.c_uint64, C.c_int]
     L.sc_share.argtypes = [i64, i64, C.c_int, i64, C.c_int, C.POINTER(i64)]
     L.sc_first_room.argtypes = [i64, i64]
@@ -140,3 +142,23 @@ def test_both_kinds_share_a_place(sc):
     total = sc.sc_area(0, 792, 100, 0, BUDGET, N_CU)
     r, stride = place(sc, total, N_CU, 12, 1000, 0, sc.sc_waves(), 100, 100)
     assert r == 0 and stride >= 384 + 64 * 256 + 100
+
+
+@pytest.mark.parametrize("n,room,R", [(1975, 1716, 3062), (1537, 1537, 2048), (2500, 2500, 3072),
+                                      (2200, 2200, 10 ** 5), (7000, 7000, 3500), (65535, 65535, 1)])
+def test_every_wave_of_a_unit_has_its_scratch(sc, n, room, R):
+    """Replicates whose KS partitions its draws, in units of a replicate per wave:
+    every wave holds one, so a unit takes one pass.  At most a sixteenth of the
+    budget is brought in for it, and none for the shortest and longest rooms."""
+    waves = sc.sc_waves_cut()
+    step = min(waves, -(-R // N_CU))
+    units = -(-R // step)
+    more = sc.sc_parted(units, step, room, BUDGET, N_CU)
+    area = max(sc.sc_area((R + 7) // 8, 0, n, 0, BUDGET, N_CU), more)
+    grid, stride, w = share(sc, area, units, step, room)
+    assert grid == min(units, N_CU) and w == step and stride >= sc.sc_need(room)
+    assert 8 * more <= BUDGET // 16
+    small = 1 << 28
+    assert 8 * sc.sc_parted(units, step, room, small, N_CU) <= small // 16
+    assert sc.sc_parted(units, step, 1536, BUDGET, N_CU) == 0
+    assert sc.sc_parted(units, step, 65536, BUDGET, N_CU) == 0
